@@ -473,7 +473,7 @@ int lanczos_destroy(lanczos lz);
  * the rotations to the rows and columns of M and to the basis W: three
  * grouped GEMMs of inner length 64 in the plan's arithmetic (emulated with
  * (slices, ndiag), or native FP64 for slices = 0).
- * rdm_eig_create allocates 4 n_p^2 doubles plus, when emulated, 2 S n_p^2
+ * rdm_eig_create allocates 5 n_p^2 doubles plus, when emulated, 2 S n_p^2
  * bytes of slices.  OZ_ERR_ARG for n outside 1..8192 or bad (slices, ndiag).
  * rdm_eig_solve: A (device, row-major, lda >= n) is read, not modified;
  * writes the nev largest eigenvalues in decreasing order to evals (device,

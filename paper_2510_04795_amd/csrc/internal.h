@@ -246,6 +246,17 @@ int dgemm_tile_for(int64_t tiles128, int num_cu);
 hipError_t launch_dgemm_single(bool ta, bool tb, const Dgemm64Args &a, int num_cu, hipStream_t s);
 hipError_t launch_dgemm_grouped(bool tb, const Dgemm64Args &a, hipStream_t s);
 
+// Cholesky QR of a square matrix (cholqr.hip), np a multiple of 64.
+// launch_shifted_copy: B (np x np) = A + mu I in the leading n x n part,
+// `unit` on the padded diagonal, 0 elsewhere.
+// launch_cholqr_pass: one pass, Q = X L^-T with L L^T = X^T X.  X and G are
+// overwritten; P (np x 64) and Linv (64 x 64) are scratch.  A pivot of the
+// factorisation outside (lo, hi) sets *bad.
+hipError_t launch_shifted_copy(const double *A, int64_t lda, int64_t n, int64_t np, double mu, double unit, double *B,
+                               hipStream_t s);
+hipError_t launch_cholqr_pass(double *G, double *X, double *Q, double *P, double *Linv, int64_t np, int *bad,
+                              double lo, double hi, int num_cu, hipStream_t s);
+
 // sigma[i] = sigma[i] + diag[i] * psi[i] (two roundings), i < n.
 hipError_t launch_diag_axpy(const double *diag, const double *psi, double *sigma, int64_t n,
                             hipStream_t s);

@@ -21,7 +21,11 @@
 //   3. M' = Q^T R^T (= Q^T M Q, M symmetric), the same GEMM on R^T;
 //   4. W <- Q^T W;
 //   5. rows and columns move to the next round's slots (copies).
-// The GEMMs of steps 2-4 run in the plan's arithmetic; step 1 in FP64.  The
+// Before the sweeps up to two steps of shifted QR iteration, M <- Q^T M Q with
+// Q R = M + mu I (mu = 3e-7 |A|_F, then 3e-12 |A|_F), gather the weight near
+// the diagonal in decreasing order (precondition below); W starts as Q^T.
+// The GEMMs of steps 2-4 run in the plan's arithmetic; step 1 and the QR
+// iteration in FP64.  The
 // largest off-diagonal |M_rc| met in step 1 over a sweep measures
 // convergence against tol |A|_F (absolute accuracy, as a tridiagonal-based
 // solver gives).  The eigenvalues are then M_cc / |w_c|^2 and the
@@ -211,9 +215,11 @@ __global__ __launch_bounds__(256) void k_pair_eig(const double *__restrict__ M, 
 }
 
 // Round-0 layout: slot s holds block slot_block[s]: M = P A P^T (zero
-// outside n x n), W = the same rows of the identity.
+// outside n x n), W = the same rows of the identity, or of W0 (of its
+// transpose when wtrans is set).
 __global__ void k_jac_init(const double *__restrict__ A, int64_t lda, int64_t n, int64_t np,
-                           const int *__restrict__ slot_block, double *__restrict__ M, double *__restrict__ W) {
+                           const int *__restrict__ slot_block, double *__restrict__ M, double *__restrict__ W,
+                           const double *__restrict__ W0, int wtrans) {
     const int slot = blockIdx.y;
     const int64_t src0 = static_cast<int64_t>(slot_block[slot]) * kBlk;
     for (int64_t c = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; c < np;
@@ -223,7 +229,7 @@ __global__ void k_jac_init(const double *__restrict__ A, int64_t lda, int64_t n,
             const int64_t src = src0 + r;
             const int64_t dst = (static_cast<int64_t>(slot) * kBlk + r) * np + c;
             M[dst] = (src < n && sc < n) ? A[src * lda + sc] : 0.0;
-            W[dst] = src == c ? 1.0 : 0.0;
+            W[dst] = !W0 ? (src == c ? 1.0 : 0.0) : wtrans ? W0[c * np + src] : W0[src * np + c];
         }
     }
 }
@@ -283,26 +289,28 @@ __global__ void k_jac_gather(const double *__restrict__ W, int64_t np, const int
     }
 }
 
-// bad <- 1 if A has a NaN or Inf; part[block] = sum of squares of the block's entries
+// bad <- 1 if A has a NaN or Inf; part[block] = sum of squares of the block's
+// entries, part[gridDim.x + block] of those off the diagonal
 __global__ __launch_bounds__(256) void k_scan(const double *__restrict__ A, int64_t lda, int64_t n,
                                               int *__restrict__ bad, double *__restrict__ part) {
     __shared__ double r[256];
     int found = 0;
-    double ss = 0.0;
+    double ss = 0.0, so = 0.0;
     for (int64_t idx = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; idx < n * n;
          idx += static_cast<int64_t>(gridDim.x) * blockDim.x) {
         const double x = A[(idx / n) * lda + idx % n];
         if (!(fabs(x) <= 1.79769313486231570e308)) found = 1;
-        else ss = fma(x, x, ss);
+        else {
+            ss = fma(x, x, ss);
+            if (idx / n != idx % n) so = fma(x, x, so);
+        }
     }
     if (found) atomicOr(bad, 1);
-    r[threadIdx.x] = ss;
-    __syncthreads();
-    for (int k = 128; k > 0; k >>= 1) {
-        if (static_cast<int>(threadIdx.x) < k) r[threadIdx.x] += r[threadIdx.x + k];
-        __syncthreads();
+    const double t = block_sum(ss, r), to = block_sum(so, r);
+    if (threadIdx.x == 0) {
+        part[blockIdx.x] = t;
+        part[gridDim.x + blockIdx.x] = to;
     }
-    if (threadIdx.x == 0) part[blockIdx.x] = r[0];
 }
 
 }  // namespace
@@ -314,6 +322,8 @@ struct rdm_eig_s {
     std::vector<void *> allocs;
     double *X = nullptr, *Y = nullptr;    // M and its ping-pong partner, np x np
     double *W = nullptr, *W2 = nullptr;   // basis rows and their rotation, np x np
+    double *V = nullptr;                  // QR iteration: Q of the first pass, then the new M, np x np
+    double *P = nullptr, *Linv = nullptr; // its panel and diagonal block
     double *Qt = nullptr, *off = nullptr, *lam = nullptr, *nrm = nullptr, *part = nullptr, *scale = nullptr;
     int *slot0 = nullptr, *maps = nullptr, *rows = nullptr, *bad = nullptr;
     int ntiles = 0;
@@ -396,8 +406,8 @@ int rotate(rdm_eig h, const double *src, double *C, bool cols, hipStream_t s) {
 }
 
 // One round (steps 1-5): M in src on entry, in dst on exit.
-int enqueue_round(rdm_eig h, int r, const double *src_c, double *dst, double inner_tol, double theta,
-                  hipStream_t s) {
+int enqueue_round(rdm_eig h, int r, const double *src_c, double *dst, double *W, double *W2, double inner_tol,
+                  double theta, hipStream_t s) {
     const int64_t np = h->np;
     double *src = const_cast<double *>(src_c);
     hipError_t e;
@@ -412,11 +422,82 @@ int enqueue_round(rdm_eig h, int r, const double *src_c, double *dst, double inn
     int rc;
     if ((rc = rotate(h, src, dst, false, s)) != OZ_OK) return rc;    // R = Q^T M
     if ((rc = rotate(h, dst, src, true, s)) != OZ_OK) return rc;     // M' = Q^T R^T
-    if ((rc = rotate(h, h->W, h->W2, false, s)) != OZ_OK) return rc;  // W <- Q^T W
+    if ((rc = rotate(h, W, W2, false, s)) != OZ_OK) return rc;       // W <- Q^T W
     const unsigned cx = static_cast<unsigned>(std::min<int64_t>(ceil_div(np, 256), 16));
-    hipLaunchKernelGGL(k_jac_permute, dim3(cx, h->nb, 2), dim3(256), 0, s, src, dst, h->W2, h->W,
+    hipLaunchKernelGGL(k_jac_permute, dim3(cx, h->nb, 2), dim3(256), 0, s, src, dst, W2, W,
                        h->maps + static_cast<int64_t>(r) * h->nb, np);
     if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "rdm_eig: permute");
+    return OZ_OK;
+}
+
+// One step of QR iteration: Q R = M + mu I (M: n x n, ldm), Mout = Q^T M Q
+// with zero padding, all np x np.  Scratch: G and T (may be one buffer), B
+// (may be Q) and Q1 (may be Mout).
+int qr_step(rdm_eig h, const double *M, int64_t ldm, double mu, double unit, double *B, double *G, double *Q1,
+            double *Q, double *T, double *Mout, int *bad, hipStream_t s) {
+    const int64_t n = h->n, np = h->np;
+    const int cu = h->ctx->num_cu;
+    hipError_t e;
+    if ((e = launch_shifted_copy(M, ldm, n, np, mu, unit, B, s)) != hipSuccess ||
+        (e = launch_cholqr_pass(G, B, Q1, h->P, h->Linv, np, bad, 0.0, INFINITY, cu, s)) != hipSuccess ||
+        (e = launch_cholqr_pass(G, Q1, Q, h->P, h->Linv, np, bad, 0.5, 2.0, cu, s)) != hipSuccess)
+        return hip_fail(e, "rdm_eig: Cholesky QR");
+    Dgemm64Args a{};
+    a.mode = kModeGemm;
+    a.term = Term64{M, Q, ldm, np, static_cast<int32_t>(n), 0, 1.0};
+    a.out = OutDesc{T, np, static_cast<int32_t>(n), static_cast<int32_t>(n)};
+    if ((e = launch_dgemm_single(false, false, a, cu, s)) != hipSuccess) return hip_fail(e, "rdm_eig: M Q");
+    if ((e = hipMemsetAsync(Mout, 0, sizeof(double) * np * np, s)) != hipSuccess) return hip_fail(e, "rdm_eig: clear");
+    a.term = Term64{Q, T, np, np, static_cast<int32_t>(n), 0, 1.0};
+    a.out = OutDesc{Mout, np, static_cast<int32_t>(n), static_cast<int32_t>(n)};
+    if ((e = launch_dgemm_single(true, false, a, cu, s)) != hipSuccess) return hip_fail(e, "rdm_eig: Q^T M Q");
+    return OZ_OK;
+}
+
+// Where the sweeps start from: M (n x n, ldm), the basis rows W0 (nullptr:
+// the identity; wtrans: its transpose) and the buffers the sweeps use.
+struct JacStart {
+    const double *M;
+    int64_t ldm;
+    const double *W0;
+    int wtrans;
+    double *X, *Y, *W, *W2;
+};
+
+// QR iteration orders the diagonal by decreasing eigenvalue magnitude and
+// shrinks the couplings by the ratio of the eigenvalues, which is what cyclic
+// Jacobi is slow at on the graded spectra of density matrices: at n = 2048 on
+// a spectrum e^(-i/32) the sweeps go from 28 to 7 and the truncation from 363
+// to 108 ms (FP64).  The shift keeps the
+// condition number of M + mu I (about 3e6 for a positive semidefinite A)
+// inside what Cholesky QR can take; the second step, on an M already graded,
+// gets by with a far smaller one, since the factorisation is invariant to the
+// scaling of its columns.  A step whose factorisation breaks down (a nearly
+// singular M + mu I of an indefinite A) is left out.
+int precondition(rdm_eig h, const double *A, int64_t lda, double fro, JacStart *st, hipStream_t s) {
+    const int64_t np = h->np;
+    hipError_t e;
+    int bad[2] = {0, 0};
+    int rc;
+    if ((e = hipMemsetAsync(h->bad, 0, 2 * sizeof(int), s)) != hipSuccess) return hip_fail(e, "rdm_eig: flags");
+    // step 1: Q1 in W2, M1 in Y; step 2: Q2 in X, M2 in V
+    if ((rc = qr_step(h, A, lda, 3e-7 * fro, fro, h->W2, h->W, h->V, h->W2, h->W, h->Y, h->bad, s)) != OZ_OK ||
+        (rc = qr_step(h, h->Y, np, 3e-12 * fro, fro, h->X, h->W, h->V, h->X, h->W, h->V, h->bad + 1, s)) != OZ_OK)
+        return rc;
+    // basis rows (Q1 Q2)^T
+    Dgemm64Args a{};
+    a.mode = kModeGemm;
+    a.term = Term64{h->X, h->W2, np, np, static_cast<int32_t>(np), 0, 1.0};
+    a.out = OutDesc{h->W, np, static_cast<int32_t>(np), static_cast<int32_t>(np)};
+    if ((e = launch_dgemm_single(true, true, a, h->ctx->num_cu, s)) != hipSuccess) return hip_fail(e, "rdm_eig: basis");
+    if ((e = hipMemcpyAsync(bad, h->bad, sizeof(bad), hipMemcpyDeviceToHost, s)) != hipSuccess ||
+        (e = hipStreamSynchronize(s)) != hipSuccess)
+        return hip_fail(e, "rdm_eig: QR flags");
+    if (bad[0]) return OZ_OK;
+    if (bad[1])
+        *st = JacStart{h->Y, np, h->W2, 1, h->X, h->V, h->W, h->W2};
+    else
+        *st = JacStart{h->V, np, h->W, 0, h->X, h->Y, h->W2, h->W};
     return OZ_OK;
 }
 
@@ -456,6 +537,9 @@ int rdm_eig_create(ozaki_ctx ctx, rdm_eig *out, int64_t n, int slices, int ndiag
     OZ_RA(Y, mat)
     OZ_RA(W, mat)
     OZ_RA(W2, mat)
+    OZ_RA(V, mat)
+    OZ_RA(P, sizeof(double) * np * kPair)
+    OZ_RA(Linv, sizeof(double) * kPair * kPair)
     OZ_RA(Qt, sizeof(double) * np * kPair)
     OZ_RA(off, sizeof(double) * h->rounds * h->npairs * 3)
     OZ_RA(lam, sizeof(double) * np)
@@ -463,7 +547,7 @@ int rdm_eig_create(ozaki_ctx ctx, rdm_eig *out, int64_t n, int slices, int ndiag
     OZ_RA(scale, sizeof(double) * np)
     OZ_RA(rows, sizeof(int) * np)
     OZ_RA(bad, sizeof(int) * 4)
-    OZ_RA(part, sizeof(double) * kScanBlocks)
+    OZ_RA(part, sizeof(double) * 2 * kScanBlocks)
 #undef OZ_RA
     // circle schedule over the nb blocks
     std::vector<int> a(h->nb);
@@ -581,29 +665,40 @@ int rdm_eig_solve(rdm_eig h, const double *A, int64_t lda, int64_t nev, double *
         return hip_fail(e, "rdm_eig_solve: flag");
     const unsigned scan_blocks = static_cast<unsigned>(std::min<int64_t>(ceil_div(n * n, 256), kScanBlocks));
     hipLaunchKernelGGL(k_scan, dim3(scan_blocks), dim3(256), 0, s, A, lda, n, h->bad, h->part);
-    std::vector<double> part(scan_blocks);
+    std::vector<double> part(2 * scan_blocks);
     if ((e = hipMemcpyAsync(hb, h->bad, sizeof(int), hipMemcpyDeviceToHost, s)) != hipSuccess ||
-        (e = hipMemcpyAsync(part.data(), h->part, sizeof(double) * scan_blocks, hipMemcpyDeviceToHost, s)) !=
+        (e = hipMemcpyAsync(part.data(), h->part, sizeof(double) * part.size(), hipMemcpyDeviceToHost, s)) !=
             hipSuccess ||
         (e = hipStreamSynchronize(s)) != hipSuccess)
         return hip_fail(e, "rdm_eig_solve: finiteness check");
     if (hb[0]) return fail(OZ_ERR_ARG, "rdm_eig_solve: A has NaN or Inf entries");
-    double fro2 = 0.0;
-    for (double x : part) fro2 += x;
+    double fro2 = 0.0, off2 = 0.0;
+    for (unsigned i = 0; i < scan_blocks; ++i) {
+        fro2 += part[i];
+        off2 += part[scan_blocks + i];
+    }
     const double fro = std::sqrt(fro2);
     const double abs_tol = tol * fro;
+    JacStart st{A, lda, nullptr, 0, h->X, h->Y, h->W, h->W2};
+    // QR iteration first, unless A is nearly diagonal already (the sweeps
+    // then converge at once and leave an exactly diagonal A exact), a single
+    // pair of blocks (one round a sweep), or |A|_F^2 is near the range's ends
+    if (np > kPair && off2 > 1e-6 * fro2 && fro > 1e-120 && fro < 1e120) {
+        const int rc = precondition(h, A, lda, fro, &st, s);
+        if (rc != OZ_OK) return rc;
+    }
     hipLaunchKernelGGL(k_jac_init, dim3(static_cast<unsigned>(std::min<int64_t>(ceil_div(np, 256), 16)), h->nb),
-                       dim3(256), 0, s, A, lda, n, np, h->slot0, h->X, h->W);
+                       dim3(256), 0, s, st.M, st.ldm, n, np, h->slot0, st.X, st.W, st.W0, st.wtrans);
     if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "rdm_eig_solve: init");
     int status = OZ_MAX_ITER, sweeps = 0, no_progress = 0;
     double best = INFINITY, last = INFINITY;
-    double *cur = h->X, *other = h->Y;
+    double *cur = st.X, *other = st.Y;
     h->host_off.resize(static_cast<size_t>(h->rounds) * h->npairs * 3);
     std::vector<double> lam(np), nrm(np);
     // Diagonal of M over the squared basis norms (Rayleigh quotients) and
     // the basis rows inside the first n coordinates (the others are padding).
     auto diagonal = [&](std::vector<int> *rows) -> int {
-        hipLaunchKernelGGL(k_jac_diag, dim3(static_cast<unsigned>(np)), dim3(256), 0, s, cur, h->W, n, np, h->lam,
+        hipLaunchKernelGGL(k_jac_diag, dim3(static_cast<unsigned>(np)), dim3(256), 0, s, cur, st.W, n, np, h->lam,
                            h->nrm);
         if ((e = hipMemcpyAsync(lam.data(), h->lam, sizeof(double) * np, hipMemcpyDeviceToHost, s)) != hipSuccess ||
             (e = hipMemcpyAsync(nrm.data(), h->nrm, sizeof(double) * np, hipMemcpyDeviceToHost, s)) != hipSuccess ||
@@ -627,7 +722,7 @@ int rdm_eig_solve(rdm_eig h, const double *A, int64_t lda, int64_t nev, double *
     double theta = -INFINITY;
     for (int sw = 0; sw < max_sweeps && fro > 0.0; ++sw) {
         for (int r = 0; r < h->rounds; ++r) {
-            const int rc = enqueue_round(h, r, cur, other, 0.1 * abs_tol, theta, s);
+            const int rc = enqueue_round(h, r, cur, other, st.W, st.W2, 0.1 * abs_tol, theta, s);
             if (rc != OZ_OK) return rc;
             std::swap(cur, other);
         }
@@ -687,7 +782,7 @@ int rdm_eig_solve(rdm_eig h, const double *A, int64_t lda, int64_t nev, double *
             (e = hipMemcpyAsync(evals, ev.data(), sizeof(double) * nev, hipMemcpyHostToDevice, s)) != hipSuccess)
             return hip_fail(e, "rdm_eig_solve: output");
         hipLaunchKernelGGL(k_jac_gather, dim3(static_cast<unsigned>(ceil_div(n, 32)), static_cast<unsigned>(ceil_div(nev, 32))),
-                           dim3(256), 0, s, h->W, np, h->rows, h->scale, n, nev, Z, ldz);
+                           dim3(256), 0, s, st.W, np, h->rows, h->scale, n, nev, Z, ldz);
         if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "rdm_eig_solve: gather");
         if ((e = hipStreamSynchronize(s)) != hipSuccess) return hip_fail(e, "rdm_eig_solve: gather");
     }

@@ -117,6 +117,34 @@ def test_random_symmetric(oz, seed):
     check_eigenpairs(A, w, Z, S)
 
 
+@pytest.mark.parametrize("n", [65, 128, 129, 320])
+@pytest.mark.parametrize("kind", ["graded", "singular_shift", "rank_one"])
+def test_qr_iteration_start(oz, n, kind):
+    """Starts of the sweeps from QR iteration around the 64-column panels: a
+    graded density matrix (both steps taken); an indefinite matrix whose
+    shifted copy is singular (an eigenvalue of -3e-7 |A|_F: the first
+    factorisation breaks down and the sweeps start from A itself, or from a
+    pass of poor orthogonality that has to be refused); rank one (all but one
+    column of the shifted copy is the shift alone)."""
+    rng = np.random.default_rng(n)
+    Q, _ = np.linalg.qr(rng.standard_normal((n, n)))
+    if kind == "graded":
+        lam = np.exp(-np.arange(n) / (n / 64.0))
+    elif kind == "rank_one":
+        lam = np.zeros(n)
+        lam[0] = 1.0
+    else:
+        lam = rng.standard_normal(n)
+        lam[n // 2] = 0.0
+        lam[n // 2] = -3e-7 * np.linalg.norm(lam)
+    A = (Q * lam) @ Q.T
+    A = 0.5 * (A + A.T)
+    nev = n // 4 if kind == "graded" else n
+    w, Z, info = solve(oz, A, nev=nev)
+    assert info.status in (1, 2, 3)
+    check_eigenpairs(A, w, Z, 0)
+
+
 def test_edge_matrices(oz):
     # zero matrix: all eigenvalues 0, orthonormal eigenvectors
     w, Z, info = solve(oz, np.zeros((50, 50)))
