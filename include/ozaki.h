@@ -468,11 +468,13 @@ int lanczos_destroy(lanczos lz);
  * rdm_eig: eigenpairs of a symmetric n x n matrix (a reduced density
  * matrix) by two-sided block Jacobi on the device (n <= 8192; blocks of 32
  * rows, padded to n_p = roundup(n, 64)).  A sweep runs n_p/32 - 1 rounds;
- * a round diagonalises the 64 x 64 diagonal blocks of the paired blocks of
- * M = W A W^T (cyclic Jacobi, one workgroup per pair, in FP64) and applies
- * the rotations to the rows and columns of M and to the basis W: three
- * grouped GEMMs of inner length 64 in the plan's arithmetic (emulated with
- * (slices, ndiag), or native FP64 for slices = 0).
+ * a round takes the 64 x 64 diagonal blocks of the paired blocks of
+ * M = W A W^T through cyclic Jacobi rotations (one workgroup per pair, in
+ * FP64) and applies them to the rows and columns of M and to the basis W:
+ * products of inner length 64 in the plan's arithmetic (emulated with
+ * (slices, ndiag), or native FP64 for slices = 0).  The sweeps start from
+ * W = Q^T of two steps of shifted QR iteration in FP64 (none for n <= 64 or
+ * a nearly diagonal A).
  * rdm_eig_create allocates 5 n_p^2 doubles plus, when emulated, 2 S n_p^2
  * bytes of slices.  OZ_ERR_ARG for n outside 1..8192 or bad (slices, ndiag).
  * rdm_eig_solve: A (device, row-major, lda >= n) is read, not modified;

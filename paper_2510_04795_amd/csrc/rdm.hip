@@ -12,15 +12,20 @@
 // blocks of 32; a sweep pairs every block with every other once (round-robin
 // "circle" schedule, np/32 - 1 rounds).  In a round the paired blocks sit
 // next to each other, so pair k owns rows and columns [64k, 64k + 64):
-//   1. eigenvectors of each pair's diagonal 64 x 64 block of M by cyclic
-//      Jacobi in LDS (one workgroup per pair; one sweep unless the block
-//      is already diagonal), accumulated from the identity, in that order:
-//      Q_k^T (sorting them by eigenvalue would make the block rotation a
-//      near-permutation between the two blocks, and block Jacobi then stalls);
-//   2. R = Q^T M (rows of each pair), a grouped GEMM of inner length 64;
-//   3. M' = Q^T R^T (= Q^T M Q, M symmetric), the same GEMM on R^T;
+//   1. one sweep of cyclic Jacobi on each pair's diagonal 64 x 64 block of M
+//      (one workgroup per pair; nothing when the block is already
+//      diagonal): all its rotations in a sweep's first round, the 1024 that
+//      couple its two blocks in the others, accumulated from the identity, in
+//      that order: Q_k^T (sorting them by eigenvalue would make the block
+//      rotation a near-permutation between the two blocks, and block Jacobi
+//      then stalls);
+//   2. R = Q^T M (rows of each pair);
+//   3. M' = Q^T R^T (= Q^T M Q, M symmetric);
 //   4. W <- Q^T W;
-//   5. rows and columns move to the next round's slots (copies).
+//   5. rows and columns move to the next round's slots.
+// In native FP64 steps 2, 3 and 5 of M are one kernel, and step 4 with its
+// move runs beside the next round's step 1; emulated, each of 2-4 is a
+// grouped GEMM of inner length 64 and step 5 a copy.
 // Before the sweeps up to two steps of shifted QR iteration, M <- Q^T M Q with
 // Q R = M + mu I (mu = 3e-7 |A|_F, then 3e-12 |A|_F), gather the weight near
 // the diagonal in decreasing order (precondition below); W starts as Q^T.
@@ -38,6 +43,7 @@
 #include <vector>
 
 #include "runtime.h"
+#include "tile64.h"
 
 using namespace oz;
 
@@ -48,7 +54,6 @@ constexpr int kPair = 64;   // rows per pair of blocks
 constexpr int kLdE = 65;    // LDS row stride of the 64 x 64 pair problems
 constexpr int64_t kMaxEigN = 8192;
 constexpr int kScanBlocks = 1024;
-constexpr int kInnerSweeps = 1;
 
 // Round-robin schedule of the 64 rows of a pair problem: row 63 fixed, the
 // others rotate; step `step` pairs (63, step) and (step + t, step - t) mod 63.
@@ -84,7 +89,7 @@ __device__ double block_sum(double v, double *red) {
 // spectrum).  Returns the largest |a_rc| of the other entries to all
 // threads; with sums set also the sum of squares of the counted entries
 // (sums[0]) and of the exempt ones (sums[1]).
-__device__ double offdiag(const double *a, double *red, double theta, double *sums = nullptr) {
+__device__ double offdiag(const double *a, double *red, double theta, double *sums) {
     const int tid = threadIdx.x;
     double m = 0.0, q = 0.0, qx = 0.0;
     for (int idx = tid; idx < kPair * kPair; idx += 256) {
@@ -106,10 +111,8 @@ __device__ double offdiag(const double *a, double *red, double theta, double *su
     }
     const double r = red[0];
     __syncthreads();
-    if (sums) {
-        sums[0] = block_sum(q, red);
-        sums[1] = block_sum(qx, red);
-    }
+    sums[0] = block_sum(q, red);
+    sums[1] = block_sum(qx, red);
     return r;
 }
 
@@ -120,9 +123,9 @@ __device__ __forceinline__ double lane_value(double x, int lane) {
 }
 
 // Step 1: one workgroup per pair k.  The pair's diagonal block of M (upper
-// triangle, mirrored) is diagonalised by cyclic Jacobi until its largest
-// off-diagonal entry is <= inner_tol or after kInnerSweeps sweeps; Qt rows
-// [64k, 64k + 64) receive the accumulated rotations (row t: column t of
+// triangle, mirrored) goes through one sweep of cyclic Jacobi over all its
+// rotations, unless its largest off-diagonal entry is <= inner_tol and its
+// exempt entries' sum of squares <= exempt_tol2; Qt rows [64k, 64k + 64) receive the accumulated rotations (row t: column t of
 // their product); off_out[3k .. 3k + 2]: the block's largest counted
 // off-diagonal |entry| and the sums of squares of the counted and of the
 // exempt entries (both diagonals below theta) before the rotations.
@@ -131,7 +134,7 @@ __device__ __forceinline__ double lane_value(double x, int lane) {
 // lanes then sweep the 64 columns (row pass) and the 64 rows (column pass).
 __global__ __launch_bounds__(256) void k_pair_eig(const double *__restrict__ M, int64_t ldm,
                                                   double *__restrict__ Qt, double *__restrict__ off_out,
-                                                  double inner_tol, double theta) {
+                                                  double inner_tol, double exempt_tol2, double theta) {
     __shared__ double a[kPair * kLdE];
     __shared__ double vt[kPair * kPair];  // transposed rotations: row t is column t of the product
     __shared__ double red[256];
@@ -146,13 +149,13 @@ __global__ __launch_bounds__(256) void k_pair_eig(const double *__restrict__ M, 
     }
     __syncthreads();
     double sums[2];
-    double off = offdiag(a, red, theta, sums);
+    const double off = offdiag(a, red, theta, sums);
     if (tid == 0) {
         off_out[3 * k] = off;
         off_out[3 * k + 1] = sums[0];
         off_out[3 * k + 2] = sums[1];
     }
-    for (int sw = 0; sw < kInnerSweeps && off > inner_tol; ++sw) {
+    if (off > inner_tol || sums[1] > exempt_tol2) {
         for (int step = 0; step < 63; ++step) {
             double cl = 1.0, sl = 0.0;
             {
@@ -208,10 +211,289 @@ __global__ __launch_bounds__(256) void k_pair_eig(const double *__restrict__ M, 
             }
             __syncthreads();
         }
-        if (sw + 1 < kInnerSweeps) off = offdiag(a, red, theta);
     }
     double *qt = Qt + static_cast<int64_t>(kPair) * k * kPair;
     for (int idx = tid; idx < kPair * kPair; idx += 256) qt[idx] = vt[idx];
+}
+
+// Rotation that zeroes a_pq of [[app, apq], [apq, aqq]]: tan of the smaller
+// angle, t = y sgn(x) / (|x| + sqrt(x^2 + y^2)) with x = aqq - app, y = 2 apq
+// (scaled by a power of two so the squares stay in range), c = 1 / sqrt(1 +
+// t^2), s = t c.  Reciprocal (square root) estimates of the hardware (about
+// 2^-23) with one third-order correction each: a third of the dependent
+// instructions of the exact divisions and square roots; c^2 + s^2 = 1 to two
+// rounding errors.
+__device__ __forceinline__ double rsqrt_refined(double x) {
+    const double y = __builtin_amdgcn_rsq(x);
+    const double e = fma(-x * y, y, 1.0);
+    return fma(y * e, fma(0.375, e, 0.5), y);
+}
+__device__ __forceinline__ double rcp_refined(double x) {
+    const double y = __builtin_amdgcn_rcp(x);
+    const double e = fma(-x, y, 1.0);
+    return fma(y, fma(e, e, e), y);
+}
+__device__ __forceinline__ void schur_rotation(double app, double aqq, double apq, double *c, double *s) {
+    double x = aqq - app, y = 2.0 * apq;
+    const int ex = -__builtin_amdgcn_frexp_exp(fmax(fabs(x), fabs(y)));
+    x = ldexp(x, ex);
+    y = ldexp(y, ex);
+    const double r2 = fma(x, x, y * y);
+    const double t = (x >= 0.0 ? y : -y) * rcp_refined(fabs(x) + r2 * rsqrt_refined(r2));
+    const double cc = rsqrt_refined(fma(t, t, 1.0));
+    *c = apq != 0.0 ? cc : 1.0;
+    *s = apq != 0.0 ? t * cc : 0.0;
+}
+
+__device__ __forceinline__ double lane_shift(double x, int addr) {
+    const int lo = __builtin_amdgcn_ds_bpermute(addr, __double2loint(x));
+    const int hi = __builtin_amdgcn_ds_bpermute(addr, __double2hiint(x));
+    return __hiloint2double(hi, lo);
+}
+
+__device__ __forceinline__ double wave_max(double v) {
+    for (int o = 32; o >= 1; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
+    return v;
+}
+__device__ __forceinline__ double wave_sum(double v) {
+    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
+    return v;
+}
+
+constexpr int kRotLds = 64 * t64::kLdK + 64 * t64::kLdN;  // doubles: one tile read along k, one across
+
+// Step 1 in the rounds after a sweep's first: only the 1024 rotations that
+// couple the pair's two blocks (the first round rotates inside the blocks
+// too, so a sweep still meets every pair of rows once).  32 steps; step t
+// rotates the disjoint pairs (i, 32 + (i + t) % 32).
+//
+// Everything stays in registers: thread (ty, tx) holds, for the pairs i = 4
+// ty + m (m < 4) and j = tx, the 2 x 2 block of rows (p_i, q_i) and columns
+// (p_j, q_j), and the entries of columns tx and tx + 32 of rows p_i, q_i of
+// the accumulated rotations.  A rotation is then local once its (c, s) pairs
+// are known, and moving on to the next step's pairing shifts the q rows and
+// columns by one: within the thread, to the next lane, or (one row in four)
+// through LDS.  Bound: the chain of 32 steps (rotation, broadcast, update,
+// shift), two barriers each: 40 us at n = 2048 with W's tiles beside it,
+// against 110 us for k_pair_eig, whose 63 steps each move 200 KB through LDS.
+__device__ void pair_cross(const double *__restrict__ g, int64_t ldm, double *__restrict__ qt,
+                           double *__restrict__ off_out, double inner_tol, double exempt_tol2, double theta,
+                           double *lds) {
+    double *a = lds;                       // 64 x kLdE staging
+    double *cs = lds + kPair * kLdE;       // 32 x (c, s)
+    double *sh = cs + 64;                  // 8 x 4 x 32 shifted values
+    double *red = sh + 1024;               // 4 x 3
+    const int tid = threadIdx.x, tx = tid & 31, ty = tid >> 5;
+    for (int idx = tid; idx < kPair * kPair; idx += 256) {
+        const int r = idx >> 6, c = idx & 63;
+        if (r <= c) {
+            const double x = g[r * ldm + c];
+            a[r * kLdE + c] = x;
+            a[c * kLdE + r] = x;
+        }
+    }
+    __syncthreads();
+    double pp[4], pq[4], qp[4], qq[4], vp[4][2], vq[4][2];
+    double mx = 0.0, sq = 0.0, sx = 0.0;
+    const double dj[2] = {a[tx * kLdE + tx], a[(32 + tx) * kLdE + 32 + tx]};
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+        const int i = 4 * ty + m;
+        pp[m] = a[i * kLdE + tx];
+        pq[m] = a[i * kLdE + 32 + tx];
+        qp[m] = a[(32 + i) * kLdE + tx];
+        qq[m] = a[(32 + i) * kLdE + 32 + tx];
+        const double di[2] = {a[i * kLdE + i], a[(32 + i) * kLdE + 32 + i]};
+        const double v[2][2] = {{pp[m], pq[m]}, {qp[m], qq[m]}};
+#pragma unroll
+        for (int r = 0; r < 2; ++r)
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                if (r == c && i == tx) continue;
+                const double x = fabs(v[r][c]);
+                if (di[r] < theta && dj[c] < theta) {
+                    sx = fma(x, x, sx);
+                } else {
+                    mx = fmax(mx, x);
+                    sq = fma(x, x, sq);
+                }
+            }
+        vp[m][0] = i == tx ? 1.0 : 0.0;
+        vp[m][1] = 0.0;
+        vq[m][0] = 0.0;
+        vq[m][1] = i == tx ? 1.0 : 0.0;
+    }
+    mx = wave_max(mx);
+    sq = wave_sum(sq);
+    sx = wave_sum(sx);
+    if ((tid & 63) == 0) {
+        red[(tid >> 6) * 3] = mx;
+        red[(tid >> 6) * 3 + 1] = sq;
+        red[(tid >> 6) * 3 + 2] = sx;
+    }
+    __syncthreads();
+    mx = fmax(fmax(red[0], red[3]), fmax(red[6], red[9]));
+    sq = (red[1] + red[4]) + (red[7] + red[10]);
+    sx = (red[2] + red[5]) + (red[8] + red[11]);
+    if (tid == 0) {
+        off_out[0] = mx;
+        off_out[1] = sq;
+        off_out[2] = sx;
+    }
+    if (mx > inner_tol || sx > exempt_tol2) {
+        const int next = 4 * ((tid & 32) + ((tx + 1) & 31));  // lane tx + 1 of the same half wave
+        const int mi = tx - 4 * ty;                           // this thread holds pair tx's own block when 0 <= mi < 4
+        for (int t = 0; t < 32; ++t) {
+            double app = pp[0], apq = pq[0], aqq = qq[0];
+#pragma unroll
+            for (int m = 1; m < 4; ++m) {
+                app = mi == m ? pp[m] : app;
+                apq = mi == m ? pq[m] : apq;
+                aqq = mi == m ? qq[m] : aqq;
+            }
+            double c, s;
+            schur_rotation(app, aqq, apq, &c, &s);
+            if (mi >= 0 && mi < 4) *reinterpret_cast<double2 *>(cs + 2 * tx) = double2{c, s};
+            __syncthreads();
+            const double2 rj = *reinterpret_cast<const double2 *>(cs + 2 * tx);
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                const double2 ri = *reinterpret_cast<const double2 *>(cs + 2 * (4 * ty + m));
+                const double p0 = ri.x * pp[m] - ri.y * qp[m], q0 = ri.y * pp[m] + ri.x * qp[m];
+                const double p1 = ri.x * pq[m] - ri.y * qq[m], q1 = ri.y * pq[m] + ri.x * qq[m];
+                pp[m] = rj.x * p0 - rj.y * p1;
+                pq[m] = rj.y * p0 + rj.x * p1;
+                qp[m] = rj.x * q0 - rj.y * q1;
+                qq[m] = rj.y * q0 + rj.x * q1;
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const double u = vp[m][h], w = vq[m][h];
+                    vp[m][h] = ri.x * u - ri.y * w;
+                    vq[m][h] = ri.y * u + ri.x * w;
+                }
+            }
+            // next pairing: q_i <- q_{i+1}, q_j <- q_{j+1}
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                pq[m] = lane_shift(pq[m], next);
+                qq[m] = lane_shift(qq[m], next);
+            }
+            double *mine = sh + ty * 128 + tx;
+            mine[0] = qp[0];
+            mine[32] = qq[0];
+            mine[64] = vq[0][0];
+            mine[96] = vq[0][1];
+#pragma unroll
+            for (int m = 0; m < 3; ++m) {
+                qp[m] = qp[m + 1];
+                qq[m] = qq[m + 1];
+                vq[m][0] = vq[m + 1][0];
+                vq[m][1] = vq[m + 1][1];
+            }
+            __syncthreads();
+            const double *other = sh + ((ty + 1) & 7) * 128 + tx;
+            qp[3] = other[0];
+            qq[3] = other[32];
+            vq[3][0] = other[64];
+            vq[3][1] = other[96];
+        }
+    }
+#pragma unroll
+    for (int m = 0; m < 4; ++m)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            qt[(4 * ty + m) * kPair + tx + 32 * h] = vp[m][h];
+            qt[(32 + 4 * ty + m) * kPair + tx + 32 * h] = vq[m][h];
+        }
+}
+
+// W' rows of pair i, columns [64 c, 64 c + 64) = Q_i^T W: block 2i + h of 32
+// rows goes to slot dst[2i + h].
+__device__ void rotate_w(const double *__restrict__ qt, const double *__restrict__ W, double *__restrict__ W2,
+                         const int *__restrict__ dst, int64_t np, int tile, double *lds) {
+    const int tiles = static_cast<int>(np / 64);
+    const int i = tile / tiles, c = tile % tiles;
+    double *sA = lds, *sB = lds + 64 * t64::kLdK;
+    t64::load(sA, t64::kLdK, qt + static_cast<int64_t>(i) * 4096, 64);
+    t64::load(sB, t64::kLdN, W + static_cast<int64_t>(i) * 64 * np + c * 64, np);
+    __syncthreads();
+    t64::Acc acc;
+    acc.zero();
+    t64::mul_nn(acc, sA, sB);
+    double *o0 = W2 + static_cast<int64_t>(dst[2 * i]) * kBlk * np + c * 64;
+    double *o1 = W2 + static_cast<int64_t>(dst[2 * i + 1]) * kBlk * np + c * 64;
+    t64::each(acc, [&](int r, int col, double x) { (r < 32 ? o0 : o1)[(r & 31) * np + col] = x; });
+}
+
+// A round's step 1 (the first npairs workgroups; none in the sweep's first
+// round, which is k_pair_eig's) and step 4 of the round before (the others):
+// nothing in a round waits for W, and step 1 leaves most of the chip idle.
+__global__ __launch_bounds__(256) void k_pair_cross(const double *__restrict__ M, int64_t np, double *__restrict__ Qt,
+                                                    double *__restrict__ off_out, double inner_tol,
+                                                    double exempt_tol2, double theta, int npairs,
+                                                    const double *__restrict__ Qt_prev, const double *__restrict__ W,
+                                                    double *__restrict__ W2, const int *__restrict__ dst_prev) {
+    __shared__ __align__(16) double lds[kRotLds];
+    const int b = blockIdx.x;
+    if (b < npairs) {
+        pair_cross(M + (static_cast<int64_t>(kPair) * np + kPair) * b, np, Qt + static_cast<int64_t>(b) * 4096,
+                   off_out + 3 * b, inner_tol, exempt_tol2, theta, lds);
+        return;
+    }
+    rotate_w(Qt_prev, W, W2, dst_prev, np, b - npairs, lds);
+}
+
+// Steps 2, 3 and 5 of M in one pass: tile (i, j), i <= j, of pairs becomes
+// Q_i^T M_ij Q_j and goes to the next round's slots.  Of M only the tiles on
+// and above the diagonal are kept (whole 64 x 64 tiles on it): a 32 x 32
+// block that lands below is stored transposed.  Reads half of M and writes
+// half of it where separate products and the permutation moved it four times
+// (measured, n = 2048: 82 us a round for the three products and the permutation
+// of M and W, against 23 us here and W hidden behind step 1).
+__global__ __launch_bounds__(256) void k_rotate_m(const double *__restrict__ M, double *__restrict__ M2,
+                                                  const double *__restrict__ Qt, const int *__restrict__ dst,
+                                                  int64_t np) {
+    __shared__ __align__(16) double lds[kRotLds];
+    // triangular index: blockIdx.x = j (j + 1) / 2 + i
+    const int b = blockIdx.x;
+    int j = static_cast<int>((sqrtf(8.0f * b + 1.0f) - 1.0f) * 0.5f);
+    while (j * (j + 1) / 2 > b) --j;
+    while ((j + 1) * (j + 2) / 2 <= b) ++j;
+    const int i = b - j * (j + 1) / 2;
+    double *sA = lds, *sB = lds + 64 * t64::kLdK;
+    t64::load(sB, t64::kLdK, M + static_cast<int64_t>(i) * 64 * np + static_cast<int64_t>(j) * 64, np);
+    t64::load(sA, t64::kLdK, Qt + static_cast<int64_t>(j) * 4096, 64);
+    __syncthreads();
+    t64::Acc acc;
+    acc.zero();
+    t64::mul_nt(acc, sB, sA);  // U = M_ij Q_j
+    __syncthreads();
+    t64::load(sA, t64::kLdK, Qt + static_cast<int64_t>(i) * 4096, 64);
+    t64::each(acc, [&](int r, int c, double x) { sB[r * t64::kLdN + c] = x; });
+    __syncthreads();
+    acc.zero();
+    t64::mul_nn(acc, sA, sB);  // Q_i^T U
+    __syncthreads();
+    t64::each(acc, [&](int r, int c, double x) { lds[r * kLdE + c] = x; });
+    __syncthreads();
+    const int x = threadIdx.x & 31, y = threadIdx.x >> 5;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int rb = q >> 1, cb = q & 1;
+        const int dr = dst[2 * i + rb], dc = dst[2 * j + cb];
+        if (i == j && rb > cb && (dr >> 1) != (dc >> 1)) continue;  // the transpose of the block rb < cb
+        const double *src = lds + rb * 32 * kLdE + cb * 32;
+        if ((dr >> 1) <= (dc >> 1)) {
+            double *o = M2 + static_cast<int64_t>(dr) * kBlk * np + static_cast<int64_t>(dc) * kBlk;
+#pragma unroll
+            for (int r = 0; r < 32; r += 8) o[(r + y) * np + x] = src[(r + y) * kLdE + x];
+        }
+        if ((dr >> 1) > (dc >> 1) || ((dr >> 1) == (dc >> 1) && i != j)) {
+            double *o = M2 + static_cast<int64_t>(dc) * kBlk * np + static_cast<int64_t>(dr) * kBlk;
+#pragma unroll
+            for (int r = 0; r < 32; r += 8) o[(r + y) * np + x] = src[x * kLdE + r + y];
+        }
+    }
 }
 
 // Round-0 layout: slot s holds block slot_block[s]: M = P A P^T (zero
@@ -325,11 +607,9 @@ struct rdm_eig_s {
     double *V = nullptr;                  // QR iteration: Q of the first pass, then the new M, np x np
     double *P = nullptr, *Linv = nullptr; // its panel and diagonal block
     double *Qt = nullptr, *off = nullptr, *lam = nullptr, *nrm = nullptr, *part = nullptr, *scale = nullptr;
-    int *slot0 = nullptr, *maps = nullptr, *rows = nullptr, *bad = nullptr;
-    int ntiles = 0;
-    // native FP64: rows (B = rows of the pair) and columns (B = columns of the pair, transposed)
+    int *slot0 = nullptr, *maps = nullptr, *dst = nullptr, *rows = nullptr, *bad = nullptr;
+    int ntiles = 0;  // pairs x 64-column tiles
     TileDesc *tiles = nullptr;
-    Term64 *t_rows = nullptr, *t_cols = nullptr;
     OutDesc *outs = nullptr;
     // emulated: Qt slices, pair panels by columns (trans) and by rows
     int32_t *eQ = nullptr, *eR = nullptr, *eC = nullptr;
@@ -367,23 +647,9 @@ void rfree(rdm_eig h) {
 }
 
 // C rows of each pair <- Q_k^T times the pair's rows of `src` (cols = false)
-// or the transpose of its columns (cols = true), in the plan's arithmetic.
+// or the transpose of its columns (cols = true), emulated.
 int rotate(rdm_eig h, const double *src, double *C, bool cols, hipStream_t s) {
-    const int64_t np = h->np;
     hipError_t e;
-    if (h->S == 0) {
-        Dgemm64Args a{};
-        a.tiles = h->tiles;
-        a.terms = cols ? h->t_cols : h->t_rows;
-        a.outs = h->outs;
-        a.ntiles = h->ntiles;
-        a.mode = kModeGemm;
-        a.tile = 64;
-        a.out_base = C;
-        a.b_base = src;
-        e = launch_dgemm_grouped(cols, a, s);
-        return e == hipSuccess ? OZ_OK : hip_fail(e, "rdm_eig: rotation");
-    }
     if (cols) {
         if ((e = launch_exponents_grouped(h->bC, h->eC_t, h->n_eC, src, h->eC, h->ctx->d_flags, s)) != hipSuccess ||
             (e = launch_slice_grouped(h->S, h->bC, h->sC_t, h->n_sC, src, h->eC, h->pC, s)) != hipSuccess)
@@ -401,25 +667,71 @@ int rotate(rdm_eig h, const double *src, double *C, bool cols, hipStream_t s) {
     a.mode = kModeGemm;
     a.out_base = C;
     e = launch_pair_grouped(h->S, h->G, 0, a, s);
-    (void)np;
     return e == hipSuccess ? OZ_OK : hip_fail(e, "rdm_eig: rotation");
 }
 
-// One round (steps 1-5): M in src on entry, in dst on exit.
+// Where the sweeps start from: M (n x n, ldm), the basis rows W0 (nullptr:
+// the identity; wtrans: its transpose) and the buffers the sweeps use.
+struct JacStart {
+    const double *M;
+    int64_t ldm;
+    const double *W0;
+    int wtrans;
+    double *X, *Y, *W, *W2;  // M and its ping-pong partner, the basis rows and theirs
+};
+
+// Step 1 of round r: every rotation of the pairs' blocks in a sweep's first
+// round, the ones that couple the two blocks in the others; with W set also
+// step 4 of round r - 1 (W -> W2).
+int pair_step(rdm_eig h, int r, const double *M, double *Qt, double inner_tol, double exempt_tol2, double theta,
+              const double *Qt_prev, const double *W, double *W2, hipStream_t s) {
+    const int64_t np = h->np;
+    double *off = h->off + static_cast<int64_t>(r) * h->npairs * 3;
+    if (r == 0)
+        hipLaunchKernelGGL(k_pair_eig, dim3(h->npairs), dim3(256), 0, s, M, np, Qt, off, inner_tol, exempt_tol2, theta);
+    else
+        hipLaunchKernelGGL(k_pair_cross, dim3(h->npairs + (W ? h->ntiles : 0)), dim3(256), 0, s, M, np, Qt, off,
+                           inner_tol, exempt_tol2, theta, h->npairs, Qt_prev, W, W2,
+                           W ? h->dst + static_cast<int64_t>(r - 1) * h->nb : nullptr);
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess ? OZ_OK : hip_fail(e, "rdm_eig: pair eigensolver");
+}
+
+// One sweep in native FP64: two launches a round, W one round behind M.
+int sweep_native(rdm_eig h, JacStart *st, double inner_tol, double exempt_tol2, double theta, hipStream_t s) {
+    const int64_t np = h->np;
+    const int tri = h->npairs * (h->npairs + 1) / 2;
+    hipError_t e;
+    for (int r = 0; r < h->rounds; ++r) {
+        double *Qt = h->Qt + (r & 1) * np * kPair, *prev = h->Qt + ((r + 1) & 1) * np * kPair;
+        const int rc = pair_step(h, r, st->X, Qt, inner_tol, exempt_tol2, theta, prev, st->W, st->W2, s);
+        if (rc != OZ_OK) return rc;
+        if (r > 0) std::swap(st->W, st->W2);
+        hipLaunchKernelGGL(k_rotate_m, dim3(tri), dim3(256), 0, s, st->X, st->Y, Qt,
+                           h->dst + static_cast<int64_t>(r) * h->nb, np);
+        if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "rdm_eig: rotation");
+        std::swap(st->X, st->Y);
+    }
+    const int last = h->rounds - 1;
+    hipLaunchKernelGGL(k_pair_cross, dim3(h->ntiles), dim3(256), 0, s, nullptr, np, nullptr, nullptr, 0.0, 0.0, 0.0, 0,
+                       h->Qt + (last & 1) * np * kPair, st->W, st->W2, h->dst + static_cast<int64_t>(last) * h->nb);
+    if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "rdm_eig: basis rotation");
+    std::swap(st->W, st->W2);
+    return OZ_OK;
+}
+
+// One round (steps 1-5) in emulated arithmetic: M in src on entry, in dst on exit.
 int enqueue_round(rdm_eig h, int r, const double *src_c, double *dst, double *W, double *W2, double inner_tol,
-                  double theta, hipStream_t s) {
+                  double exempt_tol2, double theta, hipStream_t s) {
     const int64_t np = h->np;
     double *src = const_cast<double *>(src_c);
     hipError_t e;
-    hipLaunchKernelGGL(k_pair_eig, dim3(h->npairs), dim3(256), 0, s, src, np, h->Qt,
-                       h->off + static_cast<int64_t>(r) * h->npairs * 3, inner_tol, theta);
-    if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "rdm_eig: pair eigensolver");
-    if (h->S) {
-        if ((e = launch_row_exponents(h->Qt, kPair, np, kPair, h->eQ, h->ctx->d_flags, s)) != hipSuccess ||
-            (e = launch_slice(h->S, false, h->Qt, kPair, np, kPair, h->eQ, h->pQ, np, s)) != hipSuccess)
-            return hip_fail(e, "rdm_eig: slicing Q");
-    }
     int rc;
+    if ((rc = pair_step(h, r, src, h->Qt, inner_tol, exempt_tol2, theta, nullptr, nullptr, nullptr, s)) != OZ_OK)
+        return rc;
+    if ((e = launch_row_exponents(h->Qt, kPair, np, kPair, h->eQ, h->ctx->d_flags, s)) != hipSuccess ||
+        (e = launch_slice(h->S, false, h->Qt, kPair, np, kPair, h->eQ, h->pQ, np, s)) != hipSuccess)
+        return hip_fail(e, "rdm_eig: slicing Q");
     if ((rc = rotate(h, src, dst, false, s)) != OZ_OK) return rc;    // R = Q^T M
     if ((rc = rotate(h, dst, src, true, s)) != OZ_OK) return rc;     // M' = Q^T R^T
     if ((rc = rotate(h, W, W2, false, s)) != OZ_OK) return rc;       // W <- Q^T W
@@ -453,16 +765,6 @@ int qr_step(rdm_eig h, const double *M, int64_t ldm, double mu, double unit, dou
     if ((e = launch_dgemm_single(true, false, a, cu, s)) != hipSuccess) return hip_fail(e, "rdm_eig: Q^T M Q");
     return OZ_OK;
 }
-
-// Where the sweeps start from: M (n x n, ldm), the basis rows W0 (nullptr:
-// the identity; wtrans: its transpose) and the buffers the sweeps use.
-struct JacStart {
-    const double *M;
-    int64_t ldm;
-    const double *W0;
-    int wtrans;
-    double *X, *Y, *W, *W2;
-};
 
 // QR iteration orders the diagonal by decreasing eigenvalue magnitude and
 // shrinks the couplings by the ratio of the eigenvalues, which is what cyclic
@@ -540,7 +842,7 @@ int rdm_eig_create(ozaki_ctx ctx, rdm_eig *out, int64_t n, int slices, int ndiag
     OZ_RA(V, mat)
     OZ_RA(P, sizeof(double) * np * kPair)
     OZ_RA(Linv, sizeof(double) * kPair * kPair)
-    OZ_RA(Qt, sizeof(double) * np * kPair)
+    OZ_RA(Qt, 2 * sizeof(double) * np * kPair)
     OZ_RA(off, sizeof(double) * h->rounds * h->npairs * 3)
     OZ_RA(lam, sizeof(double) * np)
     OZ_RA(nrm, sizeof(double) * np)
@@ -560,14 +862,20 @@ int rdm_eig_create(ozaki_ctx ctx, rdm_eig *out, int64_t n, int slices, int ndiag
         }
         std::rotate(a.begin() + 1, a.end() - 1, a.end());
     }
-    std::vector<int> maps(static_cast<size_t>(h->rounds) * h->nb);
+    // maps: the slot a slot's rows come from after round r; dst: the slot its rows go to
+    std::vector<int> maps(static_cast<size_t>(h->rounds) * h->nb), dst(maps.size());
     for (int r = 0; r < h->rounds; ++r) {
         const std::vector<int> &cur = slot_block[r], &nxt = slot_block[(r + 1) % h->rounds];
         std::vector<int> slot_of(h->nb);
         for (int sl = 0; sl < h->nb; ++sl) slot_of[cur[sl]] = sl;
-        for (int sl = 0; sl < h->nb; ++sl) maps[static_cast<size_t>(r) * h->nb + sl] = slot_of[nxt[sl]];
+        for (int sl = 0; sl < h->nb; ++sl) {
+            const int from = slot_of[nxt[sl]];
+            maps[static_cast<size_t>(r) * h->nb + sl] = from;
+            dst[static_cast<size_t>(r) * h->nb + from] = sl;
+        }
     }
-    if ((rc = rupload(h, slot_block[0], &h->slot0)) || (rc = rupload(h, maps, &h->maps))) {
+    if ((rc = rupload(h, slot_block[0], &h->slot0)) || (rc = rupload(h, maps, &h->maps)) ||
+        (rc = rupload(h, dst, &h->dst))) {
         rfree(h);
         return rc;
     }
@@ -583,18 +891,7 @@ int rdm_eig_create(ozaki_ctx ctx, rdm_eig *out, int64_t n, int slices, int ndiag
         rfree(h);
         return rc;
     }
-    if (slices == 0) {
-        std::vector<Term64> tr, tc;
-        for (int k = 0; k < h->npairs; ++k) {
-            const intptr_t ro = static_cast<intptr_t>(kPair) * k * np, co = static_cast<intptr_t>(kPair) * k;
-            tr.push_back(Term64{h->Qt, reinterpret_cast<const double *>(ro), kPair, np, kPair, 0, 1.0});
-            tc.push_back(Term64{h->Qt, reinterpret_cast<const double *>(co), kPair, np, kPair, 0, 1.0});
-        }
-        if ((rc = rupload(h, tr, &h->t_rows)) || (rc = rupload(h, tc, &h->t_cols))) {
-            rfree(h);
-            return rc;
-        }
-    } else {
+    if (slices) {
         if ((rc = ralloc(h, sizeof(int32_t) * np, &p)) != OZ_OK) { rfree(h); return rc; }
         h->eQ = static_cast<int32_t *>(p);
         if ((rc = ralloc(h, static_cast<size_t>(slices) * np * kPair, &p)) != OZ_OK) { rfree(h); return rc; }
@@ -692,13 +989,12 @@ int rdm_eig_solve(rdm_eig h, const double *A, int64_t lda, int64_t nev, double *
     if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "rdm_eig_solve: init");
     int status = OZ_MAX_ITER, sweeps = 0, no_progress = 0;
     double best = INFINITY, last = INFINITY;
-    double *cur = st.X, *other = st.Y;
     h->host_off.resize(static_cast<size_t>(h->rounds) * h->npairs * 3);
     std::vector<double> lam(np), nrm(np);
     // Diagonal of M over the squared basis norms (Rayleigh quotients) and
     // the basis rows inside the first n coordinates (the others are padding).
     auto diagonal = [&](std::vector<int> *rows) -> int {
-        hipLaunchKernelGGL(k_jac_diag, dim3(static_cast<unsigned>(np)), dim3(256), 0, s, cur, st.W, n, np, h->lam,
+        hipLaunchKernelGGL(k_jac_diag, dim3(static_cast<unsigned>(np)), dim3(256), 0, s, st.X, st.W, n, np, h->lam,
                            h->nrm);
         if ((e = hipMemcpyAsync(lam.data(), h->lam, sizeof(double) * np, hipMemcpyDeviceToHost, s)) != hipSuccess ||
             (e = hipMemcpyAsync(nrm.data(), h->nrm, sizeof(double) * np, hipMemcpyDeviceToHost, s)) != hipSuccess ||
@@ -719,19 +1015,25 @@ int rdm_eig_solve(rdm_eig h, const double *A, int64_t lda, int64_t nev, double *
     // Rows whose diagonal is below theta are outside the wanted part: their
     // mutual couplings are exempt from tol (nev = n: none is).  theta is the
     // midpoint of the gap at the nev-th value of the previous sweep.
-    double theta = -INFINITY;
+    // Exempt couplings are rotated away only while a round's block holds more
+    // than its share (exempt_tol2) of the mass that Weyl's bound allows.
+    double theta = -INFINITY, exempt_tol2 = 0.0;
     for (int sw = 0; sw < max_sweeps && fro > 0.0; ++sw) {
-        for (int r = 0; r < h->rounds; ++r) {
-            const int rc = enqueue_round(h, r, cur, other, st.W, st.W2, 0.1 * abs_tol, theta, s);
-            if (rc != OZ_OK) return rc;
-            std::swap(cur, other);
+        int rc = OZ_OK;
+        if (h->S == 0) {
+            rc = sweep_native(h, &st, 0.1 * abs_tol, exempt_tol2, theta, s);
+        } else {
+            for (int r = 0; r < h->rounds && rc == OZ_OK; ++r) {
+                rc = enqueue_round(h, r, st.X, st.Y, st.W, st.W2, 0.1 * abs_tol, exempt_tol2, theta, s);
+                std::swap(st.X, st.Y);
+            }
         }
+        if (rc != OZ_OK) return rc;
         sweeps = sw + 1;
         if ((e = hipMemcpyAsync(h->host_off.data(), h->off, sizeof(double) * h->host_off.size(),
                                 hipMemcpyDeviceToHost, s)) != hipSuccess)
             return hip_fail(e, "rdm_eig_solve: sweep");
-        int rc = diagonal(&rows);
-        if (rc != OZ_OK) return rc;
+        if ((rc = diagonal(&rows)) != OZ_OK) return rc;
         double sum = 0.0, exempt = 0.0;
         last = 0.0;
         for (size_t i = 0; i < h->host_off.size(); i += 3) {
@@ -747,6 +1049,7 @@ int rdm_eig_solve(rdm_eig h, const double *A, int64_t lda, int64_t nev, double *
             const double lo = lam[rows[nev - 1 < 0 ? 0 : nev - 1]], hi = lam[rows[nev]];
             separated = nev == 0 || (hi < theta && theta <= lo && hi + std::sqrt(exempt) < lo);
             theta = nev == 0 ? INFINITY : 0.5 * (lo + hi);
+            exempt_tol2 = nev == 0 ? INFINITY : 0.25 * (lo - hi) * (lo - hi) / (static_cast<double>(h->npairs) * h->rounds);
         }
         if (last <= tol && separated) {
             status = OZ_CONVERGED;

@@ -59,6 +59,21 @@ __device__ __forceinline__ void mul_nt(Acc &acc, const double *sA, const double 
     }
 }
 
+// acc += A B, A row-major along k (stride kLdK), B k-major (stride kLdN)
+__device__ __forceinline__ void mul_nn(Acc &acc, const double *sA, const double *sB) {
+    const int lane = threadIdx.x & 63, l16 = lane & 15, lq = lane >> 4;
+    const double *a = sA + (wave_row() + l16) * kLdK + lq;
+    const double *b = sB + lq * kLdN + wave_col() + l16;
+#pragma unroll
+    for (int kk = 0; kk < 64; kk += 4) {
+        const double a0 = a[kk], a1 = a[16 * kLdK + kk], b0 = b[kk * kLdN], b1 = b[kk * kLdN + 16];
+        acc.c[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0, acc.c[0][0], 0, 0, 0);
+        acc.c[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b1, acc.c[0][1], 0, 0, 0);
+        acc.c[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b0, acc.c[1][0], 0, 0, 0);
+        acc.c[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b1, acc.c[1][1], 0, 0, 0);
+    }
+}
+
 // f(row, column, value) for this lane's 16 elements of the 64 x 64 result
 template <typename F>
 __device__ __forceinline__ void each(const Acc &acc, F f) {
