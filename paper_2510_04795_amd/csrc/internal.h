@@ -92,6 +92,7 @@ enum PairMode : int32_t {
     kModeAccum = 1,    // term list; sigma = +0, then sigma = fma(alpha_t, c_t, sigma)
     kModeQ = 2,        // one term; write the int32 diagonal sums Q[g][i][j]
     kModeQ64 = 3,      // one term over one K chunk; store (qw_first) or add its sums to Qw
+    kModeGemm64 = 4,   // kModeGemm for the last K chunk: its sums are added to Qw's
 };
 
 // Counters of one streamed launch: a tile counter per XCD, then the number
@@ -114,7 +115,7 @@ struct PairArgs {
     int32_t *Q;            // kModeQ output, [G][M][N]
     double *out_base;      // grouped: when set, OutDesc::C holds an element offset from it
     // int64 partial sums [G][tiles_m*BM][tiles_n*BN] of earlier K chunks when
-    // K exceeds the exact int32 range; added in the kModeGemm epilogue if set
+    // K exceeds the exact int32 range; added in the kModeGemm64 epilogue
     int64_t *Qw;
     int64_t qw_ld;         // leading dimension of one Qw plane (tiles_n * BN)
     int64_t qw_plane;      // elements per Qw plane
@@ -186,6 +187,22 @@ struct SliceTask {
     int32_t pad_;
 };
 
+// One operand of a product for launch_slice_operands.  The caller fills X, ld,
+// R, K (R groups of length K), trans (0: stored R x K; 1: stored K x R), e,
+// packed and Rp; the rest is the launch's plan.
+struct OperandTask {
+    const double *X;
+    int64_t ld, R, K;
+    int32_t trans;
+    int32_t wide;        // trans = 0: one block per row instead of one wave
+    int32_t *e;
+    int8_t *packed;
+    int64_t Rp;
+    int32_t *codes;      // trans = 1: [nchunk][R] exponent codes of the row chunks
+    int32_t chunk, nchunk;
+    int32_t eblocks, sblocks;
+};
+
 // ---- launchers ---------------------------------------------------------
 // Shared exponents of each row of X (R x K, row-major, ld): e[r], flag on NaN/Inf.
 hipError_t launch_row_exponents(const double *X, int64_t ld, int64_t R, int64_t K, int32_t *e,
@@ -203,6 +220,11 @@ hipError_t launch_group_sumsq(bool by_rows, const double *X, int64_t ld, int64_t
 // trans = true: X is K x R (groups are columns).  Pads rows to Rp, K to Kp with 0.
 hipError_t launch_slice(int S, bool trans, const double *X, int64_t ld, int64_t R, int64_t K,
                         const int32_t *e, int8_t *packed, int64_t Rp, hipStream_t s);
+// Exponents and slices of both operands of a product (K > 0) in two launches.
+// codes: scratch of col_exponent_scratch(K, max(a.R, b.R)) bytes.  Results as
+// of the separate passes above.
+hipError_t launch_slice_operands(int S, OperandTask a, OperandTask b, int32_t *codes, int num_cu, uint32_t *flag,
+                                 hipStream_t s);
 // Grouped exponent pass (tasks of kExpTaskRows rows or kExpTaskCols columns)
 // and slice pass (tasks of 32 groups x kSliceTaskKB 32-wide K blocks).
 // With emax_base (column tasks split into row chunks of kExpColChunk), the
@@ -224,6 +246,11 @@ hipError_t launch_unpack(int S, const int8_t *packed, int64_t Rp, int64_t R, int
                          int8_t *canon, hipStream_t s);
 
 // Tile variants of the int8 pair GEMM.  v < 0 selects the default variant.
+// kSplitVariant (launch_pair_single in kModeGemm only, 32 x 32 tiles) is the
+// kernel for products of few tiles; pair_split_pays says where ozaki_dgemm
+// takes it when no variant is set.
+constexpr int kSplitVariant = 100;
+bool pair_split_pays(int64_t M, int64_t N, int64_t K, int num_cu);
 struct PairShape { int bm, bn; };
 bool pair_supported(int S, int G);
 int pair_num_variants();

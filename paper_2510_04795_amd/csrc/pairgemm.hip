@@ -14,8 +14,19 @@ bool pair_variant_ok(int G, int v) { return v >= 0 && v < pair::kNumVariants && 
 
 int pair_default_variant(int G) { return pair::default_variant(G); }
 
+// Each 32 x 32 block on a compute unit of its own, and more K blocks than
+// two.  Measured (us, split against 64 x 64 tiles, S = 6 / S = 7 with G = 8):
+// 512 x 512 x 2048 (64 tiles of 64) 36 / 43 against 49 / 63, 128 x 128 x 8192
+// 72 / 87 against 134 / 186; but 640^3 (100 tiles) 29 / 38 against 29 / 34 and
+// 1024^3 (256 tiles) 52 / 75 against 41 / 49, where the larger tile's reuse of
+// its operands counts for more.
+bool pair_split_pays(int64_t M, int64_t N, int64_t K, int num_cu) {
+    return ceil_div(M, 64) * ceil_div(N, 64) * 4 <= num_cu && K > 64;
+}
+
 PairShape pair_shape(int S, int G, int v) {
     (void)S;
+    if (v == kSplitVariant) return PairShape{32, 32};
     if (v < 0) v = pair::default_variant(G);
     return PairShape{pair::variant_bm(v), pair::variant_bn(v)};
 }

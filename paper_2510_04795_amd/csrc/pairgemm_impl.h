@@ -34,6 +34,7 @@
 #pragma once
 
 #include <algorithm>
+#include <type_traits>
 
 #include "internal.h"
 
@@ -614,9 +615,13 @@ __device__ __forceinline__ void pair_mainloop(v16i (&acc)[G][MB][NB], uint4 *lds
 // between groups keeps the registers of only one group live.
 constexpr int kEpilogueGroup = 4;
 
-// FP64 value of one output element from its diagonal sums (plus int64 carries).
-template <int G>
-__device__ __forceinline__ double horner(const long long (&q)[G], int32_t ei, int32_t fj) {
+// FP64 value of one output element from its diagonal sums: int32, or int64
+// with the carries of earlier K chunks.  The types stay apart at compile time
+// (kModeGemm64): a sum widened in case carries are added costs two
+// conversions, an ldexp and an addition instead of one conversion, four
+// times the FP64 instructions of the whole recombination.
+template <int G, typename Q>
+__device__ __forceinline__ double horner(const Q (&q)[G], int32_t ei, int32_t fj) {
     if (ei == kExpBad || fj == kExpBad) return __longlong_as_double(0x7ff8000000000000ll);
     double h = static_cast<double>(q[G - 1]);
 #pragma unroll
@@ -781,16 +786,16 @@ __device__ __forceinline__ void pair_tile(const PairArgs &a, GetTerm get_term, i
                             *p = a.qw_first ? v : *p + v;
                         }
                     } else if (ok) {
-                        long long q[G];
+                        std::conditional_t<MODE == kModeGemm64, long long, int> q[G];
 #pragma unroll
                         for (int g = 0; g < G; ++g) q[g] = acc[g][mb][nb][r];
-                        if (MODE == kModeGemm && a.Qw) {
+                        if (MODE == kModeGemm64) {
                             const int64_t idx = static_cast<int64_t>(i) * a.qw_ld + j;
 #pragma unroll
                             for (int g = 0; g < G; ++g) q[g] += a.Qw[g * a.qw_plane + idx];
                         }
                         const double c = horner<G>(q, ei[r], fj);
-                        if (MODE == kModeGemm) {
+                        if (MODE == kModeGemm || MODE == kModeGemm64) {
                             double *p = out.C + static_cast<int64_t>(i) * out.ldc + j;
                             const double v = (a.beta == 0.0) ? T.alpha * c : fma(T.alpha, c, a.beta * *p);
                             *p = v;
@@ -1615,6 +1620,97 @@ __global__ __launch_bounds__(64 * WM * WN) void k_pair_single(PairArgs a, int ti
                                           tn * C::BN, lds0, lds1, lds2);
 }
 
+// ---- split kernel for products of few tiles --------------------------------
+// One 32 x 32 output block per workgroup; its four waves take every fourth K
+// block each, so a product with few tiles still gives every SIMD work and a
+// wave's chain is a quarter as long.  A lane's operand fragments are 16
+// consecutive bytes of the packed planes (a wave reads two 512-byte runs per
+// slice), so they come straight from memory into registers, the next block's
+// behind the current one's MFMAs; nothing goes through LDS but the partial
+// sums.  These are int32 and exact, so adding the four waves' sums gives the
+// same bits in any order.  Bound: latency (a load, the MFMAs of K / 128
+// blocks, the recombination); measured against the 64 x 64 tile in
+// split_pays.
+template <int S, int G>
+__device__ __forceinline__ void split_load(Frags<S, G, 1, 1> &f, const int8_t *A, const int8_t *B, int64_t a_run,
+                                           int64_t b_run) {
+#pragma unroll
+    for (int s = 0; s < Frags<S, G, 1, 1>::T; ++s) {
+        f.a[s][0] = *reinterpret_cast<const v4i *>(A + 2 * s * a_run);
+        f.b[s][0] = *reinterpret_cast<const v4i *>(B + 2 * s * b_run);
+    }
+}
+
+template <int S, int G>
+__global__ __launch_bounds__(256) void k_pair_split(PairArgs a, int tiles_m) {
+    constexpr int PP = G <= 13 ? 4 : 2;  // 12 G KiB of LDS for all four
+    __shared__ int red[PP][3][G * 4][64];
+    int tm, tn;
+    tile_coords(blockIdx.x, tiles_m, a.tiles_n, 8, tm, tn);
+    const int m0 = tm * 32, n0 = tn * 32;
+    const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const TermDesc T = a.term;
+    const int64_t a_run = T.a_rows_p * 16, b_run = T.b_rows_p * 16;
+    const int8_t *A = T.A + half * a_run + static_cast<int64_t>(m0 + l32) * 16;
+    const int8_t *B = T.B + half * b_run + static_cast<int64_t>(n0 + l32) * 16;
+    v16i acc[G][1][1];
+#pragma unroll
+    for (int g = 0; g < G; ++g) acc[g][0][0] = v16i{};
+    const int j = n0 + l32;
+    const bool jok = j < a.out.N;
+    const int32_t fj = jok ? T.f[j] : 0;
+    int32_t ei[4];  // this wave finishes rows 8 wave + 4 half + 0..3 of the block
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int i = m0 + 8 * wave + 4 * half + q;
+        ei[q] = i < a.out.M ? T.e[i] : 0;
+    }
+    Frags<S, G, 1, 1> cur, nxt;
+    if (wave < T.kblocks) split_load<S, G>(cur, A + wave * 2 * S * a_run, B + wave * 2 * S * b_run, a_run, b_run);
+    for (int kb = wave; kb < T.kblocks; kb += 4) {
+        if (kb + 4 < T.kblocks)
+            split_load<S, G>(nxt, A + (kb + 4) * 2 * S * a_run, B + (kb + 4) * 2 * S * b_run, a_run, b_run);
+        mfma_pairs<true, S, G, 1, 1>(acc, cur);
+        mfma_pairs<false, S, G, 1, 1>(acc, cur);
+        cur = nxt;
+    }
+    // wave p adds the other waves' sums of its rows (accumulators 4 p .. 4 p +
+    // 3) and finishes them; all four at once while their sums fit in LDS
+#pragma unroll
+    for (int p0 = 0; p0 < 4; p0 += PP) {
+        if (p0) __syncthreads();
+#pragma unroll
+        for (int p = p0; p < p0 + PP; ++p) {
+            if (wave == p) continue;
+            const int slot = wave < p ? wave : wave - 1;
+#pragma unroll
+            for (int g = 0; g < G; ++g)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) red[p - p0][slot][g * 4 + q][lane] = acc[g][0][0][4 * p + q];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int p = p0; p < p0 + PP; ++p) {
+            if (wave != p) continue;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                int s[G];
+#pragma unroll
+                for (int g = 0; g < G; ++g)
+                    s[g] = acc[g][0][0][4 * p + q] + red[p - p0][0][g * 4 + q][lane] +
+                           red[p - p0][1][g * 4 + q][lane] + red[p - p0][2][g * 4 + q][lane];
+                const int i = m0 + 8 * p + 4 * half + q;
+                if (jok && i < a.out.M) {
+                    const double c = horner<G>(s, ei[q], fj);
+                    double *o = a.out.C + static_cast<int64_t>(i) * a.out.ldc + j;
+                    *o = (a.beta == 0.0) ? T.alpha * c : fma(T.alpha, c, a.beta * *o);
+                }
+            }
+        }
+    }
+}
+
 // One block per listed tile (the list is in the XCD order the plan builds).
 template <int S, int G, int WM, int WN, int MB, int NB, int MODE>
 __global__ __launch_bounds__(64 * WM * WN) void k_pair_grouped(PairArgs a) {
@@ -1661,8 +1757,13 @@ __host__ __device__ constexpr bool variant_fits(int G, int v) {
 }
 __host__ __device__ constexpr int variant_bm(int v) { return variant_wm(v) * variant_mb(v) * 32; }
 __host__ __device__ constexpr int variant_bn(int v) { return variant_wn(v) * variant_nb(v) * 32; }
-// default before tuning: the 128 x 64 four-wave tile where it fits
-__host__ __device__ constexpr int default_variant(int G) { return variant_fits(G, 1) ? 1 : 0; }
+// Default before tuning: 64 x 64 from G = 4, the 8-wave 128 x 64 tile below.
+// Measured over ten shapes from 512^3 to 4096^3 and 8192 x 8192 x 512: from
+// G = 5 the 64 x 64 ring is the fastest or within 5 % everywhere (S = 6,
+// 1024^3: 43 us against 61 for 128 x 64 in four waves, 51 for the 8-wave
+// tiles); with few slices a block is too little work per barrier for it
+// (S = 3, 4096^3: 591 us against 481).
+__host__ __device__ constexpr int default_variant(int G) { return G <= 3 ? 3 : 0; }
 
 template <int S, int G, int V>
 hipError_t run_single_v(const PairArgs &a, int tiles_m, hipStream_t s) {
@@ -1687,6 +1788,13 @@ hipError_t run_single_v(const PairArgs &a, int tiles_m, hipStream_t s) {
             case kModeQ64:
                 if constexpr (V == 0) {
                     hipLaunchKernelGGL((k_pair_single<S, G, WM, WN, MB, NB, kModeQ64>), dim3(grid), dim3(NT), 0, s, a, tiles_m);
+                } else {
+                    return hipErrorInvalidValue;
+                }
+                break;
+            case kModeGemm64:
+                if constexpr (V == 0) {
+                    hipLaunchKernelGGL((k_pair_single<S, G, WM, WN, MB, NB, kModeGemm64>), dim3(grid), dim3(NT), 0, s, a, tiles_m);
                 } else {
                     return hipErrorInvalidValue;
                 }
@@ -1790,6 +1898,13 @@ int resident_per_cu(int v) {
 
 template <int S, int G>
 hipError_t run_single(int v, const PairArgs &a, int tiles_m, hipStream_t s) {
+    if (v == kSplitVariant) {
+        if (a.mode != kModeGemm) return hipErrorInvalidValue;
+        const unsigned grid = static_cast<unsigned>(tiles_m) * static_cast<unsigned>(a.tiles_n);
+        if (grid == 0) return hipSuccess;
+        hipLaunchKernelGGL((k_pair_split<S, G>), dim3(grid), dim3(256), 0, s, a, tiles_m);
+        return hipGetLastError();
+    }
     switch (v) {
         case 0: return run_single_v<S, G, 0>(a, tiles_m, s);
         case 1: return run_single_v<S, G, 1>(a, tiles_m, s);

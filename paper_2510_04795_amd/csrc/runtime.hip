@@ -428,16 +428,22 @@ int ozaki_dgemm(ozaki_ctx ctx, char transa, char transb, int64_t M, int64_t N, i
 
     // op(A) rows are stored rows when transa = 'N'; op(B) columns are stored rows when transb = 'T'
     hipEvent_t t0 = mark(ctx, s);
-    if ((e = slice_operand(slices, !ta, A, lda, M, K, ev, adig, part, ctx->d_flags, s)) != hipSuccess)
-        return hip_fail(e, "ozaki_dgemm: slicing A");
-    if ((e = slice_operand(slices, tb, B, ldb, N, K, fv, bdig, part, ctx->d_flags, s)) != hipSuccess)
-        return hip_fail(e, "ozaki_dgemm: slicing B");
+    // one launch per pass for both operands, up to what one grid dimension of
+    // 256-thread blocks can hold; beyond that the launches no longer matter
+    if (K > 0 && (Mp + Np) / kRowQ * (Kp / kKB) <= (1 << 23)) {
+        const OperandTask oa{A, lda, M, K, ta, 0, ev, adig, Mp}, ob{B, ldb, N, K, !tb, 0, fv, bdig, Np};
+        e = launch_slice_operands(slices, oa, ob, reinterpret_cast<int32_t *>(part), ctx->num_cu, ctx->d_flags, s);
+    } else if ((e = slice_operand(slices, !ta, A, lda, M, K, ev, adig, part, ctx->d_flags, s)) == hipSuccess) {
+        e = slice_operand(slices, tb, B, ldb, N, K, fv, bdig, part, ctx->d_flags, s);
+    }
+    if (e != hipSuccess) return hip_fail(e, "ozaki_dgemm: slicing");
 
     hipEvent_t t1 = mark(ctx, s);
     phase(ctx, OZ_PHASE_SLICE, t0, t1);
     const int64_t kmax = max_exact_k(slices, G);
     // the int64 carries between K chunks are built for the 64 x 64 tile only
-    const int var = K > kmax ? 0 : ctx_variant(ctx, slices, G);
+    const bool split = K <= kmax && ctx->variant[slices][G] < 0 && pair_split_pays(M, N, K, ctx->num_cu);
+    const int var = K > kmax ? 0 : split ? kSplitVariant : ctx_variant(ctx, slices, G);
     const PairShape sh = pair_shape(slices, G, var);
     PairArgs a{};
     a.tiles_n = static_cast<int32_t>(ceil_div(N, sh.bn));
@@ -460,7 +466,7 @@ int ozaki_dgemm(ozaki_ctx ctx, char transa, char transb, int64_t M, int64_t N, i
             c.term.B = bdig + kb0 * 2 * slices * Np * 16;
             c.term.kblocks = static_cast<int32_t>(n);
             const bool last = kb0 + n >= nkb;
-            c.mode = last ? kModeGemm : kModeQ64;
+            c.mode = last ? kModeGemm64 : kModeQ64;
             c.qw_first = kb0 == 0;
             c.Qw = qw;
             if ((e = launch_pair_single(slices, G, var, c, tiles_m, s)) != hipSuccess)

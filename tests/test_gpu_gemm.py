@@ -388,3 +388,43 @@ def test_binding_checks_output_shapes(oz):
     with pytest.raises(ValueError):
         ctx.renormalize(U24, ops, outs=[torch.empty((8, 7), dtype=torch.float64, device="cuda") for _ in ops])
 
+
+
+@pytest.mark.parametrize("K", [1, 64, 65, 255, 256, 257, 1025, 2177])
+@pytest.mark.parametrize("ta,tb", ["NN", "TN", "NT", "TT"])
+def test_operand_passes_and_split_kernel(oz, K, ta, tb):
+    """The default route (no variant set) at the edges of its launches: groups
+    of up to 256 elements (exponents and slices in one launch) and above, row
+    groups a block wide (K >= 1024), column codes reduced in the slice blocks
+    and by the extra launch (more than 16 chunks: K = 2177), the split kernel
+    (K > 64) and the 64 x 64 tiles; odd leading dimensions and a base off 16
+    bytes, zero groups, subnormals, NaN and Inf.  Bit for bit the oracle's."""
+    ozaki, ctx, torch = oz
+    rng = np.random.default_rng(K * 4 + 2 * (ta == "T") + (tb == "T"))
+    M, N, S, G = {1: (33, 65, 2, 3), 64: (64, 31, 8, 15), 65: (65, 33, 6, 6), 255: (31, 97, 7, 8), 256: (96, 160, 5, 5),
+                  257: (129, 34, 4, 4), 1025: (32, 130, 3, 5), 2177: (70, 40, 8, 9)}[K]
+
+    def operand(rows, cols, odd):
+        X = wl.wide_normal(rng, (rows, cols), 10)
+        X[rng.random(X.shape) < 0.05] = 0.0
+        X[rows // 2, :] = 0.0
+        X[0, cols // 2] = 5e-324
+        if rows > 3 and cols > 3:
+            X[2, 1] = np.nan
+            X[3, 3] = -np.inf
+        buf = torch.zeros(rows * (cols + odd) + 1, dtype=torch.float64, device="cuda")
+        view = buf[1 if odd else 0:][: rows * (cols + odd)].view(rows, cols + odd)[:, :cols]
+        view.copy_(torch.from_numpy(X))
+        return X, view
+
+    A, dA = operand(*((K, M) if ta == "T" else (M, K)), odd=1)
+    B, dB = operand(*((N, K) if tb == "T" else (K, N)), odd=0)
+    C0 = wl.wide_normal(rng, (M, N), 10)
+    for alpha, beta in ((1.0, 0.0), (0.5, -2.0)):
+        C = dev(torch, C0)
+        ctx.flags()
+        ctx.dgemm(dA, dB, slices=S, ndiag=G, alpha=alpha, beta=beta, C=C, transa=ta, transb=tb)
+        bad = bool(np.isnan(A).any() or np.isinf(A).any() or np.isnan(B).any() or np.isinf(B).any())
+        assert bool(ctx.flags() & ozaki.OZ_FLAG_NONFINITE) == bad
+        ref = oracle.ozaki_dgemm(A, B, S, G, alpha=alpha, beta=beta, C=C0, transa=ta, transb=tb)
+        assert_bitexact(C.cpu().numpy(), ref)
