@@ -8,14 +8,37 @@
 // holds C[4 r + l / 16][l % 16].
 //
 // Tile: 256 threads = 2 x 2 waves of BM/2 x BM/2 outputs in blocks of 16 x 16;
-// BM = 128 (each wave 4 x 4 blocks, 64 FP64 accumulators per lane) for large
-// problems and the grouped H_eff phases, BM = 64 when the 128 tiles would
-// not give every compute unit two workgroups.  K advances 16 at a time
-// through two LDS buffers: the next step's operands are loaded into
-// registers while the current step is multiplied, then stored to the other
-// buffer, one barrier per step.  LDS rows are k-major and padded by four
-// doubles so the four k rows a wave reads at once fall in different banks;
-// the thread layout of the staging keeps the LDS stores conflict free.
+// BM = 128 (each wave 4 x 4 blocks, 64 FP64 accumulators per lane) or 64, as
+// dgemm_tile_for says.  K advances 16 at a time through two LDS stages filled
+// by direct global->LDS 16-byte loads (two doubles per lane, no staging
+// registers, one barrier a step), and the matrix cores run from fragments in
+// registers: at BM = 64 those of the next step are read behind the products
+// of this one (two sets, four workgroups per compute unit), at 128 after the
+// step's barrier (one set, two workgroups).  Bound: the matrix cores, 16
+// products of 64 cycles per wave and step at BM = 64 (8192^3: 72 TFLOP/s
+// against 64 with staging registers and strided 32-byte loads; 2048^3, B
+// transposed: 258 us against 288; the FP64 block-sparse H_eff of 40 sectors
+// 3.5 ms against 4.7).  Products of few tiles take k_dgemm_split below.
+//
+// Order of k.  Both operands hand lane (l16, lq) the elements k = 8 g + 2 lq
+// + s in the s-th product of group g, so an operand stored along K is read
+// two elements (16 bytes) at a time.
+//
+// LDS layout, in 16-byte chunks (where a chunk lands is the loading lane's
+// place, what it holds is the lane's choice of address):
+//   stored along K (op(A) = A, op(B) = B^T): eight chunks per row, the pair of
+//     k at place pair ^ ((row / 2) % 8), so the 16 rows a read takes fall in
+//     16 different places modulo 256 bytes;
+//   stored across K (op(A) = A^T, op(B) = B): BM / 2 chunks per k, the pair of
+//     rows at place pair ^ 8 ((k / 2) % 2), so the two k a half wave reads
+//     fall in different halves of the banks.
+// A workgroup of eight lanes (along) or of BM / 2 lanes (across) loads whole
+// 128-byte lines.  Rows past the operand are clamped to its last row (they
+// only feed outputs that are never stored); a last step that K does not fill,
+// or whose last pair would run past the end of the stored matrix, goes
+// through registers element by element.
+#include <type_traits>
+
 #include "internal.h"
 
 namespace oz {
@@ -25,118 +48,131 @@ typedef double v4d __attribute__((ext_vector_type(4)));
 
 constexpr int kBK = 16;
 
-// Tile geometry for a BM x BM tile.
-template <int BM>
+typedef __attribute__((address_space(3))) void lds_void;
+constexpr int kBufferDword3 = 0x00020000;  // raw buffer, 32-bit data format
+
+// Loads of one operand of a tile, E rows of A or columns of B.
+template <int E>
 struct Geo {
-    static constexpr int LD = BM + 4;            // padded LDS row (doubles): the 4 k rows a wave reads shift banks
-    static constexpr int PER = BM * kBK / 256;   // doubles per thread per operand and K step
-    static constexpr int NB = BM / 32;           // 16 x 16 blocks per wave and dimension
-    static constexpr int LDS = 4 * kBK * LD;     // two buffers of A and B
+    static constexpr int CH = E * kBK / 2 / 256;    // 16-byte chunks per thread and step
 };
 
-// Global -> register staging of one K step.  Two thread layouts, chosen by
-// which dimension of the stored operand is contiguous:
-//   along K  (op(A) = A, op(B) = B^T): thread t takes PER consecutive k of
-//            row t % BM; the LDS stores of a wave then cover 64 consecutive
-//            rows of one k row (no bank conflicts);
-//   across K (op(A) = A^T, op(B) = B): thread t takes PER consecutive rows /
-//            columns ((t % 16) PER) of k row t / 16: contiguous runs.
-// LDS holds both operands k-major: s[k][row] with rows padded to LD.
-template <int PER>
-__device__ __forceinline__ void fetch_run(double (&r)[PER], const double *p, bool full, int valid) {
-    if (full) {
-#pragma unroll
-        for (int q = 0; q < PER; q += 2) {
-            double2 v;
-            __builtin_memcpy(&v, p + q, sizeof(v));
-            r[q] = v.x;
-            r[q + 1] = v.y;
+// One operand of a tile: `rows` rows (or columns) from r0, inner length K.
+// ALONG: element (i, k) at X[i * ld + k]; else at X[k * ld + i].
+template <int BM, bool ALONG>
+struct Operand {
+    using Gm = Geo<BM>;
+    static constexpr int PR = kBK / 2;  // pairs of k per row
+    const double *X;
+    int64_t ld;
+    int rows, K, r0;
+    int voff[Gm::CH];  // byte offset of the thread's chunks from the step's base
+    int nfast;         // steps that take the direct loads
+
+    __device__ __forceinline__ void place(int i, int &row, int &k) const {
+        const int c = i * 256 + threadIdx.x;
+        if (ALONG) {
+            row = c / PR;
+            k = 2 * ((c % PR) ^ ((row >> 1) & 7));
+        } else {
+            k = c / (BM / 2);
+            row = 2 * ((c % (BM / 2)) ^ (8 * ((k >> 1) & 1)));
         }
-    } else {
-#pragma unroll
-        for (int q = 0; q < PER; ++q) r[q] = q < valid ? p[q] : 0.0;
     }
-}
 
-// rows x K operand stored with K contiguous (row i, k at X[i * ld + k])
-template <int BM>
-__device__ __forceinline__ void fetch_along_k(double (&r)[Geo<BM>::PER], const double *X, int64_t ld, int rows,
-                                              int K, int r0, int k0) {
-    constexpr int PER = Geo<BM>::PER;
-    const int t = threadIdx.x;
-    const int i = r0 + t % BM, k = k0 + (t / BM) * PER;
-    const int valid = i < rows ? (K - k < PER ? K - k : PER) : 0;
-    fetch_run<PER>(r, X + static_cast<int64_t>(i < rows ? i : 0) * ld + (valid > 0 ? k : 0), valid == PER, valid);
-}
-
-template <int BM>
-__device__ __forceinline__ void store_along_k(const double (&r)[Geo<BM>::PER], double *s) {
-    constexpr int PER = Geo<BM>::PER;
-    const int t = threadIdx.x;
-    const int i = t % BM, k = (t / BM) * PER;
+    __device__ __forceinline__ void init(const double *x, int64_t l, int n, int kk, int first) {
+        X = x;
+        ld = l;
+        rows = n;
+        K = kk;
+        r0 = first;
+        // 32-bit offsets within a step
+        const bool near = ld < (int64_t(1) << 31) / 8 / (ALONG ? BM : 2 * kBK);
+        // pairs of rows across K: the very last pair of an odd count would run
+        // past the stored matrix
+        nfast = !near ? 0 : (ALONG || (rows & 1) == 0) ? K / kBK : (K > 0 ? (K - 1) / kBK : 0);
 #pragma unroll
-    for (int q = 0; q < PER; ++q) s[(k + q) * Geo<BM>::LD + i] = r[q];
-}
+        for (int i = 0; i < Gm::CH; ++i) {
+            int row, k;
+            place(i, row, k);
+            if (ALONG) {
+                const int r = r0 + row < rows ? row : rows - 1 - r0;
+                voff[i] = static_cast<int>(r * ld * 8) + k * 8;
+            } else {
+                const int last = (rows - 1) & ~1;
+                const int r = r0 + row < last ? row : last - r0;
+                voff[i] = static_cast<int>(k * ld * 8) + r * 8;
+            }
+        }
+    }
 
-// K x cols operand stored with cols contiguous (k, col j at X[k * ld + j])
-template <int BM>
-__device__ __forceinline__ void fetch_across_k(double (&r)[Geo<BM>::PER], const double *X, int64_t ld, int cols,
-                                               int K, int c0, int k0) {
-    constexpr int PER = Geo<BM>::PER;
-    const int t = threadIdx.x;
-    const int k = k0 + (t >> 4), j = c0 + (t & 15) * PER;
-    const int valid = k < K ? (cols - j < PER ? cols - j : PER) : 0;
-    fetch_run<PER>(r, X + static_cast<int64_t>(k < K ? k : 0) * ld + (valid > 0 ? j : 0), valid == PER, valid);
-}
-
-template <int BM>
-__device__ __forceinline__ void store_across_k(const double (&r)[Geo<BM>::PER], double *s) {
-    constexpr int PER = Geo<BM>::PER;
-    const int t = threadIdx.x;
-    const int k = t >> 4, j = (t & 15) * PER;
+    __device__ __forceinline__ void issue(double *stage, int step) const {
+        const double *base = ALONG ? X + static_cast<int64_t>(r0) * ld + step * kBK
+                                   : X + static_cast<int64_t>(step) * kBK * ld + r0;
+        const __amdgpu_buffer_rsrc_t rs =
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<double *>(base), 0, 0x7fffffff, kBufferDword3);
+        const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 #pragma unroll
-    for (int q = 0; q < PER; ++q) s[k * Geo<BM>::LD + j + q] = r[q];
+        for (int i = 0; i < Gm::CH; ++i)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void *)(stage + (i * 256 + wave * 64) * 2), 16, voff[i],
+                                                     0, 0, 0);
+    }
+
+    // The same step element by element, zero past K and past the rows.
+    __device__ __forceinline__ void copy(double *stage, int step) const {
+#pragma unroll
+        for (int i = 0; i < Gm::CH; ++i) {
+            int row, k;
+            place(i, row, k);
+            k += step * kBK;
+            row += r0;
+            double2 v{0.0, 0.0};
+            if (ALONG) {
+                const double *p = X + static_cast<int64_t>(row) * ld + k;
+                if (row < rows && k < K) v.x = p[0];
+                if (row < rows && k + 1 < K) v.y = p[1];
+            } else {
+                const double *p = X + static_cast<int64_t>(k) * ld + row;
+                if (k < K && row < rows) v.x = p[0];
+                if (k < K && row + 1 < rows) v.y = p[1];
+            }
+            *reinterpret_cast<double2 *>(stage + (i * 256 + threadIdx.x) * 2) = v;
+        }
+    }
+};
+
+// This wave's fragments of one stage: [group of eight k][block], elements s = 0, 1.
+template <int E, bool ALONG>
+__device__ __forceinline__ void read_frags(double2 (&f)[2][E / 32], const double *stage, int wbase) {
+    constexpr int NB = E / 32, PR = kBK / 2;
+    const int lane = threadIdx.x & 63, lq = lane >> 4, l16 = lane & 15;
+#pragma unroll
+    for (int g = 0; g < 2; ++g)
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            if (ALONG) {
+                const int row = wbase + b * 16 + l16;
+                f[g][b] = *reinterpret_cast<const double2 *>(
+                    stage + (row * PR + ((4 * g + lq) ^ ((l16 >> 1) & 7))) * 2);
+            } else {
+                const int pair = wbase / 2 + 8 * (b ^ (lq & 1)) + (l16 >> 1);
+                const double *p = stage + ((8 * g + 2 * lq) * (E / 2) + pair) * 2 + (l16 & 1);
+                f[g][b].x = p[0];
+                f[g][b].y = p[E];
+            }
+        }
 }
 
-template <int BM, bool TA>
-__device__ __forceinline__ void fetch_a(double (&ra)[Geo<BM>::PER], const double *A, int64_t lda, int M, int K,
-                                        int m0, int k0) {
-    if (!TA) fetch_along_k<BM>(ra, A, lda, M, K, m0, k0);
-    else fetch_across_k<BM>(ra, A, lda, M, K, m0, k0);
-}
-
-template <int BM, bool TA>
-__device__ __forceinline__ void store_a(const double (&ra)[Geo<BM>::PER], double *sA) {
-    if (!TA) store_along_k<BM>(ra, sA);
-    else store_across_k<BM>(ra, sA);
-}
-
-template <int BM, bool TB>
-__device__ __forceinline__ void fetch_b(double (&rb)[Geo<BM>::PER], const double *B, int64_t ldb, int N, int K,
-                                        int n0, int k0) {
-    if (TB) fetch_along_k<BM>(rb, B, ldb, N, K, n0, k0);
-    else fetch_across_k<BM>(rb, B, ldb, N, K, n0, k0);
-}
-
-template <int BM, bool TB>
-__device__ __forceinline__ void store_b(const double (&rb)[Geo<BM>::PER], double *sB) {
-    if (TB) store_along_k<BM>(rb, sB);
-    else store_across_k<BM>(rb, sB);
-}
-
-template <int BM, bool TA, bool TB, int MODE, typename GetTerm>
+template <int BM, int BN, bool TA, bool TB, int MODE, typename GetTerm>
 __device__ __forceinline__ void dgemm_tile(const Dgemm64Args &a, GetTerm get_term, int tb, int te,
                                            const OutDesc &out, int m0, int n0, double *lds) {
-    using Gm = Geo<BM>;
-    constexpr int LD = Gm::LD, PER = Gm::PER, NB = Gm::NB;
+    constexpr int MB = BM / 32, NB = BN / 32, OPA = BM * kBK, STAGE = OPA + BN * kBK;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave >> 1;
     const int wn = wave & 1;
     const int lq = lane >> 4;   // 0..3
     const int l16 = lane & 15;
-    // buffer b: A at lds + b * 2 kBK LD, B right after it
-    constexpr int kBuf = 2 * kBK * LD;
 
     // Accumulating mode: the tile's output elements hold the running sum,
     // sigma = fma(alpha_t, c_t, sigma) after every term in list order (the
@@ -148,69 +184,99 @@ __device__ __forceinline__ void dgemm_tile(const Dgemm64Args &a, GetTerm get_ter
     if (MODE == kModeAccum && tb == te) {
         if (out.cont) return;  // nothing to add to the stored sum
 #pragma unroll
-        for (int mb = 0; mb < NB; ++mb)
+        for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const int i = m0 + wm * (BM / 2) + mb * 16 + 4 * r + lq;
-                    const int j = n0 + wn * (BM / 2) + nb * 16 + l16;
+                    const int j = n0 + wn * (BN / 2) + nb * 16 + l16;
                     if (i < out.M && j < out.N) out.C[static_cast<int64_t>(i) * out.ldc + j] = 0.0;
                 }
         return;
     }
     for (int ti = tb; ti < tend; ++ti) {
         const Term64 T = get_term(ti);
-        v4d acc[NB][NB];
+        v4d acc[MB][NB];
 #pragma unroll
-        for (int mb = 0; mb < NB; ++mb)
+        for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = v4d{0.0, 0.0, 0.0, 0.0};
-        const int K = T.K;
-        const int nk = (K + kBK - 1) / kBK;
-        double ra[PER], rb[PER];
+        const int nk = (T.K + kBK - 1) / kBK;
+        Operand<BM, !TA> oa;
+        Operand<BN, TB> ob;
+        oa.init(T.A, T.lda, out.M, T.K, m0);
+        ob.init(T.B, T.ldb, out.N, T.K, n0);
+        auto load = [&](int step) {
+            double *stage = lds + (step & 1) * STAGE;
+            if (step < oa.nfast) oa.issue(stage, step);
+            else oa.copy(stage, step);
+            if (step < ob.nfast) ob.issue(stage + OPA, step);
+            else ob.copy(stage + OPA, step);
+        };
+        // PRE: two sets of fragments, read a step ahead of their products; the
+        // 128 x 128 tile has registers for one, read after its step's barrier.
+        constexpr bool PRE = MB * NB <= 4;
+        double2 fa[PRE ? 2 : 1][2][MB], fb[PRE ? 2 : 1][2][NB];
+        auto read = [&](auto F, int step) {
+            constexpr int f = decltype(F)::value;
+            const double *stage = lds + (step & 1) * STAGE;
+            read_frags<BM, !TA>(fa[f], stage, wm * (BM / 2));
+            read_frags<BN, TB>(fb[f], stage + OPA, wn * (BN / 2));
+        };
+        // Step ks with its fragments in set F.  PRE: once step ks + 1 has landed
+        // in every wave, its fragments go to the other set and the loads of step
+        // ks + 2 start into the stage step ks came from (in registers since the
+        // step before); else once step ks has landed, its own fragments are
+        // read and the loads of step ks + 1 start.  Both run behind the products.
+        auto step = [&](auto F, int ks) {
+            constexpr int f = decltype(F)::value;
+            if (!PRE || ks + 1 < nk) {
+                __builtin_amdgcn_s_waitcnt(0);
+                __syncthreads();
+                if constexpr (PRE) read(std::integral_constant<int, 1 - f>{}, ks + 1);
+                else read(F, ks);
+                if (ks + (PRE ? 2 : 1) < nk) load(ks + (PRE ? 2 : 1));
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int g = 0; g < 2; ++g)
+#pragma unroll
+                for (int s = 0; s < 2; ++s)
+#pragma unroll
+                    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                        for (int nb = 0; nb < NB; ++nb)
+                            acc[mb][nb] = __builtin_amdgcn_mfma_f64_16x16x4f64(
+                                s ? fa[f][g][mb].y : fa[f][g][mb].x, s ? fb[f][g][nb].y : fb[f][g][nb].x, acc[mb][nb],
+                                0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        };
         if (nk > 0) {
-            fetch_a<BM, TA>(ra, T.A, T.lda, out.M, K, m0, 0);
-            fetch_b<BM, TB>(rb, T.B, T.ldb, out.N, K, n0, 0);
             __syncthreads();  // the previous term / tile may still read LDS
-            store_a<BM, TA>(ra, lds);
-            store_b<BM, TB>(rb, lds + kBK * LD);
-            __syncthreads();
+            load(0);
+            if constexpr (PRE) {
+                if (nk > 1) load(1);
+                __builtin_amdgcn_s_waitcnt(0);
+                __syncthreads();
+                read(std::integral_constant<int, 0>{}, 0);
+            }
         }
-        for (int ks = 0; ks < nk; ++ks) {
-            const int cur = ks & 1;
-            if (ks + 1 < nk) {
-                fetch_a<BM, TA>(ra, T.A, T.lda, out.M, K, m0, (ks + 1) * kBK);
-                fetch_b<BM, TB>(rb, T.B, T.ldb, out.N, K, n0, (ks + 1) * kBK);
-            }
-            const double *cA = lds + cur * kBuf;
-            const double *cB = cA + kBK * LD;
-#pragma unroll
-            for (int kk = 0; kk < kBK / 4; ++kk) {
-                double af[NB], bf[NB];
-#pragma unroll
-                for (int mb = 0; mb < NB; ++mb) af[mb] = cA[(kk * 4 + lq) * LD + wm * (BM / 2) + mb * 16 + l16];
-#pragma unroll
-                for (int nb = 0; nb < NB; ++nb) bf[nb] = cB[(kk * 4 + lq) * LD + wn * (BM / 2) + nb * 16 + l16];
-#pragma unroll
-                for (int mb = 0; mb < NB; ++mb)
-#pragma unroll
-                    for (int nb = 0; nb < NB; ++nb)
-                        acc[mb][nb] = __builtin_amdgcn_mfma_f64_16x16x4f64(af[mb], bf[nb], acc[mb][nb], 0, 0, 0);
-            }
-            if (ks + 1 < nk) {
-                store_a<BM, TA>(ra, lds + (cur ^ 1) * kBuf);
-                store_b<BM, TB>(rb, lds + (cur ^ 1) * kBuf + kBK * LD);
-            }
-            __syncthreads();
+        constexpr std::integral_constant<int, 0> set0{};
+        constexpr std::integral_constant<int, PRE ? 1 : 0> set1{};
+        int ks = 0;
+        for (; ks + 2 <= nk; ks += 2) {
+            step(set0, ks);
+            step(set1, ks + 1);
         }
+        if (ks < nk) step(set0, ks);
         // the output base is opaque to the optimiser here, so the 16 NB^2
         // element addresses are formed per term instead of being hoisted out
         // of the term loop (where they would not fit in registers)
         double *cbase = out.C;
         asm volatile("" : "+s"(cbase));
 #pragma unroll
-        for (int mb = 0; mb < NB; ++mb)
+        for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
@@ -218,7 +284,7 @@ __device__ __forceinline__ void dgemm_tile(const Dgemm64Args &a, GetTerm get_ter
                     // one element's read-modify-write at a time in registers
                     __builtin_amdgcn_sched_barrier(0);
                     const int i = m0 + wm * (BM / 2) + mb * 16 + 4 * r + lq;
-                    const int j = n0 + wn * (BM / 2) + nb * 16 + l16;
+                    const int j = n0 + wn * (BN / 2) + nb * 16 + l16;
                     if (i >= out.M || j >= out.N) continue;
                     const double c = acc[mb][nb][r];
                     double *p = cbase + static_cast<int64_t>(i) * out.ldc + j;
@@ -245,25 +311,33 @@ __device__ __forceinline__ void tile_order(int b, int tiles_m, int tiles_n, int 
     tn = w / rows;
 }
 
-template <int BM, bool TA, bool TB>
-__global__ __launch_bounds__(256, 2) void k_dgemm_single(Dgemm64Args a, int tiles_m) {
-    __shared__ double lds[Geo<BM>::LDS];
+// Workgroups per compute unit the registers are kept for: four of the 64 x 64
+// tiles (128 registers a wave; with three, a product of exactly four tiles per
+// compute unit runs them in two rounds: 2048^3 in 358 us instead of 250), two
+// of the 128 x 128 and of the accumulating mode, whose term loop keeps more
+// live (with 128 registers it spills: a small block-sparse H_eff 208 us
+// against 175).
+constexpr int tile_waves(int bm) { return bm == 64 ? 4 : 2; }
+
+template <int BM, int BN, bool TA, bool TB>
+__global__ __launch_bounds__(256, tile_waves(BM)) void k_dgemm_single(Dgemm64Args a, int tiles_m) {
+    __shared__ __align__(16) double lds[2 * (BM + BN) * kBK];
     int tm, tn;
     tile_order(blockIdx.x, tiles_m, a.tiles_n, tm, tn);
     const Term64 term = a.term;
-    dgemm_tile<BM, TA, TB, kModeGemm>(a, [&](int) { return term; }, 0, 1, a.out, tm * BM, tn * BM, lds);
+    dgemm_tile<BM, BN, TA, TB, kModeGemm>(a, [&](int) { return term; }, 0, 1, a.out, tm * BM, tn * BN, lds);
 }
 
 template <int BM, bool TB, int MODE>
-__global__ __launch_bounds__(256, 2) void k_dgemm_grouped(Dgemm64Args a) {
-    __shared__ double lds[Geo<BM>::LDS];
+__global__ __launch_bounds__(256, MODE == kModeAccum ? 2 : tile_waves(BM)) void k_dgemm_grouped(Dgemm64Args a) {
+    __shared__ __align__(16) double lds[2 * 2 * BM * kBK];
     const TileDesc td = a.tiles[blockIdx.x];
     if (td.out < 0) return;  // padding of the XCD order
     OutDesc od = a.outs[td.out];
     if (a.out_base) od.C = a.out_base + reinterpret_cast<intptr_t>(od.C);
     const Term64 *terms = a.terms;
     const double *b_base = a.b_base;
-    dgemm_tile<BM, false, TB, MODE>(a,
+    dgemm_tile<BM, BM, false, TB, MODE>(a,
                                             [&](int i) {
                                                 Term64 tm = terms[i];
                                                 if (b_base) tm.B = b_base + reinterpret_cast<intptr_t>(tm.B);
@@ -272,27 +346,165 @@ __global__ __launch_bounds__(256, 2) void k_dgemm_grouped(Dgemm64Args a) {
                                             td.term_begin, td.term_end, od, td.m0, td.n0, lds);
 }
 
-template <int BM>
-void launch_single_bm(bool ta, bool tb, Dgemm64Args a, hipStream_t s) {
-    const int tiles_m = static_cast<int>(ceil_div(a.out.M, BM));
-    a.tiles_n = static_cast<int32_t>(ceil_div(a.out.N, BM));
+// ---- split kernel for products of few tiles --------------------------------
+// One 32 x 32 output block per workgroup; the four waves take every fourth
+// group of eight k each and add their sums through LDS at the end, so a
+// product with few tiles still gives every SIMD work and a wave's chain is a
+// quarter as long.  Fragments come straight from memory into registers
+// (along K: 16 bytes per lane, the four waves' groups side by side; across K:
+// 16 consecutive elements of four rows), kDepth groups ahead of the matrix
+// cores.  Bound: latency; measured against the tiles in split_pays.
+constexpr int kDepth = 4;
+
+template <bool ALONG>
+struct SplitFrags {
+    double2 v[2];  // blocks of 16 rows / columns; elements s = 0, 1
+    __device__ __forceinline__ void load(const double *X, int64_t ld, int rows, int K, int r0, int g) {
+        const int lane = threadIdx.x & 63, lq = lane >> 4, l16 = lane & 15;
+        const int k = 8 * g + 2 * lq;
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            const int r = r0 + 16 * b + l16;
+            const int64_t rc = r < rows ? r : rows - 1;
+            v[b] = double2{0.0, 0.0};
+            if (ALONG) {
+                const double *p = X + rc * ld + k;
+                if (8 * g + 8 <= K) {
+                    __builtin_memcpy(&v[b], p, sizeof(double2));
+                } else {
+                    if (k < K) v[b].x = p[0];
+                    if (k + 1 < K) v[b].y = p[1];
+                }
+            } else {
+                const double *p = X + static_cast<int64_t>(k) * ld + rc;
+                if (8 * g + 8 <= K) {
+                    v[b].x = p[0];
+                    v[b].y = p[ld];
+                } else {
+                    if (k < K) v[b].x = p[0];
+                    if (k + 1 < K) v[b].y = p[ld];
+                }
+            }
+        }
+    }
+};
+
+template <bool TA, bool TB>
+__global__ __launch_bounds__(256) void k_dgemm_split(Dgemm64Args a, int tiles_m) {
+    __shared__ double red[4][3][4][64];  // [block][other wave][register][lane]
+    int tm, tn;
+    tile_order(blockIdx.x, tiles_m, a.tiles_n, tm, tn);
+    const Term64 T = a.term;
+    const int m0 = tm * 32, n0 = tn * 32;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63, lq = lane >> 4, l16 = lane & 15;
+    const int ng = (T.K + 7) / 8;
+    v4d acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = v4d{0.0, 0.0, 0.0, 0.0};
+    SplitFrags<!TA> fa[kDepth];
+    SplitFrags<TB> fb[kDepth];
+    auto load = [&](int d, int g) {
+        fa[d].load(T.A, T.lda, a.out.M, T.K, m0, g);
+        fb[d].load(T.B, T.ldb, a.out.N, T.K, n0, g);
+    };
+#pragma unroll
+    for (int d = 0; d < kDepth; ++d)
+        if (wave + 4 * d < ng) load(d, wave + 4 * d);
+    for (int g = wave; g < ng; g += 4 * kDepth) {
+#pragma unroll
+        for (int d = 0; d < kDepth; ++d) {
+            if (g + 4 * d >= ng) break;
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[d].v[i].x, fb[d].v[j].x, acc[i][j], 0, 0, 0);
+                    acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[d].v[i].y, fb[d].v[j].y, acc[i][j], 0, 0, 0);
+                }
+            if (g + 4 * (d + kDepth) < ng) load(d, g + 4 * (d + kDepth));
+        }
+    }
+    // block b is finished by wave b: the sums of waves 0..3 in that order
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+        if (wave == b) continue;
+        const int slot = wave < b ? wave : wave - 1;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) red[b][slot][r][lane] = acc[b >> 1][b & 1][r];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+        if (wave != b) continue;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int i = m0 + (b >> 1) * 16 + 4 * r + lq, j = n0 + (b & 1) * 16 + l16;
+            if (i >= a.out.M || j >= a.out.N) continue;
+            const double own = acc[b >> 1][b & 1][r];
+            double c = 0.0;
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                const double x = w == b ? own : red[b][w < b ? w : w - 1][r][lane];
+                c = w ? c + x : x;
+            }
+            double *p = a.out.C + static_cast<int64_t>(i) * a.out.ldc + j;
+            *p = (a.beta == 0.0) ? T.alpha * c : fma(T.alpha, c, a.beta * *p);
+        }
+    }
+}
+
+void launch_split(bool ta, bool tb, Dgemm64Args a, hipStream_t s) {
+    const int tiles_m = static_cast<int>(ceil_div(a.out.M, 32));
+    a.tiles_n = static_cast<int32_t>(ceil_div(a.out.N, 32));
     const unsigned grid = static_cast<unsigned>(tiles_m) * static_cast<unsigned>(a.tiles_n);
-    if (!ta && !tb) hipLaunchKernelGGL((k_dgemm_single<BM, false, false>), dim3(grid), dim3(256), 0, s, a, tiles_m);
-    if (!ta && tb) hipLaunchKernelGGL((k_dgemm_single<BM, false, true>), dim3(grid), dim3(256), 0, s, a, tiles_m);
-    if (ta && !tb) hipLaunchKernelGGL((k_dgemm_single<BM, true, false>), dim3(grid), dim3(256), 0, s, a, tiles_m);
-    if (ta && tb) hipLaunchKernelGGL((k_dgemm_single<BM, true, true>), dim3(grid), dim3(256), 0, s, a, tiles_m);
+    if (!ta && !tb) hipLaunchKernelGGL((k_dgemm_split<false, false>), dim3(grid), dim3(256), 0, s, a, tiles_m);
+    if (!ta && tb) hipLaunchKernelGGL((k_dgemm_split<false, true>), dim3(grid), dim3(256), 0, s, a, tiles_m);
+    if (ta && !tb) hipLaunchKernelGGL((k_dgemm_split<true, false>), dim3(grid), dim3(256), 0, s, a, tiles_m);
+    if (ta && tb) hipLaunchKernelGGL((k_dgemm_split<true, true>), dim3(grid), dim3(256), 0, s, a, tiles_m);
+}
+
+template <int BM, int BN>
+void launch_single_tile(bool ta, bool tb, Dgemm64Args a, hipStream_t s) {
+    const int tiles_m = static_cast<int>(ceil_div(a.out.M, BM));
+    a.tiles_n = static_cast<int32_t>(ceil_div(a.out.N, BN));
+    const unsigned grid = static_cast<unsigned>(tiles_m) * static_cast<unsigned>(a.tiles_n);
+    if (!ta && !tb) hipLaunchKernelGGL((k_dgemm_single<BM, BN, false, false>), dim3(grid), dim3(256), 0, s, a, tiles_m);
+    if (!ta && tb) hipLaunchKernelGGL((k_dgemm_single<BM, BN, false, true>), dim3(grid), dim3(256), 0, s, a, tiles_m);
+    if (ta && !tb) hipLaunchKernelGGL((k_dgemm_single<BM, BN, true, false>), dim3(grid), dim3(256), 0, s, a, tiles_m);
+    if (ta && tb) hipLaunchKernelGGL((k_dgemm_single<BM, BN, true, true>), dim3(grid), dim3(256), 0, s, a, tiles_m);
 }
 
 }  // namespace
 
-int dgemm_tile_for(int64_t tiles128, int num_cu) { return tiles128 < 2 * static_cast<int64_t>(num_cu) ? 64 : 128; }
+// 128 where its tiles still go round every compute unit four times (two at
+// once, so a last round that is half empty costs little) and leave no more
+// than a twentieth of their area outside the outputs; 64 otherwise.
+// Measured: 8192^3 15.2 ms against 16.3, 4096^3 1.92 against 1.96, but 3000^3
+// (576 tiles of 128) 1.19 against 0.86, 2048^3 (256) 0.27 against 0.25, and a
+// block-sparse H_eff of 40 sectors, where 128 tiles hang over the blocks'
+// edges, 4.5 ms against 3.5.
+int dgemm_tile_for(int64_t tiles64, int64_t tiles128, int num_cu) {
+    return tiles128 >= 4 * static_cast<int64_t>(num_cu) && 80 * tiles128 <= 21 * tiles64 ? 128 : 64;
+}
+
+// The split kernel: each 32 x 32 block on a compute unit of its own.
+// Measured (us, against 64 x 64 tiles): 512^3 14.3 / 22.9, 512 x 512 x 2048
+// 37 / 83, 128 x 128 x 8192 224 / 309; equal at 640^3 (100 tiles of 64, 28),
+// and 45 / 33 at 768^3.
+static bool split_pays(int64_t tiles64, int num_cu) { return 4 * tiles64 <= num_cu; }
 
 hipError_t launch_dgemm_single(bool ta, bool tb, const Dgemm64Args &a, int num_cu, hipStream_t s) {
     if (a.out.M <= 0 || a.out.N <= 0) return hipSuccess;
-    if (dgemm_tile_for(ceil_div(a.out.M, 128) * ceil_div(a.out.N, 128), num_cu) == 64)
-        launch_single_bm<64>(ta, tb, a, s);
+    const int64_t tiles64 = ceil_div(a.out.M, 64) * ceil_div(a.out.N, 64);
+    if (split_pays(tiles64, num_cu))
+        launch_split(ta, tb, a, s);
+    else if (dgemm_tile_for(tiles64, ceil_div(a.out.M, 128) * ceil_div(a.out.N, 128), num_cu) == 64)
+        launch_single_tile<64, 64>(ta, tb, a, s);
     else
-        launch_single_bm<128>(ta, tb, a, s);
+        launch_single_tile<128, 128>(ta, tb, a, s);
     return hipGetLastError();
 }
 

@@ -486,13 +486,15 @@ int heff_plan_create(ozaki_ctx ctx, heff_plan *out, const heff_layout *L, const 
     if (S == 0) {
         for (size_t c = 0; c < hc.size(); ++c) {
             const HostChunk &h = hc[c];
-            // tile edge per phase: 128, or 64 when the 128 tiles would not
-            // give every compute unit two workgroups
-            int64_t nL = 0, nR = 0;
-            for (int u : h.us) nL += ceil_div(ld[us[u].lo], 128) * ceil_div(p * rd[us[u].ri], 128);
-            for (const SigmaPart &sp : parts[c])
-                nR += ceil_div(ld[L->psi_lr[2 * sp.b]] * p, 128) * ceil_div(rd[L->psi_lr[2 * sp.b + 1]], 128);
-            const int bmL = dgemm_tile_for(nL, ctx->num_cu), bmR = dgemm_tile_for(nR, ctx->num_cu);
+            // tile edge per phase, from the tiles of either edge its outputs take
+            int64_t nL[2] = {0, 0}, nR[2] = {0, 0};
+            for (int w = 0; w < 2; ++w) {
+                const int edge = w ? 128 : 64;
+                for (int u : h.us) nL[w] += ceil_div(ld[us[u].lo], edge) * ceil_div(p * rd[us[u].ri], edge);
+                for (const SigmaPart &sp : parts[c])
+                    nR[w] += ceil_div(ld[L->psi_lr[2 * sp.b]] * p, edge) * ceil_div(rd[L->psi_lr[2 * sp.b + 1]], edge);
+            }
+            const int bmL = dgemm_tile_for(nL[0], nL[1], ctx->num_cu), bmR = dgemm_tile_for(nR[0], nR[1], ctx->num_cu);
             const PairShape sh{bmL, bmL}, shR{bmR, bmR};
             // first product: T_u = L Psi  (op(B) = B, B offsets relative to psi)
             std::vector<Term64> termsL;

@@ -268,8 +268,9 @@ bool pair_terms2_ok(int S, int G, int v);
 // FP64 MFMA GEMM.  The single launch picks its tile size from the output
 // extent (a.out) and the compute-unit count; the grouped launch takes tiles
 // of edge a.tile (64 or 128), one workgroup per listed tile.
-// dgemm_tile_for: the edge for a set of outputs with `tiles128` tiles of 128.
-int dgemm_tile_for(int64_t tiles128, int num_cu);
+// dgemm_tile_for: the edge for a set of outputs that take `tiles64` tiles of
+// 64 or `tiles128` tiles of 128.
+int dgemm_tile_for(int64_t tiles64, int64_t tiles128, int num_cu);
 hipError_t launch_dgemm_single(bool ta, bool tb, const Dgemm64Args &a, int num_cu, hipStream_t s);
 hipError_t launch_dgemm_grouped(bool tb, const Dgemm64Args &a, hipStream_t s);
 

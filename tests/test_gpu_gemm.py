@@ -428,3 +428,40 @@ def test_operand_passes_and_split_kernel(oz, K, ta, tb):
         assert bool(ctx.flags() & ozaki.OZ_FLAG_NONFINITE) == bad
         ref = oracle.ozaki_dgemm(A, B, S, G, alpha=alpha, beta=beta, C=C0, transa=ta, transb=tb)
         assert_bitexact(C.cpu().numpy(), ref)
+
+
+@pytest.mark.parametrize("M,N,K", [(1, 1, 1), (33, 31, 7), (64, 65, 8), (70, 33, 41), (500, 480, 15), (513, 641, 16),
+                                   (577, 515, 49), (641, 579, 96), (4097, 4095, 33)])
+@pytest.mark.parametrize("ta,tb", ["NN", "TN", "NT", "TT"])
+def test_fp64_paths_within_gamma_bound(oz, M, N, K, ta, tb):
+    """Native FP64 on each of its kernels (split, 64 x 64 and 128 x 128 tiles)
+    at the edges of their steps: K below, at and past the groups of 8 and the
+    steps of 16, odd extents across K (a last pair that would run past the
+    stored matrix), odd leading dimensions and a base off 16 bytes, operands
+    that end with their allocation, alpha and beta.  Sampled rows against the
+    double-double sum within the textbook bound for K + 2 roundings."""
+    ozaki, ctx, torch = oz
+    rng = np.random.default_rng(M + 7 * N + 13 * K)
+    A = wl.wide_normal(rng, (M, K), 10)
+    B = wl.wide_normal(rng, (K, N), 10)
+    C0 = rng.standard_normal((M, N))
+
+    def place(X, odd):
+        r, c = X.shape
+        buf = torch.full((r * (c + odd) + odd,), float("nan"), dtype=torch.float64, device="cuda")
+        v = buf[odd:].view(r, c + odd)[:, :c] if odd else buf.view(r, c)
+        v.copy_(torch.from_numpy(np.ascontiguousarray(X)))
+        return v
+
+    rows = np.unique([0, M // 2, max(M - 2, 0), M - 1])
+    hi, lo = oracle.dgemm_dd(A[rows], B)
+    u = 2.0 ** -53
+    gam = (K + 2) * u / (1 - (K + 2) * u)
+    for odd, alpha, beta in ((0, 1.0, 0.0), (1, -1.5, 0.5)):
+        C = dev(torch, C0)
+        ctx.dgemm(place(A.T if ta == "T" else A, odd), place(B.T if tb == "T" else B, odd), slices=0, transa=ta,
+                  transb=tb, alpha=alpha, beta=beta, C=C)
+        ref = alpha * hi + beta * C0[rows]
+        mag = abs(alpha) * (np.abs(A[rows]) @ np.abs(B)) + abs(beta) * np.abs(C0[rows])
+        err = np.abs(C.cpu().numpy()[rows] - ref - alpha * lo)
+        assert np.all(err <= gam * mag * (1 + 1e-12) + 4 * u * np.abs(ref)), (odd, err.max())
