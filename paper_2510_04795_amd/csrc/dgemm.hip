@@ -297,11 +297,13 @@ __device__ __forceinline__ void dgemm_tile(const Dgemm64Args &a, GetTerm get_ter
 }
 
 // XCD-aware tile order (blocks are dispatched to the 8 XCDs round robin).
-__device__ __forceinline__ void tile_order(int b, int tiles_m, int tiles_n, int &tm, int &tn) {
-    const int T = tiles_m * tiles_n;
-    const int q = T / 8, rem = T - q * 8;
+__device__ __forceinline__ void tile_order(int b, int tiles_m, int tiles_n, int nbatch, int &k, int &tm, int &tn) {
+    const int T = tiles_m * tiles_n, all = nbatch > 1 ? T * nbatch : T;
+    const int q = all / 8, rem = all - q * 8;
     const int x = b % 8, idx = b / 8;
-    const int lin = x * q + (x < rem ? x : rem) + idx;
+    const int at = x * q + (x < rem ? x : rem) + idx;
+    k = nbatch > 1 ? at / T : 0;
+    const int lin = at - k * T;
     const int per_group = 4 * tiles_n;
     const int gid = lin / per_group;
     const int first = gid * 4;
@@ -309,6 +311,17 @@ __device__ __forceinline__ void tile_order(int b, int tiles_m, int tiles_n, int 
     const int w = lin - gid * per_group;
     tm = first + w % rows;
     tn = w / rows;
+}
+
+// Product k of a batched single launch.
+__device__ __forceinline__ void batch_product(const Dgemm64Args &a, int k, Term64 &term, OutDesc &out) {
+    term = a.term;
+    out = a.out;
+    if (a.nbatch > 1) {
+        term.A = a.batch_A[k];
+        term.B = a.batch_B[k];
+        out.C = a.batch_C[k];
+    }
 }
 
 // Workgroups per compute unit the registers are kept for: four of the 64 x 64
@@ -322,10 +335,12 @@ constexpr int tile_waves(int bm) { return bm == 64 ? 4 : 2; }
 template <int BM, int BN, bool TA, bool TB>
 __global__ __launch_bounds__(256, tile_waves(BM)) void k_dgemm_single(Dgemm64Args a, int tiles_m) {
     __shared__ __align__(16) double lds[2 * (BM + BN) * kBK];
-    int tm, tn;
-    tile_order(blockIdx.x, tiles_m, a.tiles_n, tm, tn);
-    const Term64 term = a.term;
-    dgemm_tile<BM, BN, TA, TB, kModeGemm>(a, [&](int) { return term; }, 0, 1, a.out, tm * BM, tn * BN, lds);
+    int k, tm, tn;
+    tile_order(blockIdx.x, tiles_m, a.tiles_n, a.nbatch, k, tm, tn);
+    Term64 term;
+    OutDesc out;
+    batch_product(a, k, term, out);
+    dgemm_tile<BM, BN, TA, TB, kModeGemm>(a, [&](int) { return term; }, 0, 1, out, tm * BM, tn * BN, lds);
 }
 
 template <int BM, bool TB, int MODE>
@@ -392,9 +407,11 @@ struct SplitFrags {
 template <bool TA, bool TB>
 __global__ __launch_bounds__(256) void k_dgemm_split(Dgemm64Args a, int tiles_m) {
     __shared__ double red[4][3][4][64];  // [block][other wave][register][lane]
-    int tm, tn;
-    tile_order(blockIdx.x, tiles_m, a.tiles_n, tm, tn);
-    const Term64 T = a.term;
+    int k, tm, tn;
+    tile_order(blockIdx.x, tiles_m, a.tiles_n, a.nbatch, k, tm, tn);
+    Term64 T;
+    OutDesc out;
+    batch_product(a, k, T, out);
     const int m0 = tm * 32, n0 = tn * 32;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63, lq = lane >> 4, l16 = lane & 15;
@@ -407,8 +424,8 @@ __global__ __launch_bounds__(256) void k_dgemm_split(Dgemm64Args a, int tiles_m)
     SplitFrags<!TA> fa[kDepth];
     SplitFrags<TB> fb[kDepth];
     auto load = [&](int d, int g) {
-        fa[d].load(T.A, T.lda, a.out.M, T.K, m0, g);
-        fb[d].load(T.B, T.ldb, a.out.N, T.K, n0, g);
+        fa[d].load(T.A, T.lda, out.M, T.K, m0, g);
+        fb[d].load(T.B, T.ldb, out.N, T.K, n0, g);
     };
 #pragma unroll
     for (int d = 0; d < kDepth; ++d)
@@ -442,7 +459,7 @@ __global__ __launch_bounds__(256) void k_dgemm_split(Dgemm64Args a, int tiles_m)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int i = m0 + (b >> 1) * 16 + 4 * r + lq, j = n0 + (b & 1) * 16 + l16;
-            if (i >= a.out.M || j >= a.out.N) continue;
+            if (i >= out.M || j >= out.N) continue;
             const double own = acc[b >> 1][b & 1][r];
             double c = 0.0;
 #pragma unroll
@@ -450,7 +467,7 @@ __global__ __launch_bounds__(256) void k_dgemm_split(Dgemm64Args a, int tiles_m)
                 const double x = w == b ? own : red[b][w < b ? w : w - 1][r][lane];
                 c = w ? c + x : x;
             }
-            double *p = a.out.C + static_cast<int64_t>(i) * a.out.ldc + j;
+            double *p = out.C + static_cast<int64_t>(i) * out.ldc + j;
             *p = (a.beta == 0.0) ? T.alpha * c : fma(T.alpha, c, a.beta * *p);
         }
     }
@@ -459,7 +476,7 @@ __global__ __launch_bounds__(256) void k_dgemm_split(Dgemm64Args a, int tiles_m)
 void launch_split(bool ta, bool tb, Dgemm64Args a, hipStream_t s) {
     const int tiles_m = static_cast<int>(ceil_div(a.out.M, 32));
     a.tiles_n = static_cast<int32_t>(ceil_div(a.out.N, 32));
-    const unsigned grid = static_cast<unsigned>(tiles_m) * static_cast<unsigned>(a.tiles_n);
+    const unsigned grid = static_cast<unsigned>(tiles_m) * static_cast<unsigned>(a.tiles_n) * (a.nbatch > 1 ? a.nbatch : 1);
     if (!ta && !tb) hipLaunchKernelGGL((k_dgemm_split<false, false>), dim3(grid), dim3(256), 0, s, a, tiles_m);
     if (!ta && tb) hipLaunchKernelGGL((k_dgemm_split<false, true>), dim3(grid), dim3(256), 0, s, a, tiles_m);
     if (ta && !tb) hipLaunchKernelGGL((k_dgemm_split<true, false>), dim3(grid), dim3(256), 0, s, a, tiles_m);
@@ -470,7 +487,7 @@ template <int BM, int BN>
 void launch_single_tile(bool ta, bool tb, Dgemm64Args a, hipStream_t s) {
     const int tiles_m = static_cast<int>(ceil_div(a.out.M, BM));
     a.tiles_n = static_cast<int32_t>(ceil_div(a.out.N, BN));
-    const unsigned grid = static_cast<unsigned>(tiles_m) * static_cast<unsigned>(a.tiles_n);
+    const unsigned grid = static_cast<unsigned>(tiles_m) * static_cast<unsigned>(a.tiles_n) * (a.nbatch > 1 ? a.nbatch : 1);
     if (!ta && !tb) hipLaunchKernelGGL((k_dgemm_single<BM, BN, false, false>), dim3(grid), dim3(256), 0, s, a, tiles_m);
     if (!ta && tb) hipLaunchKernelGGL((k_dgemm_single<BM, BN, false, true>), dim3(grid), dim3(256), 0, s, a, tiles_m);
     if (ta && !tb) hipLaunchKernelGGL((k_dgemm_single<BM, BN, true, false>), dim3(grid), dim3(256), 0, s, a, tiles_m);
@@ -498,10 +515,11 @@ static bool split_pays(int64_t tiles64, int num_cu) { return 4 * tiles64 <= num_
 
 hipError_t launch_dgemm_single(bool ta, bool tb, const Dgemm64Args &a, int num_cu, hipStream_t s) {
     if (a.out.M <= 0 || a.out.N <= 0) return hipSuccess;
-    const int64_t tiles64 = ceil_div(a.out.M, 64) * ceil_div(a.out.N, 64);
+    const int64_t nb = a.nbatch > 1 ? a.nbatch : 1;
+    const int64_t tiles64 = ceil_div(a.out.M, 64) * ceil_div(a.out.N, 64) * nb;
     if (split_pays(tiles64, num_cu))
         launch_split(ta, tb, a, s);
-    else if (dgemm_tile_for(tiles64, ceil_div(a.out.M, 128) * ceil_div(a.out.N, 128), num_cu) == 64)
+    else if (dgemm_tile_for(tiles64, ceil_div(a.out.M, 128) * ceil_div(a.out.N, 128) * nb, num_cu) == 64)
         launch_single_tile<64, 64>(ta, tb, a, s);
     else
         launch_single_tile<128, 128>(ta, tb, a, s);

@@ -95,6 +95,9 @@ enum PairMode : int32_t {
     kModeGemm64 = 4,   // kModeGemm for the last K chunk: its sums are added to Qw's
 };
 
+// Products of one shape that a single launch can take.
+constexpr int kMaxBatch = 16;
+
 // Counters of one streamed launch: a tile counter per XCD, then the number
 // of workgroups that found their queue empty.
 constexpr int kStreamQueueInts = 16;
@@ -132,6 +135,12 @@ struct PairArgs {
     // grouped, accumulating mode on the 64 x 64 tiles of variant 0: 1 = the
     // paired-term kernel (eight waves per tile, two terms at a time)
     int32_t terms2;
+    // single launch in kModeGemm: nbatch > 1 products of one shape in one
+    // launch, product k from the term's pointers moved by k strides into
+    // batch_C[k]
+    int32_t nbatch;
+    int64_t batch_A, batch_e, batch_B, batch_f;  // bytes, ints, bytes, ints
+    double *batch_C[kMaxBatch];
 };
 
 // FP64 GEMM term: op(A) (M x K) times op(B) (K x N), both plain FP64.
@@ -157,6 +166,11 @@ struct Dgemm64Args {
     double beta;
     double *out_base;      // grouped: when set, OutDesc::C holds an element offset from it
     const double *b_base;  // grouped: when set, Term64::B holds an element offset from it
+    // single launch: nbatch > 1 products of one shape, product k from
+    // batch_A[k] and batch_B[k] into batch_C[k]
+    int32_t nbatch;
+    const double *batch_A[kMaxBatch], *batch_B[kMaxBatch];
+    double *batch_C[kMaxBatch];
 };
 
 // Grouped slicing: many blocks in one launch.  Offsets are relative to base
@@ -246,11 +260,12 @@ hipError_t launch_unpack(int S, const int8_t *packed, int64_t Rp, int64_t R, int
                          int8_t *canon, hipStream_t s);
 
 // Tile variants of the int8 pair GEMM.  v < 0 selects the default variant.
+// A single launch takes a.nbatch products in kModeGemm.
 // kSplitVariant (launch_pair_single in kModeGemm only, 32 x 32 tiles) is the
 // kernel for products of few tiles; pair_split_pays says where ozaki_dgemm
 // takes it when no variant is set.
 constexpr int kSplitVariant = 100;
-bool pair_split_pays(int64_t M, int64_t N, int64_t K, int num_cu);
+bool pair_split_pays(int64_t M, int64_t N, int64_t K, int nbatch, int num_cu);
 struct PairShape { int bm, bn; };
 bool pair_supported(int S, int G);
 int pair_num_variants();

@@ -20,8 +20,8 @@ int pair_default_variant(int G) { return pair::default_variant(G); }
 // 72 / 87 against 134 / 186; but 640^3 (100 tiles) 29 / 38 against 29 / 34 and
 // 1024^3 (256 tiles) 52 / 75 against 41 / 49, where the larger tile's reuse of
 // its operands counts for more.
-bool pair_split_pays(int64_t M, int64_t N, int64_t K, int num_cu) {
-    return ceil_div(M, 64) * ceil_div(N, 64) * 4 <= num_cu && K > 64;
+bool pair_split_pays(int64_t M, int64_t N, int64_t K, int nbatch, int num_cu) {
+    return ceil_div(M, 64) * ceil_div(N, 64) * nbatch * 4 <= num_cu && K > 64;
 }
 
 PairShape pair_shape(int S, int G, int v) {

@@ -1589,14 +1589,18 @@ __global__ __launch_bounds__(512) void k_pair_terms2(PairArgs a) {
 // With ~32 blocks in flight per XCD as a x b tiles, each K block fetches
 // a A slabs and b B slabs: for a BM x BN tile the fetch per tile is
 // proportional to BM / b + BN / a, smallest at a / b = BN / BM.
-__device__ __forceinline__ void tile_coords(int b, int tiles_m, int tiles_n, int group, int &tm, int &tn) {
+__device__ __forceinline__ void tile_coords(int b, int tiles_m, int tiles_n, int group, int nbatch, int &k, int &tm,
+                                            int &tn) {
     const int T = tiles_m * tiles_n;
+    const int all = nbatch > 1 ? T * nbatch : T;
     const int nx = 8;
-    const int q = T / nx;
-    const int rem = T - q * nx;
+    const int q = all / nx;
+    const int rem = all - q * nx;
     const int x = b % nx;
     const int idx = b / nx;
-    const int lin = x * q + (x < rem ? x : rem) + idx;
+    const int at = x * q + (x < rem ? x : rem) + idx;
+    k = nbatch > 1 ? at / T : 0;
+    const int lin = at - k * T;
     const int per_group = group * tiles_n;
     const int gid = lin / per_group;
     const int first = gid * group;
@@ -1606,17 +1610,32 @@ __device__ __forceinline__ void tile_coords(int b, int tiles_m, int tiles_n, int
     tn = w / rows;
 }
 
+// Product k of a batched single launch.
+__device__ __forceinline__ void batch_product(const PairArgs &a, int k, TermDesc &term, OutDesc &out) {
+    term = a.term;
+    out = a.out;
+    if (a.nbatch > 1) {
+        term.A += k * a.batch_A;
+        term.e += k * a.batch_e;
+        term.B += k * a.batch_B;
+        term.f += k * a.batch_f;
+        out.C = a.batch_C[k];
+    }
+}
+
 template <int S, int G, int WM, int WN, int MB, int NB, int MODE>
 __global__ __launch_bounds__(64 * WM * WN) void k_pair_single(PairArgs a, int tiles_m) {
     using C = Cfg<S, G, WM, WN, MB, NB>;
     __shared__ uint4 lds0[C::STAGE];
     __shared__ uint4 lds1[C::STAGE];
     __shared__ uint4 lds2[use_ring<S, G, WM, WN, MB, NB, MODE>() ? C::STAGE : 1];
-    int tm, tn;
+    int k, tm, tn;
     constexpr int group = C::BM >= 2 * C::BN ? 4 : 8;
-    tile_coords(blockIdx.x, tiles_m, a.tiles_n, group, tm, tn);
-    const TermDesc term = a.term;
-    pair_tile<S, G, WM, WN, MB, NB, MODE>(a, [&](int) { return term; }, 0, 1, a.out, tm * C::BM,
+    tile_coords(blockIdx.x, tiles_m, a.tiles_n, group, a.nbatch, k, tm, tn);
+    TermDesc term;
+    OutDesc out;
+    batch_product(a, k, term, out);
+    pair_tile<S, G, WM, WN, MB, NB, MODE>(a, [&](int) { return term; }, 0, 1, out, tm * C::BM,
                                           tn * C::BN, lds0, lds1, lds2);
 }
 
@@ -1645,12 +1664,14 @@ template <int S, int G>
 __global__ __launch_bounds__(256) void k_pair_split(PairArgs a, int tiles_m) {
     constexpr int PP = G <= 13 ? 4 : 2;  // 12 G KiB of LDS for all four
     __shared__ int red[PP][3][G * 4][64];
-    int tm, tn;
-    tile_coords(blockIdx.x, tiles_m, a.tiles_n, 8, tm, tn);
+    int k, tm, tn;
+    tile_coords(blockIdx.x, tiles_m, a.tiles_n, 8, a.nbatch, k, tm, tn);
     const int m0 = tm * 32, n0 = tn * 32;
     const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const TermDesc T = a.term;
+    TermDesc T;
+    OutDesc out;
+    batch_product(a, k, T, out);
     const int64_t a_run = T.a_rows_p * 16, b_run = T.b_rows_p * 16;
     const int8_t *A = T.A + half * a_run + static_cast<int64_t>(m0 + l32) * 16;
     const int8_t *B = T.B + half * b_run + static_cast<int64_t>(n0 + l32) * 16;
@@ -1658,13 +1679,13 @@ __global__ __launch_bounds__(256) void k_pair_split(PairArgs a, int tiles_m) {
 #pragma unroll
     for (int g = 0; g < G; ++g) acc[g][0][0] = v16i{};
     const int j = n0 + l32;
-    const bool jok = j < a.out.N;
+    const bool jok = j < out.N;
     const int32_t fj = jok ? T.f[j] : 0;
     int32_t ei[4];  // this wave finishes rows 8 wave + 4 half + 0..3 of the block
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const int i = m0 + 8 * wave + 4 * half + q;
-        ei[q] = i < a.out.M ? T.e[i] : 0;
+        ei[q] = i < out.M ? T.e[i] : 0;
     }
     Frags<S, G, 1, 1> cur, nxt;
     if (wave < T.kblocks) split_load<S, G>(cur, A + wave * 2 * S * a_run, B + wave * 2 * S * b_run, a_run, b_run);
@@ -1701,9 +1722,9 @@ __global__ __launch_bounds__(256) void k_pair_split(PairArgs a, int tiles_m) {
                     s[g] = acc[g][0][0][4 * p + q] + red[p - p0][0][g * 4 + q][lane] +
                            red[p - p0][1][g * 4 + q][lane] + red[p - p0][2][g * 4 + q][lane];
                 const int i = m0 + 8 * p + 4 * half + q;
-                if (jok && i < a.out.M) {
+                if (jok && i < out.M) {
                     const double c = horner<G>(s, ei[q], fj);
-                    double *o = a.out.C + static_cast<int64_t>(i) * a.out.ldc + j;
+                    double *o = out.C + static_cast<int64_t>(i) * out.ldc + j;
                     *o = (a.beta == 0.0) ? T.alpha * c : fma(T.alpha, c, a.beta * *o);
                 }
             }
@@ -1765,6 +1786,8 @@ __host__ __device__ constexpr int variant_bn(int v) { return variant_wn(v) * var
 // (S = 3, 4096^3: 591 us against 481).
 __host__ __device__ constexpr int default_variant(int G) { return G <= 3 ? 3 : 0; }
 
+inline unsigned batch_count(const PairArgs &a) { return a.nbatch > 1 ? static_cast<unsigned>(a.nbatch) : 1u; }
+
 template <int S, int G, int V>
 hipError_t run_single_v(const PairArgs &a, int tiles_m, hipStream_t s) {
     constexpr int WM = variant_wm(V), WN = variant_wn(V), MB = variant_mb(V), NB = variant_nb(V);
@@ -1772,8 +1795,9 @@ hipError_t run_single_v(const PairArgs &a, int tiles_m, hipStream_t s) {
     if constexpr (!variant_fits(G, V)) {
         return hipErrorInvalidValue;
     } else {
-        const unsigned grid = static_cast<unsigned>(tiles_m) * static_cast<unsigned>(a.tiles_n);
+        const unsigned grid = static_cast<unsigned>(tiles_m) * static_cast<unsigned>(a.tiles_n) * batch_count(a);
         if (grid == 0) return hipSuccess;
+        if (a.nbatch > 1 && a.mode != kModeGemm) return hipErrorInvalidValue;
         switch (a.mode) {
             case kModeGemm:
                 hipLaunchKernelGGL((k_pair_single<S, G, WM, WN, MB, NB, kModeGemm>), dim3(grid), dim3(NT), 0, s, a, tiles_m);
@@ -1900,7 +1924,7 @@ template <int S, int G>
 hipError_t run_single(int v, const PairArgs &a, int tiles_m, hipStream_t s) {
     if (v == kSplitVariant) {
         if (a.mode != kModeGemm) return hipErrorInvalidValue;
-        const unsigned grid = static_cast<unsigned>(tiles_m) * static_cast<unsigned>(a.tiles_n);
+        const unsigned grid = static_cast<unsigned>(tiles_m) * static_cast<unsigned>(a.tiles_n) * batch_count(a);
         if (grid == 0) return hipSuccess;
         hipLaunchKernelGGL((k_pair_split<S, G>), dim3(grid), dim3(256), 0, s, a, tiles_m);
         return hipGetLastError();

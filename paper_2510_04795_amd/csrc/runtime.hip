@@ -442,7 +442,7 @@ int ozaki_dgemm(ozaki_ctx ctx, char transa, char transb, int64_t M, int64_t N, i
     phase(ctx, OZ_PHASE_SLICE, t0, t1);
     const int64_t kmax = max_exact_k(slices, G);
     // the int64 carries between K chunks are built for the 64 x 64 tile only
-    const bool split = K <= kmax && ctx->variant[slices][G] < 0 && pair_split_pays(M, N, K, ctx->num_cu);
+    const bool split = K <= kmax && ctx->variant[slices][G] < 0 && pair_split_pays(M, N, K, 1, ctx->num_cu);
     const int var = K > kmax ? 0 : split ? kSplitVariant : ctx_variant(ctx, slices, G);
     const PairShape sh = pair_shape(slices, G, var);
     PairArgs a{};

@@ -123,6 +123,7 @@ _sig("rdm_eig_solve", _i32, [_ptr, _ptr, _i64, _i64, _ptr, _ptr, _i64, _dbl, _i3
                              ctypes.POINTER(RdmEigInfo), _ptr])
 _sig("rdm_eig_destroy", _i32, [_ptr])
 _sig("ozaki_renormalize_workspace_bytes", _sz, [_i64, _i64, _i32, _i32])
+_sig("ozaki_renormalize_batch_bytes", _sz, [_i64, _i64, _i32, _i32, _i32])
 _sig("ozaki_renormalize", _i32, [_ptr, _i64, _i64, _ptr, _i64, _i32, ctypes.POINTER(_ptr), _i64,
                                  ctypes.POINTER(_ptr), _i64, _i32, _i32, _ptr, _sz, _ptr])
 
@@ -141,7 +142,7 @@ EXPORTED = [
     "heff_plan_destroy", "davidson_create", "davidson_step", "davidson_get_vector",
     "davidson_set_graphs", "davidson_graph_count", "davidson_destroy", "lanczos_create", "lanczos_step", "lanczos_get_vector", "lanczos_destroy",
     "rdm_eig_create", "rdm_eig_solve", "rdm_eig_destroy", "ozaki_renormalize_workspace_bytes",
-    "ozaki_renormalize",
+    "ozaki_renormalize_batch_bytes", "ozaki_renormalize",
 ]
 
 
@@ -393,7 +394,7 @@ class Context:
         if any(_ld(o, "ops[k]") != ldo for o in ops) or any(_ld(o, "outs[k]") != ldout for o in outs):
             raise ValueError("all operators (and all outputs) must share one leading dimension")
         if workspace is None:
-            nb = _lib.ozaki_renormalize_workspace_bytes(n, D, slices, ndiag)
+            nb = _lib.ozaki_renormalize_batch_bytes(n, D, len(ops), slices, ndiag)
             workspace = torch.empty(max(nb, 1), dtype=torch.uint8, device=U.device)
         po = (_ptr * max(len(ops), 1))(*[o.data_ptr() for o in ops])
         pr = (_ptr * max(len(outs), 1))(*[o.data_ptr() for o in outs])

@@ -288,3 +288,43 @@ def test_large_rdm(oz, S):
     assert np.max(np.abs(w - t.schmidt[:512] ** 2)) <= 64 * np.sqrt(2048) * u_eff(S) * w[0]
     res = np.linalg.norm(A @ Z - Z * w, axis=0)
     assert np.max(res) <= 64 * np.sqrt(2048) * u_eff(S) * w[0]
+
+
+@pytest.mark.parametrize("S", [0, 3, 7])
+@pytest.mark.parametrize("n,D,count", [(1, 1, 3), (40, 33, 5), (130, 64, 17), (300, 257, 3)])
+def test_renormalize_batches(oz, S, n, D, count):
+    """Several operators at once: counts below, at and past a batch, an odd one
+    left over, the workspace of the per-operator query (batches of one), of the
+    batch query and between; every form gives the bits of the two ozaki_dgemm
+    calls per operator when emulated, and stays within the FP64 bound."""
+    import ctypes
+    ozaki, ctx, torch = oz
+    ops = wl.block_operators(n, count, seed=n)
+    U = np.linalg.qr(np.random.default_rng(n + D).standard_normal((n, D)))[0]
+    dU, dops = dev(torch, U), [dev(torch, o) for o in ops]
+    one = int(ozaki._lib.ozaki_renormalize_workspace_bytes(n, D, S, 0))
+    many = int(ozaki._lib.ozaki_renormalize_batch_bytes(n, D, count, S, 0))
+    assert many >= one
+    want = oracle.renormalize(U, ops, S=S) if S else None
+    gam = (n + 1) * U64 / (1 - (n + 1) * U64)
+    for size in sorted({one, (one + many) // 2, many, many + 4096}):
+        ws = torch.empty(max(size, 1), dtype=torch.uint8, device="cuda")
+        out = ctx.renormalize(dU, dops, slices=S, workspace=ws)
+        for k, got in enumerate(out):
+            if S:
+                assert_bitexact(got.cpu().numpy(), want[k], "operator %d, %d bytes" % (k, size))
+            else:
+                bound = 3 * gam * (np.abs(U).T @ np.abs(ops[k]) @ np.abs(U))
+                assert np.all(np.abs(got.cpu().numpy() - U.T @ ops[k] @ U) <= bound)
+    with pytest.raises(ozaki.OzakiError):
+        ctx.renormalize(dU, dops, slices=S, workspace=torch.empty(max(one - 256, 0) or 1, dtype=torch.uint8,
+                                                                  device="cuda")[: max(one - 256, 0)])
+    if n == D:
+        return
+    # an output over the next operator: one by one, in order
+    big = torch.zeros(2, n, n, dtype=torch.float64, device="cuda")
+    big[0], big[1] = dops[0], dops[1]
+    ctx.renormalize(dU, [big[0], big[1]], slices=S,
+                    outs=[torch.empty(D, n, dtype=torch.float64, device="cuda")[:, :D], big[0][:D, :D]])
+    ref = ctx.renormalize(dU, [dops[1]], slices=S)[0]
+    assert torch.equal(big[0][:D, :D], ref)
