@@ -159,14 +159,21 @@ def _check(rc: int, where: str) -> int:
     return rc
 
 
+# Handle of the current stream of a device; the raw query (0.2 us) where torch
+# has it, else through a Stream object (2.8 us, a fifth of a small call).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream) -> int:
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return stream.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is not None:
+        return _raw_stream(torch.cuda.current_device())
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _dev_f64(t: torch.Tensor, name: str) -> torch.Tensor:
-    if not isinstance(t, torch.Tensor) or t.dtype != torch.float64 or not t.is_cuda:
+    if not isinstance(t, torch.Tensor) or t.dtype is not torch.float64 or not t.is_cuda:
         raise TypeError("%s must be a float64 CUDA tensor" % name)
     return t
 
@@ -182,20 +189,23 @@ def _dev_vec(t: torch.Tensor, n: int, name: str) -> torch.Tensor:
 def _dev_out(t: torch.Tensor, rows: int, cols: int, name: str) -> torch.Tensor:
     """A float64 CUDA matrix of rows x cols the library writes."""
     _dev_f64(t, name)
-    if tuple(t.shape) != (rows, cols):
+    if t.shape != (rows, cols):
         raise ValueError("%s must be %d x %d, not %s" % (name, rows, cols, tuple(t.shape)))
     return t
 
 
 def _ld(t: torch.Tensor, name: str) -> int:
     """Leading dimension of a row-major 2-D view (unit column stride)."""
-    if t.dim() != 2:
+    shape = t.shape
+    if len(shape) != 2:
         raise ValueError("%s must be 2-D" % name)
-    if t.numel() == 0:
-        return max(t.size(1), 1)
-    if t.size(1) > 1 and t.stride(1) != 1:
+    rows, cols = shape
+    if rows == 0 or cols == 0:
+        return max(cols, 1)
+    ld, step = t.stride()
+    if cols > 1 and step != 1:
         raise ValueError("%s must be a row-major 2-D tensor with unit column stride" % name)
-    return max(t.stride(0), t.size(1), 1)
+    return ld if ld > cols else cols
 
 
 def pair_variants(slices: int, ndiag: int = 0):
@@ -332,11 +342,15 @@ class Context:
         """C = alpha op(A) op(B) + beta C; slices = 0 runs the native FP64 MFMA GEMM."""
         _dev_f64(A, "A")
         _dev_f64(B, "B")
-        ta, tb = transa.upper() == "T", transb.upper() == "T"
-        M = A.size(1) if ta else A.size(0)
-        K = A.size(0) if ta else A.size(1)
-        N = B.size(0) if tb else B.size(1)
-        if (B.size(1) if tb else B.size(0)) != K:
+        lda, ldb = _ld(A, "A"), _ld(B, "B")
+        transa, transb = transa.upper(), transb.upper()
+        M, K = A.shape
+        if transa == "T":
+            M, K = K, M
+        Kb, N = B.shape
+        if transb == "T":
+            Kb, N = N, Kb
+        if Kb != K:
             raise ValueError("inner dimensions differ")
         if C is None:
             C = torch.empty((M, N), dtype=torch.float64, device=A.device)
@@ -347,10 +361,11 @@ class Context:
             workspace = self.workspace(M, N, K, slices, ndiag)
         wptr = workspace.data_ptr() if workspace is not None else None
         wlen = workspace.numel() * workspace.element_size() if workspace is not None else 0
-        _check(_lib.ozaki_dgemm(self.handle, transa.upper().encode(), transb.upper().encode(), M, N,
-                                K, alpha, A.data_ptr(), _ld(A, "A"), B.data_ptr(), _ld(B, "B"),
-                                beta, C.data_ptr(), _ld(C, "C"), slices, ndiag, wptr, wlen,
-                                _stream(stream)), "ozaki_dgemm")
+        rc = _lib.ozaki_dgemm(self.handle, transa.encode(), transb.encode(), M, N, K, alpha, A.data_ptr(), lda,
+                              B.data_ptr(), ldb, beta, C.data_ptr(), _ld(C, "C"), slices, ndiag, wptr, wlen,
+                              _stream(stream))
+        if rc < 0:
+            raise OzakiError(rc, "ozaki_dgemm")
         return C
 
     def dgemm_static(self, A, B, C, slices: int = 6, ndiag: int = 0, alpha: float = 1.0, beta: float = 0.0,
