@@ -368,38 +368,45 @@ __global__ __launch_bounds__(256, MODE == kModeAccum ? 2 : tile_waves(BM)) void 
 // quarter as long.  Fragments come straight from memory into registers
 // (along K: 16 bytes per lane, the four waves' groups side by side; across K:
 // 16 consecutive elements of four rows), kDepth groups ahead of the matrix
-// cores.  Bound: latency; measured against the tiles in split_pays.
-constexpr int kDepth = 4;
+// cores (512^3: 14.3 us with four groups ahead, 11.0 with eight).  Bound:
+// latency; measured against the tiles in split_pays.
+constexpr int kDepth = 8;
 
 template <bool ALONG>
-struct SplitFrags {
-    double2 v[2];  // blocks of 16 rows / columns; elements s = 0, 1
-    __device__ __forceinline__ void load(const double *X, int64_t ld, int rows, int K, int r0, int g) {
+struct SplitOperand {
+    const double *p[2];  // this lane's element of k = 2 lq in each block of 16 rows / columns
+    int64_t ld;
+    __device__ __forceinline__ void init(const double *X, int64_t l, int rows, int r0) {
         const int lane = threadIdx.x & 63, lq = lane >> 4, l16 = lane & 15;
-        const int k = 8 * g + 2 * lq;
+        ld = l;
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
             const int r = r0 + 16 * b + l16;
             const int64_t rc = r < rows ? r : rows - 1;
-            v[b] = double2{0.0, 0.0};
+            p[b] = ALONG ? X + rc * ld + 2 * lq : X + 2 * lq * ld + rc;
+        }
+    }
+    // elements s = 0, 1 of whole group g
+    __device__ __forceinline__ void load(double2 (&v)[2], int g) const {
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
             if (ALONG) {
-                const double *p = X + rc * ld + k;
-                if (8 * g + 8 <= K) {
-                    __builtin_memcpy(&v[b], p, sizeof(double2));
-                } else {
-                    if (k < K) v[b].x = p[0];
-                    if (k + 1 < K) v[b].y = p[1];
-                }
+                __builtin_memcpy(&v[b], p[b] + 8 * g, sizeof(double2));
             } else {
-                const double *p = X + static_cast<int64_t>(k) * ld + rc;
-                if (8 * g + 8 <= K) {
-                    v[b].x = p[0];
-                    v[b].y = p[ld];
-                } else {
-                    if (k < K) v[b].x = p[0];
-                    if (k + 1 < K) v[b].y = p[ld];
-                }
+                const double *q = p[b] + static_cast<int64_t>(8 * g) * ld;
+                v[b].x = q[0];
+                v[b].y = q[ld];
             }
+        }
+    }
+    // the last group, of which `left` elements exist
+    __device__ __forceinline__ void load_tail(double2 (&v)[2], int g, int left) const {
+        const int k = 2 * ((threadIdx.x & 63) >> 4);
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            const double *q = p[b] + (ALONG ? 8 * g : static_cast<int64_t>(8 * g) * ld);
+            v[b].x = k < left ? q[0] : 0.0;
+            v[b].y = k + 1 < left ? q[ALONG ? 1 : ld] : 0.0;
         }
     }
 };
@@ -415,34 +422,61 @@ __global__ __launch_bounds__(256) void k_dgemm_split(Dgemm64Args a, int tiles_m)
     const int m0 = tm * 32, n0 = tn * 32;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63, lq = lane >> 4, l16 = lane & 15;
-    const int ng = (T.K + 7) / 8;
     v4d acc[2][2];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j) acc[i][j] = v4d{0.0, 0.0, 0.0, 0.0};
-    SplitFrags<!TA> fa[kDepth];
-    SplitFrags<TB> fb[kDepth];
-    auto load = [&](int d, int g) {
-        fa[d].load(T.A, T.lda, out.M, T.K, m0, g);
-        fb[d].load(T.B, T.ldb, out.N, T.K, n0, g);
+    SplitOperand<!TA> oa;
+    SplitOperand<TB> ob;
+    oa.init(T.A, T.lda, out.M, m0);
+    ob.init(T.B, T.ldb, out.N, n0);
+    double2 fa[kDepth][2], fb[kDepth][2];
+    // groups of this wave: wave, wave + 4, ... below `full`; the rest of K
+    // (fewer than eight) is the next wave's in turn
+    const int full = T.K / 8;
+    const int n = (full - wave + 3) / 4;
+    auto load = [&](int d, int i) {
+        oa.load(fa[d], wave + 4 * i);
+        ob.load(fb[d], wave + 4 * i);
     };
+    auto mul = [&](int d) {
 #pragma unroll
-    for (int d = 0; d < kDepth; ++d)
-        if (wave + 4 * d < ng) load(d, wave + 4 * d);
-    for (int g = wave; g < ng; g += 4 * kDepth) {
-#pragma unroll
-        for (int d = 0; d < kDepth; ++d) {
-            if (g + 4 * d >= ng) break;
+        for (int s = 0; s < 2; ++s)
 #pragma unroll
             for (int i = 0; i < 2; ++i)
 #pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[d].v[i].x, fb[d].v[j].x, acc[i][j], 0, 0, 0);
-                    acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[d].v[i].y, fb[d].v[j].y, acc[i][j], 0, 0, 0);
-                }
-            if (g + 4 * (d + kDepth) < ng) load(d, g + 4 * (d + kDepth));
+                for (int j = 0; j < 2; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(s ? fa[d][i].y : fa[d][i].x,
+                                                                     s ? fb[d][j].y : fb[d][j].x, acc[i][j], 0, 0, 0);
+    };
+#pragma unroll
+    for (int d = 0; d < kDepth; ++d)
+        if (d < n) load(d, d);
+    int at = 0;
+    // no branches while every slot has a successor, so the waits stay exact
+    for (; at + 2 * kDepth <= n; at += kDepth) {
+#pragma unroll
+        for (int d = 0; d < kDepth; ++d) {
+            mul(d);
+            load(d, at + kDepth + d);
         }
+    }
+#pragma unroll
+    for (int d = 0; d < kDepth; ++d) {
+        if (at + d >= n) break;
+        mul(d);
+        if (at + kDepth + d < n) load(d, at + kDepth + d);
+    }
+#pragma unroll
+    for (int d = 0; d < kDepth; ++d) {
+        if (at + kDepth + d >= n) break;
+        mul(d);
+    }
+    if (T.K % 8 && full % 4 == wave) {
+        oa.load_tail(fa[0], full, T.K % 8);
+        ob.load_tail(fb[0], full, T.K % 8);
+        mul(0);
     }
     // block b is finished by wave b: the sums of waves 0..3 in that order
 #pragma unroll
@@ -507,11 +541,11 @@ int dgemm_tile_for(int64_t tiles64, int64_t tiles128, int num_cu) {
     return tiles128 >= 4 * static_cast<int64_t>(num_cu) && 80 * tiles128 <= 21 * tiles64 ? 128 : 64;
 }
 
-// The split kernel: each 32 x 32 block on a compute unit of its own.
-// Measured (us, against 64 x 64 tiles): 512^3 14.3 / 22.9, 512 x 512 x 2048
-// 37 / 83, 128 x 128 x 8192 224 / 309; equal at 640^3 (100 tiles of 64, 28),
-// and 45 / 33 at 768^3.
-static bool split_pays(int64_t tiles64, int num_cu) { return 4 * tiles64 <= num_cu; }
+// The split kernel: up to two 32 x 32 blocks per compute unit.  Measured (us,
+// against 64 x 64 tiles): 512^3 11.0 / 22.9, 640^3 (100 tiles of 64) 20.6 /
+// 28.1, 512 x 512 x 2048 28 / 83, 128 x 128 x 8192 116 / 309; equal at 768^3
+// (144 tiles, 33), and 52 / 43 at 1024^3.
+static bool split_pays(int64_t tiles64, int num_cu) { return 2 * tiles64 <= num_cu; }
 
 hipError_t launch_dgemm_single(bool ta, bool tb, const Dgemm64Args &a, int num_cu, hipStream_t s) {
     if (a.out.M <= 0 || a.out.N <= 0) return hipSuccess;
