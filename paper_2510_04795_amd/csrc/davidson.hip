@@ -14,10 +14,24 @@
 //
 // All reductions use a fixed partition and a fixed tree, so a run is
 // bit-reproducible.  The host reads (theta, rho) once per step.
+//
+// A step's vector work is bound by reading V three times and W once (0.15 ms
+// of memory traffic at m = 13, n = 2^20) and, for small bases, by one launch
+// of 4 to 5 us after another.  So a reduction ends in its consumer: blocks
+// write partials, and the kernel that needs the sum adds the 512 partials
+// itself (k_project, k_normalise, k_jacobi, k_publish) instead of waiting for
+// a one-block launch, and copies ride in passes that hold the values anyway.
+// At n = 2^20, m = 13: k_jacobi 91 -> 77 us (groups of lanes sized to a row;
+// with one wave per pair 107), dot products 36 -> 19 us, projections 17 + 5 ->
+// 25 us including the norm, Ritz vectors 103 -> 62 us (4.3 TB/s, eight loads in
+// flight); a Davidson step of 0.3 ms besides its matvec loses 8 launches and a
+// copy, a Lanczos solve at n = 9216 goes from 1.25 to 1.04 ms.
+#include <algorithm>
 #include <cmath>
 #include <type_traits>
 #include <vector>
 
+#include "rotation.h"
 #include "runtime.h"
 
 using namespace oz;
@@ -44,135 +58,189 @@ __device__ inline double block_sum(double v, double *sh) {
     return r;
 }
 
-// Rows of a launch counted on the device: with m non-null the rows are
-// *m + add (the grid covers the largest count, the rows past it return),
-// else the grid's.  The Davidson basis size lives on the device, so one
-// captured step serves every basis size.
-struct DevRows {
-    const int *m;
-    int add;
-    __device__ bool skip(int row) const { return m && row >= *m + add; }
+// Basis size of a launch: a host value, or (dev set) the device's, so that one
+// captured Davidson step serves every basis size.  A full basis (full set)
+// counts as one vector: the step that finds it full starts by collapsing it
+// to the Ritz pair.
+struct BasisSize {
+    int m;
+    const int *dev;
+    int full;
+    __device__ int get() const {
+        const int k = dev ? *dev : m;
+        return full && k == full ? 1 : k;
+    }
 };
 
-// partial[row][blk] = sum over this block's share of A[row][i] * v[i]
+// partial[row][blk] = sum over this block's share of A[row][i] * v[i], rows
+// below the basis size + add (the grid covers the largest count).  With copy
+// set, the blocks of row 0 also store v as row `basis size` of copy.
 __global__ __launch_bounds__(kDotThreads) void k_dots_partial(const double *__restrict__ A, int64_t lda, const double *__restrict__ v,
                                                               int64_t n, double *__restrict__ partial, const int *gate,
-                                                              DevRows rows) {
+                                                              BasisSize size, int add, double *__restrict__ copy) {
     if (gate && *gate == 0) return;
-    if (rows.skip(blockIdx.y)) return;
+    const int m = size.get();
+    if (static_cast<int>(blockIdx.y) >= m + add) return;
     __shared__ double sh[kDotThreads];
     const int row = blockIdx.y;
     const double *a = A + row * lda;
+    double *c = copy && row == 0 ? copy + m * n : nullptr;
+    const int64_t step = static_cast<int64_t>(gridDim.x) * blockDim.x;
     double acc = 0.0;
-    for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n;
-         i += static_cast<int64_t>(gridDim.x) * blockDim.x)
+    int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+    // four elements of each vector in flight, summed in order
+    for (; i + 3 * step < n; i += 4 * step) {
+        double x[4], y[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            x[q] = a[i + q * step];
+            y[q] = v[i + q * step];
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            acc = fma(x[q], y[q], acc);
+            if (c) c[i + q * step] = y[q];
+        }
+    }
+    for (; i < n; i += step) {
         acc = fma(a[i], v[i], acc);
+        if (c) c[i] = v[i];
+    }
     const double s = block_sum(acc, sh);
     if (threadIdx.x == 0) partial[static_cast<int64_t>(row) * gridDim.x + blockIdx.x] = s;
 }
 
-// out[row * out_stride] = sum of the row's partials; optional mirror out2.
-// With rows.m set, out and out2 move by *rows.m times out_mscale / out2_mscale.
-__global__ __launch_bounds__(kDotThreads) void k_dots_final(const double *__restrict__ partial, int nblk, double *out, int64_t out_stride,
-                                                            double *out2, int64_t out2_stride, const int *gate,
-                                                            DevRows rows, int64_t out_mscale, int64_t out2_mscale) {
-    if (gate && *gate == 0) return;
-    if (rows.skip(blockIdx.x)) return;
-    __shared__ double sh[kDotThreads];
-    const int row = blockIdx.x;
-    double acc = 0.0;
-    for (int b = threadIdx.x; b < nblk; b += blockDim.x) acc += partial[static_cast<int64_t>(row) * nblk + b];
-    const double s = block_sum(acc, sh);
-    if (threadIdx.x == 0) {
-        const int64_t m = rows.m ? *rows.m : 0;
-        out[m * out_mscale + row * out_stride] = s;
-        if (out2) out2[m * out2_mscale + row * out2_stride] = s;
+// Sum of one row's partials (nblk <= 512) by one wave, in the order of
+// block_sum over 256 threads that each add partials t and t + 256.  All lanes
+// get it.
+__device__ inline double partials_sum(const double *__restrict__ p, int nblk) {
+    const int l = threadIdx.x & 63;
+    double v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int t = l + 64 * q;
+        double acc = 0.0;
+        if (t < nblk) acc += p[t];
+        if (t + 256 < nblk) acc += p[t + 256];
+        v[q] = acc;
     }
+    double s = (v[0] + v[2]) + (v[1] + v[3]);
+    for (int o = 32; o >= 1; o >>= 1) s += __shfl_down(s, o, 64);
+    return __shfl(s, 0, 64);
 }
 
-// Lowest eigenpair of the symmetric m x m matrix G (leading dimension ldg) by
-// cyclic Jacobi with the round-robin pairing; writes theta and y (largest
-// |y_i| made positive).  One workgroup of 256 threads, m <= 64.
-__global__ __launch_bounds__(256) void k_jacobi(const double *__restrict__ G, int ldg, int m_arg, const int *m_dev,
-                                                double *__restrict__ y, double *__restrict__ theta_out) {
-    const int m = m_dev ? *m_dev : m_arg;
+// out[row] = sum of the row's partials (start vectors; the steps' consumers
+// sum the partials themselves)
+__global__ __launch_bounds__(64) void k_dots_final(const double *__restrict__ partial, int nblk, double *out) {
+    const double s = partials_sum(partial + static_cast<int64_t>(blockIdx.x) * nblk, nblk);
+    if (threadIdx.x == 0) out[blockIdx.x] = s;
+}
+
+// The new row and column of G from the partials of V[i] . W[m], i <= m, then
+// the lowest eigenpair of the (m + 1) x (m + 1) matrix G (leading dimension
+// ldg) by cyclic Jacobi with the round-robin pairing; writes theta, y (largest
+// |y_i| made positive) and the new basis size.  With nblk = 0 G is complete
+// and of size m.  One workgroup of 256 threads, m + 1 <= 64.
+// Groups of 16, 32 or 64 lanes (the smallest that holds a row) share a round's
+// pairs: a group computes its pairs' rotations, sweeps the columns of rows p,
+// q (no other group touches those rows) and, after a barrier, the rows of
+// columns p, q.  Bound: the chain of rounds (a rotation, two passes through
+// LDS, two barriers).
+__global__ __launch_bounds__(256) void k_jacobi(double *__restrict__ G, int ldg, BasisSize size, int *m_dev,
+                                                const double *__restrict__ partial, int nblk, double *__restrict__ y,
+                                                double *__restrict__ theta_out) {
     __shared__ double A[64][65];
     __shared__ double Vv[64][65];
-    __shared__ double cs[32], sn[32];
-    __shared__ int pp[32], qq[32];
     __shared__ double red[256];
-    __shared__ int done;
     const int t = threadIdx.x;
-    for (int i = t; i < m * m; i += blockDim.x) {
-        const int r = i / m, c = i % m;
-        A[r][c] = G[r * ldg + c];
-        Vv[r][c] = (r == c) ? 1.0 : 0.0;
+    const int wave = t >> 6, lane = t & 63;
+    const int old = size.get();
+    const int m = old + (nblk ? 1 : 0);
+    for (int r = wave; r < m; r += 4)
+        if (lane < m) {
+            if (!nblk || (r < old && lane < old)) A[r][lane] = G[r * ldg + lane];
+            Vv[r][lane] = r == lane ? 1.0 : 0.0;
+        }
+    if (nblk) {
+        for (int r = wave; r < m; r += 4) {
+            const double s = partials_sum(partial + static_cast<int64_t>(r) * nblk, nblk);
+            if (lane == 0) {
+                A[r][old] = s;
+                A[old][r] = s;
+                G[r * ldg + old] = s;
+                G[old * ldg + r] = s;
+            }
+        }
+        __syncthreads();  // every thread has read the old basis size
+        if (t == 0) *m_dev = m;
     }
     __syncthreads();
     const int me = (m + 1) & ~1;  // even number of players (one dummy when m is odd)
+    const int gs = m <= 16 ? 16 : m <= 32 ? 32 : 64, ngrp = 256 / gs, grp = t / gs, sub = t % gs;
     for (int sweep = 0; sweep < 30 && m > 1; ++sweep) {
         // convergence test: off(A) <= 1e-14 ||A||_F
         double off = 0.0, tot = 0.0;
-        for (int i = t; i < m * m; i += blockDim.x) {
-            const int r = i / m, c = i % m;
-            const double v = A[r][c] * A[r][c];
-            tot += v;
-            if (r != c) off += v;
+        for (int r = wave; r < m; r += 4)
+            if (lane < m) {
+                const double v = A[r][lane] * A[r][lane];
+                tot += v;
+                if (r != lane) off += v;
+            }
+        for (int o = 32; o >= 1; o >>= 1) {
+            off += __shfl_xor(off, o, 64);
+            tot += __shfl_xor(tot, o, 64);
         }
-        const double soff = block_sum(off, red);
-        const double stot = block_sum(tot, red);
-        if (t == 0) done = (sqrt(soff) <= 1e-14 * sqrt(stot)) ? 1 : 0;
+        if (lane == 0) {
+            red[wave] = off;
+            red[4 + wave] = tot;
+        }
         __syncthreads();
-        if (done) break;
+        off = (red[0] + red[1]) + (red[2] + red[3]);
+        tot = (red[4] + red[5]) + (red[6] + red[7]);
+        __syncthreads();
+        if (sqrt(off) <= 1e-14 * sqrt(tot)) break;
         for (int round = 0; round < me - 1; ++round) {
-            // round-robin: player me-1 fixed, the others rotate
-            if (t < me / 2) {
-                int a, b;
-                if (t == 0) {
-                    a = me - 1;
-                    b = round;
-                } else {
-                    a = (round + t) % (me - 1);
-                    b = (round - t + (me - 1)) % (me - 1);
+            // round-robin: player me-1 fixed, the others rotate; pair k of the
+            // round is (p, q), idle when q is the dummy
+            auto pair = [&](int k, int *p, int *q) {
+                int a = me - 1, b = round;
+                if (k > 0) {
+                    a = round + k;
+                    a = a >= me - 1 ? a - (me - 1) : a;
+                    b = round - k;
+                    b = b < 0 ? b + me - 1 : b;
                 }
-                const int p = a < b ? a : b, q = a < b ? b : a;
-                double c = 1.0, s = 0.0;
-                if (q < m) {
-                    const double apq = A[p][q];
-                    if (apq != 0.0) {
-                        const double th = (A[q][q] - A[p][p]) / (2.0 * apq);
-                        const double tt = (th >= 0 ? 1.0 : -1.0) / (fabs(th) + sqrt(th * th + 1.0));
-                        c = 1.0 / sqrt(tt * tt + 1.0);
-                        s = tt * c;
-                    }
-                }
-                cs[t] = c;
-                sn[t] = s;
-                pp[t] = p;
-                qq[t] = q < m ? q : -1;
+                *p = a < b ? a : b;
+                *q = a < b ? b : a;
+            };
+            double cl = 1.0, sl = 0.0;
+            {
+                const int k = grp + ngrp * (sub & 7);
+                int p, q;
+                pair(k, &p, &q);
+                if (k < me / 2 && q < m) schur_rotation(A[p][p], A[q][q], A[p][q], &cl, &sl);
+            }
+            for (int i = 0, k = grp; i * ngrp < me / 2; ++i, k += ngrp) {  // rows: A <- J^T A
+                int p, q;
+                pair(k, &p, &q);
+                const double c = __shfl(cl, lane - sub + i, 64), s = __shfl(sl, lane - sub + i, 64);
+                if (k >= me / 2 || q >= m || sub >= m) continue;
+                const double ap = A[p][sub], aq = A[q][sub];
+                A[p][sub] = c * ap - s * aq;
+                A[q][sub] = s * ap + c * aq;
             }
             __syncthreads();
-            // rows: A <- J^T A
-            for (int i = t; i < (me / 2) * m; i += blockDim.x) {
-                const int k = i / m, c = i % m;
-                if (qq[k] < 0) continue;
-                const int p = pp[k], q = qq[k];
-                const double ap = A[p][c], aq = A[q][c];
-                A[p][c] = cs[k] * ap - sn[k] * aq;
-                A[q][c] = sn[k] * ap + cs[k] * aq;
-            }
-            __syncthreads();
-            // columns: A <- A J, eigenvectors V <- V J
-            for (int i = t; i < (me / 2) * m; i += blockDim.x) {
-                const int k = i / m, r = i % m;
-                if (qq[k] < 0) continue;
-                const int p = pp[k], q = qq[k];
-                const double ap = A[r][p], aq = A[r][q];
-                A[r][p] = cs[k] * ap - sn[k] * aq;
-                A[r][q] = sn[k] * ap + cs[k] * aq;
-                const double vp = Vv[r][p], vq = Vv[r][q];
-                Vv[r][p] = cs[k] * vp - sn[k] * vq;
-                Vv[r][q] = sn[k] * vp + cs[k] * vq;
+            for (int i = 0, k = grp; i * ngrp < me / 2; ++i, k += ngrp) {  // columns: A <- A J, V <- V J
+                int p, q;
+                pair(k, &p, &q);
+                const double c = __shfl(cl, lane - sub + i, 64), s = __shfl(sl, lane - sub + i, 64);
+                if (k >= me / 2 || q >= m || sub >= m) continue;
+                const double ap = A[sub][p], aq = A[sub][q];
+                const double vp = Vv[sub][p], vq = Vv[sub][q];
+                A[sub][p] = c * ap - s * aq;
+                A[sub][q] = s * ap + c * aq;
+                Vv[sub][p] = c * vp - s * vq;
+                Vv[sub][q] = s * vp + c * vq;
             }
             __syncthreads();
         }
@@ -202,7 +270,21 @@ __global__ __launch_bounds__(kDotThreads) void k_ritz(const double *__restrict__
     for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n;
          i += static_cast<int64_t>(gridDim.x) * blockDim.x) {
         double xi = 0.0, hi = 0.0;
-        for (int j = 0; j < m; ++j) {
+        int j = 0;
+        for (; j + 4 <= m; j += 4) {  // eight loads in flight, summed in order
+            double a[4], b[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                a[q] = V[(j + q) * n + i];
+                b[q] = W[(j + q) * n + i];
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                xi = fma(y[j + q], a[q], xi);
+                hi = fma(y[j + q], b[q], hi);
+            }
+        }
+        for (; j < m; ++j) {
             xi = fma(y[j], V[j * n + i], xi);
             hi = fma(y[j], W[j * n + i], hi);
         }
@@ -216,34 +298,96 @@ __global__ __launch_bounds__(kDotThreads) void k_ritz(const double *__restrict__
     if (threadIdx.x == 0) partial[blockIdx.x] = s;
 }
 
-__global__ void k_precond(const double *__restrict__ r, const double *__restrict__ hdiag,
-                          const double *__restrict__ theta, double *__restrict__ t, int64_t n) {
+// The start of a continuing step: t = r / (diag(H) - theta), |den| >= 1e-8.
+// A full basis (*m_dev == full) collapses to the Ritz pair: V[0] = x, W[0] =
+// hx, G = [theta] and zero elsewhere; the size stays `full` until k_jacobi
+// sets the new one, and the kernels between count it as one (BasisSize).
+__global__ __launch_bounds__(256) void k_begin(const double *__restrict__ r, const double *__restrict__ hdiag,
+                                               const double *__restrict__ theta, double *__restrict__ t, int64_t n,
+                                               const int *m_dev, int full, const double *__restrict__ x,
+                                               const double *__restrict__ hx, double *__restrict__ V,
+                                               double *__restrict__ W, double *__restrict__ G, int ldg) {
     const double th = *theta;
+    const bool collapse = *m_dev == full;
     for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n;
          i += static_cast<int64_t>(gridDim.x) * blockDim.x) {
         double den = hdiag[i] - th;
         if (fabs(den) < 1e-8) den = copysign(1e-8, den);
         t[i] = r[i] / den;
+        if (collapse) {
+            V[i] = x[i];
+            W[i] = hx[i];
+        }
     }
+    if (collapse && blockIdx.x == 0)
+        for (int i = threadIdx.x; i < full * full; i += blockDim.x) G[(i / full) * ldg + i % full] = i == 0 ? th : 0.0;
 }
 
-// t -= V^T c  (c: m projection coefficients)
-__global__ void k_project(const double *__restrict__ V, int64_t n, int m_arg, const int *m_dev,
-                          const double *__restrict__ c, double *__restrict__ t, const int *gate) {
+// t -= V^T c with c_j the sums of the partials of V[j] . t (every block sums
+// them itself); *last (nullable, host-visible) = the last one.  With norm set,
+// norm[blk] = the block's partial of |t|^2 afterwards, with k_dots_partial's
+// grid and order: thread t < 256 of its blocks adds elements 256 b + t, then
+// every 256 gridDim-th.  Here four threads share such a chain's projections
+// and the first of them adds the squares from LDS.
+constexpr int kProjThreads = 4 * kDotThreads;
+__global__ __launch_bounds__(kProjThreads) void k_project(const double *__restrict__ V, int64_t n, BasisSize size,
+                                                          const double *__restrict__ partial, double *__restrict__ t,
+                                                          const int *gate, double *last, double *__restrict__ norm) {
     if (gate && *gate == 0) return;
-    const int m = m_dev ? *m_dev : m_arg;
-    for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n;
-         i += static_cast<int64_t>(gridDim.x) * blockDim.x) {
-        double s = 0.0;
-        for (int j = 0; j < m; ++j) s = fma(c[j], V[j * n + i], s);
-        t[i] = t[i] - s;
+    __shared__ double sh[kProjThreads];
+    __shared__ double c[64];
+    const int m = size.get();
+    const int nblk = gridDim.x;
+    for (int j = threadIdx.x >> 6; j < m; j += kProjThreads / 64) {
+        const double s = partials_sum(partial + static_cast<int64_t>(j) * nblk, nblk);
+        if ((threadIdx.x & 63) == 0) c[j] = s;
     }
+    __syncthreads();
+    if (last && blockIdx.x == 0 && threadIdx.x == 0) *last = c[m - 1];
+    const int lane = threadIdx.x % kDotThreads, quarter = threadIdx.x / kDotThreads;
+    const int64_t step = static_cast<int64_t>(gridDim.x) * kDotThreads;
+    double acc = 0.0;
+    for (int64_t i0 = static_cast<int64_t>(blockIdx.x) * kDotThreads + lane; i0 - lane < n; i0 += 4 * step) {
+        const int64_t i = i0 + quarter * step;
+        double ti = 0.0;
+        if (i < n) {
+            double s = 0.0;
+            int j = 0;
+            for (; j + 8 <= m; j += 8) {  // eight loads in flight, summed in order
+                double v[8];
+#pragma unroll
+                for (int q = 0; q < 8; ++q) v[q] = V[(j + q) * n + i];
+#pragma unroll
+                for (int q = 0; q < 8; ++q) s = fma(c[j + q], v[q], s);
+            }
+            for (; j < m; ++j) s = fma(c[j], V[j * n + i], s);
+            ti = t[i] - s;
+            t[i] = ti;
+        }
+        if (!norm) continue;
+        sh[threadIdx.x] = ti;
+        __syncthreads();
+        if (quarter == 0)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (i0 + q * step < n) acc = fma(sh[q * kDotThreads + lane], sh[q * kDotThreads + lane], acc);
+        __syncthreads();
+    }
+    if (!norm) return;
+    if (quarter == 0) sh[lane] = acc;
+    __syncthreads();
+    for (int w = kDotThreads / 2; w > 0; w >>= 1) {
+        if (static_cast<int>(threadIdx.x) < w) sh[threadIdx.x] += sh[threadIdx.x + w];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) norm[blockIdx.x] = sh[0];
 }
 
-// when |t|^2 < 1e-20 replace t by r and raise the gate for a second pass
-__global__ void k_fallback(const double *__restrict__ nrm2, const double *__restrict__ r, double *__restrict__ t,
-                           int64_t n, int *gate) {
-    const bool fb = *nrm2 < 1e-20;
+// when |t|^2 (the sum of the partials) < 1e-20 replace t by r and raise the
+// gate for a second pass
+__global__ __launch_bounds__(256) void k_fallback(const double *__restrict__ norm, int nblk, const double *__restrict__ r,
+                                                  double *__restrict__ t, int64_t n, int *gate) {
+    const bool fb = partials_sum(norm, nblk) < 1e-20;
     if (blockIdx.x == 0 && threadIdx.x == 0) *gate = fb ? 1 : 0;
     if (!fb) return;
     for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n;
@@ -251,12 +395,17 @@ __global__ void k_fallback(const double *__restrict__ nrm2, const double *__rest
         t[i] = r[i];
 }
 
-// out (moved by *m_dev rows of n when m_dev is set) = t / sqrt(nrm2); the
-// same values into out2 when it is set
-__global__ void k_scale_into(const double *__restrict__ t, const double *__restrict__ nrm2, double *__restrict__ out,
-                             int64_t n, const int *m_dev = nullptr, double *__restrict__ out2 = nullptr) {
-    const double inv = 1.0 / sqrt(*nrm2);
-    double *o = out + (m_dev ? static_cast<int64_t>(*m_dev) * n : 0);
+// row `basis size` of out = t / |t| with |t|^2 the sum of the partials; the
+// same values into out2 when it is set, |t|^2 into *nrm2 (host-visible) when
+// that is.  out may be NULL: only the norm.
+__global__ __launch_bounds__(256) void k_normalise(const double *__restrict__ t, const double *__restrict__ norm, int nblk,
+                                                   double *__restrict__ out, int64_t n, BasisSize size,
+                                                   double *__restrict__ out2, double *nrm2) {
+    const double sum = partials_sum(norm, nblk);
+    if (nrm2 && blockIdx.x == 0 && threadIdx.x == 0) *nrm2 = sum;
+    if (!out) return;
+    const double inv = 1.0 / sqrt(sum);
+    double *o = out + size.get() * n;
     for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n;
          i += static_cast<int64_t>(gridDim.x) * blockDim.x) {
         const double v = t[i] * inv;
@@ -265,44 +414,26 @@ __global__ void k_scale_into(const double *__restrict__ t, const double *__restr
     }
 }
 
-// collapse the basis to the Ritz pair when it is full (*m_dev == mmax):
-// G = [theta], zero elsewhere, and the basis size becomes 1
-__global__ void k_collapse_g(double *G, int ldg, int mmax, const double *theta, int *m_dev) {
-    if (*m_dev != mmax) return;
-    for (int i = threadIdx.x; i < mmax * mmax; i += blockDim.x) G[(i / mmax) * ldg + i % mmax] = 0.0;
-    __syncthreads();
+// (theta, rho^2) into the pinned host buffer the step reads after its sync,
+// rho^2 the sum of the partials
+__global__ __launch_bounds__(64) void k_publish(double *__restrict__ scal, const double *__restrict__ partial, int nblk,
+                                                double *host) {
+    const double s = partials_sum(partial, nblk);
     if (threadIdx.x == 0) {
-        G[0] = *theta;
-        *m_dev = 1;
+        scal[1] = s;
+        host[0] = scal[0];
+        host[1] = s;
     }
-}
-
-// dst (moved by *m_dev rows of n) = src; with full set, only when the basis
-// is full (*m_dev == full), into row 0 (the collapse to the Ritz pair)
-__global__ void k_copy_row(const double *__restrict__ src, double *__restrict__ dst, int64_t n, const int *m_dev,
-                           int full) {
-    const int m = *m_dev;
-    if (full && m != full) return;
-    double *d = dst + (full ? 0 : static_cast<int64_t>(m) * n);
-    for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n;
-         i += static_cast<int64_t>(gridDim.x) * blockDim.x)
-        d[i] = src[i];
-}
-
-// *m_dev += 1 (the basis gained a vector)
-__global__ void k_bump(int *m_dev) {
-    if (threadIdx.x == 0) *m_dev += 1;
-}
-
-// (theta, rho^2) into the pinned host buffer the step reads after its sync
-__global__ void k_publish(const double *__restrict__ scal, double *host) {
-    if (threadIdx.x < 2) host[threadIdx.x] = scal[threadIdx.x];
 }
 
 unsigned grid_n(int64_t n) {
     const int64_t g = ceil_div(n, 256);
     return static_cast<unsigned>(g < 1 ? 1 : (g > 4096 ? 4096 : g));
 }
+
+// Blocks of the kernels that first sum the norm's partials: four per compute
+// unit, so the sum is not repeated more often than it overlaps.
+unsigned grid_norm(int64_t n) { return std::min(grid_n(n), 1024u); }
 
 }  // namespace
 
@@ -320,7 +451,7 @@ struct davidson_s {
     int cur = 0, rep = 0;
     double *hx = nullptr, *r = nullptr, *t = nullptr;
     double *mv_in = nullptr, *mv_out = nullptr;  // the matvec's fixed input and output
-    double *y = nullptr, *coef = nullptr, *partial = nullptr, *scal = nullptr;  // scal: theta, rho2, nrm2
+    double *y = nullptr, *partial = nullptr, *norm = nullptr, *scal = nullptr;  // scal: theta, rho2, nrm2
     int *gate = nullptr;
     int *m_dev = nullptr;  // the basis size on the device (the host keeps m too)
     double *host = nullptr;  // pinned: theta, rho2 of the latest Rayleigh-Ritz solve
@@ -353,92 +484,70 @@ void dfree(davidson d) {
     delete d;
 }
 
-// out[i] = row_i(A) . v for i < rows (rows with stride lda), into out[i * out_stride]
-hipError_t dots(davidson d, const double *A, int64_t lda, int rows, const double *v, double *out,
-                int64_t out_stride, double *out2, int64_t out2_stride, const int *gate, hipStream_t s) {
-    const int nb = dot_blocks(d->n);
-    hipLaunchKernelGGL(k_dots_partial, dim3(nb, rows), dim3(kDotThreads), 0, s, A, lda, v, d->n, d->partial, gate,
-                       DevRows{nullptr, 0});
-    hipLaunchKernelGGL(k_dots_final, dim3(rows), dim3(kDotThreads), 0, s, d->partial, nb, out, out_stride, out2,
-                       out2_stride, gate, DevRows{nullptr, 0}, 0, 0);
-    return hipGetLastError();
-}
-
-// The same over *m_dev + add rows of A (the grid covers m_max + 1); out and
-// out2 move by *m_dev times out_mscale / out2_mscale.
-hipError_t dots_m(davidson d, const double *A, int64_t lda, int add, const double *v, double *out,
-                  int64_t out_stride, int64_t out_mscale, double *out2, int64_t out2_stride, int64_t out2_mscale,
-                  const int *gate, hipStream_t s) {
-    const int nb = dot_blocks(d->n);
-    const int rows = d->m_max + add;
-    hipLaunchKernelGGL(k_dots_partial, dim3(nb, rows), dim3(kDotThreads), 0, s, A, lda, v, d->n, d->partial, gate,
-                       DevRows{d->m_dev, add});
-    hipLaunchKernelGGL(k_dots_final, dim3(rows), dim3(kDotThreads), 0, s, d->partial, nb, out, out_stride, out2,
-                       out2_stride, gate, DevRows{d->m_dev, add}, out_mscale, out2_mscale);
-    return hipGetLastError();
-}
-
-// V[m] := normalised, orthogonalised t; W[m] = H V[m]; new column of G;
-// m += 1.  m is the device's basis size.
-int expand(davidson d, hipStream_t s) {
-    hipError_t e;
-    const int64_t n = d->n;
-    double *nrm2 = d->scal + 2;
-    for (int pass = 0; pass < 2; ++pass) {
-        if ((e = dots_m(d, d->V, n, 0, d->t, d->coef, 1, 0, nullptr, 0, 0, nullptr, s)) != hipSuccess)
-            return hip_fail(e, "davidson: projection");
-        hipLaunchKernelGGL(k_project, dim3(grid_n(n)), dim3(256), 0, s, d->V, n, 0, d->m_dev, d->coef, d->t, nullptr);
-    }
-    if ((e = dots(d, d->t, n, 1, d->t, nrm2, 1, nullptr, 0, nullptr, s)) != hipSuccess) return hip_fail(e, "davidson: norm");
-    hipLaunchKernelGGL(k_fallback, dim3(grid_n(n)), dim3(256), 0, s, nrm2, d->r, d->t, n, d->gate);
-    for (int pass = 0; pass < 2; ++pass) {
-        dots_m(d, d->V, n, 0, d->t, d->coef, 1, 0, nullptr, 0, 0, d->gate, s);
-        hipLaunchKernelGGL(k_project, dim3(grid_n(n)), dim3(256), 0, s, d->V, n, 0, d->m_dev, d->coef, d->t, d->gate);
-    }
-    dots(d, d->t, n, 1, d->t, nrm2, 1, nullptr, 0, d->gate, s);
-    // V[m] and the matvec's input get the same values
-    hipLaunchKernelGGL(k_scale_into, dim3(grid_n(n)), dim3(256), 0, s, d->t, nrm2, d->V, n, d->m_dev, d->mv_in);
-    if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "davidson: orthogonalisation");
-    int rc = heff_apply(d->H, d->mv_in, d->mv_out, s);
-    if (rc != OZ_OK) return rc;
-    hipLaunchKernelGGL(k_copy_row, dim3(grid_n(n)), dim3(256), 0, s, d->mv_out, d->W, n, d->m_dev, 0);
-    // G[i][m] = G[m][i] = V[i] . W[m], i <= m
-    if ((e = dots_m(d, d->V, n, 1, d->mv_out, d->G, d->m_max, 1, d->G, 1, d->m_max, nullptr, s)) != hipSuccess)
-        return hip_fail(e, "davidson: projected column");
-    hipLaunchKernelGGL(k_bump, dim3(1), dim3(64), 0, s, d->m_dev);
-    if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "davidson: basis size");
-    return OZ_OK;
-}
-
-// Rayleigh-Ritz on the device's basis of m vectors, the Ritz pair into x_out
-// (and hx, r), rho^2, and (theta, rho^2) published to the pinned host buffer.
-int rayleigh_ritz(davidson d, double *x_out, hipStream_t s) {
-    const int64_t n = d->n;
-    double *theta = d->scal, *rho2 = d->scal + 1;
-    hipLaunchKernelGGL(k_jacobi, dim3(1), dim3(256), 0, s, d->G, d->m_max, 0, d->m_dev, d->y, theta);
+// |v|^2 into out, through d->norm
+hipError_t norm2(double *partial, const double *v, int64_t n, double *out, hipStream_t s) {
     const int nb = dot_blocks(n);
+    hipLaunchKernelGGL(k_dots_partial, dim3(nb, 1), dim3(kDotThreads), 0, s, v, n, v, n, partial, nullptr,
+                       BasisSize{1, nullptr, 0}, 0, nullptr);
+    if (out) hipLaunchKernelGGL(k_dots_final, dim3(1), dim3(64), 0, s, partial, nb, out);
+    return hipGetLastError();
+}
+
+// Two classical Gram-Schmidt passes of t against the basis; the partials of
+// |t|^2 afterwards in `norm`, the first pass's last coefficient in *last.
+hipError_t gram_schmidt(const double *V, int64_t n, int rows, BasisSize size, double *t, double *partial, double *norm,
+                        const int *gate, double *last, hipStream_t s) {
+    const int nb = dot_blocks(n);
+    for (int pass = 0; pass < 2; ++pass) {
+        hipLaunchKernelGGL(k_dots_partial, dim3(nb, rows), dim3(kDotThreads), 0, s, V, n, t, n, partial, gate, size, 0,
+                           nullptr);
+        hipLaunchKernelGGL(k_project, dim3(nb), dim3(kProjThreads), 0, s, V, n, size, partial, t, gate,
+                           pass == 0 ? last : nullptr, pass == 1 ? norm : nullptr);
+    }
+    return hipGetLastError();
+}
+
+// Rayleigh-Ritz on the device's basis (with grow set, after taking in the new
+// vector's column of G from d->partial), the Ritz pair into x_out (and hx, r),
+// and (theta, rho^2) published to the pinned host buffer.
+int rayleigh_ritz(davidson d, double *x_out, bool grow, hipStream_t s) {
+    const int64_t n = d->n;
+    const int nb = dot_blocks(n);
+    double *theta = d->scal;
+    hipLaunchKernelGGL(k_jacobi, dim3(1), dim3(256), 0, s, d->G, d->m_max, BasisSize{0, d->m_dev, grow ? d->m_max : 0},
+                       d->m_dev, d->partial, grow ? nb : 0, d->y, theta);
     hipLaunchKernelGGL(k_ritz, dim3(nb), dim3(kDotThreads), 0, s, d->V, d->W, n, d->m_dev, d->y, theta, x_out, d->hx,
                        d->r, d->partial);
-    hipLaunchKernelGGL(k_dots_final, dim3(1), dim3(kDotThreads), 0, s, d->partial, nb, rho2, 1, nullptr, 0, nullptr,
-                       DevRows{nullptr, 0}, 0, 0);
-    hipLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, s, d->scal, d->host);
+    hipLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, s, d->scal, d->partial, nb, d->host);
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? OZ_OK : hip_fail(e, "davidson: Rayleigh-Ritz");
 }
 
 // Everything a continuing step does after its decision, with current Ritz
-// buffer c: correction, collapse when the basis is full, orthogonalisation
-// and matvec, then the next Rayleigh-Ritz into xs[c ^ 1].
+// buffer c: correction (and collapse when the basis is full),
+// orthogonalisation and matvec, then the next Rayleigh-Ritz into xs[c ^ 1].
 int step_tail(davidson d, int c, hipStream_t s) {
+    hipError_t e;
     const int64_t n = d->n;
-    const double *theta = d->scal;
-    hipLaunchKernelGGL(k_precond, dim3(grid_n(n)), dim3(256), 0, s, d->r, d->hdiag, theta, d->t, n);
-    hipLaunchKernelGGL(k_copy_row, dim3(grid_n(n)), dim3(256), 0, s, d->xs[c], d->V, n, d->m_dev, d->m_max);
-    hipLaunchKernelGGL(k_copy_row, dim3(grid_n(n)), dim3(256), 0, s, d->hx, d->W, n, d->m_dev, d->m_max);
-    hipLaunchKernelGGL(k_collapse_g, dim3(1), dim3(256), 0, s, d->G, d->m_max, d->m_max, theta, d->m_dev);
-    int rc = expand(d, s);
+    const int nb = dot_blocks(n);
+    const BasisSize size{0, d->m_dev, d->m_max};
+    hipLaunchKernelGGL(k_begin, dim3(grid_n(n)), dim3(256), 0, s, d->r, d->hdiag, d->scal, d->t, n, d->m_dev, d->m_max,
+                       d->xs[c], d->hx, d->V, d->W, d->G, d->m_max);
+    if ((e = gram_schmidt(d->V, n, d->m_max, size, d->t, d->partial, d->norm, nullptr, nullptr, s)) != hipSuccess)
+        return hip_fail(e, "davidson: projection");
+    hipLaunchKernelGGL(k_fallback, dim3(grid_norm(n)), dim3(256), 0, s, d->norm, nb, d->r, d->t, n, d->gate);
+    if ((e = gram_schmidt(d->V, n, d->m_max, size, d->t, d->partial, d->norm, d->gate, nullptr, s)) != hipSuccess)
+        return hip_fail(e, "davidson: projection");
+    // V[m] and the matvec's input get the same values
+    hipLaunchKernelGGL(k_normalise, dim3(grid_norm(n)), dim3(256), 0, s, d->t, d->norm, nb, d->V, n, size, d->mv_in, nullptr);
+    if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "davidson: orthogonalisation");
+    int rc = heff_apply(d->H, d->mv_in, d->mv_out, s);
     if (rc != OZ_OK) return rc;
-    return rayleigh_ritz(d, d->xs[c ^ 1], s);
+    // V[i] . W[m], i <= m, and W[m] itself
+    hipLaunchKernelGGL(k_dots_partial, dim3(nb, d->m_max + 1), dim3(kDotThreads), 0, s, d->V, n, d->mv_out, n, d->partial,
+                       nullptr, size, 1, d->W);
+    if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "davidson: projected column");
+    return rayleigh_ritz(d, d->xs[c ^ 1], true, s);
 }
 
 // step_tail from a captured graph (captured the first time c is seen), or
@@ -512,8 +621,8 @@ int davidson_create(ozaki_ctx ctx, davidson *out, heff_plan H, const double *hdi
     OZ_DA(r, sizeof(double) * n)
     OZ_DA(t, sizeof(double) * n)
     OZ_DA(y, sizeof(double) * 64)
-    OZ_DA(coef, sizeof(double) * 64)
     OZ_DA(partial, sizeof(double) * 65 * 512)
+    OZ_DA(norm, sizeof(double) * 512)
     OZ_DA(scal, sizeof(double) * 8)
     OZ_DA(gate, sizeof(int) * 4)
 #undef OZ_DA
@@ -529,7 +638,7 @@ int davidson_create(ozaki_ctx ctx, davidson *out, heff_plan H, const double *hdi
     }
     // v0 = x0 / |x0|, W0 = H v0, G00 = v0 . W0
     double *nrm2 = d->scal + 2;
-    if ((e = dots(d, x0, n, 1, x0, nrm2, 1, nullptr, 0, nullptr, s)) != hipSuccess ||
+    if ((e = norm2(d->norm, x0, n, nrm2, s)) != hipSuccess ||
         (e = hipMemcpyAsync(d->host, nrm2, sizeof(double), hipMemcpyDeviceToHost, s)) != hipSuccess ||
         (e = hipStreamSynchronize(s)) != hipSuccess) {
         dfree(d);
@@ -539,16 +648,20 @@ int davidson_create(ozaki_ctx ctx, davidson *out, heff_plan H, const double *hdi
         dfree(d);
         return fail(OZ_ERR_ARG, "davidson_create: start vector is zero or not finite");
     }
-    hipLaunchKernelGGL(k_scale_into, dim3(grid_n(n)), dim3(256), 0, s, x0, nrm2, d->V, n);
+    const int nb = dot_blocks(n);
+    hipLaunchKernelGGL(k_normalise, dim3(grid_norm(n)), dim3(256), 0, s, x0, d->norm, nb, d->V, n, BasisSize{0, nullptr, 0},
+                       nullptr, nullptr);
     if ((rc = heff_apply(H, d->V, d->W, s)) != OZ_OK) { dfree(d); return rc; }
-    dots(d, d->V, n, 1, d->W, d->G, 1, nullptr, 0, nullptr, s);
+    hipLaunchKernelGGL(k_dots_partial, dim3(nb, 1), dim3(kDotThreads), 0, s, d->V, n, d->W, n, d->partial, nullptr,
+                       BasisSize{1, nullptr, 0}, 0, nullptr);
+    hipLaunchKernelGGL(k_dots_final, dim3(1), dim3(64), 0, s, d->partial, nb, d->G);
     const int one = 1;
     if ((e = hipMemcpyAsync(d->m_dev, &one, sizeof(int), hipMemcpyHostToDevice, s)) != hipSuccess) {
         dfree(d);
         return hip_fail(e, "davidson_create: basis size");
     }
     // the first step's Rayleigh-Ritz solve (every later one ends the step before)
-    if ((rc = rayleigh_ritz(d, d->xs[0], s)) != OZ_OK) { dfree(d); return rc; }
+    if ((rc = rayleigh_ritz(d, d->xs[0], false, s)) != OZ_OK) { dfree(d); return rc; }
     if ((e = hipStreamSynchronize(s)) != hipSuccess) { dfree(d); return hip_fail(e, "davidson_create: sync"); }
     d->m = 1;
     *out = d;
@@ -706,9 +819,8 @@ struct lanczos_s {
     int m_max = 0, max_iter = 0;
     double tol = 0;
     std::vector<void *> allocs;
-    double *Q = nullptr, *w = nullptr, *coef = nullptr, *partial = nullptr, *scal = nullptr, *y_dev = nullptr;
-    int *gate = nullptr;
-    double *host = nullptr;  // pinned: coefficients of the first pass, |w|^2
+    double *Q = nullptr, *w = nullptr, *norm = nullptr, *partial = nullptr, *scal = nullptr, *y_dev = nullptr;
+    double *host = nullptr;  // pinned: the last step's alpha and |w|^2
     std::vector<double> alpha, beta, y;
     int m = 0, iter = 0, status = OZ_OK;
     double theta = 0, rho = 0;
@@ -730,22 +842,12 @@ void lfree(lanczos l) {
     delete l;
 }
 
-// out[i] = Q_i . v for i < rows, with the Davidson dot kernels
-hipError_t ldots(lanczos l, const double *Q, int rows, const double *v, double *out, hipStream_t s) {
-    const int nb = dot_blocks(l->n);
-    hipLaunchKernelGGL(k_dots_partial, dim3(nb, rows), dim3(kDotThreads), 0, s, Q, l->n, v, l->n, l->partial, nullptr,
-                       DevRows{nullptr, 0});
-    hipLaunchKernelGGL(k_dots_final, dim3(rows), dim3(kDotThreads), 0, s, l->partial, nb, out, 1, nullptr, 0, nullptr,
-                       DevRows{nullptr, 0}, 0, 0);
-    return hipGetLastError();
-}
-
 // q_0 = x / |x| into the basis; resets T
 int lanczos_reset(lanczos l, const double *x, hipStream_t s) {
     hipError_t e;
-    double *nrm2 = l->scal;
-    if ((e = ldots(l, x, 1, x, nrm2, s)) != hipSuccess) return hip_fail(e, "lanczos: norm");
-    hipLaunchKernelGGL(k_scale_into, dim3(grid_n(l->n)), dim3(256), 0, s, x, nrm2, l->Q, l->n);
+    if ((e = norm2(l->norm, x, l->n, nullptr, s)) != hipSuccess) return hip_fail(e, "lanczos: norm");
+    hipLaunchKernelGGL(k_normalise, dim3(grid_norm(l->n)), dim3(256), 0, s, x, l->norm, dot_blocks(l->n), l->Q, l->n,
+                       BasisSize{0, nullptr, 0}, nullptr, nullptr);
     if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "lanczos: normalise");
     l->m = 1;
     l->alpha.clear();
@@ -783,11 +885,10 @@ int lanczos_create(ozaki_ctx ctx, lanczos *out, heff_plan H, const double *x0, i
     l->field = static_cast<decltype(l->field)>(p);
     OZ_LA(Q, sizeof(double) * (m_max + 1) * n)
     OZ_LA(w, sizeof(double) * n)
-    OZ_LA(coef, sizeof(double) * 72)
+    OZ_LA(norm, sizeof(double) * 512)
     OZ_LA(partial, sizeof(double) * 66 * 512)
     OZ_LA(scal, sizeof(double) * 8)
     OZ_LA(y_dev, sizeof(double) * 72)
-    OZ_LA(gate, sizeof(int) * 4)
 #undef OZ_LA
     if ((e = hipHostMalloc(reinterpret_cast<void **>(&l->host), sizeof(double) * 72, 0)) != hipSuccess) {
         l->host = nullptr;
@@ -795,7 +896,7 @@ int lanczos_create(ozaki_ctx ctx, lanczos *out, heff_plan H, const double *x0, i
         return hip_fail(e, "lanczos_create: pinned buffer");
     }
     // start vector: |x0| must be positive and finite
-    if ((e = ldots(l, x0, 1, x0, l->scal, s)) != hipSuccess ||
+    if ((e = norm2(l->norm, x0, n, l->scal, s)) != hipSuccess ||
         (e = hipMemcpyAsync(l->host, l->scal, sizeof(double), hipMemcpyDeviceToHost, s)) != hipSuccess ||
         (e = hipStreamSynchronize(s)) != hipSuccess) {
         lfree(l);
@@ -825,20 +926,20 @@ int lanczos_step(lanczos l, davidson_info *info, void *stream) {
     double *qj = l->Q + static_cast<int64_t>(m - 1) * n;
     int rc = heff_apply(l->H, qj, l->w, s);
     if (rc != OZ_OK) return rc;
-    // two classical Gram-Schmidt passes against the whole basis; alpha from the first
-    for (int pass = 0; pass < 2; ++pass) {
-        if ((e = ldots(l, l->Q, m, l->w, l->coef, s)) != hipSuccess) return hip_fail(e, "lanczos: projection");
-        if (pass == 0 && (e = hipMemcpyAsync(l->host, l->coef, sizeof(double) * m, hipMemcpyDeviceToHost, s)) != hipSuccess)
-            return hip_fail(e, "lanczos: coefficients");
-        hipLaunchKernelGGL(k_project, dim3(grid_n(n)), dim3(256), 0, s, l->Q, n, m, nullptr, l->coef, l->w, nullptr);
-    }
-    if ((e = ldots(l, l->w, 1, l->w, l->scal, s)) != hipSuccess) return hip_fail(e, "lanczos: norm");
-    if ((e = hipMemcpyAsync(l->host + 64, l->scal, sizeof(double), hipMemcpyDeviceToHost, s)) != hipSuccess ||
-        (e = hipStreamSynchronize(s)) != hipSuccess)
+    // two classical Gram-Schmidt passes against the whole basis; alpha (the
+    // first pass's coefficient of q_{m-1}) and |w|^2 go straight to the host's
+    // buffer, and q_m = w / |w| is written before the decision (unused when
+    // the step ends the iteration; a full basis restarts instead)
+    const BasisSize size{m, nullptr, 0};
+    if ((e = gram_schmidt(l->Q, n, m, size, l->w, l->partial, l->norm, nullptr, l->host, s)) != hipSuccess)
+        return hip_fail(e, "lanczos: projection");
+    hipLaunchKernelGGL(k_normalise, dim3(grid_norm(n)), dim3(256), 0, s, l->w, l->norm, dot_blocks(n),
+                       m < l->m_max ? l->Q : nullptr, n, size, nullptr, l->host + 1);
+    if ((e = hipGetLastError()) != hipSuccess || (e = hipStreamSynchronize(s)) != hipSuccess)
         return hip_fail(e, "lanczos: step");
     l->iter += 1;
-    const double a = l->host[m - 1];
-    const double b = std::sqrt(l->host[64] > 0 ? l->host[64] : 0.0);
+    const double a = l->host[0];
+    const double b = std::sqrt(l->host[1] > 0 ? l->host[1] : 0.0);
     l->alpha.push_back(a);
     // Ritz pair of T_m
     std::vector<double> T(static_cast<size_t>(m) * m, 0.0);
@@ -872,9 +973,6 @@ int lanczos_step(lanczos l, davidson_info *info, void *stream) {
             if ((rc = lanczos_reset(l, l->w, s)) != OZ_OK) return rc;
         } else {
             l->beta.push_back(b);
-            hipLaunchKernelGGL(k_scale_into, dim3(grid_n(n)), dim3(256), 0, s, l->w, l->scal,
-                               l->Q + static_cast<int64_t>(m) * n, n);
-            if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "lanczos: expand");
             l->m = m + 1;
         }
     } else {

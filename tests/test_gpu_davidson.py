@@ -169,6 +169,34 @@ def test_binding_checks_vector_sizes(oz):
 
 
 
+@pytest.mark.parametrize("D,m_max,steps", [(3, 64, 8), (8, 64, 63), (23, 5, 17), (46, 40, 45), (370, 24, 26), (740, 9, 14)])
+def test_rayleigh_ritz_and_projection_sizes(oz, D, m_max, steps):
+    """FP64 steps over vectors of one block up to several elements per thread
+    and bases on each side of 16 and 32, with and without a collapse: the Ritz
+    value never rises, the vector is a unit vector and the reported residual is
+    |H x - theta x| of the same vector, each within the rounding of the sums
+    that form it (u = 2^-53)."""
+    ozaki, ctx, torch = oz
+    kop = 2
+    prob = wl.davidson_problem(D=D, kop=kop, well=0.0, seed=900 + D)
+    norm = sum(np.linalg.norm(prob.L[k]) * np.linalg.norm(prob.R[k]) for k in range(kop)) + np.abs(prob.delta).max()
+    u = 2.0 ** -53
+    chain = D * D / (512 * 256) + 16 + m_max  # additions behind one inner product and one projection
+    dav, keep = solver(ozaki, ctx, torch, prob, 0, m_max=m_max, tol=0.0, max_iter=10 * steps)
+    last = np.inf
+    for _ in range(steps):
+        info = dav.step()
+        slack = 8 * m_max * (chain + 2 * D + kop) * u * norm
+        assert info.theta <= last + slack
+        last = info.theta
+        X = dav.vector().cpu().numpy().reshape(prob.x0.shape)
+        assert abs(np.sum(X * X) - 1) <= 8 * m_max * chain * u
+        HX = sum(prob.L[k] @ X @ prob.R[k].T for k in range(kop)) + prob.delta * X
+        assert abs(info.resnorm - np.linalg.norm(HX - info.theta * X)) <= slack
+        if info.status != 0 or info.resnorm < 1e-9 * norm:
+            break
+
+
 @pytest.mark.parametrize("seed", range(8))
 def test_random_problems_against_brute_force(oz, seed):
     """Seeded random small problems (D = 4..20, 1 to 8 operator pairs, with
