@@ -808,10 +808,20 @@ int heff_plan_create(ozaki_ctx ctx, heff_plan *out, const heff_layout *L, const 
     constexpr double kStreamMaxMeanBlocks = 16.0;
     const int forced = ctx->heff_launch;  // -1 timed, 0 per tile, k > 0 streamed, resident or paired terms
     const int stream_cus_of = forced > 0 ? std::min(forced, ctx->num_cu) : ctx->num_cu;
+    // chunks whose second phase takes the split kernel for few tiles: a rule
+    // on the outputs alone, unless the context names a launch
+    std::vector<char> split(hc.size(), 0);
+    for (size_t c = 0; c < hc.size() && (fixed_phases || forced == -1); ++c) {
+        int64_t blocks = 0;
+        for (const OutDesc &o : hl[c].outsR) blocks += ceil_div(o.M, 32) * ceil_div(o.N, 32);
+        split[c] = pair_accum_split_pays(blocks, ctx->num_cu);
+    }
     // the launches a phase may use for variant v
     auto kinds_for = [&](int ph, int v) {
         std::vector<int> k;
-        if (forced == kHeffLaunchResident) {
+        if (ph == 1 && split[0]) {
+            k.push_back(0);
+        } else if (forced == kHeffLaunchResident) {
             k.push_back(ph == 0 && pair_resident_per_cu(S, G, v) > 0 ? 2 : 0);
         } else if (forced == kHeffLaunchPairedTerms) {
             k.push_back(ph == 1 && pair_terms2_ok(S, G, v) ? 3 : 0);
@@ -936,6 +946,7 @@ int heff_plan_create(ozaki_ctx ctx, heff_plan *out, const heff_layout *L, const 
                         a.nwg = 0;
                         a.wg_off = nullptr;
                         a.terms2 = kind == 3 ? 1 : 0;
+                        a.split = ph == 1 && kind == 0 && split[0];
                         const std::vector<TileDesc> *up = &sample;
                         if (kind == 2) {
                             const int nwg = std::min(pair_resident_per_cu(S, G, v), kMaxResidentPerCu) * ctx->num_cu;
@@ -1004,6 +1015,7 @@ int heff_plan_create(ozaki_ctx ctx, heff_plan *out, const heff_layout *L, const 
             a.nwg = 0;
             a.wg_off = nullptr;
             a.terms2 = run.kind == 3 ? 1 : 0;
+            a.split = ph == 1 && run.kind == 0 && split[c];
             TileDesc *d = nullptr;
             if (run.kind == 2) {
                 const int nwg = std::min(pair_resident_per_cu(S, G, run.v), kMaxResidentPerCu) * ctx->num_cu;

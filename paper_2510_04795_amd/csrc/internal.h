@@ -135,6 +135,9 @@ struct PairArgs {
     // grouped, accumulating mode on the 64 x 64 tiles of variant 0: 1 = the
     // paired-term kernel (eight waves per tile, two terms at a time)
     int32_t terms2;
+    // grouped, accumulating mode, any tile: 1 = a workgroup per 32 x 32 block
+    // of a tile, its waves on different terms (before terms2)
+    int32_t split;
     // single launch in kModeGemm: nbatch > 1 products of one shape in one
     // launch, product k from the term's pointers moved by k strides into
     // batch_C[k]
@@ -266,6 +269,9 @@ hipError_t launch_unpack(int S, const int8_t *packed, int64_t Rp, int64_t R, int
 // takes it when no variant is set.
 constexpr int kSplitVariant = 100;
 bool pair_split_pays(int64_t M, int64_t N, int64_t K, int nbatch, int num_cu);
+// Accumulating grouped launches: whether PairArgs::split is the faster kernel
+// for outputs of this many 32 x 32 blocks altogether.
+bool pair_accum_split_pays(int64_t blocks, int num_cu);
 struct PairShape { int bm, bn; };
 bool pair_supported(int S, int G);
 int pair_num_variants();

@@ -24,6 +24,15 @@ bool pair_split_pays(int64_t M, int64_t N, int64_t K, int nbatch, int num_cu) {
     return ceil_div(M, 64) * ceil_div(N, 64) * nbatch * 4 <= num_cu && K > 64;
 }
 
+// Up to two blocks per compute unit.  Whole H_eff matvecs measured (us, split
+// against the better of one workgroup per 64 x 64 tile and paired terms, both
+// S = 6): D = 96, 8 terms (9 blocks) 40 against 61; D = 256, 24 terms (64) 103
+// against 194; D = 512, 24 terms (256) 194 against 322, 2 terms 77 against 80;
+// D = 640, 24 terms (400) 384 against 437; but D = 736, 24 terms (529) 613
+// against 564, where the third block of a compute unit and the 64 x 64 tiles'
+// reuse of their operands count for more.
+bool pair_accum_split_pays(int64_t blocks, int num_cu) { return blocks <= 2 * num_cu; }
+
 PairShape pair_shape(int S, int G, int v) {
     (void)S;
     if (v == kSplitVariant) return PairShape{32, 32};

@@ -1732,6 +1732,97 @@ __global__ __launch_bounds__(256) void k_pair_split(PairArgs a, int tiles_m) {
     }
 }
 
+// ---- split kernel for accumulating launches over few tiles ------------------
+// One workgroup per 32 x 32 block of a listed BM x BN tile, its waves on
+// different terms: wave w computes terms w, w + W, ... of the tile's list from
+// the packed planes straight into registers (as k_pair_split), the FP64 values
+// of up to W terms meet in LDS, and every element adds them in list order, so
+// the sums are those of the kernels that take the terms one by one.  W = 8
+// waves where two fit a SIMD's registers, 4 otherwise.  Bound: latency (a
+// term's K blocks, its recombination), times the terms per wave; the other
+// kernels put a tile's whole term list behind one another on a quarter of the
+// compute units.  At D = 96 with 8 terms of 3 K blocks (S = 6) 29.8 -> 8.7 us.
+// Where it pays: pair_accum_split_pays.
+template <int S, int G>
+__host__ __device__ constexpr int accum_split_waves() {
+    return 16 * G + 2 * 8 * (S < G ? S : G) + 30 <= 256 ? 8 : 4;
+}
+
+template <int S, int G>
+__global__ __launch_bounds__((64 * accum_split_waves<S, G>())) void k_pair_accum_split(PairArgs a, int subs_n) {
+    constexpr int W = accum_split_waves<S, G>();
+    constexpr int NE = 16 / W;  // elements of the block per thread
+    __shared__ double val[W][16][64];
+    const int tile = blockIdx.x % a.ntiles, sub = blockIdx.x / a.ntiles;
+    const TileDesc td = a.tiles[tile];
+    if (td.out < 0) return;  // padding of the XCD order
+    OutDesc od = a.outs[td.out];
+    if (a.out_base) od.C = a.out_base + reinterpret_cast<intptr_t>(od.C);
+    const int m0 = td.m0 + 32 * (sub / subs_n), n0 = td.n0 + 32 * (sub % subs_n);
+    if (m0 >= od.M || n0 >= od.N) return;
+    const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int j = n0 + l32;
+    const bool jok = j < od.N;
+    // this thread's elements: values wave + W q of its lane
+    auto row_of = [&](int r) { return m0 + 8 * (r >> 2) + 4 * half + (r & 3); };
+    double sig[NE];
+#pragma unroll
+    for (int q = 0; q < NE; ++q) {
+        const int i = row_of(wave + W * q);
+        sig[q] = od.cont && jok && i < od.M ? od.C[static_cast<int64_t>(i) * od.ldc + j] : 0.0;
+    }
+    const TermDesc *terms = a.terms;
+    for (int t0 = td.term_begin; t0 < td.term_end; t0 += W) {
+        const int nt = td.term_end - t0 < W ? td.term_end - t0 : W;
+        if (wave < nt) {
+            const TermDesc T = const_term(terms, t0 + wave);
+            const int64_t a_run = T.a_rows_p * 16, b_run = T.b_rows_p * 16;
+            const int8_t *A = T.A + half * a_run + static_cast<int64_t>(m0 + l32) * 16;
+            const int8_t *B = T.B + half * b_run + static_cast<int64_t>(n0 + l32) * 16;
+            v16i acc[G][1][1];
+#pragma unroll
+            for (int g = 0; g < G; ++g) acc[g][0][0] = v16i{};
+            Frags<S, G, 1, 1> cur, nxt;
+            if (0 < T.kblocks) split_load<S, G>(cur, A, B, a_run, b_run);
+            const int32_t fj = jok ? T.f[j] : 0;
+            int32_t ei[16];
+            row_exponents(ei, T.e, od.M, m0 + 4 * half, jok);
+            for (int kb = 0; kb < T.kblocks; ++kb) {
+                if (kb + 1 < T.kblocks)
+                    split_load<S, G>(nxt, A + (kb + 1) * 2 * S * a_run, B + (kb + 1) * 2 * S * b_run, a_run, b_run);
+                mfma_pairs<true, S, G, 1, 1>(acc, cur);
+                mfma_pairs<false, S, G, 1, 1>(acc, cur);
+                cur = nxt;
+            }
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                if (r % kEpilogueGroup == 0) __builtin_amdgcn_sched_barrier(0);
+                double c = 0.0;
+                if (jok && row_of(r) < od.M) {
+                    int q[G];
+#pragma unroll
+                    for (int g = 0; g < G; ++g) q[g] = acc[g][0][0][r];
+                    c = horner<G>(q, ei[r], fj);
+                }
+                val[wave][r][lane] = c;
+            }
+        }
+        __syncthreads();
+        for (int k = 0; k < nt; ++k) {
+            const double alpha = const_term(terms, t0 + k).alpha;
+#pragma unroll
+            for (int q = 0; q < NE; ++q) sig[q] = fma(alpha, val[k][wave + W * q][lane], sig[q]);
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int q = 0; q < NE; ++q) {
+        const int i = row_of(wave + W * q);
+        if (jok && i < od.M) od.C[static_cast<int64_t>(i) * od.ldc + j] = sig[q];
+    }
+}
+
 // One block per listed tile (the list is in the XCD order the plan builds).
 template <int S, int G, int WM, int WN, int MB, int NB, int MODE>
 __global__ __launch_bounds__(64 * WM * WN) void k_pair_grouped(PairArgs a) {
@@ -1837,6 +1928,12 @@ hipError_t run_grouped_v(const PairArgs &a, hipStream_t s) {
         return hipErrorInvalidValue;
     } else {
         if (a.ntiles == 0) return hipSuccess;
+        if (a.split) {
+            if (a.mode != kModeAccum) return hipErrorInvalidValue;
+            constexpr int threads = 64 * accum_split_waves<S, G>();
+            hipLaunchKernelGGL((k_pair_accum_split<S, G>), dim3(a.ntiles * WM * MB * WN * NB), dim3(threads), 0, s, a, WN * NB);
+            return hipGetLastError();
+        }
         if (a.terms2) {
             if constexpr (V == 0 && terms2_fits<S, G>()) {
                 if (a.mode != kModeAccum) return hipErrorInvalidValue;

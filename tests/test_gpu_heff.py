@@ -616,6 +616,37 @@ def test_paired_terms_bitexact(oz, S, G):
         ctx.set_variant(S, G, -1)
 
 
+@pytest.mark.parametrize("S,G", [(2, 2), (5, 5), (6, 6), (7, 8), (8, 15)])
+def test_few_tiles_split_bitexact(oz, S, G):
+    """Second phases of few output blocks (a workgroup per 32 x 32 block, its
+    waves on different terms): the oracle's bits and those of the per-tile
+    launch, with fewer terms than waves, one more than two rounds of them, odd
+    edges, empty sigma blocks and sums continued over chunks."""
+    ozaki, ctx, torch = oz
+    try:
+        for D, kop, phys, budget in ((33, 1, 1, 0), (70, 17, 1, 0), (45, 9, 3, 1)):
+            L, R, psi = wl.heff_dense(D=D, kop=kop, phys=phys, seed=190 + D)
+            ctx.set_heff_budget(budget)
+            plan, dpsi, keep = dense_plan(ozaki, ctx, torch, L, R, psi, S, G)
+            out = plan.apply(dpsi)
+            assert plan.phase(1)[2] == 0 and (plan.chunks > 1) == (budget == 1)
+            assert_bitexact(out.cpu().numpy().reshape(psi.shape), oracle.heff_dense(L, R, psi, S=S, G=G), "dense %d" % D)
+            ctx.set_heff_launch(0)
+            plan0, _, keep0 = dense_plan(ozaki, ctx, torch, L, R, psi, S, G)
+            ctx.set_heff_launch(-1)
+            assert torch.equal(out, plan0.apply(dpsi))
+            prob = wl.heff_sparse(n_sectors=6, n_triples=60, kop=3, median=20, sigma_log=1.2, lo_hi=(1, 90), density=0.5,
+                                  reach=2, U=8, seed=D)
+            plan, dpsi, keep = sparse_plan(ozaki, ctx, torch, prob, S, G)
+            sig = wl.unflatten_sparse(prob, plan.apply(dpsi).cpu().numpy())
+            ref = oracle.heff_sparse(prob, S=S, G=G)
+            for b in prob.psi_blocks:
+                assert_bitexact(sig[b], ref[b], "sparse %d block %s" % (D, b))
+    finally:
+        ctx.set_heff_budget(0)
+        ctx.set_heff_launch(-1)
+
+
 @pytest.mark.parametrize("seed", range(6))
 def test_random_sparse_every_launch(oz, seed):
     """Seeded random block-sparse problems (5 to 9 sectors of 1 to 200
