@@ -40,6 +40,7 @@ struct HeffChunk {
     SliceTask *T_etasks = nullptr, *T_stasks = nullptr;
     int n_T_etasks = 0, n_T_stasks = 0;
     bool fuse_T = false;      // T's exponents from the first phase's maxima
+    SliceCodes T_codes{};     // how T's slice pass gets them
     int64_t T_e_total = 0;
     PairArgs argsL{}, argsR{};
     // FP64 path
@@ -65,6 +66,7 @@ struct heff_plan_s {
     int32_t *T_emax = nullptr;   // exponent-code maxima left by the first phase
     int32_t *psi_emax = nullptr;  // exponent-code maxima of psi's split column pass
     int64_t psi_e_total = 0;
+    SliceCodes psi_codes{};      // how psi's slice pass gets its exponents
     int varL = -1, varR = -1;   // tile variants of the two grouped phases
     int choice[2][3] = {{-1, -1, -1}, {-1, -1, -1}};  // per phase: variant, order, launch
     std::vector<HeffChunk> chunks;
@@ -592,7 +594,13 @@ int heff_plan_create(ozaki_ctx ctx, heff_plan *out, const heff_layout *L, const 
 
     // psi blocks sliced by columns of the left x (phys * right) view, on every apply
     SliceSet Ps;
-    Ps.split_cols = true;  // row chunks of long columns in parallel, combined through codes
+    // row chunks of long columns in parallel, combined through codes: 32 rows
+    // (one load per row and wave) while 128 would leave fewer than two tasks
+    // per compute unit (D = 1024, one block: 14.2 -> 4.6 us)
+    int64_t chunk_tasks = 0;
+    for (int b = 0; b < L->n_psi_blocks; ++b)
+        chunk_tasks += ceil_div(p * rd[L->psi_lr[2 * b + 1]], kExpTaskCols) * ceil_div(ld[L->psi_lr[2 * b]], 128);
+    Ps.split_rows = chunk_tasks < 2 * ctx->num_cu ? 32 : 128;
     std::vector<int64_t> P_eoff(L->n_psi_blocks), P_poff(L->n_psi_blocks);
     for (int b = 0; b < L->n_psi_blocks; ++b) {
         const int l = L->psi_lr[2 * b], r = L->psi_lr[2 * b + 1];
@@ -656,6 +664,14 @@ int heff_plan_create(ozaki_ctx ctx, heff_plan *out, const heff_layout *L, const 
     }
     const std::vector<int32_t> emax_init(static_cast<size_t>(Te_max), kEmaxZero);
     if (any_fuse && (rc = upload(P, emax_init, &P->T_emax))) { free_plan(P); return rc; }
+    // A plan of one chunk needs no pass over the codes: each slice pass reads
+    // its own and clears the other's, which nothing uses then (T's between
+    // psi's slices and the first product, psi's from there to the next apply).
+    // Saves two of seven launches (4 to 5 us each) per apply.
+    if (hc.size() == 1 && P->chunks[0].fuse_T && Ps.e_total > 0) {
+        P->psi_codes = SliceCodes{P->psi_emax, ctx->d_flags, P->T_emax, Te_max};
+        P->chunks[0].T_codes = SliceCodes{P->T_emax, ctx->d_flags, P->psi_emax, P->psi_e_total};
+    }
 
     for (size_t c = 0; c < hc.size(); ++c) {
         const HostChunk &h = hc[c];
@@ -1074,8 +1090,10 @@ int enqueue_apply(heff_plan P, const double *psi, double *sigma, hipStream_t s) 
     } else {
         hipEvent_t t0 = mark(ctx, s);
         if ((e = launch_exponents_grouped(P->psi_blocks, P->psi_etasks, P->n_psi_etasks, psi, P->psi_e, ctx->d_flags, s, P->psi_emax)) != hipSuccess ||
-            (e = launch_emax_finish(P->psi_emax, P->psi_e, P->psi_e_total, ctx->d_flags, s)) != hipSuccess ||
-            (e = launch_slice_grouped(P->S, P->psi_blocks, P->psi_stasks, P->n_psi_stasks, psi, P->psi_e, P->psi_p, s)) != hipSuccess)
+            (!P->psi_codes.emax &&
+             (e = launch_emax_finish(P->psi_emax, P->psi_e, P->psi_e_total, ctx->d_flags, s)) != hipSuccess) ||
+            (e = launch_slice_grouped(P->S, P->psi_blocks, P->psi_stasks, P->n_psi_stasks, psi, P->psi_e, P->psi_p, s,
+                                      P->psi_codes)) != hipSuccess)
             return hip_fail(e, "heff_apply: slicing psi");
         hipEvent_t t1 = mark(ctx, s);
         phase(ctx, OZ_PHASE_HEFF_AUX, t0, t1);
@@ -1084,9 +1102,13 @@ int enqueue_apply(heff_plan P, const double *psi, double *sigma, hipStream_t s) 
             if ((e = launch_pair_grouped(P->S, P->G, P->varL, ch.argsL, s)) != hipSuccess) return hip_fail(e, "heff_apply: first product");
             hipEvent_t c1 = mark(ctx, s);
             phase(ctx, OZ_PHASE_HEFF_L, c0, c1);
-            if ((e = ch.fuse_T ? launch_emax_finish(P->T_emax, P->T_e, ch.T_e_total, ctx->d_flags, s)
-                               : launch_exponents_grouped(ch.T_blocks, ch.T_etasks, ch.n_T_etasks, P->T, P->T_e, ctx->d_flags, s)) != hipSuccess ||
-                (e = launch_slice_grouped(P->S, ch.T_blocks, ch.T_stasks, ch.n_T_stasks, P->T, P->T_e, P->T_p, s)) != hipSuccess)
+            e = hipSuccess;
+            if (!ch.fuse_T)
+                e = launch_exponents_grouped(ch.T_blocks, ch.T_etasks, ch.n_T_etasks, P->T, P->T_e, ctx->d_flags, s);
+            else if (!ch.T_codes.emax)
+                e = launch_emax_finish(P->T_emax, P->T_e, ch.T_e_total, ctx->d_flags, s);
+            if (e != hipSuccess || (e = launch_slice_grouped(P->S, ch.T_blocks, ch.T_stasks, ch.n_T_stasks, P->T, P->T_e,
+                                                             P->T_p, s, ch.T_codes)) != hipSuccess)
                 return hip_fail(e, "heff_apply: slicing T");
             hipEvent_t c2 = mark(ctx, s);
             phase(ctx, OZ_PHASE_HEFF_AUX, c1, c2);

@@ -193,15 +193,11 @@ struct SliceBlock {
 constexpr int kExpTaskRows = 16;
 constexpr int kExpTaskCols = 64;
 constexpr int kSliceTaskKB = 8;
-// Column exponent tasks of sets built with split columns cover this many
-// rows each and combine their maxima through exponent codes (atomic max).
-constexpr int kExpColChunk = 128;
-
 struct SliceTask {
     int32_t block;
     int32_t a;       // exponent task: first group; slice task: first group (32-aligned)
-    int32_t b;       // slice task: 32-wide K block index; split column task: row chunk
-    int32_t pad_;
+    int32_t b;       // slice task: 32-wide K block index; column exponent task: first row
+    int32_t rows;    // column exponent task: rows (0: all; else combined through codes)
 };
 
 // One operand of a product for launch_slice_operands.  The caller fills X, ld,
@@ -244,18 +240,28 @@ hipError_t launch_slice_operands(int S, OperandTask a, OperandTask b, int32_t *c
                                  hipStream_t s);
 // Grouped exponent pass (tasks of kExpTaskRows rows or kExpTaskCols columns)
 // and slice pass (tasks of 32 groups x kSliceTaskKB 32-wide K blocks).
-// With emax_base (column tasks split into row chunks of kExpColChunk), the
-// column tasks combine exponent codes into emax_base[e_off + group] with
-// atomic max instead of writing exponents; launch_emax_finish completes them.
+// With emax_base (column tasks split into row chunks), the column tasks
+// combine exponent codes into emax_base[e_off + group] with atomic max instead
+// of writing exponents; launch_emax_finish or the slice pass completes them.
 hipError_t launch_exponents_grouped(const SliceBlock *blocks, const SliceTask *tasks, int ntasks,
                                     const double *x_base, int32_t *e_base, uint32_t *flag,
                                     hipStream_t s, int32_t *emax_base = nullptr);
 // Exponents from code maxima left in emax by a GEMM-mode pair launch
 // (OutDesc::emax) or a split column exponent pass; emax is left at kEmaxZero.
 hipError_t launch_emax_finish(int32_t *emax, int32_t *e, int64_t n, uint32_t *flag, hipStream_t s);
+// The slice pass's exponents from codes: with emax set (code maxima as above,
+// at the blocks' e_off) the pass turns them into exponents itself, stores
+// these and raises the flag.  `reset`, another array of codes that nothing
+// uses at that time, is set to kEmaxZero.
+struct SliceCodes {
+    const int32_t *emax = nullptr;  // nullptr: exponents are in place
+    uint32_t *flag = nullptr;
+    int32_t *reset = nullptr;
+    int64_t n_reset = 0;
+};
 hipError_t launch_slice_grouped(int S, const SliceBlock *blocks, const SliceTask *tasks, int ntasks,
-                                const double *x_base, const int32_t *e_base, int8_t *p_base,
-                                hipStream_t s);
+                                const double *x_base, int32_t *e_base, int8_t *p_base,
+                                hipStream_t s, const SliceCodes &codes = {});
 // Debug conversions between [S][R][K] digits and the packed layout.
 hipError_t launch_pack(int S, const int8_t *canon, int64_t R, int64_t K, int8_t *packed,
                        int64_t Rp, hipStream_t s);

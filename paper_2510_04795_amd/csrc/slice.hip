@@ -381,6 +381,8 @@ __global__ __launch_bounds__(256) void k_exponents2(OperandTask a, OperandTask b
 // reduction costs more than this launch.
 constexpr int kMaxCodeChunks = 16;
 
+// The exponent of a group's code: the code itself, 0 for an all-zero group,
+// kExpBad for a non-finite one.
 __device__ inline int32_t code_exponent(int32_t code) {
     return code == kEmaxNaN ? kExpBad : code == kEmaxZero ? 0 : code;
 }
@@ -596,20 +598,21 @@ __global__ __launch_bounds__(256) void k_exponents_grouped(const SliceBlock *__r
     } else {
         const int c = tk.a + lane;
         const bool cok = c < bl.R;
-        const double *col = X + (cok ? c : 0);
+        const double *col = X + (cok ? c : 0);  // lanes past the edge load column 0 and drop it
         // rows [k0, k1): all of them, or one chunk of a split column task
-        const int k0 = emax_base ? tk.b * kExpColChunk : 0;
-        const int k1 = emax_base ? min(bl.K, k0 + kExpColChunk) : bl.K;
+        const int k0 = tk.b;
+        const int k1 = tk.rows ? min(bl.K, k0 + tk.rows) : bl.K;
         double m8[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) m8[u] = 0.0;
-        int k = k0 + wave;
-        for (; k + 28 < k1; k += 32) {
+        // eight loads in flight; past the chunk its last row again
+        for (int k = k0 + wave; k < k1; k += 32) {
+            double v[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u)
-                m8[u] = combine_max(m8[u], cok ? abs_or_nan(col[static_cast<int64_t>(k + 4 * u) * bl.ld]) : 0.0);
+            for (int u = 0; u < 8; ++u) v[u] = col[static_cast<int64_t>(min(k + 4 * u, k1 - 1)) * bl.ld];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) m8[u] = combine_max(m8[u], abs_or_nan(v[u]));
         }
-        for (; k < k1; k += 4) m8[0] = combine_max(m8[0], cok ? abs_or_nan(col[static_cast<int64_t>(k) * bl.ld]) : 0.0);
         double mu = m8[0];
 #pragma unroll
         for (int u = 1; u < 8; ++u) mu = combine_max(mu, m8[u]);
@@ -630,21 +633,15 @@ __global__ __launch_bounds__(256) void k_exponents_grouped(const SliceBlock *__r
 }
 
 // Exponents from the maxima a producing GEMM left in emax (one code per
-// group, combined with atomic max): the code itself, 0 for an all-zero
-// group, kExpBad and the flag for a non-finite one.  emax is reset to
-// kEmaxZero for the next product.
+// group, combined with atomic max), the flag for a non-finite group.  emax is
+// reset to kEmaxZero for the next product.  Only the plans of several chunks
+// need it: elsewhere the slice pass reads the codes itself (SliceCodes).
 __global__ __launch_bounds__(256) void k_emax_finish(int32_t *__restrict__ emax, int32_t *__restrict__ e,
                                                       int64_t n, uint32_t *flag) {
     for (int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; i < n;
          i += static_cast<int64_t>(gridDim.x) * 256) {
-        const int32_t v = emax[i];
-        int32_t x = v;
-        if (v == kEmaxNaN) {
-            atomicOr(flag, 1u);
-            x = kExpBad;
-        } else if (v == kEmaxZero) {
-            x = 0;
-        }
+        const int32_t x = code_exponent(emax[i]);
+        if (x == kExpBad) atomicOr(flag, 1u);
         e[i] = x;
         emax[i] = kEmaxZero;
     }
@@ -657,14 +654,27 @@ template <int S>
 __global__ __launch_bounds__(256) void k_slice_grouped(const SliceBlock *__restrict__ blocks,
                                                         const SliceTask *__restrict__ tasks,
                                                         const double *__restrict__ x_base,
-                                                        const int32_t *__restrict__ e_base,
-                                                        int8_t *__restrict__ p_base) {
+                                                        int32_t *__restrict__ e_base,
+                                                        int8_t *__restrict__ p_base, SliceCodes codes) {
     __shared__ uint4 tile[S * 2][32];
     const SliceTask tk = tasks[blockIdx.x];
     const SliceBlock bl = blocks[tk.block];
     const double *X = x_base + bl.x_off;
-    const int32_t *e = e_base + bl.e_off;
+    int32_t *e = e_base + bl.e_off;
     const int t = threadIdx.x;
+    for (int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + t; i < codes.n_reset; i += static_cast<int64_t>(gridDim.x) * 256)
+        codes.reset[i] = kEmaxZero;
+    // exponent of group g of the task's 32, also past the block's last group;
+    // from a code it is stored by one lane (`owner`) of the first K blocks' task
+    auto exponent = [&](int64_t g, bool owner) -> int32_t {
+        if (!codes.emax) return g < bl.R ? e[g] : 0;
+        const int32_t x = code_exponent(codes.emax[bl.e_off + g]);
+        if (owner && tk.b == 0) {
+            e[g] = x;
+            if (x == kExpBad) atomicOr(codes.flag, 1u);
+        }
+        return x;
+    };
     const int64_t r0 = tk.a;
     const int nkb = (bl.K + kKB - 1) / kKB;
     const int kb_end = tk.b + kSliceTaskKB < nkb ? tk.b + kSliceTaskKB : nkb;
@@ -682,7 +692,7 @@ __global__ __launch_bounds__(256) void k_slice_grouped(const SliceBlock *__restr
         // lanes take consecutive groups (columns): every load is coalesced
         const int r = t & 31, kq = t >> 5;
         const int64_t gr = r0 + r;
-        const int32_t ee = gr < bl.R ? e[gr] : 0;
+        const int32_t ee = exponent(gr, kq == 0);
         auto load = [&](int kb, double (&x)[4]) {
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
@@ -713,7 +723,7 @@ __global__ __launch_bounds__(256) void k_slice_grouped(const SliceBlock *__restr
     const bool aligned = (bl.ld & 1) == 0 && (reinterpret_cast<uintptr_t>(X) & 15) == 0;
     int32_t ee[2];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) ee[h] = r0 + rA + 16 * h < bl.R ? e[r0 + rA + 16 * h] : 0;
+    for (int h = 0; h < 2; ++h) ee[h] = exponent(r0 + rA + 16 * h, kp == 0);
     auto load = [&](int kb, double (&x)[4]) {
         const int64_t k = static_cast<int64_t>(kb) * 32 + 2 * kp;
 #pragma unroll
@@ -916,13 +926,13 @@ hipError_t launch_emax_finish(int32_t *emax, int32_t *e, int64_t n, uint32_t *fl
 }
 
 hipError_t launch_slice_grouped(int S, const SliceBlock *blocks, const SliceTask *tasks, int ntasks,
-                                const double *x_base, const int32_t *e_base, int8_t *p_base,
-                                hipStream_t s) {
+                                const double *x_base, int32_t *e_base, int8_t *p_base,
+                                hipStream_t s, const SliceCodes &codes) {
     if (ntasks == 0) return hipSuccess;
 #define OZ_SG(S_)                                                                                \
     case S_:                                                                                     \
         hipLaunchKernelGGL(k_slice_grouped<S_>, dim3(ntasks), dim3(256), 0, s, blocks, tasks,    \
-                           x_base, e_base, p_base);                                             \
+                           x_base, e_base, p_base, codes);                                      \
         break;
     switch (S) {
         OZ_SG(2) OZ_SG(3) OZ_SG(4) OZ_SG(5) OZ_SG(6) OZ_SG(7) OZ_SG(8)

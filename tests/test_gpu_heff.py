@@ -616,6 +616,32 @@ def test_paired_terms_bitexact(oz, S, G):
         ctx.set_variant(S, G, -1)
 
 
+@pytest.mark.parametrize("D,phys,chunks", [(31, 1, 1), (300, 1, 1), (64, 4, 1), (300, 1, 2)])
+def test_exponent_codes_between_applies(oz, D, phys, chunks):
+    """Exponents that travel as code maxima (psi's and T's slice passes turn
+    them into exponents and clear each other's in a plan of one chunk; several
+    chunks take a pass of their own): tiny, non-finite, zero and ordinary
+    vectors one after another on one plan each give the oracle's bits and raise
+    the flag when they should, so nothing is left over from the apply before."""
+    ozaki, ctx, torch = oz
+    L, R, psi = wl.heff_dense(D=D, kop=2, phys=phys, seed=70 + D)
+    ctx.set_heff_budget(1 if chunks > 1 else 0)
+    try:
+        plan, dpsi, keep = dense_plan(ozaki, ctx, torch, L, R, psi, 6)
+    finally:
+        ctx.set_heff_budget(0)
+    assert plan.chunks == chunks
+    bad = psi.copy()
+    bad[D - 1, phys - 1, D - 2] = np.nan
+    bad[0, 0, 1] = -np.inf
+    ctx.flags()
+    for x in (psi, psi * 2.0 ** -200, bad, np.zeros_like(psi), psi * 2.0 ** 90, psi):
+        sig = plan.apply(dev(torch, x.ravel())).cpu().numpy().reshape(psi.shape)
+        with np.errstate(invalid="ignore"):
+            assert_bitexact(sig, oracle.heff_dense(L, R, x, S=6), "%d %d" % (D, phys))
+        assert (ctx.flags() & 1) == (0 if np.isfinite(x).all() else 1)
+
+
 @pytest.mark.parametrize("S,G", [(2, 2), (5, 5), (6, 6), (7, 8), (8, 15)])
 def test_few_tiles_split_bitexact(oz, S, G):
     """Second phases of few output blocks (a workgroup per 32 x 32 block, its
