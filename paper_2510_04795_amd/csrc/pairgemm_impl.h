@@ -287,11 +287,22 @@ __device__ __forceinline__ void prefetch_step(v16i (&acc)[G][MB][NB], F &cur, ui
     cur = nxt;
 }
 
+// The main loops run `pre` (loads into LDS that the epilogue reads) once no
+// wave reads LDS for an earlier term any more, ahead of the first block's
+// loads, so it arrives with that block; without blocks, on its own.
+template <typename Pre>
+__device__ __forceinline__ void pre_only(Pre pre) {
+    __syncthreads();
+    pre();
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+}
+
 // Exact diagonal sums of one tile for one term, with the fragments read at
 // the start of each block (stage_step).
-template <int S, int G, int WM, int WN, int MB, int NB>
+template <int S, int G, int WM, int WN, int MB, int NB, typename Pre>
 __device__ __forceinline__ void pair_mainloop_direct(v16i (&acc)[G][MB][NB], uint4 *lds0, uint4 *lds1,
-                                              const TermDesc &T, int m0, int n0) {
+                                              const TermDesc &T, int m0, int n0, Pre pre) {
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform per wave
@@ -307,13 +318,14 @@ __device__ __forceinline__ void pair_mainloop_direct(v16i (&acc)[G][MB][NB], uin
         for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) acc[g][mb][nb] = v16i{};
-    if (nkb == 0) return;
+    if (nkb == 0) return pre_only(pre);
 
     LoadPlan<S, G, WM, WN, MB, NB> lp;
     lp.init(T.A, T.B, T.a_rows_p, T.b_rows_p, m0, n0, wave, lane);
     // a previous term of this block (accumulating mode) may still read the stages
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
+    pre();
     lp.issue(lds0, 0);
     // no block before the first: its deferred pairs multiply zeros
     Frags<S, G, MB, NB> f;
@@ -338,9 +350,9 @@ __device__ __forceinline__ void pair_mainloop_direct(v16i (&acc)[G][MB][NB], uin
 
 // Exact diagonal sums of one tile for one term, with the fragments read one
 // block ahead (prefetch_step).
-template <int S, int G, int WM, int WN, int MB, int NB>
+template <int S, int G, int WM, int WN, int MB, int NB, typename Pre>
 __device__ __forceinline__ void pair_mainloop_prefetch(v16i (&acc)[G][MB][NB], uint4 *lds0, uint4 *lds1,
-                                              const TermDesc &T, int m0, int n0) {
+                                              const TermDesc &T, int m0, int n0, Pre pre) {
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform per wave
@@ -356,7 +368,7 @@ __device__ __forceinline__ void pair_mainloop_prefetch(v16i (&acc)[G][MB][NB], u
         for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) acc[g][mb][nb] = v16i{};
-    if (nkb == 0) return;
+    if (nkb == 0) return pre_only(pre);
 
     LoadPlan<S, G, WM, WN, MB, NB> lp;
     lp.init(T.A, T.B, T.a_rows_p, T.b_rows_p, m0, n0, wave, lane);
@@ -365,6 +377,7 @@ __device__ __forceinline__ void pair_mainloop_prefetch(v16i (&acc)[G][MB][NB], u
     __syncthreads();
     // blocks 0 and 1 load together (one latency); the first step then finds
     // block 1 complete
+    pre();
     lp.issue(lds0, 0);
     if (1 < nkb) lp.issue(lds1, 1);
     __builtin_amdgcn_s_waitcnt(0);
@@ -437,9 +450,9 @@ __device__ __forceinline__ void ring_step(v16i (&acc)[G][MB][NB], F &cur, uint4 
     AsmStep<S, G>::template run<RA::OA, RA::OB>(acc, cur, RA::a(rd, wm, half, l32), RA::b(rd, wn, half, l32));
 }
 
-template <int S, int G, int WM, int WN, int MB, int NB>
+template <int S, int G, int WM, int WN, int MB, int NB, typename Pre>
 __device__ __forceinline__ void pair_mainloop_ring(v16i (&acc)[G][MB][NB], uint4 *lds0, uint4 *lds1, uint4 *lds2,
-                                                   const TermDesc &T, int m0, int n0) {
+                                                   const TermDesc &T, int m0, int n0, Pre pre) {
     using C = Cfg<S, G, WM, WN, MB, NB>;
     using RA = RingAddr<S, G, WM, WN, MB, NB>;
     const int tid = threadIdx.x;
@@ -453,13 +466,14 @@ __device__ __forceinline__ void pair_mainloop_ring(v16i (&acc)[G][MB][NB], uint4
 
 #pragma unroll
     for (int g = 0; g < G; ++g) acc[g][0][0] = v16i{};
-    if (nkb == 0) return;
+    if (nkb == 0) return pre_only(pre);
 
     LoadPlan<S, G, WM, WN, MB, NB> lp;
     lp.init(T.A, T.B, T.a_rows_p, T.b_rows_p, m0, n0, wave, lane);
     // a previous term of this block (accumulating mode) may still read the stages
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
+    pre();
     lp.issue(lds0, 0);
     if (1 < nkb) lp.issue(lds1, 1);
     if (2 < nkb) lp.issue(lds2, 2);
@@ -506,9 +520,9 @@ __device__ __forceinline__ void ring_step2(v16i (&acc)[G][MB][NB], F &cur, uint4
 // tiles where a third stage would leave room for only one workgroup per
 // compute unit (S >= 7): the second resident workgroup covers the shorter
 // lead.
-template <int S, int G, int WM, int WN, int MB, int NB>
+template <int S, int G, int WM, int WN, int MB, int NB, typename Pre>
 __device__ __forceinline__ void pair_mainloop_ring2(v16i (&acc)[G][MB][NB], uint4 *lds0, uint4 *lds1,
-                                                    const TermDesc &T, int m0, int n0) {
+                                                    const TermDesc &T, int m0, int n0, Pre pre) {
     using C = Cfg<S, G, WM, WN, MB, NB>;
     using RA = RingAddr<S, G, WM, WN, MB, NB>;
     const int tid = threadIdx.x;
@@ -522,13 +536,14 @@ __device__ __forceinline__ void pair_mainloop_ring2(v16i (&acc)[G][MB][NB], uint
 
 #pragma unroll
     for (int g = 0; g < G; ++g) acc[g][0][0] = v16i{};
-    if (nkb == 0) return;
+    if (nkb == 0) return pre_only(pre);
 
     LoadPlan<S, G, WM, WN, MB, NB> lp;
     lp.init(T.A, T.B, T.a_rows_p, T.b_rows_p, m0, n0, wave, lane);
     // a previous term of this block (accumulating mode) may still read the stages
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
+    pre();
     lp.issue(lds0, 0);
     if (1 < nkb) lp.issue(lds1, 1);
     if (1 < nkb)
@@ -597,243 +612,373 @@ __host__ __device__ constexpr bool use_ring2() {
 }
 
 // Exact diagonal sums of one tile for one term, accumulated over all K blocks.
-template <int S, int G, int WM, int WN, int MB, int NB, int MODE>
+template <int S, int G, int WM, int WN, int MB, int NB, int MODE, typename Pre>
 __device__ __forceinline__ void pair_mainloop(v16i (&acc)[G][MB][NB], uint4 *lds0, uint4 *lds1, uint4 *lds2,
-                                              const TermDesc &T, int m0, int n0) {
+                                              const TermDesc &T, int m0, int n0, Pre pre) {
     if constexpr (use_ring<S, G, WM, WN, MB, NB, MODE>())
-        pair_mainloop_ring<S, G, WM, WN, MB, NB>(acc, lds0, lds1, lds2, T, m0, n0);
+        pair_mainloop_ring<S, G, WM, WN, MB, NB>(acc, lds0, lds1, lds2, T, m0, n0, pre);
     else if constexpr (use_ring2<S, G, WM, WN, MB, NB, MODE>())
-        pair_mainloop_ring2<S, G, WM, WN, MB, NB>(acc, lds0, lds1, T, m0, n0);
+        pair_mainloop_ring2<S, G, WM, WN, MB, NB>(acc, lds0, lds1, T, m0, n0, pre);
     else if constexpr (use_prefetch<S, G, WM, WN, MB, NB, MODE>())
-        pair_mainloop_prefetch<S, G, WM, WN, MB, NB>(acc, lds0, lds1, T, m0, n0);
+        pair_mainloop_prefetch<S, G, WM, WN, MB, NB>(acc, lds0, lds1, T, m0, n0, pre);
     else
-        pair_mainloop_direct<S, G, WM, WN, MB, NB>(acc, lds0, lds1, T, m0, n0);
+        pair_mainloop_direct<S, G, WM, WN, MB, NB>(acc, lds0, lds1, T, m0, n0, pre);
 }
 
-// Output elements whose recombinations the epilogue lets the scheduler
-// interleave (their dependent FP64 chains overlap); a schedule barrier
-// between groups keeps the registers of only one group live.
-constexpr int kEpilogueGroup = 4;
+// ---- recombination and stores of one 32 x 32 block --------------------------
+// A lane holds 16 values of a block, value r at row 8 (r / 4) + 4 (l / 32) + r
+// % 4 and column l % 32.  Bound: the wave's VALU instructions and their
+// latency, with nothing else to run on its SIMD but one other wave.  So the
+// block is one straight line: four values at a time with their dependent FP64
+// chains side by side, exponents loaded four rows at once, row addresses from
+// one lane pointer and a uniform stride, no branch per value; edges mask the
+// stores only, and non-finite groups are put right afterwards where a wave has
+// any.  Against a branch, a masked exponent load and a 64-bit address per
+// value, 56 -> 29 instructions a value with the row maxima.  The matvec of the
+// block-sparse batch of 40 sectors (8 K blocks a term) 2.06 -> 1.89 ms, of a
+// dense D = 1024 (32 K blocks) 20.2 -> 19.4 ms.
+struct BlockExp {
+    v4i e[4];   // exponents of the lane's rows
+    int32_t f;  // exponent of its column
+};
 
-// FP64 value of one output element from its diagonal sums: int32, or int64
-// with the carries of earlier K chunks.  The types stay apart at compile time
-// (kModeGemm64): a sum widened in case carries are added costs two
-// conversions, an ldexp and an addition instead of one conversion, four
-// times the FP64 instructions of the whole recombination.
-template <int G, typename Q>
-__device__ __forceinline__ double horner(const Q (&q)[G], int32_t ei, int32_t fj) {
-    if (ei == kExpBad || fj == kExpBad) return __longlong_as_double(0x7ff8000000000000ll);
-    double h = static_cast<double>(q[G - 1]);
+// The exponents of the block at (i0, j0) of an output of M x N (rows past M
+// are out of the buffer's range and read 0).
+__device__ __forceinline__ BlockExp block_exponents(const TermDesc &T, int M, int N, int i0, int j0, int half, int l32) {
+    const __amdgpu_buffer_rsrc_t rows =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t *>(T.e), 0, 4 * M, kBufferDword3);
+    BlockExp x;
 #pragma unroll
-    for (int g = G - 2; g >= 0; --g) h = fma(h, 0x1p-8, static_cast<double>(q[g]));
-    return ldexp(h, ei + fj - 14);
+    for (int k = 0; k < 4; ++k)
+        x.e[k] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rows, 4 * (i0 + 8 * k + 4 * half), 0, 0));
+    x.f = T.f[min(j0 + l32, N - 1)];
+    return x;
 }
 
-// Fused row maxima of a GEMM-mode output.  For one 32 x 32 block a lane
-// holds 16 stored values, value r of lane l at row 8 (r / 4) + 4 (l / 32) +
-// r % 4, column l % 32.  Their magnitudes, as bit patterns with the sign
-// cleared (integer order is magnitude order, NaN above Inf), are reduced
-// over the 32 columns by halving exchanges: each step keeps half of the rows
-// and takes the partner's other half.  The epilogue visits the values in
-// the order 0, 8, 1, 9, ... and makes the first exchange (partner l ^ 16)
-// as soon as values q and 8 + q exist, so only 8 partial maxima stay live.
-// First exchange of values q (lo) and 8 + q (hi): the partner's half.  Its
-// result is used one pair later, so the exchange latency is hidden behind
-// the next element's recombination.
-__device__ __forceinline__ void emax_issue(long long lo, long long hi, int l32, long long &keep, long long &got) {
-    const bool b4 = l32 & 16;
-    got = __shfl_xor(b4 ? lo : hi, 16);
-    keep = b4 ? hi : lo;
+// Whether any lane of the wave has a non-finite row or column (kExpBad is the
+// smallest int32).
+__device__ __forceinline__ bool any_bad(const BlockExp &x) {
+    int32_t m = x.f;
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) m = min(m, x.e[k][q]);
+    return __any(m == kExpBad);
 }
 
+// FP64 values 4 k .. 4 k + 3 of a lane from their diagonal sums sum(g, r):
+// int32, or int64 with the carries of earlier K chunks.  The types stay apart
+// at compile time (kModeGemm64): a sum widened in case carries are added costs
+// two conversions, an ldexp and an addition instead of one conversion.
+template <int G, typename Sum>
+__device__ __forceinline__ void recombine4(double (&c)[4], const BlockExp &x, bool bad, int k, Sum sum) {
+    const uint32_t f = static_cast<uint32_t>(x.f) - 14u;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) c[q] = static_cast<double>(sum(G - 1, 4 * k + q));
+#pragma unroll
+    for (int g = G - 2; g >= 0; --g)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) c[q] = fma(c[q], 0x1p-8, static_cast<double>(sum(g, 4 * k + q)));
+#pragma unroll
+    for (int q = 0; q < 4; ++q) c[q] = ldexp(c[q], static_cast<int>(static_cast<uint32_t>(x.e[k][q]) + f));
+    if (bad)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (x.e[k][q] == kExpBad || x.f == kExpBad) c[q] = __longlong_as_double(0x7ff8000000000000ll);
+}
+
+// Global memory through its own address space: through a generic pointer
+// (which may point into LDS) an access also counts as one of LDS, and the
+// compiler first waits for every load into LDS in flight.
 typedef __attribute__((address_space(1))) int32_t global_i32;
+typedef __attribute__((address_space(1))) double global_f64;
+__device__ __forceinline__ global_f64 *global_ptr(double *p) { return (global_f64 *)reinterpret_cast<uintptr_t>(p); }
 
-// Atomic max on global memory, through the global address space: through a
-// generic pointer (which may point into LDS) the compiler first waits for
-// every load into LDS in flight.
 __device__ __forceinline__ void global_atomic_max(int32_t *p, int32_t v) {
     __hip_atomic_fetch_max((global_i32 *)reinterpret_cast<uintptr_t>(p), v, __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// The remaining exchanges (partners l ^ 8, 4, 2, 1), then the even lanes
-// turn their row's maximum into an exponent code and combine it into emax
-// with one atomic max.  The columns j0 .. j0 + 31 map to one emax group.
-__device__ __forceinline__ void emax_block(const OutDesc &out, const long long (&w8)[8], int i0, int j0,
-                                           int half, int l32) {
-    const bool b4 = l32 & 16, b3 = l32 & 8, b2 = l32 & 4, b1 = l32 & 2;
-    long long w4[4], w2[2];
+// ---- fused row maxima of a GEMM-mode output ---------------------------------
+// A magnitude's key: its high word without the sign, and whether the low word
+// is zero.  The key is monotone in the magnitude (NaN above Inf) and decides a
+// normal number's exponent code exactly, whose thresholds have low words of
+// zero.
+__device__ __forceinline__ uint32_t magnitude_key(double v) {
+    const uint64_t b = static_cast<uint64_t>(__double_as_longlong(v));
+    return (static_cast<uint32_t>(b >> 32) << 1) + (static_cast<uint32_t>(b) != 0 ? 1u : 0u);
+}
+
+template <int CTRL>
+__device__ __forceinline__ uint32_t lane_of(uint32_t v) {
+    return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), CTRL, 0xf, 0xf, true));
+}
+
+// The largest magnitude of the lane's row pair-wise from the stored values:
+// for a row whose largest is subnormal, whose code depends on the low word.
+__device__ inline long long row_magnitude(const OutDesc &out, int i, int j0, int l32) {
+    long long m = 0;
+    if (i < out.M && j0 + l32 < out.N)
+        m = __double_as_longlong(global_ptr(out.C)[static_cast<int64_t>(i) * out.ldc + j0 + l32]) & 0x7fffffffffffffffll;
+    for (int o = 16; o >= 1; o >>= 1) {
+        const long long n = __shfl_xor(m, o);
+        m = n > m ? n : m;
+    }
+    return m;
+}
+
+// Row maxima of one block from its values' keys (0 outside the output) by
+// halving exchanges over the 32 columns: each step keeps half of the rows and
+// takes the partner's other half.  Then the even lanes turn their row's
+// maximum into an exponent code and combine it into emax with one atomic max.
+// The columns j0 .. j0 + 31 map to one emax group.
+__device__ __forceinline__ void emax_block(const OutDesc &out, const uint32_t (&key)[16], int i0, int j0, int half,
+                                           int l32) {
+    const bool b3 = l32 & 8, b2 = l32 & 4, b1 = l32 & 2;
+    uint32_t w8[8], w4[4], w2[2], w;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const long long t = __shfl_xor(b3 ? w8[q] : w8[4 + q], 8);
-        const long long k = b3 ? w8[4 + q] : w8[q];
-        w4[q] = k > t ? k : t;
+    for (int q = 0; q < 8; ++q) {
+        // lanes 16 apart: the lower 16 keep value q, the upper 8 + q
+        const auto x = __builtin_amdgcn_permlane16_swap(key[q], key[8 + q], false, false);
+        w8[q] = max(static_cast<uint32_t>(x[0]), static_cast<uint32_t>(x[1]));
     }
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        const long long t = __shfl_xor(b2 ? w4[q] : w4[2 + q], 4);
-        const long long k = b2 ? w4[2 + q] : w4[q];
-        w2[q] = k > t ? k : t;
-    }
-    long long w;
-    {
-        const long long t = __shfl_xor(b1 ? w2[0] : w2[1], 2);
-        const long long k = b1 ? w2[1] : w2[0];
-        w = k > t ? k : t;
-    }
-    {
-        const long long t = __shfl_xor(w, 1);
-        w = w > t ? w : t;
-    }
+    for (int q = 0; q < 4; ++q) w4[q] = max(b3 ? w8[4 + q] : w8[q], lane_of<0x128>(b3 ? w8[q] : w8[4 + q]));  // lane ^ 8
+#pragma unroll
+    for (int q = 0; q < 2; ++q) w2[q] = max(b2 ? w4[2 + q] : w4[q], lane_of<0x141>(b2 ? w4[q] : w4[2 + q]));  // lane ^ 7
+    w = max(b1 ? w2[1] : w2[0], lane_of<0x4e>(b1 ? w2[0] : w2[1]));  // lane ^ 2
+    w = max(w, lane_of<0xb1>(w));                                    // lane ^ 1
     // this lane's row: r = 8 b4 + 4 b3 + 2 b2 + b1
-    const int r = (b4 ? 8 : 0) + (b3 ? 4 : 0) + (b2 ? 2 : 0) + (b1 ? 1 : 0);
+    const int r = (l32 >> 1) & 15;
     const int i = i0 + 8 * (r >> 2) + 4 * half + (r & 3);
-    if (!(l32 & 1) && i < out.M && j0 < out.N && w != 0) {
-        const int32_t code = w >= 0x7ff0000000000000ll ? kEmaxNaN : shared_exponent(__longlong_as_double(w));
+    constexpr uint32_t kNormal = 1u << 21;  // key of the smallest normal number
+    int32_t code = w >= (0x7ffu << 21) ? kEmaxNaN
+                                       : static_cast<int32_t>(w >> 21) - 1022 + ((w & (kNormal - 1)) > (63u << 15) ? 1 : 0);
+    if (__any(w != 0 && w < kNormal)) {
+#pragma unroll 1
+        for (int q = 0; q < 16; ++q) {
+            const long long m = row_magnitude(out, i0 + 8 * (q >> 2) + 4 * half + (q & 3), j0, l32);
+            if (q == r && w < kNormal) code = shared_exponent(__longlong_as_double(m));
+        }
+    }
+    if (!(l32 & 1) && i < out.M && j0 < out.N && w != 0)
         global_atomic_max(out.emax + static_cast<int64_t>(i) * out.ep + j0 / out.en, code);
+}
+
+// GEMM mode: the block's values scaled, combined with C where beta is set and
+// stored; with EMAX (and out.emax) also its row maxima.
+template <int G, bool EMAX, typename Sum>
+__device__ __forceinline__ void store_block(const OutDesc &out, double alpha, double beta, const BlockExp &x, int i0,
+                                            int j0, int half, int l32, Sum sum) {
+    const int ib = i0 + 4 * half, j = j0 + l32;
+    const bool bad = any_bad(x);
+    global_f64 *p = global_ptr(out.C) + static_cast<int64_t>(ib) * out.ldc + j;
+    uint32_t key[16];
+    auto rows = [&](auto full) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            __builtin_amdgcn_sched_barrier(0);  // four values at a time in registers
+            double c[4];
+            recombine4<G>(c, x, bad, k, sum);
+            if (beta == 0.0) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) c[q] = alpha * c[q];
+            } else {
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    if (full || (j < out.N && ib + 8 * k + q < out.M))
+                        c[q] = fma(alpha, c[q], beta * p[(8 * k + q) * out.ldc]);
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const bool ok = full || (j < out.N && ib + 8 * k + q < out.M);
+                if (ok) p[(8 * k + q) * out.ldc] = c[q];
+                if (EMAX) key[4 * k + q] = ok ? magnitude_key(c[q]) : 0u;
+            }
+        }
+    };
+    if (i0 + 32 <= out.M && j0 + 32 <= out.N)
+        rows(std::true_type{});
+    else
+        rows(std::false_type{});
+    if (EMAX && out.emax) emax_block(out, key, i0, j0, half, l32);
+}
+
+// Accumulating mode: the running sums' start (an earlier launch's stored
+// values or +0), one term's values added, and the final store.
+__device__ __forceinline__ void load_sums(double (&sig)[16], const OutDesc &out, int i0, int j0, int half, int l32) {
+    const int ib = i0 + 4 * half, j = j0 + l32;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) sig[r] = 0.0;
+    if (!out.cont) return;
+    // straight-line loads (outside the output, of its first element; the value is then dropped)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int i = ib + 8 * (r >> 2) + (r & 3);
+        const bool ok = i < out.M && j < out.N;
+        const double v = global_ptr(out.C)[ok ? static_cast<int64_t>(i) * out.ldc + j : 0];
+        sig[r] = ok ? v : 0.0;
     }
 }
 
-// The row exponents of one 32 x 32 block's recombination (the lane's 16
-// values, rows i0 + 8 (r / 4) + r % 4), loaded together before it starts.
-// Inside the recombination every value is kept apart from the next (so
-// only one is live at a time), which would also wait for each of these
-// loads in turn.
-__device__ __forceinline__ void row_exponents(int32_t (&ei)[16], const int32_t *e, int M, int i0, bool jok) {
+template <int G, typename Sum>
+__device__ __forceinline__ void add_block(double (&sig)[16], double alpha, const BlockExp &x, Sum sum) {
+    const bool bad = any_bad(x);
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const int i = i0 + 8 * (r >> 2) + (r & 3);
-        ei[r] = (jok && i < M) ? e[i] : 0;
+    for (int k = 0; k < 4; ++k) {
+        __builtin_amdgcn_sched_barrier(0);
+        double c[4];
+        recombine4<G>(c, x, bad, k, sum);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) sig[4 * k + q] = fma(alpha, c[q], sig[4 * k + q]);
     }
 }
+
+__device__ __forceinline__ void store_sums(const double (&sig)[16], const OutDesc &out, int i0, int j0, int half,
+                                           int l32) {
+    const int ib = i0 + 4 * half, j = j0 + l32;
+    global_f64 *p = global_ptr(out.C) + static_cast<int64_t>(ib) * out.ldc + j;
+    const bool full = i0 + 32 <= out.M && j0 + 32 <= out.N;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int d = 8 * (r >> 2) + (r & 3);
+        if (full || (j < out.N && ib + d < out.M)) p[d * out.ldc] = sig[r];
+    }
+}
+
+// The exponents of one tile into LDS slot `ex` (BM row exponents, then BN
+// column exponents), so they arrive with the first K block instead of after
+// the last: one 64-entry load per wave for the first BM / 64 + BN / 64 waves;
+// entries past the output's edge are out of the buffer's range and left unused
+// by the epilogue.
+template <int BM, int BN>
+__device__ __forceinline__ void stage_exponents(int32_t *ex, const TermDesc &T, const OutDesc &od, int m0, int n0,
+                                                int wave, int lane) {
+    constexpr int NE = BM / 64, NF = BN / 64;
+    if (wave < NE + NF) {
+        const bool rows = wave < NE;
+        const int first = rows ? m0 + wave * 64 : n0 + (wave - NE) * 64;
+        const int valid = (rows ? od.M : od.N) - first;
+        const int32_t *base = rows ? T.e : T.f;
+        const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<int32_t *>(valid > 0 ? base + first : base), 0, valid > 0 ? 4 * min(valid, 64) : 0,
+            kBufferDword3);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void *)(ex + wave * 64), 4, 4 * lane, 0, 0, 0);
+    }
+}
+
+// The exponents of the block at row `mi` and column `nj` of a tile of BM rows
+// from its LDS slot, in one asm block that waits for them itself.  A read the
+// compiler sees would first wait for every load into LDS in flight, a next
+// item's blocks among them.
+template <int BM>
+__device__ __forceinline__ BlockExp staged_exponents(const int32_t *ex, int mi, int nj, int half, int l32) {
+    const unsigned rows = static_cast<unsigned>(reinterpret_cast<uintptr_t>(ex + mi + 4 * half));
+    const unsigned col = static_cast<unsigned>(reinterpret_cast<uintptr_t>(ex + BM + nj + l32));
+    BlockExp x;
+    asm volatile(
+        "ds_read_b128 %0, %5\n\t"
+        "ds_read_b128 %1, %5 offset:32\n\t"
+        "ds_read_b128 %2, %5 offset:64\n\t"
+        "ds_read_b128 %3, %5 offset:96\n\t"
+        "ds_read_b32 %4, %6\n\t"
+        "s_waitcnt lgkmcnt(0)"
+        : "=&v"(x.e[0]), "=&v"(x.e[1]), "=&v"(x.e[2]), "=&v"(x.e[3]), "=&v"(x.f)
+        : "v"(rows), "v"(col)
+        : "memory");
+    return x;
+}
+
+// stage_exponents as a main loop's `pre` (nothing without ex).  One type for
+// all modes: with a second specialization of a main loop over the same
+// LoadPlan hipcc's host pass refuses its steps.
+template <int BM, int BN>
+struct StageExponents {
+    int32_t *ex;
+    const TermDesc &T;
+    const OutDesc &out;
+    int m0, n0, wave, lane;
+    __device__ __forceinline__ void operator()() const {
+        if (ex) stage_exponents<BM, BN>(ex, T, out, m0, n0, wave, lane);
+    }
+};
 
 template <int S, int G, int WM, int WN, int MB, int NB, int MODE, bool EMAX = false, typename GetTerm>
 __device__ __forceinline__ void pair_tile(const PairArgs &a, GetTerm get_term, int tb, int te,
                                           const OutDesc &out, int m0, int n0, uint4 *lds0,
-                                          uint4 *lds1, uint4 *lds2) {
+                                          uint4 *lds1, uint4 *lds2, int32_t *ex) {
+    using C = Cfg<S, G, WM, WN, MB, NB>;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave / WN;
     const int wn = wave % WN;
     const int half = lane >> 5;
     const int l32 = lane & 31;
+    constexpr bool kSums = MODE == kModeQ || MODE == kModeQ64;  // no recombination
 
-    constexpr int SIG = (MODE == kModeAccum) ? 16 : 1;
-    double sig[MB][NB][SIG];
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-            for (int r = 0; r < SIG; ++r) sig[mb][nb][r] = 0.0;
-    if (MODE == kModeAccum && out.cont) {
-        // continuing an earlier launch's sums: straight-line loads (outside
-        // the output, of its first element; the value is then dropped)
+    double sig[MB][NB][MODE == kModeAccum ? 16 : 1];
+    if constexpr (MODE == kModeAccum)
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-                for (int r = 0; r < SIG; ++r) {
-                    const int i = m0 + (wm * MB + mb) * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
-                    const int j = n0 + (wn * NB + nb) * 32 + l32;
-                    const bool ok = i < out.M && j < out.N;
-                    const double v = out.C[ok ? static_cast<int64_t>(i) * out.ldc + j : 0];
-                    sig[mb][nb][r] = ok ? v : 0.0;
-                }
-    }
+                load_sums(sig[mb][nb], out, m0 + (wm * MB + mb) * 32, n0 + (wn * NB + nb) * 32, half, l32);
 
     // only the accumulating mode sums several terms into one tile
     const int tend = (MODE == kModeAccum) ? te : tb + 1;
     for (int ti = tb; ti < tend; ++ti) {
         const TermDesc T = get_term(ti);
         v16i acc[G][MB][NB];
-        pair_mainloop<S, G, WM, WN, MB, NB, MODE>(acc, lds0, lds1, lds2, T, m0, n0);
+        pair_mainloop<S, G, WM, WN, MB, NB, MODE>(acc, lds0, lds1, lds2, T, m0, n0,
+                                                  StageExponents<C::BM, C::BN>{kSums ? nullptr : ex, T, out, m0, n0, wave, lane});
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
-            const int j = n0 + (wn * NB + nb) * 32 + l32;
-            const bool jok = j < out.N;
-            int32_t fj = 0;
-            if (MODE != kModeQ && MODE != kModeQ64 && jok) fj = T.f[j];
+            const int j0 = n0 + (wn * NB + nb) * 32;
+            const int j = j0 + l32;
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb) {
-                long long w8[8], mlo = 0, keep = 0, got = 0;
-                int32_t ei[16];
-                if constexpr (MODE != kModeQ && MODE != kModeQ64)
-                    row_exponents(ei, T.e, out.M, m0 + (wm * MB + mb) * 32 + 4 * half, jok);
+                const int i0 = m0 + (wm * MB + mb) * 32;
+                auto row = [&](int r) { return i0 + 8 * (r >> 2) + 4 * half + (r & 3); };
+                auto sum = [&](int g, int r) -> int { return acc[g][mb][nb][r]; };
+                if constexpr (MODE == kModeQ) {
+                    const int64_t plane = static_cast<int64_t>(out.M) * out.N;
 #pragma unroll
-                for (int rr = 0; rr < 16; ++rr) {
-                    // with the fused maxima, values q and 8 + q in turn
-                    const int r = EMAX ? ((rr & 1) ? 8 + (rr >> 1) : (rr >> 1)) : rr;
-                    // keep kEpilogueGroup elements' recombinations at a time in registers
-                    if (rr % kEpilogueGroup == 0) __builtin_amdgcn_sched_barrier(0);
-                    const int i = m0 + (wm * MB + mb) * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
-                    const bool ok = jok && i < out.M;
-                    long long mag = 0;
-                    if (MODE == kModeQ) {
-                        if (ok) {
-                            const int64_t plane = static_cast<int64_t>(out.M) * out.N;
+                    for (int r = 0; r < 16; ++r)
+                        if (j < out.N && row(r) < out.M)
 #pragma unroll
                             for (int g = 0; g < G; ++g)
-                                a.Q[g * plane + static_cast<int64_t>(i) * out.N + j] = acc[g][mb][nb][r];
-                        }
-                    } else if (MODE == kModeQ64) {
-                        const int64_t idx = static_cast<int64_t>(i) * a.qw_ld + j;
+                                a.Q[g * plane + static_cast<int64_t>(row(r)) * out.N + j] = sum(g, r);
+                } else if constexpr (MODE == kModeQ64) {
+#pragma unroll
+                    for (int r = 0; r < 16; ++r)
 #pragma unroll
                         for (int g = 0; g < G; ++g) {
-                            int64_t *p = a.Qw + g * a.qw_plane + idx;
-                            const long long v = acc[g][mb][nb][r];
+                            int64_t *p = a.Qw + g * a.qw_plane + static_cast<int64_t>(row(r)) * a.qw_ld + j;
+                            const long long v = sum(g, r);
                             *p = a.qw_first ? v : *p + v;
                         }
-                    } else if (ok) {
-                        std::conditional_t<MODE == kModeGemm64, long long, int> q[G];
-#pragma unroll
-                        for (int g = 0; g < G; ++g) q[g] = acc[g][mb][nb][r];
-                        if (MODE == kModeGemm64) {
-                            const int64_t idx = static_cast<int64_t>(i) * a.qw_ld + j;
-#pragma unroll
-                            for (int g = 0; g < G; ++g) q[g] += a.Qw[g * a.qw_plane + idx];
-                        }
-                        const double c = horner<G>(q, ei[r], fj);
-                        if (MODE == kModeGemm || MODE == kModeGemm64) {
-                            double *p = out.C + static_cast<int64_t>(i) * out.ldc + j;
-                            const double v = (a.beta == 0.0) ? T.alpha * c : fma(T.alpha, c, a.beta * *p);
-                            *p = v;
-                            mag = __double_as_longlong(v) & 0x7fffffffffffffffll;
-                        } else {
-                            sig[mb][nb][r % SIG] = fma(T.alpha, c, sig[mb][nb][r % SIG]);
-                        }
+                } else {
+                    const BlockExp x = staged_exponents<C::BM>(ex, (wm * MB + mb) * 32, (wn * NB + nb) * 32, half, l32);
+                    if constexpr (MODE == kModeAccum) {
+                        add_block<G>(sig[mb][nb], T.alpha, x, sum);
+                    } else if constexpr (MODE == kModeGemm64) {
+                        store_block<G, false>(out, T.alpha, a.beta, x, i0, j0, half, l32, [&](int g, int r) -> long long {
+                            return sum(g, r) + a.Qw[g * a.qw_plane + static_cast<int64_t>(row(r)) * a.qw_ld + j];
+                        });
+                    } else {
+                        store_block<G, EMAX>(out, T.alpha, EMAX ? 0.0 : a.beta, x, i0, j0, half, l32, sum);
                     }
-                    if (EMAX && out.emax) {
-                        if (rr & 1) {
-                            if (rr > 1) w8[(rr >> 1) - 1] = keep > got ? keep : got;
-                            emax_issue(mlo, mag, l32, keep, got);
-                        } else {
-                            mlo = mag;
-                        }
-                    }
-                }
-                if (EMAX && out.emax) {
-                    w8[7] = keep > got ? keep : got;
-                    emax_block(out, w8, m0 + (wm * MB + mb) * 32, n0 + (wn * NB + nb) * 32, half, l32);
                 }
             }
         }
     }
 
-    if (MODE == kModeAccum) {
+    if constexpr (MODE == kModeAccum)
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-                for (int r = 0; r < SIG; ++r) {
-                    const int i = m0 + (wm * MB + mb) * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
-                    const int j = n0 + (wn * NB + nb) * 32 + l32;
-                    if (i < out.M && j < out.N)
-                        out.C[static_cast<int64_t>(i) * out.ldc + j] = sig[mb][nb][r];
-                }
-    }
+                store_sums(sig[mb][nb], out, m0 + (wm * MB + mb) * 32, n0 + (wn * NB + nb) * 32, half, l32);
 }
 
 // ---- streamed grouped kernel ----------------------------------------------
@@ -985,27 +1130,19 @@ __device__ __forceinline__ void stream_tiles(const PairArgs &a, GetTerm get_term
     TileDesc td = a.tiles[t];
     bool pending = false;  // the current item's first block is on its way into lds0 (in0) or lds1
     bool in0 = true;
-    constexpr int SIG = (MODE == kModeAccum) ? 16 : 1;
     while (true) {
         OutDesc od = a.outs[td.out];
         if (a.out_base) od.C = a.out_base + reinterpret_cast<intptr_t>(od.C);
         const int m0 = td.m0, n0 = td.n0;
         const int te = stream_term_end<MODE>(td);
         const int tn = stream_take(a, slots, slot);
-        double sig[MB][NB][SIG];
+        double sig[MB][NB][MODE == kModeAccum ? 16 : 1];
+        if constexpr (MODE == kModeAccum)
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
+            for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-                for (int r = 0; r < SIG; ++r) {
-                    sig[mb][nb][r] = 0.0;
-                    if (MODE == kModeAccum && od.cont) {
-                        const int i = m0 + (wm * MB + mb) * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
-                        const int j = n0 + (wn * NB + nb) * 32 + l32;
-                        if (i < od.M && j < od.N) sig[mb][nb][r] = od.C[static_cast<int64_t>(i) * od.ldc + j];
-                    }
-                }
+                for (int nb = 0; nb < NB; ++nb)
+                    load_sums(sig[mb][nb], od, m0 + (wm * MB + mb) * 32, n0 + (wn * NB + nb) * 32, half, l32);
         for (int ti = td.term_begin; ti < te; ++ti) {
             const TermDesc T = get_term(ti);
             // the next item: this tile's next term, else the next tile's first
@@ -1039,63 +1176,25 @@ __device__ __forceinline__ void stream_tiles(const PairArgs &a, GetTerm get_term
             if (has_next && (T.kblocks & 1)) in0 = !in0;
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) {
-                const int j = n0 + (wn * NB + nb) * 32 + l32;
-                const bool jok = j < od.N;
-                const int32_t fj = jok ? T.f[j] : 0;
+                const int j0 = n0 + (wn * NB + nb) * 32;
 #pragma unroll
                 for (int mb = 0; mb < MB; ++mb) {
-                    constexpr bool EMAX = MODE == kModeGemm;
-                    long long w8[8], mlo = 0, keep = 0, got = 0;
-                    int32_t ei[16];
-                    row_exponents(ei, T.e, od.M, m0 + (wm * MB + mb) * 32 + 4 * half, jok);
-#pragma unroll
-                    for (int rr = 0; rr < 16; ++rr) {
-                        const int r = EMAX ? ((rr & 1) ? 8 + (rr >> 1) : (rr >> 1)) : rr;
-                        if (rr % kEpilogueGroup == 0) __builtin_amdgcn_sched_barrier(0);
-                        const int i = m0 + (wm * MB + mb) * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
-                        long long mag = 0;
-                        if (jok && i < od.M) {
-                            long long q[G];
-#pragma unroll
-                            for (int g = 0; g < G; ++g) q[g] = acc[g][mb][nb][r];
-                            const double c = horner<G>(q, ei[r], fj);
-                            if (MODE == kModeGemm) {
-                                double *p = od.C + static_cast<int64_t>(i) * od.ldc + j;
-                                const double v = (a.beta == 0.0) ? T.alpha * c : fma(T.alpha, c, a.beta * *p);
-                                *p = v;
-                                mag = __double_as_longlong(v) & 0x7fffffffffffffffll;
-                            } else {
-                                sig[mb][nb][r % SIG] = fma(T.alpha, c, sig[mb][nb][r % SIG]);
-                            }
-                        }
-                        if (EMAX && od.emax) {
-                            if (rr & 1) {
-                                if (rr > 1) w8[(rr >> 1) - 1] = keep > got ? keep : got;
-                                emax_issue(mlo, mag, l32, keep, got);
-                            } else {
-                                mlo = mag;
-                            }
-                        }
-                    }
-                    if (EMAX && od.emax) {
-                        w8[7] = keep > got ? keep : got;
-                        emax_block(od, w8, m0 + (wm * MB + mb) * 32, n0 + (wn * NB + nb) * 32, half, l32);
-                    }
+                    const int i0 = m0 + (wm * MB + mb) * 32;
+                    const BlockExp x = block_exponents(T, od.M, od.N, i0, j0, half, l32);
+                    auto sum = [&](int g, int r) -> int { return acc[g][mb][nb][r]; };
+                    if constexpr (MODE == kModeGemm)
+                        store_block<G, true>(od, T.alpha, 0.0, x, i0, j0, half, l32, sum);
+                    else
+                        add_block<G>(sig[mb][nb], T.alpha, x, sum);
                 }
             }
         }
-        if (MODE == kModeAccum) {
+        if constexpr (MODE == kModeAccum)
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
                 for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-                    for (int r = 0; r < SIG; ++r) {
-                        const int i = m0 + (wm * MB + mb) * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
-                        const int j = n0 + (wn * NB + nb) * 32 + l32;
-                        if (i < od.M && j < od.N) od.C[static_cast<int64_t>(i) * od.ldc + j] = sig[mb][nb][r];
-                    }
-        }
+                    store_sums(sig[mb][nb], od, m0 + (wm * MB + mb) * 32, n0 + (wn * NB + nb) * 32, half, l32);
         if (tn >= a.ntiles) break;
         t = tn;
         td = a.tiles[t];
@@ -1166,26 +1265,6 @@ __device__ __forceinline__ int32_t const_i32(const int32_t *p, int i) {
 template <int S, int G, int WM, int WN, int MB, int NB>
 __host__ __device__ constexpr bool resident_fits() {
     return MB == 1 && NB == 1 && use_ring<S, G, WM, WN, MB, NB, kModeGemm>();
-}
-
-// The exponents of one tile into LDS slot `ex` (BM row exponents, then BN
-// column exponents): one 64-entry load per wave for the first BM / 64 + BN
-// / 64 waves; entries past the output's edge are out of the buffer's range
-// and left unused by the epilogue.
-template <int BM, int BN>
-__device__ __forceinline__ void resident_exponents(int32_t *ex, const TermDesc &T, const OutDesc &od, int m0, int n0,
-                                                   int wave, int lane) {
-    constexpr int NE = BM / 64, NF = BN / 64;
-    if (wave < NE + NF) {
-        const bool rows = wave < NE;
-        const int first = rows ? m0 + wave * 64 : n0 + (wave - NE) * 64;
-        const int valid = (rows ? od.M : od.N) - first;
-        const int32_t *base = rows ? T.e : T.f;
-        const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<int32_t *>(valid > 0 ? base + first : base), 0, valid > 0 ? 4 * min(valid, 64) : 0,
-            kBufferDword3);
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void *)(ex + wave * 64), 4, 4 * lane, 0, 0, 0);
-    }
 }
 
 // One step of a resident item: as ring_step, except that the block three
@@ -1282,80 +1361,19 @@ __device__ __forceinline__ void resident_item(v16i (&acc)[G][1][1], uint4 *s0, u
     asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" ::: "memory");
 }
 
-// The epilogue's exponents from LDS slot `ex`: the lane's 16 row exponents
-// (four runs of four) and its column's, read in one asm block that waits for
-// them itself.  A read the compiler sees would first wait for every load
-// into LDS in flight, the next item's blocks among them.
-template <int BM>
-__device__ __forceinline__ void resident_read_exponents(int32_t (&ei)[16], int32_t &fj, const int32_t *ex, int wm,
-                                                        int wn, int half, int l32) {
-    const unsigned rows = static_cast<unsigned>(reinterpret_cast<uintptr_t>(ex + wm * 32 + 4 * half));
-    const unsigned col = static_cast<unsigned>(reinterpret_cast<uintptr_t>(ex + BM + wn * 32 + l32));
-    v4i q0, q1, q2, q3;
-    int32_t c;
-    asm volatile(
-        "ds_read_b128 %0, %5\n\t"
-        "ds_read_b128 %1, %5 offset:32\n\t"
-        "ds_read_b128 %2, %5 offset:64\n\t"
-        "ds_read_b128 %3, %5 offset:96\n\t"
-        "ds_read_b32 %4, %6\n\t"
-        "s_waitcnt lgkmcnt(0)"
-        : "=v"(q0), "=v"(q1), "=v"(q2), "=v"(q3), "=v"(c)
-        : "v"(rows), "v"(col)
-        : "memory");
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        ei[k] = q0[k];
-        ei[4 + k] = q1[k];
-        ei[8 + k] = q2[k];
-        ei[12 + k] = q3[k];
-    }
-    fj = c;
-}
-
 // The GEMM-mode epilogue of one item (beta = 0) with its exponents from LDS.
 template <int S, int G, int WM, int WN>
 __device__ __forceinline__ void resident_epilogue(const OutDesc &out, const TermDesc &T, v16i (&acc)[G][1][1],
                                                   int m0, int n0, const int32_t *ex) {
-    using C = Cfg<S, G, WM, WN, 1, 1>;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave / WN;
     const int wn = wave % WN;
     const int half = lane >> 5;
     const int l32 = lane & 31;
-    const int j = n0 + wn * 32 + l32;
-    const bool jok = j < out.N;
-    int32_t ei[16], fj;
-    resident_read_exponents<C::BM>(ei, fj, ex, wm, wn, half, l32);
-    long long w8[8], mlo = 0, keep = 0, got = 0;
-#pragma unroll
-    for (int rr = 0; rr < 16; ++rr) {
-        const int r = (rr & 1) ? 8 + (rr >> 1) : (rr >> 1);
-        if (rr % kEpilogueGroup == 0) __builtin_amdgcn_sched_barrier(0);
-        const int i = m0 + wm * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
-        long long mag = 0;
-        if (jok && i < out.M) {
-            long long q[G];
-#pragma unroll
-            for (int g = 0; g < G; ++g) q[g] = acc[g][0][0][r];
-            const double v = T.alpha * horner<G>(q, ei[r], fj);
-            out.C[static_cast<int64_t>(i) * out.ldc + j] = v;
-            mag = __double_as_longlong(v) & 0x7fffffffffffffffll;
-        }
-        if (out.emax) {
-            if (rr & 1) {
-                if (rr > 1) w8[(rr >> 1) - 1] = keep > got ? keep : got;
-                emax_issue(mlo, mag, l32, keep, got);
-            } else {
-                mlo = mag;
-            }
-        }
-    }
-    if (out.emax) {
-        w8[7] = keep > got ? keep : got;
-        emax_block(out, w8, m0 + wm * 32, n0 + wn * 32, half, l32);
-    }
+    const BlockExp x = staged_exponents<Cfg<S, G, WM, WN, 1, 1>::BM>(ex, wm * 32, wn * 32, half, l32);
+    store_block<G, true>(out, T.alpha, 0.0, x, m0 + wm * 32, n0 + wn * 32, half, l32,
+                         [&](int g, int r) -> int { return acc[g][0][0][r]; });
 }
 
 template <int S, int G, int WM, int WN>
@@ -1374,7 +1392,7 @@ __global__ __launch_bounds__(64 * WM * WN) void k_pair_resident(PairArgs a) {
     TermDesc T = const_term(a.terms, td.term_begin);
     LP lp;
     lp.init(T.A, T.B, T.a_rows_p, T.b_rows_p, td.m0, td.n0, wave, lane);
-    resident_exponents<C::BM, C::BN>(ex[0], T, od, td.m0, td.n0, wave, lane);
+    stage_exponents<C::BM, C::BN>(ex[0], T, od, td.m0, td.n0, wave, lane);
     if (0 < T.kblocks) lp.issue(st[0], 0);
     if (1 < T.kblocks) lp.issue(st[1], 1);
     if (2 < T.kblocks) lp.issue(st[2], 2);
@@ -1395,7 +1413,7 @@ __global__ __launch_bounds__(64 * WM * WN) void k_pair_resident(PairArgs a) {
         uint4 *s1 = st[ph == 2 ? 0 : ph + 1];
         uint4 *s2 = st[ph == 0 ? 2 : ph - 1];
         resident_item<S, G, WM, WN>(acc, s0, s1, s2, lp, T.kblocks, np, nxt, [&]() {
-            if (more) resident_exponents<C::BM, C::BN>(nex, N, nod, nd.m0, nd.n0, wave, lane);
+            if (more) stage_exponents<C::BM, C::BN>(nex, N, nod, nd.m0, nd.n0, wave, lane);
         });
         resident_epilogue<S, G, WM, WN>(od, T, acc, td.m0, td.n0, ex[slot]);
         ph = (ph + T.kblocks) % 3;
@@ -1449,18 +1467,18 @@ __device__ __forceinline__ void group_step(v16i (&acc)[G][1][1], F &cur, uint4 *
 
 // The diagonal sums of a group's term of `nvalid` K blocks over a round of
 // `nsteps` >= nvalid steps; returns with the group's loads all arrived.
-template <int S, int G, typename LP>
+template <int S, int G, typename LP, typename Exps>
 __device__ __forceinline__ void group_ring(v16i (&acc)[G][1][1], uint4 *s0, uint4 *s1, uint4 *s2, const LP &lp,
-                                           int nvalid, int nsteps, int wm, int wn, int half, int l32) {
+                                           int nvalid, int nsteps, int wm, int wn, int half, int l32, Exps exps) {
     using C = Cfg<S, G, 2, 2, 1, 1>;
     using RA = RingAddr<S, G, 2, 2, 1, 1>;
 #pragma unroll
     for (int g = 0; g < G; ++g) acc[g][0][0] = v16i{};
-    if (nsteps == 0) return;
     // the previous round's reads of LDS (fragments, exchanged values) are done
     __builtin_amdgcn_s_waitcnt(C::WAIT_LDS);
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
+    exps();  // the term's exponents, ahead of its blocks
     if (0 < nvalid) lp.issue(s0, 0);
     if (1 < nvalid) lp.issue(s1, 1);
     if (2 < nvalid) lp.issue(s2, 2);
@@ -1472,6 +1490,7 @@ __device__ __forceinline__ void group_ring(v16i (&acc)[G][1][1], uint4 *s0, uint
         __builtin_amdgcn_s_waitcnt(C::WAIT_ALL);
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
+    if (nsteps == 0) return;
     // (a group without blocks reads values it never uses)
     Frags<S, G, 1, 1> f;
     AsmStep<S, G>::template read<RA::OA, RA::OB>(f, RA::a(s0, wm, half, l32), RA::b(s0, wn, half, l32));
@@ -1495,6 +1514,7 @@ __global__ __launch_bounds__(512) void k_pair_terms2(PairArgs a) {
     constexpr int kRings = 2 * 3 * C::STAGE;
     constexpr int kExchange = 2 * 4 * 16 * 64 * 8 / 16;
     __shared__ uint4 lds[kRings > kExchange ? kRings : kExchange];
+    __shared__ __align__(16) int32_t ex[2][C::BM + C::BN];  // each group's exponents
     const TileDesc td = a.tiles[blockIdx.x];
     if (td.out < 0) return;  // padding of the XCD order
     OutDesc od = a.outs[td.out];
@@ -1522,7 +1542,7 @@ __global__ __launch_bounds__(512) void k_pair_terms2(PairArgs a) {
             const int r = 8 * grp + q;
             const int i = m0 + wm * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
             const bool ok = jok && i < od.M;
-            const double v = od.C[ok ? static_cast<int64_t>(i) * od.ldc + j : 0];
+            const double v = global_ptr(od.C)[ok ? static_cast<int64_t>(i) * od.ldc + j : 0];
             sig[q] = ok ? v : 0.0;
         }
     }
@@ -1542,25 +1562,21 @@ __global__ __launch_bounds__(512) void k_pair_terms2(PairArgs a) {
         LP lp;
         lp.init(T.A, T.B, T.a_rows_p, T.b_rows_p, m0, n0, w4, lane);
         v16i acc[G][1][1];
-        group_ring<S, G>(acc, s0, s1, s2, lp, nvalid, nsteps, wm, wn, half, l32);
+        group_ring<S, G>(acc, s0, s1, s2, lp, nvalid, nsteps, wm, wn, half, l32, [&]() {
+            stage_exponents<C::BM, C::BN>(ex[grp], T, od, m0, n0, w4, lane);
+        });
         // every wave is done with the stages before they take the values
         __syncthreads();
         if (grp == 0 || hb) {
-            const int32_t fj = jok ? T.f[j] : 0;
-            int32_t ei[16];
-            row_exponents(ei, T.e, od.M, m0 + wm * 32 + 4 * half, jok);
+            const BlockExp x = staged_exponents<C::BM>(ex[grp], wm * 32, wn * 32, half, l32);
+            const bool bad = any_bad(x);
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                if (r % kEpilogueGroup == 0) __builtin_amdgcn_sched_barrier(0);
-                const int i = m0 + wm * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
-                double c = 0.0;
-                if (jok && i < od.M) {
-                    long long q[G];
+            for (int k = 0; k < 4; ++k) {
+                __builtin_amdgcn_sched_barrier(0);
+                double c[4];
+                recombine4<G>(c, x, bad, k, [&](int g, int r) -> int { return acc[g][0][0][r]; });
 #pragma unroll
-                    for (int g = 0; g < G; ++g) q[g] = acc[g][0][0][r];
-                    c = horner<G>(q, ei[r], fj);
-                }
-                xch[((grp * 4 + w4) * 16 + r) * 64 + lane] = c;
+                for (int q = 0; q < 4; ++q) xch[((grp * 4 + w4) * 16 + 4 * k + q) * 64 + lane] = c[q];
             }
         }
         __syncthreads();
@@ -1568,18 +1584,15 @@ __global__ __launch_bounds__(512) void k_pair_terms2(PairArgs a) {
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
             const int r = 8 * grp + q;
-            const int i = m0 + wm * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
-            if (jok && i < od.M) {
-                sig[q] = fma(Ta.alpha, xch[(w4 * 16 + r) * 64 + lane], sig[q]);
-                if (hb) sig[q] = fma(Tb.alpha, xch[((4 + w4) * 16 + r) * 64 + lane], sig[q]);
-            }
+            sig[q] = fma(Ta.alpha, xch[(w4 * 16 + r) * 64 + lane], sig[q]);
+            if (hb) sig[q] = fma(Tb.alpha, xch[((4 + w4) * 16 + r) * 64 + lane], sig[q]);
         }
     }
+    global_f64 *p = global_ptr(od.C) + static_cast<int64_t>(m0 + wm * 32 + 4 * half) * od.ldc + j;
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
-        const int r = 8 * grp + q;
-        const int i = m0 + wm * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
-        if (jok && i < od.M) od.C[static_cast<int64_t>(i) * od.ldc + j] = sig[q];
+        const int r = 8 * grp + q, d = 8 * (r >> 2) + (r & 3);
+        if (jok && m0 + wm * 32 + 4 * half + d < od.M) p[d * od.ldc] = sig[q];
     }
 }
 
@@ -1629,6 +1642,7 @@ __global__ __launch_bounds__(64 * WM * WN) void k_pair_single(PairArgs a, int ti
     __shared__ uint4 lds0[C::STAGE];
     __shared__ uint4 lds1[C::STAGE];
     __shared__ uint4 lds2[use_ring<S, G, WM, WN, MB, NB, MODE>() ? C::STAGE : 1];
+    __shared__ __align__(16) int32_t ex[C::BM + C::BN];
     int k, tm, tn;
     constexpr int group = C::BM >= 2 * C::BN ? 4 : 8;
     tile_coords(blockIdx.x, tiles_m, a.tiles_n, group, a.nbatch, k, tm, tn);
@@ -1636,7 +1650,7 @@ __global__ __launch_bounds__(64 * WM * WN) void k_pair_single(PairArgs a, int ti
     OutDesc out;
     batch_product(a, k, term, out);
     pair_tile<S, G, WM, WN, MB, NB, MODE>(a, [&](int) { return term; }, 0, 1, out, tm * C::BM,
-                                          tn * C::BN, lds0, lds1, lds2);
+                                          tn * C::BN, lds0, lds1, lds2, ex);
 }
 
 // ---- split kernel for products of few tiles --------------------------------
@@ -1680,13 +1694,12 @@ __global__ __launch_bounds__(256) void k_pair_split(PairArgs a, int tiles_m) {
     for (int g = 0; g < G; ++g) acc[g][0][0] = v16i{};
     const int j = n0 + l32;
     const bool jok = j < out.N;
-    const int32_t fj = jok ? T.f[j] : 0;
-    int32_t ei[4];  // this wave finishes rows 8 wave + 4 half + 0..3 of the block
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int i = m0 + 8 * wave + 4 * half + q;
-        ei[q] = i < out.M ? T.e[i] : 0;
-    }
+    // this wave finishes rows 8 wave + 4 half + 0..3 of the block
+    const int ib = m0 + 8 * wave + 4 * half;
+    BlockExp x{};
+    x.e[0] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t *>(T.e), 0, 4 * out.M, kBufferDword3), 4 * ib, 0, 0));
+    x.f = T.f[min(j, out.N - 1)];
     Frags<S, G, 1, 1> cur, nxt;
     if (wave < T.kblocks) split_load<S, G>(cur, A + wave * 2 * S * a_run, B + wave * 2 * S * b_run, a_run, b_run);
     for (int kb = wave; kb < T.kblocks; kb += 4) {
@@ -1714,20 +1727,20 @@ __global__ __launch_bounds__(256) void k_pair_split(PairArgs a, int tiles_m) {
 #pragma unroll
         for (int p = p0; p < p0 + PP; ++p) {
             if (wave != p) continue;
+            int s[G][4];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                int s[G];
+            for (int g = 0; g < G; ++g)
 #pragma unroll
-                for (int g = 0; g < G; ++g)
-                    s[g] = acc[g][0][0][4 * p + q] + red[p - p0][0][g * 4 + q][lane] +
-                           red[p - p0][1][g * 4 + q][lane] + red[p - p0][2][g * 4 + q][lane];
-                const int i = m0 + 8 * p + 4 * half + q;
-                if (jok && i < out.M) {
-                    const double c = horner<G>(s, ei[q], fj);
-                    double *o = out.C + static_cast<int64_t>(i) * out.ldc + j;
-                    *o = (a.beta == 0.0) ? T.alpha * c : fma(T.alpha, c, a.beta * *o);
-                }
-            }
+                for (int q = 0; q < 4; ++q)
+                    s[g][q] = acc[g][0][0][4 * p + q] + red[p - p0][0][g * 4 + q][lane] + red[p - p0][1][g * 4 + q][lane] +
+                              red[p - p0][2][g * 4 + q][lane];
+            double c[4];
+            recombine4<G>(c, x, any_bad(x), 0, [&](int g, int r) -> int { return s[g][r]; });
+            global_f64 *o = global_ptr(out.C) + static_cast<int64_t>(ib) * out.ldc + j;
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (jok && ib + q < out.M)
+                    o[q * out.ldc] = (a.beta == 0.0) ? T.alpha * c[q] : fma(T.alpha, c[q], a.beta * o[q * out.ldc]);
         }
     }
 }
@@ -1785,9 +1798,7 @@ __global__ __launch_bounds__((64 * accum_split_waves<S, G>())) void k_pair_accum
             for (int g = 0; g < G; ++g) acc[g][0][0] = v16i{};
             Frags<S, G, 1, 1> cur, nxt;
             if (0 < T.kblocks) split_load<S, G>(cur, A, B, a_run, b_run);
-            const int32_t fj = jok ? T.f[j] : 0;
-            int32_t ei[16];
-            row_exponents(ei, T.e, od.M, m0 + 4 * half, jok);
+            const BlockExp x = block_exponents(T, od.M, od.N, m0, n0, half, l32);
             for (int kb = 0; kb < T.kblocks; ++kb) {
                 if (kb + 1 < T.kblocks)
                     split_load<S, G>(nxt, A + (kb + 1) * 2 * S * a_run, B + (kb + 1) * 2 * S * b_run, a_run, b_run);
@@ -1795,17 +1806,14 @@ __global__ __launch_bounds__((64 * accum_split_waves<S, G>())) void k_pair_accum
                 mfma_pairs<false, S, G, 1, 1>(acc, cur);
                 cur = nxt;
             }
+            const bool bad = any_bad(x);
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                if (r % kEpilogueGroup == 0) __builtin_amdgcn_sched_barrier(0);
-                double c = 0.0;
-                if (jok && row_of(r) < od.M) {
-                    int q[G];
+            for (int k = 0; k < 4; ++k) {
+                __builtin_amdgcn_sched_barrier(0);
+                double c[4];
+                recombine4<G>(c, x, bad, k, [&](int g, int r) -> int { return acc[g][0][0][r]; });
 #pragma unroll
-                    for (int g = 0; g < G; ++g) q[g] = acc[g][0][0][r];
-                    c = horner<G>(q, ei[r], fj);
-                }
-                val[wave][r][lane] = c;
+                for (int q = 0; q < 4; ++q) val[wave][4 * k + q][lane] = c[q];
             }
         }
         __syncthreads();
@@ -1830,6 +1838,7 @@ __global__ __launch_bounds__(64 * WM * WN) void k_pair_grouped(PairArgs a) {
     __shared__ uint4 lds0[C::STAGE];
     __shared__ uint4 lds1[C::STAGE];
     __shared__ uint4 lds2[use_ring<S, G, WM, WN, MB, NB, MODE>() ? C::STAGE : 1];
+    __shared__ __align__(16) int32_t ex[C::BM + C::BN];
     const TileDesc td = a.tiles[blockIdx.x];
     if (td.out < 0) return;  // padding of the XCD order
     OutDesc od = a.outs[td.out];
@@ -1837,7 +1846,8 @@ __global__ __launch_bounds__(64 * WM * WN) void k_pair_grouped(PairArgs a) {
     const TermDesc *terms = a.terms;
     pair_tile<S, G, WM, WN, MB, NB, MODE, MODE == kModeGemm>(a, [&](int i) { return const_term(terms, i); },
                                                             td.term_begin, td.term_end, od, td.m0, td.n0, lds0,
-                                                            lds1, lds2);
+                                                            lds1, lds2,
+                                                            ex);
 }
 
 // Per-(S, G) tile shape: as wide as the accumulators allow.
@@ -1928,6 +1938,7 @@ hipError_t run_grouped_v(const PairArgs &a, hipStream_t s) {
         return hipErrorInvalidValue;
     } else {
         if (a.ntiles == 0) return hipSuccess;
+        if (a.beta != 0.0) return hipErrorInvalidValue;  // grouped outputs are stored, not combined
         if (a.split) {
             if (a.mode != kModeAccum) return hipErrorInvalidValue;
             constexpr int threads = 64 * accum_split_waves<S, G>();
@@ -1945,7 +1956,7 @@ hipError_t run_grouped_v(const PairArgs &a, hipStream_t s) {
         }
         if (a.nwg > 0) {
             if constexpr (resident_fits<S, G, WM, WN, MB, NB>()) {
-                if (a.mode != kModeGemm || !a.wg_off || a.beta != 0.0 || a.Qw) return hipErrorInvalidValue;
+                if (a.mode != kModeGemm || !a.wg_off || a.Qw) return hipErrorInvalidValue;
                 hipLaunchKernelGGL((k_pair_resident<S, G, WM, WN>), dim3(a.nwg), dim3(NT), 0, s, a);
                 return hipGetLastError();
             } else {

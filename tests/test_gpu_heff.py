@@ -642,6 +642,34 @@ def test_exponent_codes_between_applies(oz, D, phys, chunks):
         assert (ctx.flags() & 1) == (0 if np.isfinite(x).all() else 1)
 
 
+@pytest.mark.parametrize("D,phys", [(31, 1), (64, 4), (150, 1)])
+@pytest.mark.parametrize("launch", [-1, 0, 100000, -2])
+def test_subnormal_row_maxima(oz, D, phys, launch):
+    """Rows of the first product whose largest magnitude is subnormal, or next
+    to the smallest normal number or to an exponent's threshold: the fused row
+    maxima give the exponents of a pass over the values (the oracle's bits)."""
+    ozaki, ctx, torch = oz
+    L, R, psi = wl.heff_dense(D=D, kop=2, phys=phys, seed=170 + D)
+    rng = np.random.default_rng(D)
+    # L = power-of-two diagonals: T's rows are psi's rows, scaled one by one
+    L[:] = 0.0
+    for k in range(2):
+        L[k][np.arange(D), np.arange(D)] = 2.0 ** rng.integers(-20, 3, D)
+    psi *= 2.0 ** rng.integers(-1070, -1000, (D, 1, 1))
+    thr = 127.0 / 128.0 * 2.0 ** -1015
+    psi[0, 0, :4] = [thr, np.nextafter(thr, 1), np.nextafter(thr, 0), -2.0 ** -1022]
+    ctx.set_heff_launch(launch)
+    if launch == -2:
+        ctx.set_variant(6, 0, 0)
+    try:
+        plan, dpsi, keep = dense_plan(ozaki, ctx, torch, L, R, psi, 6)
+    finally:
+        ctx.set_heff_launch(-1)
+        ctx.set_variant(6, 0, -1)
+    sig = plan.apply(dpsi).cpu().numpy().reshape(psi.shape)
+    assert_bitexact(sig, oracle.heff_dense(L, R, psi, S=6), "D=%d" % D)
+
+
 @pytest.mark.parametrize("S,G", [(2, 2), (5, 5), (6, 6), (7, 8), (8, 15)])
 def test_few_tiles_split_bitexact(oz, S, G):
     """Second phases of few output blocks (a workgroup per 32 x 32 block, its
