@@ -124,6 +124,25 @@ __device__ __forceinline__ double lane_value(double x, int lane) {
     return __hiloint2double(hi, lo);
 }
 
+// A pair's own rotated tile, element (r, c) = f(r, c) of 64 x 64, in the next
+// round's slots: whole when its two 32 x 32 blocks stay together, else its
+// diagonal blocks and the block between them on the upper side.  Threads (ty,
+// tx) of an 8 x 32 grid, rows 4 ty + m and columns tx of each block.
+template <typename F>
+__device__ __forceinline__ void store_pair_tile(double *__restrict__ M2, int64_t np, int d0, int d1, F f) {
+    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+    const int d[2] = {d0, d1};
+#pragma unroll
+    for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+        for (int cb = 0; cb < 2; ++cb) {
+            if ((d[rb] >> 1) > (d[cb] >> 1)) continue;
+            double *o = M2 + static_cast<int64_t>(d[rb]) * kBlk * np + static_cast<int64_t>(d[cb]) * kBlk + tx;
+#pragma unroll
+            for (int m = 0; m < 4; ++m) o[(4 * ty + m) * np] = f(rb, cb, m);
+        }
+}
+
 // Step 1: one workgroup per pair k.  The pair's diagonal block of M (upper
 // triangle, mirrored) goes through one sweep of cyclic Jacobi over all its
 // rotations, unless its largest off-diagonal entry is <= inner_tol and its
@@ -136,7 +155,9 @@ __device__ __forceinline__ double lane_value(double x, int lane) {
 // lanes then sweep the 64 columns (row pass) and the 64 rows (column pass).
 __global__ __launch_bounds__(256) void k_pair_eig(const double *__restrict__ M, int64_t ldm,
                                                   double *__restrict__ Qt, double *__restrict__ off_out,
-                                                  double inner_tol, double exempt_tol2, double theta) {
+                                                  double inner_tol, double exempt_tol2, double theta,
+                                                  double *__restrict__ M2, const int *__restrict__ dst,
+                                                  int *__restrict__ act) {
     __shared__ double a[kPair * kLdE];
     __shared__ double vt[kPair * kPair];  // transposed rotations: row t is column t of the product
     __shared__ double red[256];
@@ -156,6 +177,7 @@ __global__ __launch_bounds__(256) void k_pair_eig(const double *__restrict__ M, 
         off_out[3 * k] = off;
         off_out[3 * k + 1] = sums[0];
         off_out[3 * k + 2] = sums[1];
+        if (act) act[k] = off > inner_tol || sums[1] > exempt_tol2;
     }
     if (off > inner_tol || sums[1] > exempt_tol2) {
         for (int step = 0; step < 63; ++step) {
@@ -216,6 +238,10 @@ __global__ __launch_bounds__(256) void k_pair_eig(const double *__restrict__ M, 
     }
     double *qt = Qt + static_cast<int64_t>(kPair) * k * kPair;
     for (int idx = tid; idx < kPair * kPair; idx += 256) qt[idx] = vt[idx];
+    if (M2)
+        store_pair_tile(M2, ldm, dst[2 * k], dst[2 * k + 1], [&](int rb, int cb, int m) {
+            return a[(32 * rb + 4 * (tid >> 5) + m) * kLdE + 32 * cb + (tid & 31)];
+        });
 }
 
 __device__ __forceinline__ double lane_shift(double x, int addr) {
@@ -246,16 +272,18 @@ constexpr int kRotLds = 64 * t64::kLdK + 64 * t64::kLdN;  // doubles: one tile r
 // the accumulated rotations.  A rotation is then local once its (c, s) pairs
 // are known, and moving on to the next step's pairing shifts the q rows and
 // columns by one: within the thread, to the next lane, or (one row in four)
-// through LDS.  Bound: the chain of 32 steps (rotation, broadcast, update,
-// shift), two barriers each: 40 us at n = 2048 with W's tiles beside it,
-// against 110 us for k_pair_eig, whose 63 steps each move 200 KB through LDS.
+// through LDS, along with the three elements each of the next rotations needs,
+// so that every half wave computes all of them and one barrier a step is
+// enough.  The finished tile is the pair's part of the next M.  Bound: the
+// chain of 32 steps (rotation, broadcast, update, shift) of about 1.1 us: 38 us
+// a round at n = 2048 where k_pair_eig, whose 63 steps each move 200 KB
+// through LDS, takes 110.
 __device__ void pair_cross(const double *__restrict__ g, int64_t ldm, double *__restrict__ qt,
                            double *__restrict__ off_out, double inner_tol, double exempt_tol2, double theta,
-                           double *lds) {
+                           double *lds, double *__restrict__ M2, int d0, int d1, int *__restrict__ act) {
     double *a = lds;                       // 64 x kLdE staging
-    double *cs = lds + kPair * kLdE;       // 32 x (c, s)
-    double *sh = cs + 64;                  // 8 x 4 x 32 shifted values
-    double *red = sh + 1024;               // 4 x 3
+    double *red = lds + kPair * kLdE;      // 4 x 3
+    double *next = red + 12;               // 2 x (8 x 4 x 32 shifted values, 3 x 32 of the next pairs)
     const int tid = threadIdx.x, tx = tid & 31, ty = tid >> 5;
     for (int idx = tid; idx < kPair * kPair; idx += 256) {
         const int r = idx >> 6, c = idx & 63;
@@ -312,63 +340,81 @@ __device__ void pair_cross(const double *__restrict__ g, int64_t ldm, double *__
         off_out[0] = mx;
         off_out[1] = sq;
         off_out[2] = sx;
+        if (act) *act = mx > inner_tol || sx > exempt_tol2;
     }
     if (mx > inner_tol || sx > exempt_tol2) {
-        const int next = 4 * ((tid & 32) + ((tx + 1) & 31));  // lane tx + 1 of the same half wave
-        const int mi = tx - 4 * ty;                           // this thread holds pair tx's own block when 0 <= mi < 4
+        const int up = (tx + 1) & 31, down = (tx + 31) & 31;
+        const int up_lane = 4 * ((tid & 32) + up);  // lane tx + 1 of the same half wave
+        const int mi = tx - 4 * ty;                 // 0 <= mi < 4: this thread holds the elements of p_tx, q_tx alone
+        const int md = down - 4 * ty;               // and 0 <= md < 4: of rows p_down, column q_tx
+        double app = a[tx * kLdE + tx], apq = a[tx * kLdE + 32 + tx], aqq = a[(32 + tx) * kLdE + 32 + tx];
         for (int t = 0; t < 32; ++t) {
-            double app = pp[0], apq = pq[0], aqq = qq[0];
-#pragma unroll
-            for (int m = 1; m < 4; ++m) {
-                app = mi == m ? pp[m] : app;
-                apq = mi == m ? pq[m] : apq;
-                aqq = mi == m ? qq[m] : aqq;
-            }
+            // every half wave computes all 32 rotations, lane tx pair tx's,
+            // and takes those of its rows from its lanes
             double c, s;
             schur_rotation(app, aqq, apq, &c, &s);
-            if (mi >= 0 && mi < 4) *reinterpret_cast<double2 *>(cs + 2 * tx) = double2{c, s};
-            __syncthreads();
-            const double2 rj = *reinterpret_cast<const double2 *>(cs + 2 * tx);
+            double rc[4], rs[4];
 #pragma unroll
             for (int m = 0; m < 4; ++m) {
-                const double2 ri = *reinterpret_cast<const double2 *>(cs + 2 * (4 * ty + m));
-                const double p0 = ri.x * pp[m] - ri.y * qp[m], q0 = ri.y * pp[m] + ri.x * qp[m];
-                const double p1 = ri.x * pq[m] - ri.y * qq[m], q1 = ri.y * pq[m] + ri.x * qq[m];
-                pp[m] = rj.x * p0 - rj.y * p1;
-                pq[m] = rj.y * p0 + rj.x * p1;
-                qp[m] = rj.x * q0 - rj.y * q1;
-                qq[m] = rj.y * q0 + rj.x * q1;
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const double u = vp[m][h], w = vq[m][h];
-                    vp[m][h] = ri.x * u - ri.y * w;
-                    vq[m][h] = ri.y * u + ri.x * w;
-                }
+                const int lane = 4 * ((tid & 32) + 4 * ty + m);
+                rc[m] = lane_shift(c, lane);
+                rs[m] = lane_shift(s, lane);
             }
-            // next pairing: q_i <- q_{i+1}, q_j <- q_{j+1}
 #pragma unroll
             for (int m = 0; m < 4; ++m) {
-                pq[m] = lane_shift(pq[m], next);
-                qq[m] = lane_shift(qq[m], next);
+                const double p0 = rc[m] * pp[m] - rs[m] * qp[m], q0 = rs[m] * pp[m] + rc[m] * qp[m];
+                const double p1 = rc[m] * pq[m] - rs[m] * qq[m], q1 = rs[m] * pq[m] + rc[m] * qq[m];
+                pp[m] = c * p0 - s * p1;
+                pq[m] = s * p0 + c * p1;
+                qp[m] = c * q0 - s * q1;
+                qq[m] = s * q0 + c * q1;
             }
+            // next pairing: q_i <- q_{i+1}, q_j <- q_{j+1}; its rotations come
+            // from p_i p_i, p_i q_{i+1} and q_{i+1} q_{i+1}
+            double *sh = next + ((t + 1) & 1) * 1120, *el = sh + 1024;
             double *mine = sh + ty * 128 + tx;
             mine[0] = qp[0];
             mine[32] = qq[0];
+            double dpp = pp[0], dqq = qq[0], dpq = pq[0];
+#pragma unroll
+            for (int m = 1; m < 4; ++m) {
+                dpp = mi == m ? pp[m] : dpp;
+                dqq = mi == m ? qq[m] : dqq;
+                dpq = md == m ? pq[m] : dpq;
+            }
+            if (mi >= 0 && mi < 4) {
+                el[tx] = dpp;
+                el[64 + down] = dqq;
+            }
+            if (md >= 0 && md < 4) el[32 + down] = dpq;
+#pragma unroll
+            for (int m = 0; m < 4; ++m)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const double u = vp[m][h], w = vq[m][h];
+                    vp[m][h] = rc[m] * u - rs[m] * w;
+                    vq[m][h] = rs[m] * u + rc[m] * w;
+                }
             mine[64] = vq[0][0];
             mine[96] = vq[0][1];
+            __syncthreads();
+            app = el[tx];
+            apq = el[32 + tx];
+            aqq = el[64 + tx];
+            const double *other = sh + ((ty + 1) & 7) * 128;
 #pragma unroll
             for (int m = 0; m < 3; ++m) {
                 qp[m] = qp[m + 1];
-                qq[m] = qq[m + 1];
+                qq[m] = lane_shift(qq[m + 1], up_lane);
                 vq[m][0] = vq[m + 1][0];
                 vq[m][1] = vq[m + 1][1];
             }
-            __syncthreads();
-            const double *other = sh + ((ty + 1) & 7) * 128 + tx;
-            qp[3] = other[0];
-            qq[3] = other[32];
-            vq[3][0] = other[64];
-            vq[3][1] = other[96];
+#pragma unroll
+            for (int m = 0; m < 4; ++m) pq[m] = lane_shift(pq[m], up_lane);
+            qp[3] = other[tx];
+            qq[3] = other[32 + up];
+            vq[3][0] = other[64 + tx];
+            vq[3][1] = other[96 + tx];
         }
     }
 #pragma unroll
@@ -378,14 +424,30 @@ __device__ void pair_cross(const double *__restrict__ g, int64_t ldm, double *__
             qt[(4 * ty + m) * kPair + tx + 32 * h] = vp[m][h];
             qt[(32 + 4 * ty + m) * kPair + tx + 32 * h] = vq[m][h];
         }
+    if (M2)
+        store_pair_tile(M2, ldm, d0, d1, [&](int rb, int cb, int m) {
+            return rb ? (cb ? qq[m] : qp[m]) : (cb ? pq[m] : pp[m]);
+        });
 }
 
 // W' rows of pair i, columns [64 c, 64 c + 64) = Q_i^T W: block 2i + h of 32
-// rows goes to slot dst[2i + h].
+// rows goes to slot dst[2i + h].  A pair that rotated nothing only moves.
 __device__ void rotate_w(const double *__restrict__ qt, const double *__restrict__ W, double *__restrict__ W2,
-                         const int *__restrict__ dst, int64_t np, int tile, double *lds) {
+                         const int *__restrict__ dst, const int *__restrict__ act, int64_t np, int tile, double *lds) {
     const int tiles = static_cast<int>(np / 64);
     const int i = tile / tiles, c = tile % tiles;
+    if (!act[i]) {
+        const int r0 = threadIdx.x >> 5, x = (threadIdx.x & 31) * 2;
+        const double *w = W + static_cast<int64_t>(i) * 64 * np + c * 64 + x;
+        double2 v[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v[q] = *reinterpret_cast<const double2 *>(w + (r0 + 8 * q) * np);
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+            *reinterpret_cast<double2 *>(W2 + (static_cast<int64_t>(dst[2 * i + (q >> 2)]) * kBlk + r0 + 8 * (q & 3)) * np +
+                                         c * 64 + x) = v[q];
+        return;
+    }
     double *sA = lds, *sB = lds + 64 * t64::kLdK;
     t64::load(sA, t64::kLdK, qt + static_cast<int64_t>(i) * 4096, 64);
     t64::load(sB, t64::kLdN, W + static_cast<int64_t>(i) * 64 * np + c * 64, np);
@@ -405,63 +467,87 @@ __global__ __launch_bounds__(256) void k_pair_cross(const double *__restrict__ M
                                                     double *__restrict__ off_out, double inner_tol,
                                                     double exempt_tol2, double theta, int npairs,
                                                     const double *__restrict__ Qt_prev, const double *__restrict__ W,
-                                                    double *__restrict__ W2, const int *__restrict__ dst_prev) {
+                                                    double *__restrict__ W2, const int *__restrict__ dst_prev,
+                                                    const int *__restrict__ act_prev, double *__restrict__ M2,
+                                                    const int *__restrict__ dst, int *__restrict__ act) {
     __shared__ __align__(16) double lds[kRotLds];
     const int b = blockIdx.x;
     if (b < npairs) {
+        __builtin_amdgcn_s_setprio(3);  // the round waits for this chain, not for W's tiles beside it
         pair_cross(M + (static_cast<int64_t>(kPair) * np + kPair) * b, np, Qt + static_cast<int64_t>(b) * 4096,
-                   off_out + 3 * b, inner_tol, exempt_tol2, theta, lds);
+                   off_out + 3 * b, inner_tol, exempt_tol2, theta, lds, M2, M2 ? dst[2 * b] : 0, M2 ? dst[2 * b + 1] : 0,
+                   act ? act + b : nullptr);
         return;
     }
-    rotate_w(Qt_prev, W, W2, dst_prev, np, b - npairs, lds);
+    rotate_w(Qt_prev, W, W2, dst_prev, act_prev, np, b - npairs, lds);
 }
 
-// Steps 2, 3 and 5 of M in one pass: tile (i, j), i <= j, of pairs becomes
-// Q_i^T M_ij Q_j and goes to the next round's slots.  Of M only the tiles on
-// and above the diagonal are kept (whole 64 x 64 tiles on it): a 32 x 32
-// block that lands below is stored transposed.  Reads half of M and writes
-// half of it where separate products and the permutation moved it four times
-// (measured, n = 2048: 82 us a round for the three products and the permutation
-// of M and W, against 23 us here and W hidden behind step 1).
+// Steps 2, 3 and 5 of M in one pass: tile (i, j), i < j, of pairs becomes
+// Q_i^T M_ij Q_j and goes to the next round's slots (the tiles (i, i) are step
+// 1's own result).  Of M only the tiles on and above the diagonal are kept
+// (whole 64 x 64 tiles on it): a 32 x 32 block that lands below is stored
+// transposed.  Reads half of M and writes half of it where separate products
+// and the permutation moved it four times, and at n = 2048 the 496 tiles run
+// at once, two on a compute unit, where the 32 diagonal ones made a second,
+// almost empty wave.  A pair that rotated nothing takes no product: from the
+// second sweep half of the pairs of a truncation are outside the wanted part
+// and most of the last sweeps' are done (measured a round: 82 us for the three
+// products and the permutation of M and W, 23 us here with the diagonal, 16.5
+// without, 6 when no pair rotated; W hidden behind step 1).
 __global__ __launch_bounds__(256) void k_rotate_m(const double *__restrict__ M, double *__restrict__ M2,
                                                   const double *__restrict__ Qt, const int *__restrict__ dst,
-                                                  int64_t np) {
+                                                  const int *__restrict__ act, int64_t np) {
     __shared__ __align__(16) double lds[kRotLds];
-    // triangular index: blockIdx.x = j (j + 1) / 2 + i
+    // triangular index: blockIdx.x = j (j - 1) / 2 + i, i < j
     const int b = blockIdx.x;
-    int j = static_cast<int>((sqrtf(8.0f * b + 1.0f) - 1.0f) * 0.5f);
-    while (j * (j + 1) / 2 > b) --j;
-    while ((j + 1) * (j + 2) / 2 <= b) ++j;
-    const int i = b - j * (j + 1) / 2;
+    int j = static_cast<int>((sqrtf(8.0f * b + 1.0f) + 1.0f) * 0.5f);
+    while (j * (j - 1) / 2 > b) --j;
+    while (j * (j + 1) / 2 <= b) ++j;
+    const int i = b - j * (j - 1) / 2;
     double *sA = lds, *sB = lds + 64 * t64::kLdK;
-    t64::load(sB, t64::kLdK, M + static_cast<int64_t>(i) * 64 * np + static_cast<int64_t>(j) * 64, np);
-    t64::load(sA, t64::kLdK, Qt + static_cast<int64_t>(j) * 4096, 64);
-    __syncthreads();
-    t64::Acc acc;
-    acc.zero();
-    t64::mul_nt(acc, sB, sA);  // U = M_ij Q_j
-    __syncthreads();
-    t64::load(sA, t64::kLdK, Qt + static_cast<int64_t>(i) * 4096, 64);
-    t64::each(acc, [&](int r, int c, double x) { sB[r * t64::kLdN + c] = x; });
-    __syncthreads();
-    acc.zero();
-    t64::mul_nn(acc, sA, sB);  // Q_i^T U
-    __syncthreads();
-    t64::each(acc, [&](int r, int c, double x) { lds[r * kLdE + c] = x; });
+    const double *tile = M + static_cast<int64_t>(i) * 64 * np + static_cast<int64_t>(j) * 64;
+    const bool ai = act[i] != 0, aj = act[j] != 0;  // otherwise Q_i, Q_j is the identity
+    if (!ai && !aj) {
+        double v[16];
+#pragma unroll
+        for (int q = 0; q < 16; ++q) v[q] = tile[((threadIdx.x >> 6) + 4 * q) * np + (threadIdx.x & 63)];
+#pragma unroll
+        for (int q = 0; q < 16; ++q) lds[((threadIdx.x >> 6) + 4 * q) * kLdE + (threadIdx.x & 63)] = v[q];
+    } else {
+        t64::Acc acc;
+        acc.zero();
+        if (aj) {
+            t64::load(sB, t64::kLdK, tile, np);
+            t64::load(sA, t64::kLdK, Qt + static_cast<int64_t>(j) * 4096, 64);
+            __syncthreads();
+            t64::mul_nt(acc, sB, sA);  // U = M_ij Q_j
+            __syncthreads();
+        } else {
+            t64::load(sB, t64::kLdN, tile, np);  // U = M_ij
+        }
+        if (ai) {
+            t64::load(sA, t64::kLdK, Qt + static_cast<int64_t>(i) * 4096, 64);
+            if (aj) t64::each(acc, [&](int r, int c, double x) { sB[r * t64::kLdN + c] = x; });
+            __syncthreads();
+            acc.zero();
+            t64::mul_nn(acc, sA, sB);  // Q_i^T U
+            __syncthreads();
+        }
+        t64::each(acc, [&](int r, int c, double x) { lds[r * kLdE + c] = x; });
+    }
     __syncthreads();
     const int x = threadIdx.x & 31, y = threadIdx.x >> 5;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const int rb = q >> 1, cb = q & 1;
         const int dr = dst[2 * i + rb], dc = dst[2 * j + cb];
-        if (i == j && rb > cb && (dr >> 1) != (dc >> 1)) continue;  // the transpose of the block rb < cb
         const double *src = lds + rb * 32 * kLdE + cb * 32;
         if ((dr >> 1) <= (dc >> 1)) {
             double *o = M2 + static_cast<int64_t>(dr) * kBlk * np + static_cast<int64_t>(dc) * kBlk;
 #pragma unroll
             for (int r = 0; r < 32; r += 8) o[(r + y) * np + x] = src[(r + y) * kLdE + x];
         }
-        if ((dr >> 1) > (dc >> 1) || ((dr >> 1) == (dc >> 1) && i != j)) {
+        if ((dr >> 1) >= (dc >> 1)) {
             double *o = M2 + static_cast<int64_t>(dc) * kBlk * np + static_cast<int64_t>(dr) * kBlk;
 #pragma unroll
             for (int r = 0; r < 32; r += 8) o[(r + y) * np + x] = src[x * kLdE + r + y];
@@ -544,6 +630,42 @@ __global__ void k_jac_gather(const double *__restrict__ W, int64_t np, const int
     }
 }
 
+// What a block's rows of M hold above the diagonal: out[3 blk ..] = the largest
+// counted magnitude, the counted and the exempt sum of squares (offdiag).
+__global__ __launch_bounds__(256) void k_offdiag(const double *__restrict__ M, int64_t np, double theta,
+                                                 double *__restrict__ out) {
+    __shared__ double red[256];
+    double m = 0.0, q = 0.0, qx = 0.0;
+    for (int64_t r = blockIdx.x; r < np; r += gridDim.x) {
+        const double *row = M + r * np;
+        const bool low = row[r] < theta;
+        for (int64_t c = r + 1 + threadIdx.x; c < np; c += 256) {
+            const double x = fabs(row[c]);
+            if (low && M[c * np + c] < theta) {
+                qx = fma(x, x, qx);
+            } else {
+                m = fmax(m, x);
+                q = fma(x, x, q);
+            }
+        }
+    }
+    red[threadIdx.x] = m;
+    __syncthreads();
+    for (int w = 128; w > 0; w >>= 1) {
+        if (static_cast<int>(threadIdx.x) < w) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + w]);
+        __syncthreads();
+    }
+    m = red[0];
+    __syncthreads();
+    q = block_sum(q, red);
+    qx = block_sum(qx, red);
+    if (threadIdx.x == 0) {
+        out[3 * blockIdx.x] = m;
+        out[3 * blockIdx.x + 1] = q;
+        out[3 * blockIdx.x + 2] = qx;
+    }
+}
+
 // bad <- 1 if A has a NaN or Inf; part[block] = sum of squares of the block's
 // entries, part[gridDim.x + block] of those off the diagonal
 __global__ __launch_bounds__(256) void k_scan(const double *__restrict__ A, int64_t lda, int64_t n,
@@ -581,6 +703,8 @@ struct rdm_eig_s {
     double *P = nullptr, *Linv = nullptr; // its panel and diagonal block
     double *Qt = nullptr, *off = nullptr, *lam = nullptr, *nrm = nullptr, *part = nullptr, *scale = nullptr;
     int *slot0 = nullptr, *maps = nullptr, *dst = nullptr, *rows = nullptr, *bad = nullptr;
+    unsigned cross_lds = 0;               // bytes of LDS on top of k_pair_cross's own
+    int *act = nullptr;                   // pairs that rotated, of this round and the one before
     int ntiles = 0;  // pairs x 64-column tiles
     TileDesc *tiles = nullptr;
     OutDesc *outs = nullptr;
@@ -655,17 +779,20 @@ struct JacStart {
 
 // Step 1 of round r: every rotation of the pairs' blocks in a sweep's first
 // round, the ones that couple the two blocks in the others; with W set also
-// step 4 of round r - 1 (W -> W2).
+// step 4 of round r - 1 (W -> W2), with M2 set the pairs' own tiles into it.
 int pair_step(rdm_eig h, int r, const double *M, double *Qt, double inner_tol, double exempt_tol2, double theta,
-              const double *Qt_prev, const double *W, double *W2, hipStream_t s) {
+              const double *Qt_prev, const double *W, double *W2, double *M2, hipStream_t s) {
     const int64_t np = h->np;
+    const int *dst = h->dst + static_cast<int64_t>(r) * h->nb;
+    int *act = M2 ? h->act + (r & 1) * h->npairs : nullptr;
     double *off = h->off + static_cast<int64_t>(r) * h->npairs * 3;
     if (r == 0)
-        hipLaunchKernelGGL(k_pair_eig, dim3(h->npairs), dim3(256), 0, s, M, np, Qt, off, inner_tol, exempt_tol2, theta);
+        hipLaunchKernelGGL(k_pair_eig, dim3(h->npairs), dim3(256), 0, s, M, np, Qt, off, inner_tol, exempt_tol2, theta,
+                           M2, dst, act);
     else
-        hipLaunchKernelGGL(k_pair_cross, dim3(h->npairs + (W ? h->ntiles : 0)), dim3(256), 0, s, M, np, Qt, off,
-                           inner_tol, exempt_tol2, theta, h->npairs, Qt_prev, W, W2,
-                           W ? h->dst + static_cast<int64_t>(r - 1) * h->nb : nullptr);
+        hipLaunchKernelGGL(k_pair_cross, dim3(h->npairs + (W ? h->ntiles : 0)), dim3(256), W ? h->cross_lds : 0, s, M, np,
+                           Qt, off, inner_tol, exempt_tol2, theta, h->npairs, Qt_prev, W, W2,
+                           W ? dst - h->nb : nullptr, W ? h->act + ((r + 1) & 1) * h->npairs : nullptr, M2, dst, act);
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? OZ_OK : hip_fail(e, "rdm_eig: pair eigensolver");
 }
@@ -673,21 +800,23 @@ int pair_step(rdm_eig h, int r, const double *M, double *Qt, double inner_tol, d
 // One sweep in native FP64: two launches a round, W one round behind M.
 int sweep_native(rdm_eig h, JacStart *st, double inner_tol, double exempt_tol2, double theta, hipStream_t s) {
     const int64_t np = h->np;
-    const int tri = h->npairs * (h->npairs + 1) / 2;
+    const int tri = h->npairs * (h->npairs - 1) / 2;
     hipError_t e;
     for (int r = 0; r < h->rounds; ++r) {
         double *Qt = h->Qt + (r & 1) * np * kPair, *prev = h->Qt + ((r + 1) & 1) * np * kPair;
-        const int rc = pair_step(h, r, st->X, Qt, inner_tol, exempt_tol2, theta, prev, st->W, st->W2, s);
+        const int rc = pair_step(h, r, st->X, Qt, inner_tol, exempt_tol2, theta, prev, st->W, st->W2, st->Y, s);
         if (rc != OZ_OK) return rc;
         if (r > 0) std::swap(st->W, st->W2);
-        hipLaunchKernelGGL(k_rotate_m, dim3(tri), dim3(256), 0, s, st->X, st->Y, Qt,
-                           h->dst + static_cast<int64_t>(r) * h->nb, np);
+        if (tri > 0)
+            hipLaunchKernelGGL(k_rotate_m, dim3(tri), dim3(256), 0, s, st->X, st->Y, Qt,
+                               h->dst + static_cast<int64_t>(r) * h->nb, h->act + (r & 1) * h->npairs, np);
         if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "rdm_eig: rotation");
         std::swap(st->X, st->Y);
     }
     const int last = h->rounds - 1;
     hipLaunchKernelGGL(k_pair_cross, dim3(h->ntiles), dim3(256), 0, s, nullptr, np, nullptr, nullptr, 0.0, 0.0, 0.0, 0,
-                       h->Qt + (last & 1) * np * kPair, st->W, st->W2, h->dst + static_cast<int64_t>(last) * h->nb);
+                       h->Qt + (last & 1) * np * kPair, st->W, st->W2, h->dst + static_cast<int64_t>(last) * h->nb,
+                       h->act + (last & 1) * h->npairs, nullptr, nullptr, nullptr);
     if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "rdm_eig: basis rotation");
     std::swap(st->W, st->W2);
     return OZ_OK;
@@ -700,7 +829,7 @@ int enqueue_round(rdm_eig h, int r, const double *src_c, double *dst, double *W,
     double *src = const_cast<double *>(src_c);
     hipError_t e;
     int rc;
-    if ((rc = pair_step(h, r, src, h->Qt, inner_tol, exempt_tol2, theta, nullptr, nullptr, nullptr, s)) != OZ_OK)
+    if ((rc = pair_step(h, r, src, h->Qt, inner_tol, exempt_tol2, theta, nullptr, nullptr, nullptr, nullptr, s)) != OZ_OK)
         return rc;
     if ((e = launch_row_exponents(h->Qt, kPair, np, kPair, h->eQ, h->ctx->d_flags, s)) != hipSuccess ||
         (e = launch_slice(h->S, false, h->Qt, kPair, np, kPair, h->eQ, h->pQ, np, s)) != hipSuccess)
@@ -822,8 +951,17 @@ int rdm_eig_create(ozaki_ctx ctx, rdm_eig *out, int64_t n, int slices, int ndiag
     OZ_RA(scale, sizeof(double) * np)
     OZ_RA(rows, sizeof(int) * np)
     OZ_RA(bad, sizeof(int) * 4)
+    OZ_RA(act, sizeof(int) * 2 * h->npairs)
     OZ_RA(part, sizeof(double) * 2 * kScanBlocks)
 #undef OZ_RA
+    // A workgroup of step 1 slows down when a tile of W shares its compute
+    // unit (45 us against 38 at n = 2048).  While W's tiles go round the other
+    // compute units one at a time within step 1's time (8 us each, so up to
+    // five rounds), every workgroup of the launch takes more than
+    // half of a compute unit's 160 KiB; with more tiles two at a time are
+    // faster.
+    if (static_cast<int64_t>(h->npairs) * (np / 64) <= 5 * static_cast<int64_t>(ctx->num_cu - h->npairs))
+        h->cross_lds = 84 * 1024 - sizeof(double) * kRotLds;
     // circle schedule over the nb blocks
     std::vector<int> a(h->nb);
     std::iota(a.begin(), a.end(), 0);
@@ -1018,11 +1156,33 @@ int rdm_eig_solve(rdm_eig h, const double *A, int64_t lda, int64_t nev, double *
         // the wanted rows are decoupled to tol, and by Weyl's bound the
         // exempt couplings cannot lift an unwanted eigenvalue above them
         bool separated = true;
+        double lo = 0.0, hi = 0.0;
         if (nev < n) {
-            const double lo = lam[rows[nev - 1 < 0 ? 0 : nev - 1]], hi = lam[rows[nev]];
+            lo = lam[rows[nev - 1 < 0 ? 0 : nev - 1]];
+            hi = lam[rows[nev]];
             separated = nev == 0 || (hi < theta && theta <= lo && hi + std::sqrt(exempt) < lo);
             theta = nev == 0 ? INFINITY : 0.5 * (lo + hi);
             exempt_tol2 = nev == 0 ? INFINITY : 0.25 * (lo - hi) * (lo - hi) / (static_cast<double>(h->npairs) * h->rounds);
+        }
+        if (h->S == 0 && !(last <= tol && separated)) {
+            // the sweep's figures are those met on the way; what it left
+            // behind is one read of M, where a sweep that only finds the same
+            // takes 63 rounds at n = 2048
+            const int blocks = static_cast<int>(std::min<int64_t>({np, 1024, static_cast<int64_t>(h->rounds) * h->npairs}));
+            hipLaunchKernelGGL(k_offdiag, dim3(blocks), dim3(256), 0, s, st.X, np, theta, h->off);
+            if ((e = hipMemcpyAsync(h->host_off.data(), h->off, sizeof(double) * 3 * blocks, hipMemcpyDeviceToHost, s)) !=
+                    hipSuccess ||
+                (e = hipStreamSynchronize(s)) != hipSuccess)
+                return hip_fail(e, "rdm_eig_solve: off-diagonal");
+            double now = 0.0, left = 0.0;
+            for (int i = 0; i < 3 * blocks; i += 3) {
+                now = std::max(now, h->host_off[i]);
+                left += h->host_off[i + 2];
+            }
+            if (now / fro <= tol && (nev == 0 || nev == n || (hi < theta && theta <= lo && hi + std::sqrt(2.0 * left) < lo))) {
+                last = now / fro;
+                separated = true;
+            }
         }
         if (last <= tol && separated) {
             status = OZ_CONVERGED;

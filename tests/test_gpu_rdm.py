@@ -145,6 +145,28 @@ def test_qr_iteration_start(oz, n, kind):
     check_eigenpairs(A, w, Z, 0)
 
 
+@pytest.mark.parametrize("n", [65, 130, 200, 330])
+@pytest.mark.parametrize("nev", ["all", "few", "none"])
+def test_pairs_that_rotate_nothing(oz, n, nev):
+    """Nearly diagonal matrices whose couplings sit in some 32-row blocks only:
+    most pairs rotate nothing in a round (their tiles and basis rows are only
+    moved), next to pairs that do, on both sides of either product; every
+    coupling small enough that the sweeps start from the matrix itself."""
+    rng = np.random.default_rng(n)
+    lam = np.sort(rng.uniform(0.5, 2.0, n))[::-1].copy()
+    A = np.diag(lam)
+    nb = -(-n // 32)
+    for b, c in ((0, 0), (0, nb - 1), (nb // 2, nb - 1), (nb - 1, nb - 1)):
+        r, q = slice(32 * b, min(32 * b + 32, n)), slice(32 * c, min(32 * c + 32, n))
+        E = 1e-5 * rng.standard_normal(A[r, q].shape)
+        A[r, q] += E
+        A[q, r] += E.T
+    A = 0.5 * (A + A.T)
+    w, Z, info = solve(oz, A, nev={"all": n, "few": n // 4, "none": 1}[nev])
+    assert info.status == 1
+    check_eigenpairs(A, w, Z, 0)
+
+
 def test_edge_matrices(oz):
     # zero matrix: all eigenvalues 0, orthonormal eigenvectors
     w, Z, info = solve(oz, np.zeros((50, 50)))
