@@ -10,26 +10,40 @@
 // orthogonality that forming G lost (about cond(X)^2 u after the first, a few
 // u after the second).
 //
-// Per 64 columns: k_cq_diag (one workgroup, Cholesky and inverse of the 64 x
-// 64 diagonal block, a chain of 64 dependent steps), k_cq_panel and
-// k_cq_update (64 x 64 tiles on the FP64 matrix cores).  Bound: the chain of
-// three dependent launches per 64 columns, not arithmetic (4/3 n^3 flop a
-// pass).
+// Per 64 columns: the Cholesky factor and inverse of the 64 x 64 diagonal block
+// (one workgroup, a chain of 64 dependent steps), k_cq_panel and k_cq_update
+// (64 x 64 tiles on the FP64 matrix cores), the next diagonal block beside the
+// update.  Bound: the chain of the diagonal block and two dependent launches
+// per 64 columns, not arithmetic (4/3 n^3 flop a pass).
 #include "internal.h"
 #include "tile64.h"
 
 namespace oz {
 namespace {
 
-// Cholesky of the 64 x 64 block at G (row-major, ld), the inverse of its
+// 1 / w to one rounding error: the hardware's estimate (about 2^-23) with one
+// third-order correction.
+__device__ __forceinline__ double reciprocal(double w) {
+    const double y = __builtin_amdgcn_rcp(w);
+    const double e = fma(-w, y, 1.0);
+    return fma(y, fma(e, e, e), y);
+}
+
+constexpr int kDiagLds = 5 * 64;  // doubles
+
+// Cholesky of a 64 x 64 block, element (r, c) = at(r, c), the inverse of its
 // factor into Linv (64 x 64 row-major).  Symmetric elimination of [G | I]:
 // thread (ti, tj) holds rows ti + 16 a and columns tj + 16 b of both halves
 // in registers; a step broadcasts column k of G and row k of the other half
 // through LDS (double-buffered, one barrier a step).  A pivot outside
-// (lo, hi) sets *bad and is replaced by 1, so every step stays finite.
-__global__ __launch_bounds__(256) void k_cq_diag(const double *__restrict__ G, int64_t ld, double *__restrict__ Linv,
-                                                 int *__restrict__ bad, double lo, double hi) {
-    __shared__ double col[2][64], vrow[2][64], dinv[64];
+// (lo, hi) sets *bad and is replaced by 1, so every step stays finite.  Bound:
+// the chain of 64 steps (broadcast, reciprocal, update), so the pivots' square
+// roots wait for the end (32 us with them and an exact division inside,
+// 30 without).
+template <typename At>
+__device__ __forceinline__ void cq_diag(At at, double *__restrict__ Linv, int *__restrict__ bad, double lo, double hi,
+                                        double *lds) {
+    double (*col)[64] = reinterpret_cast<double (*)[64]>(lds), (*vrow)[64] = col + 2, *piv = lds + 256;
     const int ti = threadIdx.x >> 4, tj = threadIdx.x & 15;
     double g[4][4], v[4][4];
 #pragma unroll
@@ -37,11 +51,12 @@ __global__ __launch_bounds__(256) void k_cq_diag(const double *__restrict__ G, i
 #pragma unroll
         for (int b = 0; b < 4; ++b) {
             const int r = ti + 16 * a, c = tj + 16 * b;
-            g[a][b] = G[r * ld + c];
+            g[a][b] = at(r, c);
             v[a][b] = r == c ? 1.0 : 0.0;
         }
 #pragma unroll
     for (int kq = 0; kq < 4; ++kq) {
+#pragma unroll 1
         for (int kr = 0; kr < 16; ++kr) {
             const int k = 16 * kq + kr, p = k & 1;
             if (tj == kr) {
@@ -58,8 +73,8 @@ __global__ __launch_bounds__(256) void k_cq_diag(const double *__restrict__ G, i
                 if (threadIdx.x == 0) atomicOr(bad, 1);
                 w = 1.0;
             }
-            if (threadIdx.x == 0) dinv[k] = 1.0 / sqrt(w);
-            const double inv = 1.0 / w;
+            if (threadIdx.x == 0) piv[k] = w;
+            const double inv = reciprocal(w);
             double f[4], gc[4], vc[4];
 #pragma unroll
             for (int a = 0; a < 4; ++a) f[a] = ti + 16 * a > k ? col[p][ti + 16 * a] * inv : 0.0;
@@ -79,9 +94,18 @@ __global__ __launch_bounds__(256) void k_cq_diag(const double *__restrict__ G, i
     }
     __syncthreads();
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
+    for (int a = 0; a < 4; ++a) {
+        const double dinv = 1.0 / sqrt(piv[ti + 16 * a]);
 #pragma unroll
-        for (int b = 0; b < 4; ++b) Linv[(ti + 16 * a) * 64 + tj + 16 * b] = v[a][b] * dinv[ti + 16 * a];
+        for (int b = 0; b < 4; ++b) Linv[(ti + 16 * a) * 64 + tj + 16 * b] = v[a][b] * dinv;
+    }
+}
+
+// The first diagonal block (the others follow their update).
+__global__ __launch_bounds__(256) void k_cq_diag(const double *__restrict__ G, int64_t ld, double *__restrict__ Linv,
+                                                 int *__restrict__ bad, double lo, double hi) {
+    __shared__ double lds[kDiagLds];
+    cq_diag([&](int r, int c) { return G[r * ld + c]; }, Linv, bad, lo, hi, lds);
 }
 
 // Column block k of the factor: rows of G below the diagonal block into P
@@ -107,15 +131,20 @@ __global__ __launch_bounds__(256) void k_cq_panel(const double *__restrict__ G, 
 
 // Trailing update: tile (i, j) of [G; X] right of column block k loses
 // P_i P_j^T (rows of Q in the place of P_i for X's rows).  Tiles of G above
-// the diagonal are never read and are left alone.
+// the diagonal are never read and are left alone.  The first workgroup's tile
+// is the next diagonal block: it goes on to factorise it beside the others'
+// tiles, a chain that would otherwise leave the chip idle between this launch
+// and the next panel's.
 __global__ __launch_bounds__(256) void k_cq_update(double *__restrict__ G, double *__restrict__ X,
                                                    const double *__restrict__ Q, const double *__restrict__ P,
-                                                   int64_t np, int k) {
+                                                   int64_t np, int k, double *__restrict__ Linv, int *__restrict__ bad,
+                                                   double lo, double hi) {
     __shared__ double sA[64 * t64::kLdK], sB[64 * t64::kLdK];
     const int below = static_cast<int>(np / 64) - k - 1;
     const int j = blockIdx.x, i = blockIdx.y;
     const bool top = i < below;
     if (top && i < j) return;
+    const bool next = i == 0 && j == 0;  // (top: this launch has below > 0)
     const int64_t row = static_cast<int64_t>(top ? k + 1 + i : i - below) * 64;
     if (top)
         t64::load(sA, t64::kLdK, P + static_cast<int64_t>(i) * 4096, 64);
@@ -127,7 +156,14 @@ __global__ __launch_bounds__(256) void k_cq_update(double *__restrict__ G, doubl
     t64::Acc acc;
     acc.zero();
     t64::mul_nt(acc, sA, sB);
-    t64::each(acc, [&](int r, int cc, double x) { c[r * np + cc] -= x; });
+    if (!next) {
+        t64::each(acc, [&](int r, int cc, double x) { c[r * np + cc] -= x; });
+        return;
+    }
+    __syncthreads();
+    t64::each(acc, [&](int r, int cc, double x) { sA[r * t64::kLdK + cc] = c[r * np + cc] - x; });  // nothing else reads it
+    __syncthreads();
+    cq_diag([&](int r, int cc) { return sA[r * t64::kLdK + cc]; }, Linv, bad, lo, hi, sB);
 }
 
 // B = A + mu I in the leading n x n part, `unit` on the padded diagonal, 0 elsewhere
@@ -163,13 +199,13 @@ hipError_t launch_cholqr_pass(double *G, double *X, double *Q, double *P, double
     hipError_t e = launch_dgemm_single(true, false, a, num_cu, s);  // G = X^T X
     if (e != hipSuccess) return e;
     const int nb = static_cast<int>(np / 64);
+    hipLaunchKernelGGL(k_cq_diag, dim3(1), dim3(256), 0, s, G, np, Linv, bad, lo, hi);
     for (int k = 0; k < nb; ++k) {
         const int below = nb - k - 1;
-        const int64_t kk = static_cast<int64_t>(k) * 64 * (np + 1);
-        hipLaunchKernelGGL(k_cq_diag, dim3(1), dim3(256), 0, s, G + kk, np, Linv, bad, lo, hi);
         hipLaunchKernelGGL(k_cq_panel, dim3(below + nb), dim3(256), 0, s, G, X, Q, P, Linv, np, k);
         if (below > 0)
-            hipLaunchKernelGGL(k_cq_update, dim3(below, below + nb), dim3(256), 0, s, G, X, Q, P, np, k);
+            hipLaunchKernelGGL(k_cq_update, dim3(below, below + nb), dim3(256), 0, s, G, X, Q, P, np, k, Linv, bad,
+                               lo, hi);
     }
     return hipGetLastError();
 }
