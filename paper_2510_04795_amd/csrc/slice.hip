@@ -2,8 +2,12 @@
 // one power-of-two exponent per row of A / column of B, then S balanced
 // int8 slices per element, written in the packed layout of internal.h.
 //
-// All three kernels are HBM-bound: the exponent pass reads X once (8 B per
+// Large operands are HBM-bound: the exponent pass reads X once (8 B per
 // element); the slice pass reads it again and writes S bytes per element.
+// Small ones are bound by their launches, so a call's two operands share a
+// launch per pass (k_exponents2, k_slice2; one launch for both passes up to K =
+// 256, k_slice_groups2), and maxima travel as exponent codes that the slice
+// pass turns into exponents.
 #include <algorithm>
 
 #include "internal.h"
