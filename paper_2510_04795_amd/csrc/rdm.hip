@@ -33,8 +33,9 @@
 // iteration in FP64.  The
 // largest off-diagonal |M_rc| met in step 1 over a sweep measures
 // convergence against tol |A|_F (absolute accuracy, as a tridiagonal-based
-// solver gives).  The eigenvalues are then M_cc / |w_c|^2 and the
-// eigenvectors the rows of W.  Padding rows and columns stay exactly zero (a
+// solver gives).  The eigenvectors are then the rows of W and the eigenvalues
+// M_cc / |w_c|^2 when emulated, the quotients w_c A w_c^T / |w_c|^2 in native
+// FP64 (k_rayleigh).  Padding rows and columns stay exactly zero (a
 // zero entry gives an exact identity rotation), so the padding basis vectors
 // are recognised by their zero restriction to the first n coordinates.
 #include <algorithm>
@@ -612,6 +613,33 @@ __global__ __launch_bounds__(256) void k_jac_diag(const double *__restrict__ M, 
     }
 }
 
+// lam[c] = t_c . w_c with T = W A, nrm[c] = |w_c|^2 (first n coordinates): the
+// native path's final eigenvalues.  Its M is not W A W^T to rounding: a tile on
+// the diagonal goes through 32 rotations a round one after another, and a
+// rotation by a small angle (s^2 below u / 2, as between rows of nearly equal
+// eigenvalues) lengthens its row of W by s^2 while M's entry rounds that away,
+// always in the same direction.  On four clusters of 256 at n = 1024 the
+// diagonal had drifted by up to 7300 u, the quotients are within 62 u.  One
+// product of n_p x n x n: 0.29 ms of a truncation of 33 at n = 2048.
+__global__ __launch_bounds__(256) void k_rayleigh(const double *__restrict__ T, const double *__restrict__ W,
+                                                  int64_t n, int64_t np, double *__restrict__ lam,
+                                                  double *__restrict__ nrm) {
+    __shared__ double red[256];
+    const int64_t row = blockIdx.x;
+    const double *w = W + row * np, *t = T + row * np;
+    double q = 0.0, s = 0.0;
+    for (int64_t i = threadIdx.x; i < n; i += 256) {
+        q = fma(t[i], w[i], q);
+        s = fma(w[i], w[i], s);
+    }
+    q = block_sum(q, red);
+    s = block_sum(s, red);
+    if (threadIdx.x == 0) {
+        lam[row] = q;
+        nrm[row] = s;
+    }
+}
+
 // Z[i][j] = scale[j] W[rows[j]][i], i < n, j < nev (through a 32 x 32 LDS tile)
 __global__ void k_jac_gather(const double *__restrict__ W, int64_t np, const int *__restrict__ rows,
                              const double *__restrict__ scale, int64_t n, int64_t nev, double *__restrict__ Z,
@@ -1102,11 +1130,23 @@ int rdm_eig_solve(rdm_eig h, const double *A, int64_t lda, int64_t nev, double *
     double best = INFINITY, last = INFINITY;
     h->host_off.resize(static_cast<size_t>(h->rounds) * h->npairs * 3);
     std::vector<double> lam(np), nrm(np);
-    // Diagonal of M over the squared basis norms (Rayleigh quotients) and
-    // the basis rows inside the first n coordinates (the others are padding).
-    auto diagonal = [&](std::vector<int> *rows) -> int {
-        hipLaunchKernelGGL(k_jac_diag, dim3(static_cast<unsigned>(np)), dim3(256), 0, s, st.X, st.W, n, np, h->lam,
-                           h->nrm);
+    // Diagonal of M over the squared basis norms (with `quotients`, w A w^T
+    // over them) and the basis rows inside the first n coordinates (the others
+    // are padding).
+    auto diagonal = [&](std::vector<int> *rows, bool quotients) -> int {
+        if (quotients) {
+            Dgemm64Args a{};
+            a.mode = kModeGemm;
+            a.term = Term64{st.W, A, np, lda, static_cast<int32_t>(n), 0, 1.0};
+            a.out = OutDesc{st.Y, np, static_cast<int32_t>(np), static_cast<int32_t>(n)};
+            if ((e = launch_dgemm_single(false, false, a, h->ctx->num_cu, s)) != hipSuccess)
+                return hip_fail(e, "rdm_eig_solve: W A");
+            hipLaunchKernelGGL(k_rayleigh, dim3(static_cast<unsigned>(np)), dim3(256), 0, s, st.Y, st.W, n, np, h->lam,
+                               h->nrm);
+        } else {
+            hipLaunchKernelGGL(k_jac_diag, dim3(static_cast<unsigned>(np)), dim3(256), 0, s, st.X, st.W, n, np, h->lam,
+                               h->nrm);
+        }
         if ((e = hipMemcpyAsync(lam.data(), h->lam, sizeof(double) * np, hipMemcpyDeviceToHost, s)) != hipSuccess ||
             (e = hipMemcpyAsync(nrm.data(), h->nrm, sizeof(double) * np, hipMemcpyDeviceToHost, s)) != hipSuccess ||
             (e = hipStreamSynchronize(s)) != hipSuccess)
@@ -1144,7 +1184,7 @@ int rdm_eig_solve(rdm_eig h, const double *A, int64_t lda, int64_t nev, double *
         if ((e = hipMemcpyAsync(h->host_off.data(), h->off, sizeof(double) * h->host_off.size(),
                                 hipMemcpyDeviceToHost, s)) != hipSuccess)
             return hip_fail(e, "rdm_eig_solve: sweep");
-        if ((rc = diagonal(&rows)) != OZ_OK) return rc;
+        if ((rc = diagonal(&rows, false)) != OZ_OK) return rc;
         double sum = 0.0, exempt = 0.0;
         last = 0.0;
         for (size_t i = 0; i < h->host_off.size(); i += 3) {
@@ -1201,7 +1241,7 @@ int rdm_eig_solve(rdm_eig h, const double *A, int64_t lda, int64_t nev, double *
         last = 0.0;
     }
     {
-        const int rc = diagonal(&rows);
+        const int rc = diagonal(&rows, h->S == 0);
         if (rc != OZ_OK) return rc;
     }
     double trace = 0.0;

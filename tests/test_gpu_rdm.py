@@ -350,3 +350,24 @@ def test_renormalize_batches(oz, S, n, D, count):
                     outs=[torch.empty(D, n, dtype=torch.float64, device="cuda")[:, :D], big[0][:D, :D]])
     ref = ctx.renormalize(dU, [dops[1]], slices=S)[0]
     assert torch.equal(big[0][:D, :D], ref)
+
+
+@pytest.mark.parametrize("n", [320, 513])
+@pytest.mark.parametrize("nev", ["all", "quarter"])
+def test_clustered_eigenvalues_do_not_drift(oz, n, nev):
+    """Native FP64 on clusters of nearly equal eigenvalues, whose rows keep
+    rotating by small angles for many sweeps: every eigenvalue within the
+    rounding of a quotient w A w^T (two sums of length n) and of LAPACK's, 8
+    sqrt(n) u |A|_2 each, and the residuals with it."""
+    rng = np.random.default_rng(n)
+    lam = np.repeat([4.0, 3.0, 2.0, 1.0], -(-n // 4))[:n] + 1e-9 * rng.standard_normal(n)
+    Q, _ = np.linalg.qr(rng.standard_normal((n, n)))
+    A = (Q * lam) @ Q.T
+    A = 0.5 * (A + A.T)
+    k = n if nev == "all" else n // 4
+    w, Z, info = solve(oz, A, nev=k)
+    assert info.status == 1
+    bound = 16 * np.sqrt(n) * U64 * 4.0
+    assert np.max(np.abs(w - np.linalg.eigvalsh(A)[::-1][:k])) <= bound
+    assert np.all(np.diff(w) <= 0)
+    assert abs(info.trace - np.trace(A)) <= n * bound
