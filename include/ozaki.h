@@ -484,22 +484,25 @@ int lanczos_destroy(lanczos lz);
  * the unit roundoff of the arithmetic (2^-53, or 2^(1-8S) when emulated).
  * The iteration ends when a whole sweep meets no off-diagonal entry of M
  * larger than tol |A|_F (absolute accuracy, as a tridiagonal-based solver
- * gives), when three sweeps in a row fail to halve the best off-diagonal
- * mass (the arithmetic's floor), or after max_sweeps.  With nev < n the
- * couplings between two rows outside the wanted part (diagonal below the
- * middle of the gap at the nev-th value of the previous sweep) are exempt
- * from tol, provided their Frobenius mass cannot lift an unwanted eigenvalue
- * above the nev-th one (Weyl's bound): the tail of a graded spectrum is not
- * resolved beyond what the kept eigenpairs need.  info (may be NULL):
- * sweeps run, status (OZ_CONVERGED, OZ_STAGNATED or OZ_MAX_ITER), the last
- * sweep's largest off-diagonal entry over |A|_F and the sum of all n
- * eigenvalues.  Results are written in all three cases.  The upper triangle
- * of the diagonal blocks is used where symmetry is assumed; NaN or Inf in
+ * gives; native FP64 looks at what a sweep leaves and ends at 0.1 tol |A|_F,
+ * or at the second sweep that meets nothing above tol |A|_F), when three
+ * sweeps in a row fail to halve the best off-diagonal mass (the arithmetic's
+ * floor), or after max_sweeps.  With nev < n the couplings between two rows
+ * outside the wanted part (diagonal below the middle of the gap at the
+ * nev-th value of the previous sweep) are exempt from tol, provided their
+ * Frobenius mass cannot lift an unwanted eigenvalue above the nev-th one
+ * (Weyl's bound): the tail of a graded spectrum is not resolved beyond what
+ * the kept eigenpairs need.  info (may be NULL): sweeps run, status
+ * (OZ_CONVERGED, OZ_STAGNATED or OZ_MAX_ITER), the largest off-diagonal
+ * entry over |A|_F that the last sweep met (or left, where that ended the
+ * iteration) and the sum of all n eigenvalues.  Results are written in all
+ * three cases.  The upper triangle of the diagonal blocks is used where
+ * symmetry is assumed; NaN or Inf in
  * A: OZ_ERR_ARG.  Synchronises the stream.  One solve at a time per plan. */
 typedef struct rdm_eig_s *rdm_eig;
 typedef struct {
     int32_t sweeps, status;
-    double off;    /* largest off-diagonal entry of the last sweep over |A|_F */
+    double off;    /* largest off-diagonal entry the last sweep met or left over |A|_F */
     double trace;  /* sum of all n eigenvalues (discarded weight = trace - kept sum) */
 } rdm_eig_info;
 int rdm_eig_create(ozaki_ctx ctx, rdm_eig *out, int64_t n, int slices, int ndiag);

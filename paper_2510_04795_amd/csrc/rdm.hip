@@ -825,12 +825,13 @@ int pair_step(rdm_eig h, int r, const double *M, double *Qt, double inner_tol, d
     return e == hipSuccess ? OZ_OK : hip_fail(e, "rdm_eig: pair eigensolver");
 }
 
-// One sweep in native FP64: two launches a round, W one round behind M.
-int sweep_native(rdm_eig h, JacStart *st, double inner_tol, double exempt_tol2, double theta, hipStream_t s) {
+// The first `rounds` rounds of a sweep in native FP64: two launches a round, W
+// one round behind M.
+int sweep_native(rdm_eig h, JacStart *st, int rounds, double inner_tol, double exempt_tol2, double theta, hipStream_t s) {
     const int64_t np = h->np;
     const int tri = h->npairs * (h->npairs - 1) / 2;
     hipError_t e;
-    for (int r = 0; r < h->rounds; ++r) {
+    for (int r = 0; r < rounds; ++r) {
         double *Qt = h->Qt + (r & 1) * np * kPair, *prev = h->Qt + ((r + 1) & 1) * np * kPair;
         const int rc = pair_step(h, r, st->X, Qt, inner_tol, exempt_tol2, theta, prev, st->W, st->W2, st->Y, s);
         if (rc != OZ_OK) return rc;
@@ -841,7 +842,7 @@ int sweep_native(rdm_eig h, JacStart *st, double inner_tol, double exempt_tol2, 
         if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "rdm_eig: rotation");
         std::swap(st->X, st->Y);
     }
-    const int last = h->rounds - 1;
+    const int last = rounds - 1;
     hipLaunchKernelGGL(k_pair_cross, dim3(h->ntiles), dim3(256), 0, s, nullptr, np, nullptr, nullptr, 0.0, 0.0, 0.0, 0,
                        h->Qt + (last & 1) * np * kPair, st->W, st->W2, h->dst + static_cast<int64_t>(last) * h->nb,
                        h->act + (last & 1) * h->npairs, nullptr, nullptr, nullptr);
@@ -1169,10 +1170,11 @@ int rdm_eig_solve(rdm_eig h, const double *A, int64_t lda, int64_t nev, double *
     // Exempt couplings are rotated away only while a round's block holds more
     // than its share (exempt_tol2) of the mass that Weyl's bound allows.
     double theta = -INFINITY, exempt_tol2 = 0.0;
+    bool met = false;  // native: an earlier sweep met nothing above tol
     for (int sw = 0; sw < max_sweeps && fro > 0.0; ++sw) {
         int rc = OZ_OK;
         if (h->S == 0) {
-            rc = sweep_native(h, &st, 0.1 * abs_tol, exempt_tol2, theta, s);
+            rc = sweep_native(h, &st, h->rounds, 0.1 * abs_tol, exempt_tol2, theta, s);
         } else {
             for (int r = 0; r < h->rounds && rc == OZ_OK; ++r) {
                 rc = enqueue_round(h, r, st.X, st.Y, st.W, st.W2, 0.1 * abs_tol, exempt_tol2, theta, s);
@@ -1204,27 +1206,48 @@ int rdm_eig_solve(rdm_eig h, const double *A, int64_t lda, int64_t nev, double *
             theta = nev == 0 ? INFINITY : 0.5 * (lo + hi);
             exempt_tol2 = nev == 0 ? INFINITY : 0.25 * (lo - hi) * (lo - hi) / (static_cast<double>(h->npairs) * h->rounds);
         }
-        if (h->S == 0 && !(last <= tol && separated)) {
+        bool done = last <= tol && separated;
+        if (h->S == 0) {
             // the sweep's figures are those met on the way; what it left
             // behind is one read of M, where a sweep that only finds the same
             // takes 63 rounds at n = 2048
             const int blocks = static_cast<int>(std::min<int64_t>({np, 1024, static_cast<int64_t>(h->rounds) * h->npairs}));
-            hipLaunchKernelGGL(k_offdiag, dim3(blocks), dim3(256), 0, s, st.X, np, theta, h->off);
-            if ((e = hipMemcpyAsync(h->host_off.data(), h->off, sizeof(double) * 3 * blocks, hipMemcpyDeviceToHost, s)) !=
-                    hipSuccess ||
-                (e = hipStreamSynchronize(s)) != hipSuccess)
-                return hip_fail(e, "rdm_eig_solve: off-diagonal");
-            double now = 0.0, left = 0.0;
-            for (int i = 0; i < 3 * blocks; i += 3) {
-                now = std::max(now, h->host_off[i]);
-                left += h->host_off[i + 2];
+            double now = 0.0;
+            bool clean = false;
+            auto left_behind = [&]() -> int {
+                hipLaunchKernelGGL(k_offdiag, dim3(blocks), dim3(256), 0, s, st.X, np, theta, h->off);
+                if ((e = hipMemcpyAsync(h->host_off.data(), h->off, sizeof(double) * 3 * blocks, hipMemcpyDeviceToHost,
+                                        s)) != hipSuccess ||
+                    (e = hipStreamSynchronize(s)) != hipSuccess)
+                    return hip_fail(e, "rdm_eig_solve: off-diagonal");
+                double left = 0.0;
+                now = 0.0;
+                for (int i = 0; i < 3 * blocks; i += 3) {
+                    now = std::max(now, h->host_off[i]);
+                    left += h->host_off[i + 2];
+                }
+                now /= fro;
+                clean = now <= 0.1 * tol &&
+                        (nev == 0 || nev == n || (hi < theta && theta <= lo && hi + std::sqrt(2.0 * left) < lo));
+                return OZ_OK;
+            };
+            if ((rc = left_behind()) != OZ_OK) return rc;
+            if (!clean && (done || now <= tol)) {
+                // Nothing above tol met or left, yet more than the tenth of it
+                // that a sweep leaves unrotated: where that is what the later
+                // rounds moved into the 32 x 32 diagonal blocks, which only a
+                // first round rotates, one such round takes it away; else one
+                // more sweep does, or the arithmetic's floor is reached.
+                if ((rc = sweep_native(h, &st, 1, 0.1 * abs_tol, exempt_tol2, theta, s)) != OZ_OK ||
+                    (rc = left_behind()) != OZ_OK)
+                    return rc;
             }
-            if (now / fro <= tol && (nev == 0 || nev == n || (hi < theta && theta <= lo && hi + std::sqrt(2.0 * left) < lo))) {
-                last = now / fro;
-                separated = true;
-            }
+            if (clean && !done) last = now;
+            const bool again = done && !clean && !met && sweeps < max_sweeps;
+            met = met || done;
+            done = clean || (done && !again);
         }
-        if (last <= tol && separated) {
+        if (done) {
             status = OZ_CONVERGED;
             break;
         }

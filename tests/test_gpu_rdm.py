@@ -371,3 +371,22 @@ def test_clustered_eigenvalues_do_not_drift(oz, n, nev):
     assert np.max(np.abs(w - np.linalg.eigvalsh(A)[::-1][:k])) <= bound
     assert np.all(np.diff(w) <= 0)
     assert abs(info.trace - np.trace(A)) <= n * bound
+
+
+@pytest.mark.parametrize("n", [65, 200, 513])
+@pytest.mark.parametrize("kind", ["flat", "clusters", "graded"])
+@pytest.mark.parametrize("tol", [1e-4, 1e-7])
+def test_tolerance_of_the_caller(oz, n, kind, tol):
+    """What a solve with a tolerance of its own leaves between the eigenvectors:
+    at most the 0.1 tol |A|_F below which a sweep rotates nothing, and twice
+    that where the second sweep that meets nothing above tol ends it."""
+    rng = np.random.default_rng(n)
+    lam = {"flat": np.linspace(2.0, 1.0, n), "graded": np.exp(-np.arange(n) / (n / 64.0)),
+           "clusters": np.repeat([4.0, 3.0, 2.0, 1.0], -(-n // 4))[:n] + 1e-9 * rng.standard_normal(n)}[kind]
+    Q, _ = np.linalg.qr(rng.standard_normal((n, n)))
+    A = (Q * lam) @ Q.T
+    A = 0.5 * (A + A.T)
+    w, Z, info = solve(oz, A, tol=tol)
+    assert info.status == 1 and info.off <= tol
+    M = Z.T @ A @ Z
+    assert np.max(np.abs(M - np.diag(np.diag(M)))) <= 0.2 * tol * np.linalg.norm(A)
