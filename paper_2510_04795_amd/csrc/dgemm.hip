@@ -24,7 +24,7 @@
 // + s in the s-th product of group g, so an operand stored along K is read
 // two elements (16 bytes) at a time.
 //
-// LDS layout, in 16-byte chunks (where a chunk lands is the loading lane's
+// LDS layout (OperandMap), in 16-byte chunks (where a chunk lands is the loading lane's
 // place, what it holds is the lane's choice of address):
 //   stored along K (op(A) = A, op(B) = B^T): eight chunks per row, the pair of
 //     k at place pair ^ ((row / 2) % 8), so the 16 rows a read takes fall in
@@ -39,6 +39,7 @@
 // through registers element by element.
 #include <type_traits>
 
+#include "dgemm_operand.h"
 #include "internal.h"
 
 namespace oz {
@@ -46,39 +47,26 @@ namespace {
 
 typedef double v4d __attribute__((ext_vector_type(4)));
 
-constexpr int kBK = 16;
-
+typedef __attribute__((address_space(1))) const void global_void;
 typedef __attribute__((address_space(3))) void lds_void;
 constexpr int kBufferDword3 = 0x00020000;  // raw buffer, 32-bit data format
 
-// Loads of one operand of a tile, E rows of A or columns of B.
-template <int E>
-struct Geo {
-    static constexpr int CH = E * kBK / 2 / 256;    // 16-byte chunks per thread and step
-};
-
 // One operand of a tile: `rows` rows (or columns) from r0, inner length K.
-// ALONG: element (i, k) at X[i * ld + k]; else at X[k * ld + i].
-template <int BM, bool ALONG>
+// ALONG: element (i, k) at X[i * ld + k]; else at X[k * ld + i].  FAR: 64-bit
+// addresses, for leading dimensions whose steps do not fit 32-bit offsets (the
+// single launch picks it; the grouped one, whose blocks never get there, falls
+// back to element copies).
+template <int BM, bool ALONG, bool FAR = false>
 struct Operand {
-    using Gm = Geo<BM>;
-    static constexpr int PR = kBK / 2;  // pairs of k per row
+    using Map = OperandMap<BM, ALONG>;
+    static constexpr int CH = Map::CHUNKS / 256;  // 16-byte chunks per thread and step
     const double *X;
     int64_t ld;
     int rows, K, r0;
-    int voff[Gm::CH];  // byte offset of the thread's chunks from the step's base
-    int nfast;         // steps that take the direct loads
+    int voff[FAR ? 1 : CH];  // byte offset of the thread's chunks from the step's base
+    int nfast;               // steps that take the direct loads
 
-    __device__ __forceinline__ void place(int i, int &row, int &k) const {
-        const int c = i * 256 + threadIdx.x;
-        if (ALONG) {
-            row = c / PR;
-            k = 2 * ((c % PR) ^ ((row >> 1) & 7));
-        } else {
-            k = c / (BM / 2);
-            row = 2 * ((c % (BM / 2)) ^ (8 * ((k >> 1) & 1)));
-        }
-    }
+    __device__ __forceinline__ void place(int i, int &row, int &k) const { Map::place(i * 256 + threadIdx.x, row, k); }
 
     __device__ __forceinline__ void init(const double *x, int64_t l, int n, int kk, int first) {
         X = x;
@@ -86,42 +74,41 @@ struct Operand {
         rows = n;
         K = kk;
         r0 = first;
-        // 32-bit offsets within a step
-        const bool near = ld < (int64_t(1) << 31) / 8 / (ALONG ? BM : 2 * kBK);
-        // pairs of rows across K: the very last pair of an odd count would run
-        // past the stored matrix
-        nfast = !near ? 0 : (ALONG || (rows & 1) == 0) ? K / kBK : (K > 0 ? (K - 1) / kBK : 0);
+        nfast = FAR || Map::near(ld) ? Map::direct_steps(rows, K) : 0;
+        if (FAR) return;
 #pragma unroll
-        for (int i = 0; i < Gm::CH; ++i) {
+        for (int i = 0; i < CH; ++i) {
             int row, k;
             place(i, row, k);
-            if (ALONG) {
-                const int r = r0 + row < rows ? row : rows - 1 - r0;
-                voff[i] = static_cast<int>(r * ld * 8) + k * 8;
-            } else {
-                const int last = (rows - 1) & ~1;
-                const int r = r0 + row < last ? row : last - r0;
-                voff[i] = static_cast<int>(k * ld * 8) + r * 8;
-            }
+            voff[i] = Map::byte_offset(row, k, rows, ld, r0);
         }
     }
 
     __device__ __forceinline__ void issue(double *stage, int step) const {
-        const double *base = ALONG ? X + static_cast<int64_t>(r0) * ld + step * kBK
-                                   : X + static_cast<int64_t>(step) * kBK * ld + r0;
-        const __amdgpu_buffer_rsrc_t rs =
-            __builtin_amdgcn_make_buffer_rsrc(const_cast<double *>(base), 0, 0x7fffffff, kBufferDword3);
+        const double *base = X + Map::base(ld, r0, step);
         const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        if constexpr (FAR) {
 #pragma unroll
-        for (int i = 0; i < Gm::CH; ++i)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void *)(stage + (i * 256 + wave * 64) * 2), 16, voff[i],
-                                                     0, 0, 0);
+            for (int i = 0; i < CH; ++i) {
+                int row, k;
+                place(i, row, k);
+                __builtin_amdgcn_global_load_lds((global_void *)(base + Map::offset(row, k, rows, ld, r0)),
+                                                 (lds_void *)(stage + (i * 256 + wave * 64) * 2), 16, 0, 0);
+            }
+        } else {
+            const __amdgpu_buffer_rsrc_t rs =
+                __builtin_amdgcn_make_buffer_rsrc(const_cast<double *>(base), 0, 0x7fffffff, kBufferDword3);
+#pragma unroll
+            for (int i = 0; i < CH; ++i)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void *)(stage + (i * 256 + wave * 64) * 2), 16,
+                                                         voff[i], 0, 0, 0);
+        }
     }
 
     // The same step element by element, zero past K and past the rows.
     __device__ __forceinline__ void copy(double *stage, int step) const {
 #pragma unroll
-        for (int i = 0; i < Gm::CH; ++i) {
+        for (int i = 0; i < CH; ++i) {
             int row, k;
             place(i, row, k);
             k += step * kBK;
@@ -163,7 +150,7 @@ __device__ __forceinline__ void read_frags(double2 (&f)[2][E / 32], const double
         }
 }
 
-template <int BM, int BN, bool TA, bool TB, int MODE, typename GetTerm>
+template <int BM, int BN, bool TA, bool TB, int MODE, bool FAR = false, typename GetTerm>
 __device__ __forceinline__ void dgemm_tile(const Dgemm64Args &a, GetTerm get_term, int tb, int te,
                                            const OutDesc &out, int m0, int n0, double *lds) {
     constexpr int MB = BM / 32, NB = BN / 32, OPA = BM * kBK, STAGE = OPA + BN * kBK;
@@ -203,8 +190,8 @@ __device__ __forceinline__ void dgemm_tile(const Dgemm64Args &a, GetTerm get_ter
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = v4d{0.0, 0.0, 0.0, 0.0};
         const int nk = (T.K + kBK - 1) / kBK;
-        Operand<BM, !TA> oa;
-        Operand<BN, TB> ob;
+        Operand<BM, !TA, FAR> oa;
+        Operand<BN, TB, FAR> ob;
         oa.init(T.A, T.lda, out.M, T.K, m0);
         ob.init(T.B, T.ldb, out.N, T.K, n0);
         auto load = [&](int step) {
@@ -332,7 +319,7 @@ __device__ __forceinline__ void batch_product(const Dgemm64Args &a, int k, Term6
 // against 175).
 constexpr int tile_waves(int bm) { return bm == 64 ? 4 : 2; }
 
-template <int BM, int BN, bool TA, bool TB>
+template <int BM, int BN, bool TA, bool TB, bool FAR>
 __global__ __launch_bounds__(256, tile_waves(BM)) void k_dgemm_single(Dgemm64Args a, int tiles_m) {
     __shared__ __align__(16) double lds[2 * (BM + BN) * kBK];
     int k, tm, tn;
@@ -340,7 +327,7 @@ __global__ __launch_bounds__(256, tile_waves(BM)) void k_dgemm_single(Dgemm64Arg
     Term64 term;
     OutDesc out;
     batch_product(a, k, term, out);
-    dgemm_tile<BM, BN, TA, TB, kModeGemm>(a, [&](int) { return term; }, 0, 1, out, tm * BM, tn * BN, lds);
+    dgemm_tile<BM, BN, TA, TB, kModeGemm, FAR>(a, [&](int) { return term; }, 0, 1, out, tm * BM, tn * BN, lds);
 }
 
 template <int BM, bool TB, int MODE>
@@ -517,15 +504,29 @@ void launch_split(bool ta, bool tb, Dgemm64Args a, hipStream_t s) {
     if (ta && tb) hipLaunchKernelGGL((k_dgemm_split<true, true>), dim3(grid), dim3(256), 0, s, a, tiles_m);
 }
 
-template <int BM, int BN>
+template <int BM, int BN, bool FAR>
 void launch_single_tile(bool ta, bool tb, Dgemm64Args a, hipStream_t s) {
     const int tiles_m = static_cast<int>(ceil_div(a.out.M, BM));
     a.tiles_n = static_cast<int32_t>(ceil_div(a.out.N, BN));
     const unsigned grid = static_cast<unsigned>(tiles_m) * static_cast<unsigned>(a.tiles_n) * (a.nbatch > 1 ? a.nbatch : 1);
-    if (!ta && !tb) hipLaunchKernelGGL((k_dgemm_single<BM, BN, false, false>), dim3(grid), dim3(256), 0, s, a, tiles_m);
-    if (!ta && tb) hipLaunchKernelGGL((k_dgemm_single<BM, BN, false, true>), dim3(grid), dim3(256), 0, s, a, tiles_m);
-    if (ta && !tb) hipLaunchKernelGGL((k_dgemm_single<BM, BN, true, false>), dim3(grid), dim3(256), 0, s, a, tiles_m);
-    if (ta && tb) hipLaunchKernelGGL((k_dgemm_single<BM, BN, true, true>), dim3(grid), dim3(256), 0, s, a, tiles_m);
+    if (!ta && !tb) hipLaunchKernelGGL((k_dgemm_single<BM, BN, false, false, FAR>), dim3(grid), dim3(256), 0, s, a, tiles_m);
+    if (!ta && tb) hipLaunchKernelGGL((k_dgemm_single<BM, BN, false, true, FAR>), dim3(grid), dim3(256), 0, s, a, tiles_m);
+    if (ta && !tb) hipLaunchKernelGGL((k_dgemm_single<BM, BN, true, false, FAR>), dim3(grid), dim3(256), 0, s, a, tiles_m);
+    if (ta && tb) hipLaunchKernelGGL((k_dgemm_single<BM, BN, true, true, FAR>), dim3(grid), dim3(256), 0, s, a, tiles_m);
+}
+
+// 64-bit addresses where a step of either operand does not fit 32-bit offsets
+// (a leading dimension from 2^24 elements across K, from 2^22 along it with 64
+// rows).  1024 x 1024 x 512, both operands past that, 64-bit against element
+// copies: NT 28 us / 54, NN 42 / 55, TT 34 / 58, TN 43 / 61 (26 within the
+// 32-bit offsets).
+template <int E>
+void launch_tile_edge(bool ta, bool tb, const Dgemm64Args &a, hipStream_t s) {
+    auto near = [](bool along, int64_t ld) { return along ? OperandMap<E, true>::near(ld) : OperandMap<E, false>::near(ld); };
+    if (near(!ta, a.term.lda) && near(tb, a.term.ldb))
+        launch_single_tile<E, E, false>(ta, tb, a, s);
+    else
+        launch_single_tile<E, E, true>(ta, tb, a, s);
 }
 
 }  // namespace
@@ -554,9 +555,9 @@ hipError_t launch_dgemm_single(bool ta, bool tb, const Dgemm64Args &a, int num_c
     if (split_pays(tiles64, num_cu))
         launch_split(ta, tb, a, s);
     else if (dgemm_tile_for(tiles64, ceil_div(a.out.M, 128) * ceil_div(a.out.N, 128) * nb, num_cu) == 64)
-        launch_single_tile<64, 64>(ta, tb, a, s);
+        launch_tile_edge<64>(ta, tb, a, s);
     else
-        launch_single_tile<128, 128>(ta, tb, a, s);
+        launch_tile_edge<128>(ta, tb, a, s);
     return hipGetLastError();
 }
 

@@ -465,3 +465,32 @@ def test_fp64_paths_within_gamma_bound(oz, M, N, K, ta, tb):
         mag = abs(alpha) * (np.abs(A[rows]) @ np.abs(B)) + abs(beta) * np.abs(C0[rows])
         err = np.abs(C.cpu().numpy()[rows] - ref - alpha * lo)
         assert np.all(err <= gam * mag * (1 + 1e-12) + 4 * u * np.abs(ref)), (odd, err.max())
+
+
+@pytest.mark.parametrize("ta,tb,M,N,K,far", [("N", "T", 65, 4163, 41, "a"), ("N", "N", 65, 4163, 33, "ab"),
+                                             ("T", "N", 65, 4163, 32, "ab"), ("T", "T", 65, 4163, 50, "a"),
+                                             ("N", "N", 127, 131071, 35, "a"), ("T", "N", 4097, 4095, 33, "ab")])
+def test_fp64_far_leading_dimensions(oz, ta, tb, M, N, K, far):
+    """Leading dimensions past the 32-bit offsets of a step (2^22 or 2^21 along
+    K with 64 or 128 rows, 2^24 across it; odd ones, so rows are 8 bytes off
+    16): both tile edges on 64-bit addresses, against torch's product of
+    packed copies within twice the textbook bound for K + 2 roundings."""
+    ozaki, ctx, torch = oz
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M + N + K)
+
+    def operand(rows, cols, along, is_far):
+        X = torch.randn(rows, cols, generator=g, device="cuda", dtype=torch.float64)
+        ld = (2 ** 22 + 5 if along else 2 ** 24 + 3) if is_far else cols + 1
+        buf = torch.empty(rows * ld, dtype=torch.float64, device="cuda")
+        view = buf.view(rows, ld)[:, :cols]
+        view.copy_(X)
+        return X, view
+
+    A, dA = operand(*((K, M) if ta == "T" else (M, K)), along=ta == "N", is_far="a" in far)
+    B, dB = operand(*((N, K) if tb == "T" else (K, N)), along=tb == "T", is_far="b" in far)
+    got = ctx.dgemm(dA, dB, slices=0, transa=ta, transb=tb)
+    opA, opB = (A.T if ta == "T" else A).contiguous(), (B.T if tb == "T" else B).contiguous()
+    u = 2.0 ** -53
+    gam = (K + 2) * u / (1 - (K + 2) * u)
+    assert bool(((got - opA @ opB).abs() <= 2 * gam * (opA.abs() @ opB.abs())).all())
