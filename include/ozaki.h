@@ -203,12 +203,19 @@ int ozaki_dgemm_auto(ozaki_ctx ctx, char transa, char transb, int64_t M, int64_t
  * variant v to tile_m[v] x tile_n[v] (0 x 0 when v is not built for this G)
  * and returns the number of variant slots. */
 int ozaki_pair_variants(int slices, int ndiag, int32_t *tile_m, int32_t *tile_n, int32_t max_variants);
-/* Use variant `variant` for (slices, ndiag) in this context (-1: library
- * default; heff plans then autotune if enabled).  OZ_ERR_ARG for a variant
- * that is not built. */
+/* Use variant `variant` for (slices, ndiag) in this context, for products of
+ * every size (-1: library default; heff plans then autotune if enabled).
+ * OZ_ERR_ARG for a variant that is not built. */
 int ozaki_ctx_set_variant(ozaki_ctx ctx, int slices, int ndiag, int variant);
-/* Variant ozaki_dgemm currently uses for (slices, ndiag). */
+/* Tile variant ozaki_dgemm currently uses for (slices, ndiag). */
 int ozaki_ctx_get_variant(ozaki_ctx ctx, int slices, int ndiag);
+/* Kernel ozaki_dgemm takes for an emulated M x N x K product: the tile
+ * variant, or OZ_VARIANT_SPLIT for the kernel for few tiles (a workgroup per
+ * 32 x 32 block of the output, its waves on different parts of K), which it
+ * prefers where it pays unless a variant was set with ozaki_ctx_set_variant
+ * (one that ozaki_dgemm_tune chose does not count).  Results are the same. */
+#define OZ_VARIANT_SPLIT 100
+int ozaki_dgemm_variant(ozaki_ctx ctx, int64_t M, int64_t N, int64_t K, int slices, int ndiag);
 /* Whether heff_plan_create times the variants of its two grouped phases and
  * keeps the fastest (default on; a variant fixed with ozaki_ctx_set_variant
  * takes precedence). */
@@ -264,9 +271,10 @@ int ozaki_ctx_set_heff_budget(ozaki_ctx ctx, size_t bytes);
  * (S, G), or a resident or paired-term launch not built for it or asked
  * for the other phase, makes heff_plan_create fail with OZ_ERR_ARG. */
 int ozaki_ctx_set_heff_phase(ozaki_ctx ctx, int phase, int variant, int order, int launch);
-/* Time every built variant of this GEMM (alpha = 1, beta = 0 into C, one
- * warm-up and three timed calls each) and fix the fastest for (slices,
- * ndiag) in the context.  ms_out (host, nullable, one slot per variant) gets
+/* Time every built tile variant of this GEMM (alpha = 1, beta = 0 into C, one
+ * warm-up and three timed calls each) and keep the fastest for (slices,
+ * ndiag) in the context, where products run on tiles (heff plans take it
+ * too; see ozaki_dgemm_variant).  ms_out (host, nullable, one slot per variant) gets
  * the mean milliseconds or -1.  Returns the chosen variant (>= 0) or an
  * error; synchronises the stream. */
 int ozaki_dgemm_tune(ozaki_ctx ctx, char transa, char transb, int64_t M, int64_t N, int64_t K,

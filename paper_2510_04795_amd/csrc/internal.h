@@ -271,8 +271,8 @@ hipError_t launch_unpack(int S, const int8_t *packed, int64_t Rp, int64_t R, int
 // Tile variants of the int8 pair GEMM.  v < 0 selects the default variant.
 // A single launch takes a.nbatch products in kModeGemm.
 // kSplitVariant (launch_pair_single in kModeGemm only, 32 x 32 tiles) is the
-// kernel for products of few tiles; pair_split_pays says where ozaki_dgemm
-// takes it when no variant is set.
+// kernel for products of few tiles; pair_split_pays says where it is the faster
+// one.  OZ_VARIANT_SPLIT of the interface.
 constexpr int kSplitVariant = 100;
 bool pair_split_pays(int64_t M, int64_t N, int64_t K, int nbatch, int num_cu);
 // Accumulating grouped launches: whether PairArgs::split is the faster kernel

@@ -1346,14 +1346,13 @@ int renorm_batch(int64_t n, int64_t D, int count, int slices, int ndiag) {
 
 // Whether the call takes the batched form: everything ozaki_dgemm would
 // refuse is left to it, and so are inner lengths above the exact int32 range
-// (int64 carries), sizes whose slice passes do not fit one grid, a tile
-// variant fixed by the caller and phase timing (one record per product).
-bool renorm_batched(ozaki_ctx ctx, int64_t n, const double *U, int slices, int ndiag) {
-    if (!U || ctx->timing || n > INT32_MAX / 2) return false;
+// (int64 carries) and sizes whose slice passes do not fit one grid.
+bool renorm_batched(int64_t n, const double *U, int slices, int ndiag) {
+    if (!U || n > INT32_MAX / 2) return false;
     if (slices == 0) return true;
     if (slices < 2 || slices > 8) return false;
     const int G = resolve_ndiag(slices, ndiag);
-    if (!valid_sg(slices, G) || n > max_exact_k(slices, G) || ctx->variant[slices][G] >= 0) return false;
+    if (!valid_sg(slices, G) || n > max_exact_k(slices, G)) return false;
     return 2 * (round_up(n, kRowQ) / kRowQ) * ceil_div(n, kKB) <= (1 << 23);
 }
 
@@ -1391,6 +1390,13 @@ hipError_t renorm_emulated(ozaki_ctx ctx, int64_t n, int64_t D, const double *U,
     int8_t *ud = reinterpret_cast<int8_t *>(ws + w.u_dig);
     int32_t *ue = reinterpret_cast<int32_t *>(ws + w.u_e);
     int32_t *codes = reinterpret_cast<int32_t *>(ws + w.part);
+    // one phase record per pass over a batch
+    hipEvent_t t = mark(ctx, s);
+    auto done = [&](int id) {
+        const hipEvent_t now = mark(ctx, s);
+        phase(ctx, id, t, now);
+        t = now;
+    };
     // slices of up to two operands per pair of launches
     auto slice = [&](OperandTask a, OperandTask b) {
         return launch_slice_operands(S, a, b, codes, ctx->num_cu, ctx->d_flags, s);
@@ -1398,9 +1404,10 @@ hipError_t renorm_emulated(ozaki_ctx ctx, int64_t n, int64_t D, const double *U,
     const OperandTask none{nullptr, 1, 0, n, 0, 0, nullptr, nullptr, 0};
     hipError_t e = slice(OperandTask{U, ldu, D, n, 1, 0, ue, ud, Dp}, none);
     if (e != hipSuccess) return e;
+    done(OZ_PHASE_SLICE);
     auto product = [&](int64_t M, const PairArgs &base, int nk) {
         PairArgs a = base;
-        const int v = pair_split_pays(M, D, n, nk, ctx->num_cu) ? kSplitVariant : ctx_variant(ctx, S, G);
+        const int v = gemm_variant(ctx, S, G, M, D, n, nk);
         const PairShape sh = pair_shape(S, G, v);
         a.tiles_n = static_cast<int32_t>(ceil_div(D, sh.bn));
         a.mode = kModeGemm;
@@ -1419,6 +1426,7 @@ hipError_t renorm_emulated(ozaki_ctx ctx, int64_t n, int64_t D, const double *U,
         };
         for (int k = 0; k < nk; k += 2)
             if ((e = slice(o_task(k), k + 1 < nk ? o_task(k + 1) : none)) != hipSuccess) return e;
+        done(OZ_PHASE_SLICE);
         // T_k = O_k U
         PairArgs a{};
         int8_t *dig = reinterpret_cast<int8_t *>(at(0, w.dig));
@@ -1429,8 +1437,10 @@ hipError_t renorm_emulated(ozaki_ctx ctx, int64_t n, int64_t D, const double *U,
         a.batch_e = static_cast<int64_t>(w.slot / sizeof(int32_t));
         for (int k = 0; k < nk; ++k) a.batch_C[k] = reinterpret_cast<double *>(at(k, w.T));
         if ((e = product(n, a, nk)) != hipSuccess) return e;
+        done(OZ_PHASE_PAIR);
         for (int k = 0; k < nk; k += 2)
             if ((e = slice(t_task(k), k + 1 < nk ? t_task(k + 1) : none)) != hipSuccess) return e;
+        done(OZ_PHASE_SLICE);
         // O'_k = U^T T_k
         a.term = TermDesc{ud, ue, dig, ex, Dp, Dp, static_cast<int32_t>(Kp / kKB), 0, 1.0};
         a.out = OutDesc{outs[k0], ldout, static_cast<int32_t>(D), static_cast<int32_t>(D)};
@@ -1439,6 +1449,7 @@ hipError_t renorm_emulated(ozaki_ctx ctx, int64_t n, int64_t D, const double *U,
         a.batch_A = a.batch_e = 0;
         for (int k = 0; k < nk; ++k) a.batch_C[k] = outs[k0 + k];
         if ((e = product(D, a, nk)) != hipSuccess) return e;
+        done(OZ_PHASE_PAIR);
     }
     return hipSuccess;
 }
@@ -1459,7 +1470,10 @@ hipError_t renorm_native(ozaki_ctx ctx, int64_t n, int64_t D, const double *U, i
             a.batch_B[k] = U;
             a.batch_C[k] = T + k * stride;
         }
+        const hipEvent_t t0 = mark(ctx, s);
         if ((e = launch_dgemm_single(false, false, a, ctx->num_cu, s)) != hipSuccess) return e;
+        const hipEvent_t t1 = mark(ctx, s);
+        phase(ctx, OZ_PHASE_FP64, t0, t1);
         a.term = Term64{U, T, ldu, D, static_cast<int32_t>(n), 0, 1.0};
         a.out = OutDesc{outs[k0], ldout, static_cast<int32_t>(D), static_cast<int32_t>(D)};
         for (int k = 0; k < a.nbatch; ++k) {
@@ -1468,6 +1482,7 @@ hipError_t renorm_native(ozaki_ctx ctx, int64_t n, int64_t D, const double *U, i
             a.batch_C[k] = outs[k0 + k];
         }
         if ((e = launch_dgemm_single(true, false, a, ctx->num_cu, s)) != hipSuccess) return e;
+        phase(ctx, OZ_PHASE_FP64, t1, mark(ctx, s));
     }
     return hipSuccess;
 }
@@ -1507,7 +1522,7 @@ int ozaki_renormalize(ozaki_ctx ctx, int64_t n, int64_t D, const double *U, int6
         return fail(OZ_ERR_WORKSPACE, "ozaki_renormalize: workspace not 256-byte aligned");
     for (int k = 0; k < count; ++k)
         if (!ops[k] || !outs[k]) return fail(OZ_ERR_ARG, "ozaki_renormalize: operator %d is NULL", k);
-    if (renorm_batched(ctx, n, U, slices, ndiag) && !renorm_overlaps(n, D, U, ldu, count, ops, ldo, outs, ldout)) {
+    if (renorm_batched(n, U, slices, ndiag) && !renorm_overlaps(n, D, U, ldu, count, ops, ldo, outs, ldout)) {
         const int most = renorm_batch(n, D, count, slices, ndiag);
         const size_t more = (workspace_bytes - need) / renorm_slot(n, D, slices);
         const int nb = more < static_cast<size_t>(most - 1) ? static_cast<int>(more) + 1 : most;

@@ -18,8 +18,10 @@ struct ozaki_ctx_s {
     void *scratch = nullptr;      // grow-only scratch of the debug entry points
     void *static_ws = nullptr;    // this device's copy of the static workspace (ozaki_dgemm_static)
     size_t scratch_bytes = 0;
-    // tile variant of the pair GEMM per (S, G); -1 = library default
+    // tile variant of the pair GEMM per (S, G); -1 = library default.  tuned:
+    // ozaki_dgemm_tune's choice among the tiles, not named by the caller
     int variant[9][16];
+    bool tuned[9][16] = {};
     bool autotune = true;  // heff plans time the variants of their grouped phases
     int heff_launch = -1;  // grouped heff phases: -1 timed choice, 0 one workgroup per tile, k > 0 streamed on k CUs,
                            // OZ_HEFF_LAUNCH_RESIDENT resident first phase, OZ_HEFF_LAUNCH_PAIRED_TERMS paired-term second
@@ -65,8 +67,12 @@ GemmWorkspace gemm_workspace(int64_t M, int64_t N, int64_t K, int S, int G);
 hipEvent_t mark(ozaki_ctx ctx, hipStream_t s);
 void phase(ozaki_ctx ctx, int id, hipEvent_t a, hipEvent_t b);
 
-// Variant for (S, G) in this context (explicit choice or the default).
+// Tile variant for (S, G) in this context (explicit or tuned choice, or the default).
 int ctx_variant(ozaki_ctx ctx, int S, int G);
+// Kernel of nbatch products in one launch (K within the exact int32 range): the
+// split kernel where it pays, unless the caller named a variant, else the tile
+// variant.
+int gemm_variant(ozaki_ctx ctx, int S, int G, int64_t M, int64_t N, int64_t K, int nbatch);
 
 hipError_t slice_operand(int S, bool by_rows, const double *X, int64_t ld, int64_t R, int64_t K,
                          int32_t *e, int8_t *packed, double *part, uint32_t *flag, hipStream_t s);

@@ -119,6 +119,11 @@ int ctx_variant(ozaki_ctx ctx, int S, int G) {
     return v >= 0 ? v : pair_default_variant(G);
 }
 
+int gemm_variant(ozaki_ctx ctx, int S, int G, int64_t M, int64_t N, int64_t K, int nbatch) {
+    const bool named = ctx->variant[S][G] >= 0 && !ctx->tuned[S][G];
+    return !named && pair_split_pays(M, N, K, nbatch, ctx->num_cu) ? kSplitVariant : ctx_variant(ctx, S, G);
+}
+
 }  // namespace oz
 
 using namespace oz;
@@ -258,6 +263,7 @@ int ozaki_ctx_set_variant(ozaki_ctx ctx, int slices, int ndiag, int variant) {
     if (variant >= 0 && !pair_variant_ok(G, variant))
         return fail(OZ_ERR_ARG, "ozaki_ctx_set_variant: variant %d is not built for G = %d", variant, G);
     ctx->variant[slices][G] = variant < 0 ? -1 : variant;
+    ctx->tuned[slices][G] = false;
     return OZ_OK;
 }
 
@@ -267,6 +273,16 @@ int ozaki_ctx_get_variant(ozaki_ctx ctx, int slices, int ndiag) {
     const int G = resolve_ndiag(slices, ndiag);
     if (!valid_sg(slices, G)) return fail(OZ_ERR_ARG, "ozaki_ctx_get_variant: ndiag = %d", ndiag);
     return ctx_variant(ctx, slices, G);
+}
+
+int ozaki_dgemm_variant(ozaki_ctx ctx, int64_t M, int64_t N, int64_t K, int slices, int ndiag) {
+    if (!ctx) return fail(OZ_ERR_ARG, "ozaki_dgemm_variant: ctx is NULL");
+    if (M < 0 || N < 0 || K < 0) return fail(OZ_ERR_ARG, "ozaki_dgemm_variant: negative size");
+    if (slices < 2 || slices > 8) return fail(OZ_ERR_ARG, "ozaki_dgemm_variant: slices = %d", slices);
+    const int G = resolve_ndiag(slices, ndiag);
+    if (!valid_sg(slices, G)) return fail(OZ_ERR_ARG, "ozaki_dgemm_variant: ndiag = %d", ndiag);
+    // the int64 carries between K chunks are built for the 64 x 64 tile only
+    return K > max_exact_k(slices, G) ? 0 : gemm_variant(ctx, slices, G, M, N, K, 1);
 }
 
 int ozaki_ctx_set_autotune(ozaki_ctx ctx, int enable) {
@@ -314,6 +330,8 @@ int ozaki_dgemm_tune(ozaki_ctx ctx, char transa, char transb, int64_t M, int64_t
     if ((e = hipEventCreate(&ev0)) != hipSuccess) return hip_fail(e, "hipEventCreate");
     if ((e = hipEventCreate(&ev1)) != hipSuccess) { hipEventDestroy(ev0); return hip_fail(e, "hipEventCreate"); }
     const int saved = ctx->variant[slices][G];
+    const bool saved_tuned = ctx->tuned[slices][G];
+    ctx->tuned[slices][G] = false;  // each candidate is timed on its tiles
     int best = -1;
     float best_ms = 0.f;
     int rc = OZ_OK;
@@ -339,7 +357,9 @@ int ozaki_dgemm_tune(ozaki_ctx ctx, char transa, char transb, int64_t M, int64_t
     }
     hipEventDestroy(ev0);
     hipEventDestroy(ev1);
-    ctx->variant[slices][G] = (rc == OZ_OK && best >= 0) ? best : saved;
+    const bool chosen = rc == OZ_OK && best >= 0;
+    ctx->variant[slices][G] = chosen ? best : saved;
+    ctx->tuned[slices][G] = chosen || saved_tuned;
     return rc == OZ_OK ? best : rc;
 }
 
@@ -441,9 +461,7 @@ int ozaki_dgemm(ozaki_ctx ctx, char transa, char transb, int64_t M, int64_t N, i
     hipEvent_t t1 = mark(ctx, s);
     phase(ctx, OZ_PHASE_SLICE, t0, t1);
     const int64_t kmax = max_exact_k(slices, G);
-    // the int64 carries between K chunks are built for the 64 x 64 tile only
-    const bool split = K <= kmax && ctx->variant[slices][G] < 0 && pair_split_pays(M, N, K, 1, ctx->num_cu);
-    const int var = K > kmax ? 0 : split ? kSplitVariant : ctx_variant(ctx, slices, G);
+    const int var = ozaki_dgemm_variant(ctx, M, N, K, slices, G);
     const PairShape sh = pair_shape(slices, G, var);
     PairArgs a{};
     a.tiles_n = static_cast<int32_t>(ceil_div(N, sh.bn));

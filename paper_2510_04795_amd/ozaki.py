@@ -20,6 +20,7 @@ OZ_OK, OZ_CONVERGED, OZ_STAGNATED, OZ_MAX_ITER = 0, 1, 2, 3
 OZ_STATIC_WORKSPACE_BYTES = 96 << 20
 OZ_FLAG_NONFINITE = 1
 OZ_EXP_NONFINITE = -(2 ** 31)
+OZ_VARIANT_SPLIT = 100
 OZ_HEFF_LAUNCH_RESIDENT = -2
 OZ_HEFF_LAUNCH_PAIRED_TERMS = -3
 PHASES = {1: "slice", 2: "pair", 3: "fp64", 4: "heff_L", 5: "heff_R", 6: "heff_aux"}
@@ -74,6 +75,7 @@ _sig("ozaki_ctx_phase_times", _i32, [_ptr, _ptr, _ptr, _i32])
 _sig("ozaki_pair_variants", _i32, [_i32, _i32, _ptr, _ptr, _i32])
 _sig("ozaki_ctx_set_variant", _i32, [_ptr, _i32, _i32, _i32])
 _sig("ozaki_ctx_get_variant", _i32, [_ptr, _i32, _i32])
+_sig("ozaki_dgemm_variant", _i32, [_ptr, _i64, _i64, _i64, _i32, _i32])
 _sig("ozaki_ctx_set_autotune", _i32, [_ptr, _i32])
 _sig("ozaki_dgemm_tune", _i32, [_ptr, ctypes.c_char, ctypes.c_char, _i64, _i64, _i64, _ptr, _i64, _ptr,
                                 _i64, _ptr, _i64, _i32, _i32, _ptr, _sz, _ptr, _ptr])
@@ -130,7 +132,7 @@ _sig("ozaki_renormalize", _i32, [_ptr, _i64, _i64, _ptr, _i64, _i32, ctypes.POIN
 EXPORTED = [
     "ozaki_status_string", "ozaki_last_error", "ozaki_version", "ozaki_ctx_create",
     "ozaki_ctx_destroy", "ozaki_ctx_flags", "ozaki_ctx_set_timing", "ozaki_ctx_phase_times",
-    "ozaki_pair_variants", "ozaki_ctx_set_variant", "ozaki_ctx_get_variant",
+    "ozaki_pair_variants", "ozaki_ctx_set_variant", "ozaki_ctx_get_variant", "ozaki_dgemm_variant",
     "ozaki_ctx_set_autotune", "ozaki_ctx_set_heff_launch", "ozaki_ctx_set_heff_budget",
     "ozaki_ctx_set_heff_phase", "ozaki_dgemm_tune", "heff_plan_variants",
     "heff_plan_launches", "ozaki_slices_for_bits", "ozaki_pair_count",
@@ -278,6 +280,11 @@ class Context:
 
     def get_variant(self, slices: int, ndiag: int = 0) -> int:
         return _check(_lib.ozaki_ctx_get_variant(self.handle, slices, ndiag), "ozaki_ctx_get_variant")
+
+    def gemm_variant(self, M: int, N: int, K: int, slices: int, ndiag: int = 0) -> int:
+        """Kernel dgemm takes for an emulated M x N x K product: a tile variant
+        or OZ_VARIANT_SPLIT."""
+        return _check(_lib.ozaki_dgemm_variant(self.handle, M, N, K, slices, ndiag), "ozaki_dgemm_variant")
 
     def set_autotune(self, enable: bool = True):
         _check(_lib.ozaki_ctx_set_autotune(self.handle, int(bool(enable))), "ozaki_ctx_set_autotune")

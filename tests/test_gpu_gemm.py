@@ -494,3 +494,34 @@ def test_fp64_far_leading_dimensions(oz, ta, tb, M, N, K, far):
     u = 2.0 ** -53
     gam = (K + 2) * u / (1 - (K + 2) * u)
     assert bool(((got - opA @ opB).abs() <= 2 * gam * (opA.abs() @ opB.abs())).all())
+
+
+def test_tuned_context_keeps_the_split_kernel(oz):
+    """ozaki_dgemm_tune chooses among the tiles: products of few tiles stay on
+    the split kernel, also at the shape that was timed; a variant that the
+    caller names holds for every size.  Bit for bit the oracle's on each."""
+    ozaki, ctx, torch = oz
+    rng = np.random.default_rng(77)
+    S, G = 7, 8
+    A, B = wl.wide_normal(rng, (200, 300), 10), wl.wide_normal(rng, (300, 150), 10)
+    dA, dB = dev(torch, A), dev(torch, B)
+    ref = oracle.ozaki_dgemm(A, B, S, G)
+    small, large = (200, 150, 300), (2048, 2048, 300)
+    try:
+        assert ctx.gemm_variant(*small, S, G) == ozaki.OZ_VARIANT_SPLIT
+        assert ctx.gemm_variant(*large, S, G) == ctx.get_variant(S, G)
+        v, _ = ctx.tune(dA, dB, slices=S, ndiag=G)
+        assert ctx.gemm_variant(*small, S, G) == ozaki.OZ_VARIANT_SPLIT
+        assert ctx.gemm_variant(*large, S, G) == v
+        assert_bitexact(ctx.dgemm(dA, dB, slices=S, ndiag=G).cpu().numpy(), ref, "tuned")
+        ctx.set_variant(S, G, v)
+        assert ctx.gemm_variant(*small, S, G) == v
+        assert_bitexact(ctx.dgemm(dA, dB, slices=S, ndiag=G).cpu().numpy(), ref, "named")
+        # a failed call leaves the named variant in force
+        with pytest.raises(ozaki.OzakiError):
+            ctx.tune(dA, dB, slices=S, ndiag=G, workspace=torch.empty(256, dtype=torch.uint8, device="cuda"))
+        assert ctx.gemm_variant(*small, S, G) == v
+    finally:
+        ctx.set_variant(S, G, -1)
+    assert ctx.gemm_variant(*small, S, G) == ozaki.OZ_VARIANT_SPLIT
+    assert ctx.gemm_variant(64, 64, 40000, 8, 15) == 0  # K chunks run on the 64 x 64 tile

@@ -390,3 +390,39 @@ def test_tolerance_of_the_caller(oz, n, kind, tol):
     assert info.status == 1 and info.off <= tol
     M = Z.T @ A @ Z
     assert np.max(np.abs(M - np.diag(np.diag(M)))) <= 0.2 * tol * np.linalg.norm(A)
+
+
+@pytest.mark.parametrize("S", [0, 6])
+@pytest.mark.parametrize("how", ["default", "tuned", "named"])
+def test_renormalize_batches_on_every_context(oz, S, how):
+    """Contexts that were tuned, or whose caller named a tile variant, work on
+    several operators at once like any other (phase timing records a pass over
+    a batch each: fewer records than operators), with the same bits."""
+    ozaki, ctx, torch = oz
+    n, D, count = 300, 130, 5
+    ops = wl.block_operators(n, count, seed=7)
+    U = np.linalg.qr(np.random.default_rng(3).standard_normal((n, D)))[0]
+    dU, dops = dev(torch, U), [dev(torch, o) for o in ops]
+    variants = [v for v, _, _ in ozaki.pair_variants(6)] if how == "named" and S else [None]
+    want = ctx.renormalize(dU, dops, slices=S)
+    if S:
+        for got, ref in zip(want, oracle.renormalize(U, ops, S=S)):
+            assert_bitexact(got.cpu().numpy(), ref)
+    try:
+        if how == "tuned":
+            ctx.tune(dops[0], dU, slices=6)
+        for v in variants:
+            if v is not None:
+                ctx.set_variant(6, 0, v)
+            ctx.set_timing(True)
+            ctx.phase_times()
+            out = ctx.renormalize(dU, dops, slices=S)
+            rec = ctx.phase_times()
+            ctx.set_timing(False)
+            assert len(rec) == (5 if S else 2), rec
+            assert [r for r in rec if r[1] < 0] == []
+            for a, b in zip(out, want):
+                assert torch.equal(a, b)
+    finally:
+        ctx.set_timing(False)
+        ctx.set_variant(6, 0, -1)
