@@ -225,6 +225,12 @@ int ozaki_ctx_set_autotune(ozaki_ctx ctx, int enable);
  * ozaki_ctx_set_heff_phase, heff_plan_phase). */
 #define OZ_HEFF_LAUNCH_RESIDENT (-2)
 #define OZ_HEFF_LAUNCH_PAIRED_TERMS (-3)
+/* Part of the second phase's order (ozaki_ctx_set_heff_phase,
+ * heff_plan_phase): chunks whose outputs have at most two 32 x 32 blocks per
+ * compute unit run on the split kernel, a workgroup per block whose waves take
+ * different terms and add their FP64 values in list order; the rest of the
+ * choice is the other chunks'. */
+#define OZ_HEFF_ORDER_SPLIT 4
 /* How heff plans created afterwards launch their two grouped pair phases:
  * 0 = one workgroup per output tile; k > 0 = the streamed kernel, in which
  * as many workgroups as fit at once on min(k, number of CUs) compute units
@@ -245,7 +251,9 @@ int ozaki_ctx_set_autotune(ozaki_ctx ctx, int enable);
  * waves otherwise); -1 (default) = when autotuning is on, time the first
  * phase one workgroup per tile, streamed (if its items average at most 16
  * K blocks) and resident (where built), the second one workgroup per tile
- * and paired (where built); else 0.  Results are bit-identical in every
+ * and paired (where built); else 0; with -1 and no variant set
+ * (ozaki_ctx_set_variant) the second phase's chunks of few output blocks take
+ * the split kernel (OZ_HEFF_ORDER_SPLIT).  Results are bit-identical in every
  * mode.  OZ_ERR_ARG for mode < -3. */
 int ozaki_ctx_set_heff_launch(ozaki_ctx ctx, int mode);
 /* Device bytes that heff plans created afterwards may use for the
@@ -260,7 +268,8 @@ int ozaki_ctx_set_heff_budget(ozaki_ctx ctx, size_t bytes);
  * emulated heff plans created afterwards: tile variant (see
  * ozaki_pair_variants; < 0 clears the fix), tile order (0 = cost-balanced
  * contiguous parts per XCD, 1 = longest tile first, 2 = whole outputs to
- * the least loaded XCD, heaviest first) and launch (0 = one
+ * the least loaded XCD, heaviest first; second phase: plus
+ * OZ_HEFF_ORDER_SPLIT) and launch (0 = one
  * workgroup per tile, k > 0 = streamed on k compute units,
  * OZ_HEFF_LAUNCH_RESIDENT = the resident kernel, first phase only,
  * OZ_HEFF_LAUNCH_PAIRED_TERMS = the paired-term kernel, second phase
@@ -379,18 +388,23 @@ int heff_plan_graph_count(heff_plan plan);
 /* Tile variants the plan's two grouped phases use (emulated plans; -1 for
  * native FP64 plans). */
 int heff_plan_variants(heff_plan plan, int32_t *first, int32_t *second);
-/* Launch kind of the plan's two grouped phases (0 one workgroup per tile,
- * 1 streamed, 2 resident, 3 paired terms; -1 for native FP64 plans). */
+/* Launch kind of the plan's two grouped phases on its first chunk (0 one
+ * workgroup per tile, also where the split kernel runs, 1 streamed, 2
+ * resident, 3 paired terms; -1 for native FP64 plans). */
 int heff_plan_launches(heff_plan plan, int32_t *first, int32_t *second);
 /* Total elements of psi for the plan's layout. */
 int64_t heff_vector_length(heff_plan plan);
 /* The choice of grouped phase `phase` (0 = first product, 1 = second) in an
  * emulated plan: tile variant, order (0 XCD parts, 1 longest tile first,
- * 2 whole outputs per XCD) and
+ * 2 whole outputs per XCD; second phase: plus OZ_HEFF_ORDER_SPLIT when some
+ * chunk takes the split kernel, the launch then being the other chunks') and
  * launch (0 one workgroup per tile, k > 0 streamed on k CUs,
  * OZ_HEFF_LAUNCH_RESIDENT resident, OZ_HEFF_LAUNCH_PAIRED_TERMS paired
  * terms); all -1 for a native FP64 plan. */
 int heff_plan_phase(heff_plan plan, int phase, int32_t *variant, int32_t *order, int32_t *launch);
+/* Number of chunks whose second phase takes the split kernel
+ * (OZ_HEFF_ORDER_SPLIT). */
+int heff_plan_split_chunks(heff_plan plan);
 /* Number of chunks the plan's triple list runs in (ozaki_ctx_set_heff_budget). */
 int heff_plan_chunks(heff_plan plan);
 /* Device bytes the plan holds (all its allocations); *T_bytes (nullable)

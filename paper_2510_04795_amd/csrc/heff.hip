@@ -69,6 +69,7 @@ struct heff_plan_s {
     SliceCodes psi_codes{};      // how psi's slice pass gets its exponents
     int varL = -1, varR = -1;   // tile variants of the two grouped phases
     int choice[2][3] = {{-1, -1, -1}, {-1, -1, -1}};  // per phase: variant, order, launch
+    int split_chunks = 0;       // chunks whose second phase takes the split kernel
     std::vector<HeffChunk> chunks;
     size_t T_bytes = 0;         // T buffer, its slices and exponents
     size_t bytes = 0;           // every device allocation of the plan
@@ -264,6 +265,7 @@ void output_lpt_order(const std::vector<std::vector<TileWork>> &outputs, std::ve
 
 constexpr int kHeffLaunchResident = OZ_HEFF_LAUNCH_RESIDENT;
 constexpr int kHeffLaunchPairedTerms = OZ_HEFF_LAUNCH_PAIRED_TERMS;
+constexpr int kHeffOrderSplit = OZ_HEFF_ORDER_SPLIT;
 // workgroups per compute unit the resident schedules are built for, at most
 constexpr int kMaxResidentPerCu = 8;
 
@@ -784,8 +786,9 @@ int heff_plan_create(ozaki_ctx ctx, heff_plan *out, const heff_layout *L, const 
     for (int v = 0; v < pair_num_variants(); ++v)
         if (pair_variant_ok(G, v) && (fixed < 0 ? (ctx->autotune || v == pair_default_variant(G)) : v == fixed))
             cands.push_back(v);
-    // Autotuning on the first chunk: time each candidate (tile variant, tile
-    // order, launch) on its whole tile list or an even sample of it, scaled
+    // Autotuning on the first chunk (the second phase on the first that does not
+    // take the split kernel; not at all when every chunk does): time each
+    // candidate (tile variant, tile order, launch) on its whole tile list or an even sample of it, scaled
     // by the sample's share of the total cost; inputs are zeroed scratch (the
     // timing does not depend on the values).  Every chunk then uses the
     // choice per phase.
@@ -825,19 +828,22 @@ int heff_plan_create(ozaki_ctx ctx, heff_plan *out, const heff_layout *L, const 
     const int forced = ctx->heff_launch;  // -1 timed, 0 per tile, k > 0 streamed, resident or paired terms
     const int stream_cus_of = forced > 0 ? std::min(forced, ctx->num_cu) : ctx->num_cu;
     // chunks whose second phase takes the split kernel for few tiles: a rule
-    // on the outputs alone, unless the context names a launch
+    // on each chunk's outputs, unless the context names a launch or a variant
+    // (fixed phases: where they ask for it)
+    const bool may_split = fixed_phases ? (ctx->heff_fix[1][1] & kHeffOrderSplit) != 0
+                                        : forced == -1 && (fixed < 0 || ctx->tuned[S][G]);
     std::vector<char> split(hc.size(), 0);
-    for (size_t c = 0; c < hc.size() && (fixed_phases || forced == -1); ++c) {
+    size_t cR = hc.size();  // the chunk the second phase's other launches are timed on
+    for (size_t c = 0; c < hc.size(); ++c) {
         int64_t blocks = 0;
         for (const OutDesc &o : hl[c].outsR) blocks += ceil_div(o.M, 32) * ceil_div(o.N, 32);
-        split[c] = pair_accum_split_pays(blocks, ctx->num_cu);
+        split[c] = may_split && pair_accum_split_pays(blocks, ctx->num_cu);
+        if (!split[c] && cR == hc.size()) cR = c;
     }
     // the launches a phase may use for variant v
     auto kinds_for = [&](int ph, int v) {
         std::vector<int> k;
-        if (ph == 1 && split[0]) {
-            k.push_back(0);
-        } else if (forced == kHeffLaunchResident) {
+        if (forced == kHeffLaunchResident) {
             k.push_back(ph == 0 && pair_resident_per_cu(S, G, v) > 0 ? 2 : 0);
         } else if (forced == kHeffLaunchPairedTerms) {
             k.push_back(ph == 1 && pair_terms2_ok(S, G, v) ? 3 : 0);
@@ -893,7 +899,7 @@ int heff_plan_create(ozaki_ctx ctx, heff_plan *out, const heff_layout *L, const 
         for (int ph = 0; ph < 2; ++ph) {
             const int l = ctx->heff_fix[ph][2];
             Run &r = ph == 0 ? chosenL : chosenR;
-            r = Run{ctx->heff_fix[ph][0], ctx->heff_fix[ph][1], 0, 0};
+            r = Run{ctx->heff_fix[ph][0], ctx->heff_fix[ph][1] & ~kHeffOrderSplit, 0, 0};
             if (l == kHeffLaunchResident) {
                 if (ph != 0 || pair_resident_per_cu(S, G, r.v) <= 0) {
                     free_plan(P);
@@ -918,7 +924,13 @@ int heff_plan_create(ozaki_ctx ctx, heff_plan *out, const heff_layout *L, const 
         for (int v : cands)
             for (int order : {0, 1, 2}) {
                 tiles_for(0, v, order, &tl, &tr, &cl, &cr);
+                if (cR > 0 && cR < hc.size()) {
+                    std::vector<TileDesc> other;
+                    std::vector<int64_t> other_cost;
+                    tiles_for(cR, v, order, &other, &tr, &other_cost, &cr);
+                }
                 for (int ph = 0; ph < 2; ++ph) {
+                    if (ph == 1 && cR == hc.size()) continue;  // every chunk splits
                     const std::vector<int64_t> &cost = ph == 0 ? cl : cr;
                     const std::vector<TileDesc> &list = ph == 0 ? tl : tr;
                     int64_t total = 0, items = 0;
@@ -957,12 +969,11 @@ int heff_plan_create(ozaki_ctx ctx, heff_plan *out, const heff_layout *L, const 
                         // accumulating phase it was slower at every measured
                         // shape.
                         if (kind == 1 && forced < 0 && (ph == 1 || blocks_per_tile > kStreamMaxMeanBlocks)) continue;
-                        PairArgs a = ph == 0 ? P->chunks[0].argsL : P->chunks[0].argsR;
+                        PairArgs a = ph == 0 ? P->chunks[0].argsL : P->chunks[cR].argsR;
                         a.stream_cus = kind == 1 ? stream_cus_of : 0;
                         a.nwg = 0;
                         a.wg_off = nullptr;
                         a.terms2 = kind == 3 ? 1 : 0;
-                        a.split = ph == 1 && kind == 0 && split[0];
                         const std::vector<TileDesc> *up = &sample;
                         if (kind == 2) {
                             const int nwg = std::min(pair_resident_per_cu(S, G, v), kMaxResidentPerCu) * ctx->num_cu;
@@ -1023,7 +1034,8 @@ int heff_plan_create(ozaki_ctx ctx, heff_plan *out, const heff_layout *L, const 
         tiles_for(c, chosenR.v, chosenR.order, &l2, &r2, &cl2, &cr2);
         HeffChunk &ch = P->chunks[c];
         for (int ph = 0; ph < 2; ++ph) {
-            const Run &run = ph == 0 ? chosenL : chosenR;
+            const bool few = ph == 1 && split[c];
+            const Run run = few ? Run{chosenR.v, chosenR.order, 0, 0} : ph == 0 ? chosenL : chosenR;
             const std::vector<TileDesc> &list = ph == 0 ? l1 : r2;
             const std::vector<int64_t> &cost = ph == 0 ? cl1 : cr2;
             PairArgs &a = ph == 0 ? ch.argsL : ch.argsR;
@@ -1031,7 +1043,8 @@ int heff_plan_create(ozaki_ctx ctx, heff_plan *out, const heff_layout *L, const 
             a.nwg = 0;
             a.wg_off = nullptr;
             a.terms2 = run.kind == 3 ? 1 : 0;
-            a.split = ph == 1 && run.kind == 0 && split[c];
+            a.split = few ? 1 : 0;
+            P->split_chunks += few;
             TileDesc *d = nullptr;
             if (run.kind == 2) {
                 const int nwg = std::min(pair_resident_per_cu(S, G, run.v), kMaxResidentPerCu) * ctx->num_cu;
@@ -1060,7 +1073,7 @@ int heff_plan_create(ozaki_ctx ctx, heff_plan *out, const heff_layout *L, const 
     };
     P->choice[0][2] = launch_code(chosenL);
     P->choice[1][0] = chosenR.v;
-    P->choice[1][1] = chosenR.order;
+    P->choice[1][1] = chosenR.order | (P->split_chunks ? kHeffOrderSplit : 0);
     P->choice[1][2] = launch_code(chosenR);
     if ((e = hipStreamSynchronize(s)) != hipSuccess) { free_plan(P); return hip_fail(e, "heff_plan_create: sync"); }
     *out = P;
@@ -1229,6 +1242,11 @@ int heff_plan_phase(heff_plan P, int phase, int32_t *variant, int32_t *order, in
     if (order) *order = P->choice[phase][1];
     if (launch) *launch = P->choice[phase][2];
     return OZ_OK;
+}
+
+int heff_plan_split_chunks(heff_plan P) {
+    if (!P) return fail(OZ_ERR_ARG, "heff_plan_split_chunks: plan is NULL");
+    return P->split_chunks;
 }
 
 int heff_plan_chunks(heff_plan P) {

@@ -27,8 +27,9 @@ struct ozaki_ctx_s {
                            // OZ_HEFF_LAUNCH_RESIDENT resident first phase, OZ_HEFF_LAUNCH_PAIRED_TERMS paired-term second
     size_t heff_budget = 0;  // bytes for a heff plan's intermediates T; 0 = kHeffDefaultBudget
     // fixed choice per grouped phase of later emulated heff plans (variant < 0:
-    // timed): tile variant, order (0 XCD parts, 1 longest tile first), launch
-    // (0 one workgroup per tile, k > 0 streamed on k CUs)
+    // timed): tile variant, order (0 XCD parts, 1 longest tile first, 2 whole
+    // outputs; second phase: plus OZ_HEFF_ORDER_SPLIT), launch (0 one workgroup
+    // per tile, k > 0 streamed on k CUs)
     int heff_fix[2][3] = {{-1, 0, 0}, {-1, 0, 0}};
     // phase timing (ozaki_ctx_set_timing)
     bool timing = false;

@@ -23,6 +23,7 @@ OZ_EXP_NONFINITE = -(2 ** 31)
 OZ_VARIANT_SPLIT = 100
 OZ_HEFF_LAUNCH_RESIDENT = -2
 OZ_HEFF_LAUNCH_PAIRED_TERMS = -3
+OZ_HEFF_ORDER_SPLIT = 4
 PHASES = {1: "slice", 2: "pair", 3: "fp64", 4: "heff_L", 5: "heff_R", 6: "heff_aux"}
 STATUS = {0: "running", 1: "converged", 2: "stagnated", 3: "max_iter"}
 
@@ -106,6 +107,7 @@ _sig("heff_plan_set_graphs", _i32, [_ptr, _i32])
 _sig("heff_plan_graph_count", _i32, [_ptr])
 _sig("heff_vector_length", _i64, [_ptr])
 _sig("heff_plan_chunks", _i32, [_ptr])
+_sig("heff_plan_split_chunks", _i32, [_ptr])
 _sig("heff_plan_phase", _i32, [_ptr, _i32, _ptr, _ptr, _ptr])
 _sig("heff_plan_bytes", _i64, [_ptr, _ptr])
 _sig("heff_flops", _dbl, [_ptr])
@@ -139,7 +141,7 @@ EXPORTED = [
     "ozaki_max_exact_k", "ozaki_dgemm_workspace_bytes", "ozaki_dgemm", "ozaki_dgemm_static", "ozaki_split",
     "ozaki_choose_slices", "ozaki_dgemm_auto_workspace_bytes", "ozaki_dgemm_auto",
     "ozaki_pair_products", "heff_plan_create", "heff_apply", "heff_plan_set_graphs",
-    "heff_plan_graph_count", "heff_vector_length", "heff_plan_chunks", "heff_plan_bytes",
+    "heff_plan_graph_count", "heff_vector_length", "heff_plan_chunks", "heff_plan_split_chunks", "heff_plan_bytes",
     "heff_plan_phase", "heff_flops",
     "heff_plan_destroy", "davidson_create", "davidson_step", "davidson_get_vector",
     "davidson_set_graphs", "davidson_graph_count", "davidson_destroy", "lanczos_create", "lanczos_step", "lanczos_get_vector", "lanczos_destroy",
@@ -302,7 +304,8 @@ class Context:
         """Fix grouped phase `phase` (0 first product, 1 second) of later
         emulated heff plans: tile variant (-1 clears), order (0 XCD parts,
         1 longest tile first, 2 whole outputs per XCD, heaviest first to the
-        least loaded), launch (0 per tile, k > 0 streamed on k CUs,
+        least loaded; second phase: plus OZ_HEFF_ORDER_SPLIT, the split kernel
+        for chunks of few output blocks), launch (0 per tile, k > 0 streamed on k CUs,
         OZ_HEFF_LAUNCH_RESIDENT resident, first phase only,
         OZ_HEFF_LAUNCH_PAIRED_TERMS paired terms, second phase only).
         With both phases fixed a plan times nothing."""
@@ -600,6 +603,11 @@ class HeffPlan:
     @property
     def chunks(self) -> int:
         return _check(_lib.heff_plan_chunks(self.handle), "heff_plan_chunks")
+
+    @property
+    def split_chunks(self) -> int:
+        """Chunks whose second phase takes the split kernel."""
+        return _check(_lib.heff_plan_split_chunks(self.handle), "heff_plan_split_chunks")
 
     @property
     def bytes(self):

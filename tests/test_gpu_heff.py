@@ -889,3 +889,97 @@ def test_graph_cache_eviction(oz):
     torch.cuda.synchronize()
     for i, o in enumerate(outs):
         assert_bitexact(o.cpu().numpy(), ref, "pair %d" % i)
+
+
+def test_split_second_phase_is_named(oz):
+    """The split kernel of second phases of few output blocks runs by default
+    and on a tuned context, not where the caller names a launch, a variant or a
+    fixed phase without it; a plan's reported choice, fixed again, reproduces
+    it.  One set of bits."""
+    ozaki, ctx, torch = oz
+    prob = small_sparse(33)
+    ref = oracle.heff_sparse(prob, S=6)
+
+    def check(plan, dpsi, split, what):
+        assert plan.split_chunks == (plan.chunks if split else 0), what
+        assert bool(plan.phase(1)[1] & ozaki.OZ_HEFF_ORDER_SPLIT) == split, what
+        sig = wl.unflatten_sparse(prob, plan.apply(dpsi).cpu().numpy())
+        for b in prob.psi_blocks:
+            assert_bitexact(sig[b], ref[b], "%s block %s" % (what, b))
+
+    try:
+        plan, dpsi, keep = sparse_plan(ozaki, ctx, torch, prob, 6)
+        check(plan, dpsi, True, "default")
+        want = (plan.phase(0), plan.phase(1))
+        for order in (0, 1, 2):
+            ctx.set_heff_phase(0, 0, order, 0)
+            ctx.set_heff_phase(1, 0, order, 0)
+            check(*sparse_plan(ozaki, ctx, torch, prob, 6)[:2], False, "fixed per tile, order %d" % order)
+        for ph in (0, 1):
+            ctx.set_heff_phase(ph, *want[ph])
+        again, dpsi2, keep2 = sparse_plan(ozaki, ctx, torch, prob, 6)
+        assert (again.phase(0), again.phase(1)) == want
+        check(again, dpsi2, True, "fixed to the reported choice")
+        for ph, order in ((0, ozaki.OZ_HEFF_ORDER_SPLIT), (1, 3), (1, 7), (1, 8), (1, -1)):
+            with pytest.raises(ozaki.OzakiError):
+                ctx.set_heff_phase(ph, 0, order, 0)
+        ctx.set_heff_phase(0, -1)
+        ctx.set_heff_phase(1, -1)
+        for launch in (0, 100000, ozaki.OZ_HEFF_LAUNCH_RESIDENT, ozaki.OZ_HEFF_LAUNCH_PAIRED_TERMS):
+            ctx.set_heff_launch(launch)
+            check(*sparse_plan(ozaki, ctx, torch, prob, 6)[:2], False, "launch %d" % launch)
+        ctx.set_heff_launch(-1)
+        ctx.set_variant(6, 0, 0)
+        check(*sparse_plan(ozaki, ctx, torch, prob, 6)[:2], False, "named variant")
+        ctx.set_variant(6, 0, -1)
+        A = dev(torch, np.ones((128, 96)))
+        v, _ = ctx.tune(A, dev(torch, np.ones((96, 64))), slices=6)
+        plan, dpsi, keep = sparse_plan(ozaki, ctx, torch, prob, 6)
+        assert plan.variants == (v, v)
+        check(plan, dpsi, True, "tuned")
+    finally:
+        ctx.set_heff_phase(0, -1)
+        ctx.set_heff_phase(1, -1)
+        ctx.set_heff_launch(-1)
+        ctx.set_variant(6, 0, -1)
+
+
+@pytest.mark.parametrize("first", ["small", "large"])
+def test_split_is_decided_chunk_by_chunk(oz, first):
+    """Chunks of few output blocks beside chunks of many (sectors of 100 and of
+    760 states), either kind first: the few ones alone take the split kernel,
+    whatever launch the others chose; the reported choice reproduces the plan
+    and every form gives the bits of the plan of one chunk."""
+    ozaki, ctx, torch = oz
+    dims, ops = [760, 100], 3
+    rng = np.random.default_rng(5)
+    L = [wl.wide_normal(rng, (d, d), 6) for k in range(ops) for d in dims]
+    R = [wl.wide_normal(rng, (d, d), 6) for k in range(ops) for d in dims]
+    off = np.concatenate([[0], np.cumsum([x.size for x in L])[:-1]])
+    key = [x for k in range(ops) for s in (0, 1) for x in (k, s, s)]
+    layout = {"left_dim": dims, "right_dim": dims, "phys": 1, "psi_lr": [0, 0, 1, 1], "psi_offset": [0, dims[0] ** 2],
+              "L_key": key, "L_offset": [int(x) for x in off], "R_key": key, "R_offset": [int(x) for x in off]}
+    big, small = ([(k, s, s, s, s, 1.0) for k in range(ops)] for s in (0, 1))
+    triples = big + small if first == "large" else small + big
+    dL, dR = (dev(torch, np.concatenate([x.ravel() for x in X])) for X in (L, R))
+    dpsi = dev(torch, wl.wide_normal(rng, (sum(d * d for d in dims),), 6))
+    try:
+        one = ozaki.HeffPlan(ctx, layout, dL, dR, triples, slices=6)
+        assert one.chunks == 1 and one.split_chunks == 0
+        want = one.apply(dpsi)
+        ctx.set_heff_budget(1)
+        plan = ozaki.HeffPlan(ctx, layout, dL, dR, triples, slices=6)
+        assert (plan.chunks, plan.split_chunks) == (2 * ops, ops)
+        assert torch.equal(plan.apply(dpsi), want)
+        choice = (plan.phase(0), plan.phase(1))
+        assert choice[1][1] & ozaki.OZ_HEFF_ORDER_SPLIT
+        for launch in (choice[1][2], 0, ozaki.OZ_HEFF_LAUNCH_PAIRED_TERMS):
+            ctx.set_heff_phase(0, *choice[0])
+            ctx.set_heff_phase(1, 0 if launch else choice[1][0], choice[1][1], launch)
+            again = ozaki.HeffPlan(ctx, layout, dL, dR, triples, slices=6)
+            assert again.split_chunks == ops and again.phase(1)[1:] == (choice[1][1], launch)
+            assert torch.equal(again.apply(dpsi), want)
+    finally:
+        ctx.set_heff_budget(0)
+        ctx.set_heff_phase(0, -1)
+        ctx.set_heff_phase(1, -1)
