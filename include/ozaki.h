@@ -540,9 +540,9 @@ int rdm_eig_destroy(rdm_eig plan);
  * those of the two ozaki_dgemm calls.  workspace: device, 256-byte aligned,
  * ozaki_renormalize_workspace_bytes(n, D, slices, ndiag) bytes (the
  * intermediate T and the GEMM workspace), or up to
- * ozaki_renormalize_batch_bytes(n, D, count, slices, ndiag), with which the
- * call works on several operators at once (as many as the workspace holds).
- * Asynchronous on the stream. */
+ * ozaki_renormalize_batch_bytes(n, D, count, slices, ndiag) (at most 2 GiB
+ * more), with which the call works on several operators at once (as many as
+ * the workspace holds).  Asynchronous on the stream. */
 size_t ozaki_renormalize_workspace_bytes(int64_t n, int64_t D, int slices, int ndiag);
 size_t ozaki_renormalize_batch_bytes(int64_t n, int64_t D, int count, int slices, int ndiag);
 int ozaki_renormalize(ozaki_ctx ctx, int64_t n, int64_t D, const double *U, int64_t ldu, int count,

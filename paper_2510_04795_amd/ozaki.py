@@ -420,7 +420,11 @@ class Context:
             raise ValueError("all operators (and all outputs) must share one leading dimension")
         if workspace is None:
             nb = _lib.ozaki_renormalize_batch_bytes(n, D, len(ops), slices, ndiag)
-            workspace = torch.empty(max(nb, 1), dtype=torch.uint8, device=U.device)
+            try:
+                workspace = torch.empty(max(nb, 1), dtype=torch.uint8, device=U.device)
+            except torch.cuda.OutOfMemoryError:
+                nb = _lib.ozaki_renormalize_workspace_bytes(n, D, slices, ndiag)
+                workspace = torch.empty(max(nb, 1), dtype=torch.uint8, device=U.device)
         po = (_ptr * max(len(ops), 1))(*[o.data_ptr() for o in ops])
         pr = (_ptr * max(len(outs), 1))(*[o.data_ptr() for o in outs])
         _check(_lib.ozaki_renormalize(self.handle, n, D, U.data_ptr(), _ld(U, "U"), len(ops), po, ldo, pr,

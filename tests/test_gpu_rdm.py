@@ -426,3 +426,30 @@ def test_renormalize_batches_on_every_context(oz, S, how):
     finally:
         ctx.set_timing(False)
         ctx.set_variant(6, 0, -1)
+
+
+@pytest.mark.parametrize("S", [0, 7])
+def test_renormalize_without_memory_for_a_batch(oz, S, monkeypatch):
+    """Where the batch's workspace cannot be had, the call takes the
+    per-operator one; results are the same."""
+    ozaki, ctx, torch = oz
+    n, D, count = 260, 40, 6
+    ops = [dev(torch, o) for o in wl.block_operators(n, count, seed=11)]
+    U = dev(torch, np.linalg.qr(np.random.default_rng(11).standard_normal((n, D)))[0])
+    want = ctx.renormalize(U, ops, slices=S)
+    one = int(ozaki._lib.ozaki_renormalize_workspace_bytes(n, D, S, 0))
+    assert ozaki._lib.ozaki_renormalize_batch_bytes(n, D, count, S, 0) > one
+    empty, asked = torch.empty, []
+
+    def scarce(*size, **kw):
+        if kw.get("dtype") is torch.uint8:
+            asked.append(size[0])
+            if size[0] > one:
+                raise torch.cuda.OutOfMemoryError("no memory for the batch")
+        return empty(*size, **kw)
+
+    monkeypatch.setattr(ozaki.torch, "empty", scarce)
+    out = ctx.renormalize(U, ops, slices=S)
+    assert len(asked) == 2 and asked[1] == one
+    for a, b in zip(out, want):
+        assert torch.equal(a, b)

@@ -103,3 +103,24 @@ def test_new_entry_points_reject_bad_arguments_on_the_host():
     w6 = L.ozaki_renormalize_workspace_bytes(100, 20, 6, 0)
     assert w6 == t + max(L.ozaki_dgemm_workspace_bytes(100, 20, 100, 6, 0),
                          L.ozaki_dgemm_workspace_bytes(20, 20, 100, 6, 0))
+
+
+@pytest.mark.parametrize("slices", [0, 2, 6, 7, 8])
+def test_batched_renormalisation_workspace_is_bounded(slices):
+    """The batch query asks for at most 2 GiB beyond the per-operator
+    workspace, whatever the operators' size and number, and for nothing more
+    when one operator's slot is larger than that."""
+    from paper_2510_04795_amd import ozaki
+    L = ozaki._lib
+    for n in (1, 100, 2048, 4096, 8192, 16384, 30000):
+        for D in (1, 64, 512, n):
+            if D > n:
+                continue
+            one = L.ozaki_renormalize_workspace_bytes(n, D, slices, 0)
+            sizes = [L.ozaki_renormalize_batch_bytes(n, D, count, slices, 0) for count in (1, 2, 3, 16, 1000)]
+            assert sizes == sorted(sizes) and sizes[0] == one and sizes[-1] - one <= 2 << 30
+            if slices * n * n > 2 << 30:
+                assert sizes[-1] == one
+    # the usual sizes keep their whole batch: 8 operators of n = 2048, D = 512
+    one = L.ozaki_renormalize_workspace_bytes(2048, 512, 7, 0)
+    assert L.ozaki_renormalize_batch_bytes(2048, 512, 16, 7, 0) - one >= 7 * (7 * 2048 * 2048 + 8 * 2048 * 512)
