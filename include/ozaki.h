@@ -530,6 +530,9 @@ typedef struct {
 int rdm_eig_create(ozaki_ctx ctx, rdm_eig *out, int64_t n, int slices, int ndiag);
 int rdm_eig_solve(rdm_eig plan, const double *A, int64_t lda, int64_t nev, double *evals, double *Z,
                   int64_t ldz, double tol, int max_sweeps, rdm_eig_info *info, void *stream);
+/* Steps of QR iteration (0, 1 or 2) that the last solve's sweeps started from:
+ * a step whose factorisation breaks down, and those after it, are left out. */
+int rdm_eig_start_steps(rdm_eig plan);
 int rdm_eig_destroy(rdm_eig plan);
 
 /* ozaki_renormalize: O'_k = U^T O_k U for k < count, with U (device, n x D

@@ -733,6 +733,7 @@ struct rdm_eig_s {
     int *slot0 = nullptr, *maps = nullptr, *dst = nullptr, *rows = nullptr, *bad = nullptr;
     unsigned cross_lds = 0;               // bytes of LDS on top of k_pair_cross's own
     int *act = nullptr;                   // pairs that rotated, of this round and the one before
+    int start_steps = 0;                  // steps of QR iteration the last solve's sweeps started from
     int ntiles = 0;  // pairs x 64-column tiles
     TileDesc *tiles = nullptr;
     OutDesc *outs = nullptr;
@@ -926,6 +927,7 @@ int precondition(rdm_eig h, const double *A, int64_t lda, double fro, JacStart *
     if ((e = hipMemcpyAsync(bad, h->bad, sizeof(bad), hipMemcpyDeviceToHost, s)) != hipSuccess ||
         (e = hipStreamSynchronize(s)) != hipSuccess)
         return hip_fail(e, "rdm_eig: QR flags");
+    h->start_steps = bad[0] ? 0 : bad[1] ? 1 : 2;
     if (bad[0]) return OZ_OK;
     if (bad[1])
         *st = JacStart{h->Y, np, h->W2, 1, h->X, h->V, h->W, h->W2};
@@ -1117,6 +1119,7 @@ int rdm_eig_solve(rdm_eig h, const double *A, int64_t lda, int64_t nev, double *
     const double fro = std::sqrt(fro2);
     const double abs_tol = tol * fro;
     JacStart st{A, lda, nullptr, 0, h->X, h->Y, h->W, h->W2};
+    h->start_steps = 0;
     // QR iteration first, unless A is nearly diagonal already (the sweeps
     // then converge at once and leave an exactly diagonal A exact), a single
     // pair of blocks (one round a sweep), or |A|_F^2 is near the range's ends
@@ -1287,6 +1290,11 @@ int rdm_eig_solve(rdm_eig h, const double *A, int64_t lda, int64_t nev, double *
     }
     if (info) *info = rdm_eig_info{sweeps, status, last, trace};
     return OZ_OK;
+}
+
+int rdm_eig_start_steps(rdm_eig h) {
+    if (!h) return fail(OZ_ERR_ARG, "rdm_eig_start_steps: NULL solver");
+    return h->start_steps;
 }
 
 int rdm_eig_destroy(rdm_eig h) {

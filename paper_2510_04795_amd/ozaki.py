@@ -125,6 +125,7 @@ _sig("lanczos_destroy", _i32, [_ptr])
 _sig("rdm_eig_create", _i32, [_ptr, ctypes.POINTER(_ptr), _i64, _i32, _i32])
 _sig("rdm_eig_solve", _i32, [_ptr, _ptr, _i64, _i64, _ptr, _ptr, _i64, _dbl, _i32,
                              ctypes.POINTER(RdmEigInfo), _ptr])
+_sig("rdm_eig_start_steps", _i32, [_ptr])
 _sig("rdm_eig_destroy", _i32, [_ptr])
 _sig("ozaki_renormalize_workspace_bytes", _sz, [_i64, _i64, _i32, _i32])
 _sig("ozaki_renormalize_batch_bytes", _sz, [_i64, _i64, _i32, _i32, _i32])
@@ -145,7 +146,7 @@ EXPORTED = [
     "heff_plan_phase", "heff_flops",
     "heff_plan_destroy", "davidson_create", "davidson_step", "davidson_get_vector",
     "davidson_set_graphs", "davidson_graph_count", "davidson_destroy", "lanczos_create", "lanczos_step", "lanczos_get_vector", "lanczos_destroy",
-    "rdm_eig_create", "rdm_eig_solve", "rdm_eig_destroy", "ozaki_renormalize_workspace_bytes",
+    "rdm_eig_create", "rdm_eig_solve", "rdm_eig_start_steps", "rdm_eig_destroy", "ozaki_renormalize_workspace_bytes",
     "ozaki_renormalize_batch_bytes", "ozaki_renormalize",
 ]
 
@@ -755,6 +756,11 @@ class RdmEig:
                                   Z.stride(0), tol, max_sweeps, ctypes.byref(info), _stream(stream)),
                "rdm_eig_solve")
         return evals, Z[:, :nev], info
+
+    @property
+    def start_steps(self) -> int:
+        """Steps of QR iteration (0, 1 or 2) the last solve's sweeps started from."""
+        return _check(_lib.rdm_eig_start_steps(self.handle), "rdm_eig_start_steps")
 
     def close(self):
         if getattr(self, "handle", None):

@@ -453,3 +453,67 @@ def test_renormalize_without_memory_for_a_batch(oz, S, monkeypatch):
     assert len(asked) == 2 and asked[1] == one
     for a, b in zip(out, want):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("S", [0, 6])
+@pytest.mark.parametrize("n", [65, 128, 129, 320])
+@pytest.mark.parametrize("kind,steps", [("graded", 2), ("goe", 2), ("diagonal", 0), ("singular_first", 0),
+                                        ("singular_second", 1)])
+def test_qr_iteration_steps(oz, S, n, kind, steps):
+    """How many steps of QR iteration the sweeps start from: both on a graded
+    and on a random spectrum, none on a diagonal matrix; none where half of the
+    eigenvalues sit at minus the first step's shift (3e-7 |A|_F: M + mu I is
+    singular) and one where they sit at minus the second's (3e-12 |A|_F, which
+    the first step still takes).  Each converges, and on the graded spectrum in
+    ten sweeps at most where the matrix itself takes 15 to 29.  (Emulated sweeps
+    that start from the matrix itself, half of its values one cluster, are left
+    out of the accuracy check: their rounding gathers over 34 sweeps, to 1.2
+    times the bound on residuals at n = 320, S = 6, and to 2.3 times over 39
+    where no solve starts from QR iteration.)"""
+    ozaki, ctx, torch = oz
+    rng = np.random.default_rng(n)
+    Q, _ = np.linalg.qr(rng.standard_normal((n, n)))
+    lam = rng.uniform(0.5, 1.0, n)
+    if kind == "graded":
+        lam = np.exp(-np.arange(n) / (n / 64.0))
+    elif kind == "goe":
+        lam = rng.standard_normal(n)
+    elif kind != "diagonal":
+        lam[: n // 2] = -(3e-7 if kind == "singular_first" else 3e-12) * np.linalg.norm(lam[n // 2:])
+    A = np.diag(lam) if kind == "diagonal" else (Q * lam) @ Q.T
+    A = 0.5 * (A + A.T)
+    nev = n // 4 if kind == "graded" else n
+    eig = ozaki.RdmEig(ctx, n, S)
+    try:
+        # (from the matrix itself, half of its values one cluster: up to 39 sweeps at n = 320, S = 6)
+        w, Z, info = eig.solve(dev(torch, A), nev, max_sweeps=60)
+        assert eig.start_steps == steps
+        assert info.status == 1
+        if S == 0 or kind != "singular_first":
+            check_eigenpairs(A, w.cpu().numpy(), Z.cpu().numpy(), S)
+        if kind == "graded":
+            assert info.sweeps <= 10
+        # of the last solve: a diagonal matrix next, on the same plan
+        eig.solve(dev(torch, np.diag(np.arange(n) + 1.0)), nev)
+        assert eig.start_steps == 0
+    finally:
+        eig.close()
+
+
+@pytest.mark.parametrize("n,D,count", [(1025, 321, 5), (700, 255, 16), (4095, 255, 16)])
+def test_renormalize_native_batches_on_tiles(oz, n, D, count):
+    """Native batches of more 64 x 64 tiles than the split kernel takes, odd
+    extents: both products on 64 x 64 tiles, and (16 operators of n = 4095) the
+    first on 128 x 128; within the FP64 bound of the two products."""
+    ozaki, ctx, torch = oz
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    ops = [torch.randn(n, n, generator=g, device="cuda", dtype=torch.float64) for _ in range(count)]
+    U = torch.linalg.qr(torch.randn(n, D, generator=g, device="cuda", dtype=torch.float64))[0].contiguous()
+    out = ctx.renormalize(U, ops, slices=0)
+    gam = (n + 1) * U64 / (1 - (n + 1) * U64)
+    aU = U.abs()
+    aUt, Ut = aU.T.contiguous(), U.T.contiguous()
+    for o, got in zip(ops, out):
+        bound = 3 * gam * (aUt @ (o.abs() @ aU))
+        assert bool(((got - Ut @ (o @ U)).abs() <= bound).all())
