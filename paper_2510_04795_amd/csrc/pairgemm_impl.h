@@ -1663,7 +1663,7 @@ __global__ __launch_bounds__(64 * WM * WN) void k_pair_single(PairArgs a, int ti
 // sums.  These are int32 and exact, so adding the four waves' sums gives the
 // same bits in any order.  Bound: latency (a load, the MFMAs of K / 128
 // blocks, the recombination); measured against the 64 x 64 tile in
-// split_pays.
+// pair_split_pays.
 template <int S, int G>
 __device__ __forceinline__ void split_load(Frags<S, G, 1, 1> &f, const int8_t *A, const int8_t *B, int64_t a_run,
                                            int64_t b_run) {

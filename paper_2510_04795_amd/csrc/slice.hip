@@ -877,8 +877,9 @@ hipError_t launch_slice_operands(int S, OperandTask a, OperandTask b, int32_t *c
     }
     // rows of a column chunk: 256 when both operands need codes (their scratch
     // holds ceil(K / 256) codes for each of the larger one's groups twice),
-    // 128 when one does; more for a long K, so that at most 32 chunks are
-    // reduced in every slice block
+    // 128 when one does; more for a long K, at most 32 chunks.  Every slice
+    // block reduces up to kMaxCodeChunks codes itself: K <= 2048 with one
+    // operand in codes, K <= 4096 with both; past that k_codes_final does
     const int64_t base = a.trans && b.trans ? 256 : 128;
     int64_t at = 0;
     for (OperandTask *o : {&a, &b}) {

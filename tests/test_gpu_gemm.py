@@ -525,3 +525,23 @@ def test_tuned_context_keeps_the_split_kernel(oz):
         ctx.set_variant(S, G, -1)
     assert ctx.gemm_variant(*small, S, G) == ozaki.OZ_VARIANT_SPLIT
     assert ctx.gemm_variant(64, 64, 40000, 8, 15) == 0  # K chunks run on the 64 x 64 tile
+
+
+@pytest.mark.parametrize("K", [4096, 4097, 4353])
+def test_both_operands_in_column_codes(oz, K):
+    """Both operands' groups stored as columns (TN) around the longest K whose
+    codes the slice blocks reduce themselves (16 chunks of 256: K = 4096) and
+    past it, where a launch of its own does; zero and non-finite groups.  Bit
+    for bit the oracle's."""
+    ozaki, ctx, torch = oz
+    rng = np.random.default_rng(K)
+    M, N, S = 70, 33, 3
+    A, B = wl.wide_normal(rng, (K, M), 10), wl.wide_normal(rng, (K, N), 10)
+    A[:, 5] = 0.0
+    A[K - 1, 69] = np.inf
+    B[4095, 32] = np.nan
+    A[K - 1, 7] = 2.0 ** 40  # the largest of its column, in the last chunk
+    ctx.flags()
+    got = ctx.dgemm(dev(torch, A), dev(torch, B), slices=S, transa="T").cpu().numpy()
+    assert ctx.flags() & ozaki.OZ_FLAG_NONFINITE
+    assert_bitexact(got, oracle.ozaki_dgemm(A, B, S, transa="T"))
