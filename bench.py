@@ -596,7 +596,7 @@ def rdm_section(args, ozaki, ctx, torch):
     ops = [torch.from_numpy(o).cuda() for o in wl.block_operators(n, kop, seed=13)]
     ref = None
     for S in [0, 3, 6, 7]:
-        ws = torch.empty(ozaki._lib.ozaki_renormalize_workspace_bytes(n, D, S, 0), dtype=torch.uint8, device="cuda")
+        ws = torch.empty(ozaki._lib.ozaki_renormalize_batch_bytes(n, D, kop, S, 0), dtype=torch.uint8, device="cuda")
         res = ctx.renormalize(U64, ops, slices=S, workspace=ws)
         torch.cuda.synchronize()
         t0 = time.perf_counter()
