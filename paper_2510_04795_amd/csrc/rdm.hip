@@ -619,7 +619,7 @@ __global__ __launch_bounds__(256) void k_jac_diag(const double *__restrict__ M, 
 // rotation by a small angle (s^2 below u / 2, as between rows of nearly equal
 // eigenvalues) lengthens its row of W by s^2 while M's entry rounds that away,
 // always in the same direction.  On four clusters of 256 at n = 1024 the
-// diagonal had drifted by up to 7300 u, the quotients are within 62 u.  One
+// diagonal had drifted by up to 7300 u, the quotients are within 52 u.  One
 // product of n_p x n x n: 0.29 ms of a truncation of 33 at n = 2048.
 __global__ __launch_bounds__(256) void k_rayleigh(const double *__restrict__ T, const double *__restrict__ W,
                                                   int64_t n, int64_t np, double *__restrict__ lam,
