@@ -182,7 +182,7 @@ __global__ __launch_bounds__(256) void k_pair_eig(const double *__restrict__ M, 
     }
     if (off > inner_tol || sums[1] > exempt_tol2) {
         for (int step = 0; step < 63; ++step) {
-            double cl = 1.0, sl = 0.0;
+            double hl = 0.0, sl = 0.0;  // tan(a / 2) and sin(a)
             {
                 // rotation wave + 4 (lane & 7): rows other waves leave alone in the row pass
                 int p, q;
@@ -192,14 +192,15 @@ __global__ __launch_bounds__(256) void k_pair_eig(const double *__restrict__ M, 
                     // symmetric Schur rotation zeroing a_pq (smaller root of t^2 + 2 th t - 1 = 0)
                     const double th = (a[q * kLdE + q] - a[p * kLdE + p]) / (2.0 * apq);
                     const double t = (th >= 0.0 ? 1.0 : -1.0) / (fabs(th) + sqrt(th * th + 1.0));
-                    cl = 1.0 / sqrt(t * t + 1.0);
-                    sl = t * cl;
+                    const double c = 1.0 / sqrt(t * t + 1.0);
+                    sl = t * c;
+                    hl = sl / (1.0 + c);
                 }
             }
-            double cs[8], ss[8];
+            double hs[8], ss[8];
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
-                cs[i] = lane_value(cl, i);
+                hs[i] = lane_value(hl, i);
                 ss[i] = lane_value(sl, i);
             }
             // the 8 rotations touch disjoint rows (columns): all loads of a
@@ -215,8 +216,9 @@ __global__ __launch_bounds__(256) void k_pair_eig(const double *__restrict__ M, 
             }
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
-                a[pp[i] * kLdE + lane] = cs[i] * x[i] - ss[i] * y[i];
-                a[qq[i] * kLdE + lane] = ss[i] * x[i] + cs[i] * y[i];
+                rotate(ss[i], hs[i], x[i], y[i]);
+                a[pp[i] * kLdE + lane] = x[i];
+                a[qq[i] * kLdE + lane] = y[i];
             }
             __syncthreads();
             double u[8], v[8];
@@ -229,10 +231,12 @@ __global__ __launch_bounds__(256) void k_pair_eig(const double *__restrict__ M, 
             }
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
-                a[lane * kLdE + pp[i]] = cs[i] * x[i] - ss[i] * y[i];
-                a[lane * kLdE + qq[i]] = ss[i] * x[i] + cs[i] * y[i];
-                vt[pp[i] * kPair + lane] = cs[i] * u[i] - ss[i] * v[i];
-                vt[qq[i] * kPair + lane] = ss[i] * u[i] + cs[i] * v[i];
+                rotate(ss[i], hs[i], x[i], y[i]);
+                rotate(ss[i], hs[i], u[i], v[i]);
+                a[lane * kLdE + pp[i]] = x[i];
+                a[lane * kLdE + qq[i]] = y[i];
+                vt[pp[i] * kPair + lane] = u[i];
+                vt[qq[i] * kPair + lane] = v[i];
             }
             __syncthreads();
         }
@@ -354,21 +358,20 @@ __device__ void pair_cross(const double *__restrict__ g, int64_t ldm, double *__
             // and takes those of its rows from its lanes
             double c, s;
             schur_rotation(app, aqq, apq, &c, &s);
-            double rc[4], rs[4];
+            const double h = half_tangent(c, s);
+            double rh[4], rs[4];
 #pragma unroll
             for (int m = 0; m < 4; ++m) {
                 const int lane = 4 * ((tid & 32) + 4 * ty + m);
-                rc[m] = lane_shift(c, lane);
+                rh[m] = lane_shift(h, lane);
                 rs[m] = lane_shift(s, lane);
             }
 #pragma unroll
             for (int m = 0; m < 4; ++m) {
-                const double p0 = rc[m] * pp[m] - rs[m] * qp[m], q0 = rs[m] * pp[m] + rc[m] * qp[m];
-                const double p1 = rc[m] * pq[m] - rs[m] * qq[m], q1 = rs[m] * pq[m] + rc[m] * qq[m];
-                pp[m] = c * p0 - s * p1;
-                pq[m] = s * p0 + c * p1;
-                qp[m] = c * q0 - s * q1;
-                qq[m] = s * q0 + c * q1;
+                rotate(rs[m], rh[m], pp[m], qp[m]);
+                rotate(rs[m], rh[m], pq[m], qq[m]);
+                rotate(s, h, pp[m], pq[m]);
+                rotate(s, h, qp[m], qq[m]);
             }
             // next pairing: q_i <- q_{i+1}, q_j <- q_{j+1}; its rotations come
             // from p_i p_i, p_i q_{i+1} and q_{i+1} q_{i+1}
@@ -391,11 +394,7 @@ __device__ void pair_cross(const double *__restrict__ g, int64_t ldm, double *__
 #pragma unroll
             for (int m = 0; m < 4; ++m)
 #pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const double u = vp[m][h], w = vq[m][h];
-                    vp[m][h] = rc[m] * u - rs[m] * w;
-                    vq[m][h] = rs[m] * u + rc[m] * w;
-                }
+                for (int g = 0; g < 2; ++g) rotate(rs[m], rh[m], vp[m][g], vq[m][g]);
             mine[64] = vq[0][0];
             mine[96] = vq[0][1];
             __syncthreads();
@@ -619,8 +618,8 @@ __global__ __launch_bounds__(256) void k_jac_diag(const double *__restrict__ M, 
 // rotation by a small angle (s^2 below u / 2, as between rows of nearly equal
 // eigenvalues) lengthens its row of W by s^2 while M's entry rounds that away,
 // always in the same direction.  On four clusters of 256 at n = 1024 the
-// diagonal had drifted by up to 7300 u, the quotients are within 52 u.  One
-// product of n_p x n x n: 0.29 ms of a truncation of 33 at n = 2048.
+// diagonal drifts by up to 680 u, the quotients are within 24 u.  One
+// product of n_p x n x n: 0.29 ms of a truncation of 32 at n = 2048.
 __global__ __launch_bounds__(256) void k_rayleigh(const double *__restrict__ T, const double *__restrict__ W,
                                                   int64_t n, int64_t np, double *__restrict__ lam,
                                                   double *__restrict__ nrm) {

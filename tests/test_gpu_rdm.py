@@ -517,3 +517,22 @@ def test_renormalize_native_batches_on_tiles(oz, n, D, count):
     for o, got in zip(ops, out):
         bound = 3 * gam * (aUt @ (o.abs() @ aU))
         assert bool(((got - Ut @ (o @ U)).abs() <= bound).all())
+
+
+@pytest.mark.parametrize("n", [320, 513, 640])
+def test_clustered_couplings_do_not_drift(oz, n):
+    """Native FP64 on clusters of nearly equal eigenvalues: what a solve leaves
+    between its eigenvectors is what it says of its own matrix, 0.1 tol |A|_F
+    with the default tol = 4 sqrt(n_p) u, up to the rounding of A's products
+    with the vectors (4 sqrt(n) u |A|_2)."""
+    rng = np.random.default_rng(n + 1)
+    lam = np.repeat([4.0, 3.0, 2.0, 1.0], -(-n // 4))[:n] + 1e-9 * rng.standard_normal(n)
+    Q, _ = np.linalg.qr(rng.standard_normal((n, n)))
+    A = (Q * lam) @ Q.T
+    A = 0.5 * (A + A.T)
+    w, Z, info = solve(oz, A)
+    assert info.status == 1
+    tol = 4 * np.sqrt(-(-n // 64) * 64) * U64
+    M = Z.T @ A @ Z
+    left = np.max(np.abs(M - np.diag(np.diag(M))))
+    assert left <= 0.1 * tol * np.linalg.norm(A) + 4 * np.sqrt(n) * U64 * 4.0, left / (tol * np.linalg.norm(A))
