@@ -280,7 +280,7 @@ constexpr int kRotLds = 64 * t64::kLdK + 64 * t64::kLdN;  // doubles: one tile r
 // through LDS, along with the three elements each of the next rotations needs,
 // so that every half wave computes all of them and one barrier a step is
 // enough.  The finished tile is the pair's part of the next M.  Bound: the
-// chain of 32 steps (rotation, broadcast, update, shift) of about 1.1 us: 38 us
+// chain of 32 steps (rotation, broadcast, update, shift) of about 1.1 us: 37 us
 // a round at n = 2048 where k_pair_eig, whose 63 steps each move 200 KB
 // through LDS, takes 110.
 __device__ void pair_cross(const double *__restrict__ g, int64_t ldm, double *__restrict__ qt,
